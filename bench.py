@@ -150,7 +150,7 @@ def make_workload(torch, fc, name, dev):
                          red_src=fc.R_ATTN_RECV if with_vv else fc.R_SIM_MEAN,
                          corr_src=fc.C_ATTN if with_vv else fc.C_COSINE),
                  dominant="qk" if from_qk else "reduce" if with_vv else "gram",
-                 qk_elements=B * H * q_rows * n_tot, d_head=d_head, qk_long=True,
+                 qk_elements=B * H * q_rows * n_tot, d_head=d_head,
                  qk_bytes=2 * B * H * n_tot * d_head * 2 + B * N * M * 8 + (B * N * N * 4 if with_vv else 0),
                  reduce_bytes=B * H * N * N * 2 + B * N * N * 4 + B * H * M * N * 2,
                  gram_flops=2.0 * B * (N - keep) * keep * D, step_bytes=None)
@@ -481,8 +481,7 @@ def main():
         # 2 * d_head matrix-core flops; the vector operations are what the kernel waits for.
         algo = 7.0 * W["qk_elements"]
         achieved = algo / (alone_ms * 1e-3) / 1e12
-        roof = {"kernel": "%s (softmax(QK^T) on bf16 MFMA 16x16x32, reduced on the fly)"
-                          % ("attn_qk_long_kernel" if W.get("qk_long") or W["N"] + 1 > 640 else "attn_qk_kernel"), "bound": "alu",
+        roof = {"kernel": "qk_norm_kernel + qk_mean_kernel (softmax(QK^T) on bf16 MFMA 16x16x32, reduced on the fly)", "bound": "alu",
                 "achieved": achieved, "peak": 157.3, "unit": "TFLOP/s", "frac": achieved / 157.3, "traffic": None,
                 "algorithmic_flops": algo, "mfma_flops": 2.0 * W["d_head"] * W["qk_elements"],
                 "hbm_bytes_algorithmic": W["qk_bytes"],

@@ -167,8 +167,8 @@ typedef struct {
    * causal (row r attends rows 0 .. r of the block); the M text tokens are the positions
    * vis_begin + N .. vis_begin + N + M - 1 and must lie inside the block; their rows give the
    * text profiles of Eq. 3 / Eq. 4, the visual rows the visual-to-visual terms where selected.  bfloat16 only (qk_dtype = FICOCO_BF16, whatever
-   * `dtype` the tokens have), d_head in {32, 64, 128}; with qk_n > 640 (the keys are then taken in blocks of 640, in two
-   * sweeps) and for FiCoCo-L at most 64 heads: FICOCO_EUNSUPPORTED otherwise.  Logits, exponentials and row sums are single precision (bf16 products are exact
+   * `dtype` the tokens have), d_head in {32, 64, 128}; with qk_n > 640
+   * and for FiCoCo-L at most 64 heads: FICOCO_EUNSUPPORTED otherwise.  Logits, exponentials and row sums are single precision (bf16 products are exact
    * in it), so scores and map entries agree with a double-precision evaluation to about 1e-6
    * relative, not to the last bit: a top-K or threshold decision whose margin is below that may
    * differ from one taken on double-precision values. */
@@ -353,7 +353,8 @@ int ficoco_l_step(ficoco_ctx *ctx, const ficoco_problem *p, void *ws, size_t ws_
  * ficoco_v_step without `ws` / `ws_bytes`: the step's workspace is a static device array of
  * FICOCO_STATIC_SCRATCH_BYTES inside the library (one copy per GPU, held until the process
  * ends).  The call allocates and frees nothing and launches the same kernels.
- *   - A problem whose ficoco_workspace_bytes exceeds FICOCO_STATIC_SCRATCH_BYTES is rejected
+ *   - A problem whose ficoco_workspace_bytes exceeds FICOCO_STATIC_SCRATCH_BYTES (up to 8 MiB of
+ *     softmax normalisers of the query/key form not counted) is rejected
  *     with FICOCO_ENOMEM before anything is launched (the batched 576-token ViT shape,
  *     B = 16, needs about 25 MB and fits).
  *   - All calls on one GPU share that GPU's array: calls that overlap in time on one GPU

@@ -13,7 +13,9 @@
 // on holds its own copy for the life of the process.  Host code never passes the array's name to
 // a kernel (on the host it is a stand-in symbol, not a device address): ficoco_create asks the
 // runtime for the array's address on the ctx's device and keeps it in g_static_ws.
-constexpr size_t kStaticScratchBytes = FICOCO_STATIC_SCRATCH_BYTES;
+// Behind FICOCO_STATIC_SCRATCH_BYTES there is room for the row normalisers of the query/key form,
+// which that limit does not count.
+constexpr size_t kStaticScratchBytes = FICOCO_STATIC_SCRATCH_BYTES + ficoco::kQkNormBytes;
 static __device__ __align__(256) unsigned char g_static_scratch[kStaticScratchBytes];
 constexpr int kMaxDevices = 64;
 static void* g_static_ws[kMaxDevices];    // per device, filled by ficoco_create (written once per device with the same value)
@@ -171,10 +173,11 @@ int make_plan(const ficoco_problem& p, Plan& pl, const char** why) {
   };
   pl.qk = qk;
   if (qk) {
-    // one column partial per tile of query rows: all rows of the block, or (FiCoCo-L) the visual and
-    // text rows, or the text rows alone where no visual-to-visual term is needed
-    const int q_rows = !L ? p.qk_n : (p.red_src == FICOCO_R_ATTN_RECV || p.corr_src == FICOCO_C_ATTN) ? p.N + p.M : p.M;
-    pl.n_chunks = (q_rows + kQkTile - 1) / kQkTile;
+    // the visual queries where a visual-to-visual term is selected, then the [CLS] query or the text
+    // queries; one column partial per tile of visual queries
+    pl.qk_visq = p.red_src == FICOCO_R_ATTN_RECV || p.corr_src == FICOCO_C_ATTN ? p.N : 0;
+    pl.qk_nq = pl.qk_visq + (L ? p.M : p.sem_src == FICOCO_G_CLS_ATTN ? 1 : 0);
+    pl.n_chunks = (pl.qk_visq + kQkTile - 1) / kQkTile;
   } else if (need_A) {
     int lo = p.vis_begin - p.a_q_begin, hi = lo + p.N;  // visual query rows
     const bool vis_rows = p.red_src == FICOCO_R_ATTN_RECV || p.corr_src == FICOCO_C_ATTN;
@@ -244,19 +247,14 @@ int make_plan(const ficoco_problem& p, Plan& pl, const char** why) {
   pl.hub_cnt = take(B * sizeof(int32_t));
   pl.share_cnt = take(edges_inverted(pl) ? B * (size_t)invert_groups(pl) * p.n_keep * sizeof(int32_t) : 0);
   pl.pair_tab = take(pair_records(p, pl) ? B * (size_t)pl.n_disc * sizeof(PairRec) : 0);
-  pl.qk_groups = 1;
-  if (qk && (L || p.qk_n > kQkMaxKeys)) {
-    // Few query tiles (a decoder's 64 text queries are two): the heads are split over up to sixteen
-    // workgroups per tile until the chip has about one workgroup per compute unit.
-    const int64_t base = (int64_t)pl.n_chunks * p.B;
-    const int want = (int)std::max<int64_t>(1, std::min<int64_t>(std::min(p.H, 16), 256 / std::max<int64_t>(base, 1)));
-    const int per = (p.H + want - 1) / want;
-    pl.qk_groups = (p.H + per - 1) / per;            // no group without heads
-  }
-  {
-    const size_t g = pl.qk_groups > 1 ? (size_t)pl.qk_groups : 0;
-    const size_t map = p.corr_src == FICOCO_C_ATTN ? B * N * (size_t)pl.map_pitch : 0;
-    pl.qk_part = take(g * (map + (L ? B * N * (size_t)p.M : 0) + B * (size_t)pl.n_chunks * N + B * N) * sizeof(float));
+  if (qk) {
+    // equal rounds of as many images as have room
+    const size_t per = (size_t)p.H * pl.qk_nq * sizeof(float2);
+    const size_t most = std::max<size_t>(1, kQkNormBytes / std::max<size_t>(per, 1));
+    const size_t rounds = (B + most - 1) / most;
+    pl.qk_images = (int)((B + rounds - 1) / rounds);
+    pl.qk_norm_bytes = align_up(per * pl.qk_images);
+    pl.qk_norm = take(pl.qk_norm_bytes);
   }
   pl.rowbuf = take(pl.dense_rows ? B * (size_t)pl.n_disc * p.n_keep * sizeof(double) : 0);
   pl.use_gram = p.corr_src == FICOCO_C_COSINE && !pl.dense_rows && pl.Df % 8 == 0 && p.k_max <= 64 &&
@@ -561,7 +559,7 @@ int ficoco_v_step_static(ficoco_ctx* ctx, const ficoco_problem* p, void* X_out, 
   const char* why;
   const int rc = make_plan(*p, pl, &why);
   if (rc != FICOCO_OK) return fail(ctx, rc, fn, why);
-  if (pl.total > kStaticScratchBytes)
+  if (pl.total - pl.qk_norm_bytes > FICOCO_STATIC_SCRATCH_BYTES || pl.total > kStaticScratchBytes)
     return fail(ctx, FICOCO_ENOMEM, fn, "the step's workspace exceeds the 32 MiB static scratch: use ficoco_v_step with a caller workspace");
   void* ws = ctx->device < kMaxDevices ? g_static_ws[ctx->device] : nullptr;
   if (!ws) return fail(ctx, FICOCO_EHIP, fn, "no static scratch on this device");

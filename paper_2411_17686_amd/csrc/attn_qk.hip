@@ -1,11 +1,19 @@
 // Attention reduction from queries and keys (Sec. "Self-Attention": A = Softmax(Q K^T / sqrt(D))):
 // the per-head maps are formed on the matrix cores and reduced on the fly, so the [B,H,n,n]
 // maps never exist in memory.  Outputs are those of attn_reduce.hip -- per-tile column partials of
-// the received attention (first term of Eq. 1), the [CLS] row (second term), and the head-mean
-// map in single precision, transposed, for the correlate stage (Algorithm 1, stage 2).
+// the received attention (first term of Eq. 1), the [CLS] row (second term), the head-mean map
+// in single precision, transposed, for the correlate stage (Algorithm 1, stage 2), and for FiCoCo-L
+// (causal maps) the text profiles of Eq. 3 / Eq. 4.
 //
-// Single precision throughout (products of bfloat16 values are exact in it); the vector arithmetic
-// of the softmax, not memory, bounds the kernel.
+// Two kernels (before: one workgroup per 48 query rows that exchanged maxima and sums between its
+// wavefronts head by head; whole stage 81 -> 70 us at 16 x 577 tokens, 590 -> 290 us at 4 x 2881, 361 -> 98 us
+// at the causal 8 x 675): qk_norm_kernel leaves (reference, 1 / row sum) of every (head, query) row, and
+// qk_mean_kernel forms the probabilities of one (query tile, key tile) from them, adds the heads in
+// registers and writes the tile's outputs.  The logits are computed twice, but once the normalisers
+// are known nothing ties the keys of a row together: wavefronts exchange neither maxima nor sums, and
+// the work can be cut to fill the chip whatever the numbers of queries, keys and heads are.
+//
+// Single precision (products of bfloat16 values are exact in it), row sums and column sums in double.
 #include "common.hpp"
 
 #include <algorithm>
@@ -14,597 +22,586 @@ namespace ficoco {
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
-constexpr int kQkWaves = 8;                         // wavefronts per workgroup: they split the keys
-constexpr int kQkKB = 5;                            // 16-key blocks per wavefront
-constexpr int kQkQB = kQkTile / 16;                 // 16-query blocks per workgroup
-static_assert(kQkWaves * kQkKB * 16 == kQkMaxKeys, "the wavefronts split the keys");
+constexpr int kQkWaves = 4;                         // wavefronts side by side on the queries, a tile each
+constexpr int kQkQB = kQkTile / 16;                 // 16-query blocks of a wavefront
+constexpr int kQkKB = 2;                            // 16-key blocks a wavefront takes together
+constexpr int kQkKeys = 64;                         // keys staged together: two such steps, or one of each of two wavefronts
+static_assert(kQkKeys == 2 * kQkKB * 16, "two steps of keys");
 static_assert(kQkTile % 16 == 0, "whole 16-query blocks");
 
 struct QkArgs {
   const bf16_t* Q;
   const bf16_t* K;
   int64_t sb, sh, sn;
-  int H, n;             // heads, rows of the block (queries = keys)
+  int H, n;             // heads, rows of the block
   int N;                // visual tokens
   int vis0;             // block row of visual token 0
-  int cls_r;            // block row of the [CLS] query, or -1
+  // The queries that are needed, numbered 0 .. nq: the n_visq visual ones (all or none), then the
+  // others from block row x0 on: the [CLS] query (FiCoCo-V) or the text queries (FiCoCo-L).
+  int nq, n_visq, x0;
   float scale_log2e;    // qk_scale * log2(e): exponentials are taken as powers of two
+  float2* norm;         // [images of this launch][H][nq]: reference, 1 / (row sum relative to it)
   float* abar;          // [B][N][map_pitch] or null
   int map_pitch;
-  double* recv_part;    // [B][n_tiles][N]
-  double* cls;          // [B][N]
-  int n_tiles, B;
-  // the two-sweep kernel only:
-  int q_begin, q_count; // block rows whose queries are needed (the tiles cover these)
-  int text0, M;         // FiCoCo-L: block row of the first text query, number of text queries
+  double* recv_part;    // [B][n_tiles][N] or null
+  double* cls;          // [B][N] or null
   double* ttext;        // FiCoCo-L: [B][N][M] head-mean attention of the text queries on the visual keys, or null
-  // Few tiles: the heads are split over `groups` workgroups per tile (heads_per_group consecutive
-  // heads each), which leave head SUMS in single precision; a second kernel adds the groups in
-  // order and divides by H.  groups == 1: the outputs are written directly.
-  int groups, heads_per_group;
-  float* part_map;      // [groups][B][N][map_pitch]
-  float* part_text;     // [groups][B][N][M]
-  float* part_recv;     // [groups][B][n_tiles][N]
-  float* part_cls;      // [groups][B][N]
+  int M;
+  int n_tiles;          // query tiles that hold visual queries
+  int b0, nb;           // images of this launch
+  int q_groups, k_tiles; // workgroups of one image: query tiles or groups of them, key tiles
+  __device__ __forceinline__ int row(int v) const { return v < n_visq ? vis0 + v : x0 + (v - n_visq); }
 };
 
 // v_mfma_f32_16x16x32_bf16: operand A is 16 rows x 32 features (lane: row lane % 16, features
 // 8 (lane / 16) .. + 8), operand B 16 columns x 32 features (same), the result 16 x 16 (lane: column
 // lane % 16, rows 4 (lane / 16) + v for its four registers v).  Rows are keys here, columns queries:
-// a lane's 16-byte operand loads of one key cover 64 contiguous bytes of the key's row across the
-// four lane groups, and a query's probabilities sit in the registers of four lanes.
+// a query's logits sit in the registers of four lanes, and sixteen lanes hold consecutive queries of one
+// key, which is a piece of a row of the transposed map.
+
+// A lane's 16-byte operand loads from global memory would touch a row of its own in every lane, and
+// the address unit takes such a load apart into 64 accesses (measured: it was busy 74 % of the time
+// and bound both kernels).  So rows are brought in whole -- neighbouring lanes on neighbouring 16-byte
+// chunks -- and turned into operands through LDS.  CH chunks per row; the chunk of row r lies at
+// chunk ^ swizzle, which spreads the sixteen rows of an operand read over all 64 banks.
+template <int CH>
+__device__ __forceinline__ int lds_chunk(int r, int c) { return r * CH + (c ^ ((r / (16 / CH)) & (CH - 1))); }
+
+// ---- row normalisers ---------------------------------------------------------------------------
+// A workgroup takes 4 x 48 queries of one head and walks its keys 64 at a time, the next 64 being
+// loaded while the current ones are added.  The exponentials are taken relative to a whole number
+// (units of log2) at the largest logit of the first 32 keys, not of the whole row: any reference
+// serves as long as nothing overflows, and then the sums need no running maximum.  A row whose sum
+// does overflow (its largest logit more than ~70 above those of the first 32 keys) is seen in the
+// sum and done again with its own maximum.
 //
-// A workgroup owns kQkTile query rows of one image; its 8 wavefronts split the keys (80 each, 640 at
-// most) and walk the heads in order, the operands of the next head being loaded while the current
-// head's softmax is computed.
-template <int KS>     // 32-feature steps of the head dimension
-__global__ __launch_bounds__(kQkWaves * kWave) void attn_qk_kernel(QkArgs a) {
-  __shared__ float xmax[2][kQkWaves][kQkTile];
-  __shared__ float xsum[2][kQkWaves][kQkTile];
-  const int total = a.n_tiles * a.B;
-  const int logical = xcd_logical_id(blockIdx.x, total);     // the tiles of one image share an XCD and its L2 (the keys)
-  if (logical >= total) return;
-  const int tile = logical % a.n_tiles;
-  const int64_t b = logical / a.n_tiles;
-  const int lane = threadIdx.x % kWave;
-  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);   // the same in every lane: scalar, so tests on it are branches
-  const int l16 = lane % 16, lg = lane / 16;
+// Bound by the vector unit: exponential, multiply-add and add per logit (VALU busy 66 % of the time at
+// 4 x 2881 tokens, 16 heads of 64: 116 us; with operands straight from memory 165-205 us).
+template <int KS, bool DEC>
+__global__ __launch_bounds__(kQkWaves * kWave) __attribute__((amdgpu_waves_per_eu(2))) void qk_norm_kernel(QkArgs a) {
+  constexpr int CH = KS * 4, T = kQkWaves * kWave, RPI = T / CH, NL = kQkKeys / RPI;
+  __shared__ u32x4_t stage[2][kQkKeys * CH];
+  const int units = a.nb * a.H * a.q_groups;
+  const int unit = xcd_logical_id(blockIdx.x, units);     // the workgroups of a head share an L2 (its keys)
+  if (unit >= units) return;
+  const int tid = threadIdx.x, lane = tid % kWave, l16 = lane % 16, lg = lane / 16;
+  const int wv = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const int w0 = (unit % a.q_groups) * kQkWaves * kQkTile;
+  const bool narrow = a.nq - w0 <= 16;     // one block of queries in all (the [CLS] query behind 576 visual ones): the wavefronts share its keys
+  const int v0 = narrow ? w0 : w0 + wv * kQkTile;
+  const int h = (unit / a.q_groups) % a.H;
+  const int64_t bi = unit / (a.q_groups * a.H);
   const float NEG = -__builtin_huge_valf();
-  const int key_base = wv * kQkKB * 16;             // first key of this wavefront
+  const bf16_t* Qh = a.Q + (a.b0 + bi) * a.sb + (int64_t)h * a.sh;
+  const bf16_t* Kh = a.K + (a.b0 + bi) * a.sb + (int64_t)h * a.sh;
+  // keys below full_end count for every query of this wavefront, from k_end on for none
+  const bool active = v0 < a.nq;
+  const int q_lo = a.row(min(v0, a.nq - 1)), q_hi = a.row(min(v0 + kQkTile, a.nq) - 1);
+  const int k_end = !active ? 0 : DEC ? min(a.n, q_hi + 1) : a.n;
+  const int full_end = DEC ? min(a.n, q_lo + 1) : a.n;
+  const int wg_end = DEC ? min(a.n, a.row(min(w0 + kQkWaves * kQkTile, a.nq) - 1) + 1) : a.n;
 
-  // operand addresses (clamped to valid rows: what lies past the block is masked later)
-  int64_t q_off[kQkQB], k_off[kQkKB];
+  int qrow[kQkQB];
+  bf16x8_t qf[kQkQB][KS];
 #pragma unroll
-  for (int qb = 0; qb < kQkQB; ++qb) q_off[qb] = (int64_t)min(tile * kQkTile + qb * 16 + l16, a.n - 1) * a.sn + lg * 8;
+  for (int qb = 0; qb < kQkQB; ++qb) {
+    qrow[qb] = a.row(min(v0 + qb * 16 + l16, a.nq - 1));
 #pragma unroll
-  for (int kb = 0; kb < kQkKB; ++kb) k_off[kb] = (int64_t)min(key_base + kb * 16 + l16, a.n - 1) * a.sn + lg * 8;
+    for (int ks = 0; ks < KS; ++ks) __builtin_memcpy(&qf[qb][ks], Qh + (int64_t)qrow[qb] * a.sn + lg * 8 + ks * 32, 16);
+  }
 
-  bf16x8_t kf[kQkKB][KS], qf[kQkQB][KS];
-  auto load_head = [&](int h) {
-    const bf16_t* Qh = a.Q + b * a.sb + (int64_t)h * a.sh;
-    const bf16_t* Kh = a.K + b * a.sb + (int64_t)h * a.sh;
+  u32x4_t next[NL];
+  auto load_stage = [&](int k0) {
 #pragma unroll
-    for (int kb = 0; kb < kQkKB; ++kb)
+    for (int i = 0; i < NL; ++i)
+      __builtin_memcpy(&next[i], Kh + (int64_t)min(k0 + tid / CH + i * RPI, a.n - 1) * a.sn + tid % CH * 8, 16);
+  };
+  auto store_stage = [&](int buf) {
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) __builtin_memcpy(&kf[kb][ks], Kh + k_off[kb] + ks * 32, 16);
-#pragma unroll
-    for (int qb = 0; qb < kQkQB; ++qb)
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) __builtin_memcpy(&qf[qb][ks], Qh + q_off[qb] + ks * 32, 16);
+    for (int i = 0; i < NL; ++i) stage[buf][lds_chunk<CH>(tid / CH + i * RPI, tid % CH)] = next[i];
   };
 
-  f32x4_t P[kQkKB][kQkQB];
+  f32x4_t S[kQkKB][kQkQB];
+  // logits of 32 keys; `key_op(kb, ks)` gives this lane's operand
+  auto logits = [&](auto qbn, auto key_op) __attribute__((always_inline)) {
+    constexpr int QB = decltype(qbn)::value;
 #pragma unroll
-  for (int kb = 0; kb < kQkKB; ++kb)
+    for (int kb = 0; kb < kQkKB; ++kb) {
+#pragma unroll
+      for (int qb = 0; qb < QB; ++qb) S[kb][qb] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) {
+        const bf16x8_t kf = key_op(kb, ks);
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) S[kb][qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, qf[qb][ks], S[kb][qb], 0, 0, 0);
+      }
+    }
+  };
+  auto counts = [&](int key, int qb) { return key < a.n && (!DEC || key <= qrow[qb]); };
+  // the largest logit of the 32 keys from k0 on that count, and of the four lanes of a query
+  float ref[kQkQB];
+  double sum[kQkQB];
+  auto max_of = [&](auto qbn, int k0) __attribute__((always_inline)) {
+    constexpr int QB = decltype(qbn)::value;
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb)
+#pragma unroll
+      for (int kb = 0; kb < kQkKB; ++kb)
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          ref[qb] = fmaxf(ref[qb], counts(k0 + kb * 16 + lg * 4 + v, qb) ? S[kb][qb][v] : NEG);
+  };
+  auto set_ref = [&](auto qbn) __attribute__((always_inline)) {       // (key 0 counts for every query, so the maximum is a logit)
+    constexpr int QB = decltype(qbn)::value;
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+      ref[qb] = fmaxf(ref[qb], __shfl_xor(ref[qb], 16, kWave));
+      ref[qb] = fmaxf(ref[qb], __shfl_xor(ref[qb], 32, kWave));
+      ref[qb] = ceilf(ref[qb] * a.scale_log2e);
+    }
+  };
+  auto add_chunk = [&](auto qbn, int k0) __attribute__((always_inline)) {
+    constexpr int QB = decltype(qbn)::value;
+    if (k0 + kQkKB * 16 <= full_end) {               // uniform
+#pragma unroll
+      for (int qb = 0; qb < QB; ++qb) {
+        float part = 0.0f;
+#pragma unroll
+        for (int kb = 0; kb < kQkKB; ++kb)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) part += __builtin_amdgcn_exp2f(fmaf(S[kb][qb][v], a.scale_log2e, -ref[qb]));
+        sum[qb] += (double)part;
+      }
+    } else {
+#pragma unroll
+      for (int kb = 0; kb < kQkKB; ++kb)
+        if (k0 + kb * 16 < k_end) {                  // uniform
+#pragma unroll
+          for (int qb = 0; qb < QB; ++qb) {
+            float part = 0.0f;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+              const float x = counts(k0 + kb * 16 + lg * 4 + v, qb) ? fmaf(S[kb][qb][v], a.scale_log2e, -ref[qb]) : NEG;
+              part += __builtin_amdgcn_exp2f(x);
+            }
+            sum[qb] += (double)part;
+          }
+        }
+    }
+  };
+  auto across = [&]() {
+#pragma unroll
+    for (int qb = 0; qb < kQkQB; ++qb) {
+      sum[qb] += __shfl_xor(sum[qb], 16, kWave);
+      sum[qb] += __shfl_xor(sum[qb], 32, kWave);
+    }
+  };
+#pragma unroll
+  for (int qb = 0; qb < kQkQB; ++qb) { ref[qb] = NEG; sum[qb] = 0.0; }
+
+  const std::integral_constant<int, kQkQB> all{};
+  auto direct = [&](int k0) {
+    return [&, k0](int kb, int ks) {
+      bf16x8_t kf;
+      __builtin_memcpy(&kf, Kh + (int64_t)min(k0 + kb * 16 + l16, a.n - 1) * a.sn + lg * 8 + ks * 32, 16);
+      return kf;
+    };
+  };
+  bool over = false;
+  if (narrow) {
+    // each wavefront every fourth 32 keys, with a reference of its own; the four sums are combined in order
+    const std::integral_constant<int, 1> one{};
+    __shared__ float part_ref[kQkWaves][16];
+    __shared__ double part_sum[kQkWaves][16];
+    const int first = wv * kQkKB * 16;
+#pragma unroll 1
+    for (int k0 = first; k0 < k_end; k0 += kQkWaves * kQkKB * 16) {
+      logits(one, direct(k0));
+      if (k0 == first) { max_of(one, k0); set_ref(one); }     // (-inf where none of them counts: then none of the later ones does)
+      add_chunk(one, k0);
+    }
+    across();
+    if (lg == 0) { part_ref[wv][l16] = ref[0]; part_sum[wv][l16] = sum[0]; }
+    __syncthreads();
+    if (wv != 0) return;
+    for (int w = 0; w < kQkWaves; ++w) ref[0] = fmaxf(ref[0], part_ref[w][l16]);
+    sum[0] = 0.0;
+    for (int w = 0; w < kQkWaves; ++w) {
+      const float r = part_ref[w][l16];
+      const double t = part_sum[w][l16];
+      over |= !(t < 0x1p100);
+      sum[0] += r > NEG ? ldexp(t, (int)fmaxf(r - ref[0], -3000.0f)) : 0.0;
+    }
+  } else {
+    load_stage(0);
+    store_stage(0);
+    __syncthreads();
+#pragma unroll 1
+    for (int k0 = 0; k0 < wg_end; k0 += kQkKeys) {
+      const int buf = k0 / kQkKeys % 2;
+      load_stage(k0 + kQkKeys);       // on their way while the current keys are added (past the end: the last row)
+      issue_fence();
+      if (k0 < k_end) {
+        const bf16x8_t* st = (const bf16x8_t*)stage[buf];
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+          logits(all, [&](int kb, int ks) { return st[lds_chunk<CH>((half * kQkKB + kb) * 16 + l16, ks * 4 + lg)]; });
+          if (half == 0 && k0 == 0) { max_of(all, 0); set_ref(all); }
+          add_chunk(all, k0 + half * kQkKB * 16);
+        }
+      }
+      store_stage(1 - buf);
+      __syncthreads();
+    }
+    if (!active) return;
+    across();
+#pragma unroll
+    for (int qb = 0; qb < kQkQB; ++qb) over |= !(sum[qb] < 0x1p100);
+  }
+  if (__any(over)) {                                 // rare: with the row's own maximum, keys straight from memory
+#pragma unroll
+    for (int qb = 0; qb < kQkQB; ++qb) { ref[qb] = NEG; sum[qb] = 0.0; }
+#pragma unroll 1
+    for (int k0 = 0; k0 < k_end; k0 += kQkKB * 16) { logits(all, direct(k0)); max_of(all, k0); }
+    set_ref(all);
+#pragma unroll 1
+    for (int k0 = 0; k0 < k_end; k0 += kQkKB * 16) { logits(all, direct(k0)); add_chunk(all, k0); }
+    across();
+  }
+#pragma unroll
+  for (int qb = 0; qb < kQkQB; ++qb) {
+    const int v = v0 + qb * 16 + l16;
+    if (lg == 0 && v < a.nq) a.norm[((int64_t)bi * a.H + h) * a.nq + v] = make_float2(ref[qb], (float)(1.0 / sum[qb]));
+  }
+}
+
+// ---- probabilities, head mean, outputs -----------------------------------------------------------
+// A wavefront forms 48 queries x 32 visual keys of an image, the heads added in order in registers.
+// SPLIT = false: the four wavefronts of a workgroup sit two by two on 96 queries x 64 keys and
+// share the staged rows.  SPLIT = true (few tiles): 48 x 64 by two wavefronts, and four such pairs
+// take consecutive shares of the heads, each with a staging area of its own; their sums are added
+// pairwise (a fixed tree) in LDS.  Rows are staged 64 features at a time in two buffers, loaded into
+// registers two stages ahead; the exponentials of a head are computed beside the matrix
+// instructions and LDS reads of the next one.
+//
+// Bound by the vector unit (exponential, two multiply-adds per logit) and the trips between
+// barriers.  Measured at 4 x 2881 tokens, 16 heads of 64 / 16 x 577, 16 of 64 / 8 x 675 causal, 32
+// of 128: operands straight from memory 314 / 70 / 99 us; staged, 192 x 64 by eight wavefronts, each head
+// on its own 180 / 44 / 56; the next head's matrix instructions under this head's exponentials, 96 x 64 by
+// four wavefronts (three workgroups on a compute unit instead of two) 170 / 40 / 51.
+constexpr int kQkBand = 8;                          // key tiles side by side in the order of the workgroups
+constexpr int kQkCols = 2;                          // wavefronts side by side on the keys
+constexpr int kQkMB = kQkKeys / 16 / kQkCols;       // 16-key blocks of a wavefront
+template <bool SPLIT> struct QkMeanShape {
+  static constexpr int kRows = SPLIT ? 1 : 2;         // wavefronts side by side on the queries
+  static constexpr int kShares = SPLIT ? 4 : 1;       // shares of the heads
+  static constexpr int kThreads = kRows * kQkCols * kShares * kWave;
+};
+template <int KS, bool DEC, bool SPLIT>
+__global__ __launch_bounds__(QkMeanShape<SPLIT>::kThreads) __attribute__((amdgpu_waves_per_eu(SPLIT || KS == 4 ? 2 : 3))) void qk_mean_kernel(QkArgs a) {
+  constexpr int KSS = KS > 2 ? 2 : KS, NST = KS / KSS, CH = KSS * 4;     // 32-feature steps of a stage, stages of a head
+  using Shape = QkMeanShape<SPLIT>;
+  constexpr int QR = Shape::kRows * kQkTile;                              // query rows of a stage
+  constexpr int T = Shape::kRows * kQkCols * kWave, RPI = T / CH;
+  constexpr int NL = (QR + kQkKeys + RPI - 1) / RPI;                      // rounds of RPI rows (past the last key: that key again)
+  extern __shared__ u32x4_t stage_m[];                 // [2][SPLIT ? 4 : 1][rounded-up rows of a stage]
+  constexpr int kArea = NL * RPI * CH;
+  const int units = a.nb * a.q_groups * a.k_tiles;
+  const int unit = xcd_logical_id(blockIdx.x, units);
+  if (unit >= units) return;
+  const int tid = threadIdx.x, lane = tid % kWave, l16 = lane % 16, lg = lane / 16;
+  const int wv = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const int share = SPLIT ? wv / kQkCols : 0;                // of the heads
+  // the tiles of an image in columns kQkBand key tiles wide: the workgroups that run together on an
+  // XCD then need few rows of either side, which its L2 holds for all heads
+  const int64_t bi = unit / (a.k_tiles * a.q_groups), b = a.b0 + bi;
+  const int in_img = unit - (int)bi * a.k_tiles * a.q_groups;
+  const int band = in_img / (kQkBand * a.q_groups), in_band = in_img - band * kQkBand * a.q_groups;
+  const int band_w = min(kQkBand, a.k_tiles - band * kQkBand);
+  const int kt = band * kQkBand + in_band % band_w;
+  const int w0 = in_band / band_w * QR;
+  const bool narrow = a.nq - w0 <= 16;                 // one block of queries in all (uniform)
+  const int v0 = SPLIT || narrow ? w0 : w0 + wv / kQkCols * kQkTile;
+  const int wk0 = kt * kQkKeys, ik0 = wk0 + wv % kQkCols * kQkMB * 16;         // first visual key of the stage, of this wavefront
+  const int per = (a.H + Shape::kShares - 1) / Shape::kShares;            // heads of a share (the last may have fewer)
+  const int h_lo = min(share * per, a.H), h_hi = min(h_lo + per, a.H);
+  // (decoder: a tile all of whose keys lie behind its queries is zero)
+  const bool wg_dead = DEC && a.vis0 + wk0 > a.row(min(w0 + QR, a.nq) - 1);
+  const bool active = v0 < a.nq && !(DEC && a.vis0 + ik0 > a.row(min(v0 + kQkTile, a.nq) - 1));
+
+  f32x4_t P[kQkMB][kQkQB];
+#pragma unroll
+  for (int kb = 0; kb < kQkMB; ++kb)
 #pragma unroll
     for (int qb = 0; qb < kQkQB; ++qb) P[kb][qb] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
 
-  load_head(0);
-#pragma unroll 1
-  for (int h = 0; h < a.H; ++h) {
-    // logits of this head: S[kb][qb][v] = key (key_base + 16 kb + 4 lg + v) . query (16 qb + l16)
-    f32x4_t S[kQkKB][kQkQB];
+  auto heads = [&]() __attribute__((always_inline)) {
+    constexpr int QB = kQkQB;
+    const int t = tid % T;
+    u32x4_t* area = stage_m + share * kArea;
+    constexpr int kBuf = Shape::kShares * kArea;
+    const bf16_t* src[NL];                             // this thread's chunk of the stage's rows: queries, then keys
 #pragma unroll
-    for (int kb = 0; kb < kQkKB; ++kb)
+    for (int i = 0; i < NL; ++i) {
+      const int r = t / CH + i * RPI;
+      const int row = r < QR ? a.row(min(w0 + r, a.nq - 1)) : a.vis0 + min(wk0 + r - QR, a.N - 1);
+      src[i] = (r < QR ? a.Q : a.K) + b * a.sb + (int64_t)row * a.sn + t % CH * 8;
+    }
+    const float2* nrm = a.norm + bi * a.H * a.nq;
+    u32x4_t next[NL];
+    auto load_stage = [&](int h, int part) {
+      const int64_t off = (int64_t)h * a.sh + part * KSS * 32;
 #pragma unroll
-      for (int qb = 0; qb < kQkQB; ++qb) {
-        S[kb][qb] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+      for (int i = 0; i < NL; ++i) __builtin_memcpy(&next[i], src[i] + off, 16);
+    };
+    auto store_stage = [&](int buf) {
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
-          S[kb][qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[kb][ks], qf[qb][ks], S[kb][qb], 0, 0, 0);
-      }
-    // the next head's operands are on their way while this head's softmax is computed (past the
-    // last head the last one is loaded again)
-    load_head(min(h + 1, a.H - 1));
-    issue_fence();                  // the loads go out here, not where the next head first uses them
-    // keys past the block read as -inf (only the last wavefronts can hold any: a scalar test, so the
-    // others skip the selects altogether)
-    if (key_base + kQkKB * 16 > a.n) {
+      for (int i = 0; i < NL; ++i) area[buf * kBuf + lds_chunk<CH>(t / CH + i * RPI, t % CH)] = next[i];
+    };
+    const int cnt = h_hi - h_lo, last = max(cnt - 1, 0), h0 = min(h_lo, a.H - 1);
+    auto load_at = [&](int i, int part) { load_stage(h0 + min(i, last), part); };     // (past the last head: that one again)
+    auto add = [&](const f32x4_t (&S)[kQkMB][QB], const float2 (&nf)[QB], int kb) __attribute__((always_inline)) {
 #pragma unroll
-    for (int kb = 0; kb < kQkKB; ++kb) {
-      if (key_base + (kb + 1) * 16 > a.n) {
+      for (int qb = 0; qb < QB; ++qb)
 #pragma unroll
         for (int v = 0; v < 4; ++v)
-          if (key_base + kb * 16 + lg * 4 + v >= a.n) {
+          P[kb][qb][v] = fmaf(__builtin_amdgcn_exp2f(fmaf(S[kb][qb][v], a.scale_log2e, -nf[qb].x)), nf[qb].y, P[kb][qb][v]);
+    };
+    // Head i: its logits into S, beside the exponentials of head i - 1 from Sp -- the matrix
+    // instructions and the trips through LDS run under the vector work of the head before.
+    auto step = [&](int i, const f32x4_t (&Sp)[kQkMB][QB], const float2 (&np)[QB], f32x4_t (&S)[kQkMB][QB],
+                    float2 (&nf)[QB]) __attribute__((always_inline)) {
 #pragma unroll
-            for (int qb = 0; qb < kQkQB; ++qb) S[kb][qb][v] = NEG;
-          }
-      }
-    }
-    }
-    // Softmax of every query's row with ONE exchange between the wavefronts: a wavefront takes the
-    // exponentials relative to a reference at or above the maximum of ITS keys (the maximum in
-    // units of log2, rounded up to a whole number) and sums them; the (reference, sum) pairs are
-    // exchanged, and its probabilities are its exponentials times 2^(own reference - largest
-    // reference) / row sum.  scale_log2e > 0.
-    const int par = h & 1;          // two sets of slots: the next head's writes do not wait for this head's reads
-    // The three query blocks go through every stage side by side (maxima, their two exchanges
-    // between the lane groups, exponentials, sums, their exchanges, one write): taken one block
-    // after the other, each of the twelve lane exchanges of a head waits out its own trip
-    // through the permute path.
-    float mc[kQkQB], mw[kQkQB], lw[kQkQB];
-    bool any_key[kQkQB];
+      for (int part = 0; part < NST; ++part) {
+        const int buf = NST == 1 ? i % 2 : part % 2;
+        store_stage(1 - buf);                          // the stage after this one, loaded a step ago
+        if (part == 0) {
 #pragma unroll
-    for (int qb = 0; qb < kQkQB; ++qb) {
-      mw[qb] = NEG;
-#pragma unroll
-      for (int kb = 0; kb < kQkKB; ++kb)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) mw[qb] = fmaxf(mw[qb], S[kb][qb][v]);
-    }
-    {
-      float o[kQkQB];
-#pragma unroll
-      for (int qb = 0; qb < kQkQB; ++qb) o[qb] = __shfl_xor(mw[qb], 16, kWave);
-#pragma unroll
-      for (int qb = 0; qb < kQkQB; ++qb) mw[qb] = fmaxf(mw[qb], o[qb]);
-#pragma unroll
-      for (int qb = 0; qb < kQkQB; ++qb) o[qb] = __shfl_xor(mw[qb], 32, kWave);
-#pragma unroll
-      for (int qb = 0; qb < kQkQB; ++qb) mw[qb] = fmaxf(mw[qb], o[qb]);
-    }
-#pragma unroll
-    for (int qb = 0; qb < kQkQB; ++qb) {
-      any_key[qb] = mw[qb] > NEG;                   // a wavefront whose keys all lie past the block has none
-      mc[qb] = any_key[qb] ? ceilf(mw[qb] * a.scale_log2e) : 0.0f;  // a whole number: rescaling between wavefronts is exact
-      lw[qb] = 0.0f;
-#pragma unroll
-      for (int kb = 0; kb < kQkKB; ++kb)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const float e = __builtin_amdgcn_exp2f(fmaf(S[kb][qb][v], a.scale_log2e, -mc[qb]));
-          S[kb][qb][v] = e;
-          lw[qb] += e;
+          for (int qb = 0; qb < QB; ++qb)
+            nf[qb] = (nrm + (int64_t)(h0 + min(i, last)) * a.nq)[(uint32_t)min(v0 + qb * 16 + l16, a.nq - 1)];
         }
-    }
-    {
-      float o[kQkQB];
+        load_at(i + (part + 2) / NST, (part + 2) % NST);
+        issue_fence();
+        if (active) {                                  // uniform in the wavefront
+          const bf16x8_t* st = (const bf16x8_t*)(area + buf * kBuf);
+          bf16x8_t qf[QB][KSS], kf[kQkMB][KSS];
 #pragma unroll
-      for (int qb = 0; qb < kQkQB; ++qb) o[qb] = __shfl_xor(lw[qb], 16, kWave);
+          for (int qb = 0; qb < QB; ++qb)
 #pragma unroll
-      for (int qb = 0; qb < kQkQB; ++qb) lw[qb] += o[qb];
+            for (int ks = 0; ks < KSS; ++ks)
+              qf[qb][ks] = st[lds_chunk<CH>(v0 - w0 + qb * 16 + l16, ks * 4 + lg)];
 #pragma unroll
-      for (int qb = 0; qb < kQkQB; ++qb) o[qb] = __shfl_xor(lw[qb], 32, kWave);
+          for (int kb = 0; kb < kQkMB; ++kb)
 #pragma unroll
-      for (int qb = 0; qb < kQkQB; ++qb) lw[qb] += o[qb];
-    }
-    if (lg == 0) {
+            for (int ks = 0; ks < KSS; ++ks) kf[kb][ks] = st[lds_chunk<CH>(QR + ik0 - wk0 + kb * 16 + l16, ks * 4 + lg)];
+          if (i > 0 && i <= cnt) {                     // uniform
 #pragma unroll
-      for (int qb = 0; qb < kQkQB; ++qb) {
-        xmax[par][wv][qb * 16 + l16] = any_key[qb] ? mc[qb] : NEG;
-        xsum[par][wv][qb * 16 + l16] = lw[qb];
+            for (int kb = 0; kb < kQkMB; ++kb)
+              if (NST == 1 || kb * NST / kQkMB == part) add(Sp, np, kb);
+          }
+#pragma unroll
+          for (int kb = 0; kb < kQkMB; ++kb)
+#pragma unroll
+            for (int ks = 0; ks < KSS; ++ks)
+#pragma unroll
+              for (int qb = 0; qb < QB; ++qb)
+                S[kb][qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[kb][ks], qf[qb][ks], part == 0 && ks == 0 ? f32x4_t{0.0f, 0.0f, 0.0f, 0.0f} : S[kb][qb], 0, 0, 0);
+        }
+        __syncthreads();
       }
-    }
+    };
+    f32x4_t Sa[kQkMB][QB], Sb[kQkMB][QB];
+    float2 na[QB], nb[QB];
+    load_at(0, 0);
+    store_stage(0);
+    load_at(1 / NST, 1 % NST);
     __syncthreads();
-#pragma unroll
-    for (int qb = 0; qb < kQkQB; ++qb) {
-      const int qi = qb * 16 + l16;
-      float m = NEG;
-#pragma unroll
-      for (int w = 0; w < kQkWaves; ++w) m = fmaxf(m, xmax[par][w][qi]);          // finite: key 0 is valid
-      float l = 0.0f;
-#pragma unroll
-      for (int w = 0; w < kQkWaves; ++w)                                         // wavefronts in order; 2^(whole number) is exact
-        l += xsum[par][w][qi] * __builtin_amdgcn_exp2f(fmaxf(xmax[par][w][qi] - m, -150.0f));
-      // the quotient is taken by every lane (l > 0: key 0 is valid) and dropped where the wavefront
-      // has no key: as the value of a choice it would sit in a branch of its own
-      const float q = __builtin_amdgcn_exp2f(fmaxf(mc[qb] - m, -150.0f)) / l;
-      const float inv = any_key[qb] ? q : 0.0f;
-#pragma unroll
-      for (int kb = 0; kb < kQkKB; ++kb)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) P[kb][qb][v] = fmaf(S[kb][qb][v], inv, P[kb][qb][v]);
+#pragma unroll 1
+    for (int i = 0; i < per; i += 2) {
+      step(i, Sb, nb, Sa, na);
+      if (i + 1 < per) step(i + 1, Sa, na, Sb, nb);
     }
-  }
-
-  const float invH = 1.0f / (float)a.H;
+    if (active && cnt == per) {
 #pragma unroll
-  for (int kb = 0; kb < kQkKB; ++kb) {
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int ik = key_base + kb * 16 + lg * 4 + v - a.vis0;      // visual key index
-      const bool k_vis = ik >= 0 && ik < a.N;
-      float cs = 0.0f;                                              // received from this tile's visual queries
-#pragma unroll
-      for (int qb = 0; qb < kQkQB; ++qb) {
-        const int q = tile * kQkTile + qb * 16 + l16;
-        const int jq = q - a.vis0;                                  // visual query index
-        const bool q_vis = q < a.n && jq >= 0 && jq < a.N;
-        const float pm = P[kb][qb][v] * invH;                       // head-mean probability P[q][key]
-        if (a.abar && q_vis && k_vis) a.abar[(b * a.N + ik) * a.map_pitch + jq] = pm;
-        if (q == a.cls_r && k_vis) a.cls[b * a.N + ik] = (double)pm;
-        cs += q_vis ? pm : 0.0f;
+      for (int kb = 0; kb < kQkMB; ++kb) {
+        if (per % 2) add(Sa, na, kb); else add(Sb, nb, kb);
       }
-      // sum over the 16 lanes that hold the tile's other queries of this key (a fixed butterfly)
-#pragma unroll
-      for (int off = 8; off > 0; off >>= 1) cs += __shfl_xor(cs, off, kWave);
-      if (l16 == 0 && k_vis) a.recv_part[(b * a.n_tiles + tile) * a.N + ik] = (double)cs;
-    }
-  }
-}
-
-// More keys than one workgroup holds in registers (kQkMaxKeys): the keys are taken in blocks of
-// kQkMaxKeys (each wavefront 80 of a block, as above), in two sweeps.  Sweep 1, head by head: the
-// row maximum and the row sum of every query over all key blocks, kept per wavefront as a running
-// (reference, sum) pair -- the reference a whole number in units of log2, so that rescaling the sum
-// when a later block raises it is exact -- and combined across the wavefronts once per head; the
-// results (reference, 1 / sum) of all heads wait in LDS.  Sweep 2, key block by key block: the
-// logits of every head are formed again, turned into probabilities with the stored pair and
-// accumulated over the heads in registers; the block's piece of the head-mean map, of the [CLS] row
-// and of the column partials is written as above.  The logits are computed twice; the maps still
-// never exist in memory.  The same kernel serves the decoder of FiCoCo-L (DEC: a key behind
-// its query reads as -inf like a key past the sequence; the tiles cover the visual and the text
-// queries, or the text queries alone where no visual-to-visual term is needed; the rows of the text
-// queries leave as the text profiles of Eq. 3 / Eq. 4).
-template <int KS, int KBU, bool DEC>     // KBU: groups of 16 keys a wavefront holds of a key block (<= kQkKB); DEC: the decoder's causal maps
-__global__ __launch_bounds__(kQkWaves * kWave) void attn_qk_long_kernel(QkArgs a) {
-  extern __shared__ float norm[];                    // [heads of this workgroup][kQkTile][2]: reference, 1 / row sum
-  __shared__ float xmax[kQkWaves][kQkTile];
-  __shared__ float xsum[kQkWaves][kQkTile];
-  const int total = a.n_tiles * a.B * a.groups;
-  const int logical = xcd_logical_id(blockIdx.x, total);
-  if (logical >= total) return;
-  const int grp = logical % a.groups;               // the groups of a tile are neighbours: same operands
-  const int tile = (logical / a.groups) % a.n_tiles;
-  const int64_t b = logical / (a.groups * a.n_tiles);
-  const int h_lo = grp * a.heads_per_group, h_hi = min(h_lo + a.heads_per_group, a.H);
-  if (h_lo >= h_hi) return;                         // (the launcher leaves no group without heads)
-  const int lane = threadIdx.x % kWave;
-  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  const int l16 = lane % 16, lg = lane / 16;
-  const float NEG = -__builtin_huge_valf();
-  // A key block is KBU groups of 16 keys per wavefront: 640 keys with five groups, 384 with three
-  // (675 keys are two blocks of 384 instead of 640 + 35, with three fifths of the registers).
-  constexpr int kbu = KBU;
-  constexpr int blk_keys = kQkWaves * KBU * 16;
-  const int key_base = wv * KBU * 16;               // first key of this wavefront inside a key block
-  const int n_blocks = (a.n + blk_keys - 1) / blk_keys;
-  const int q_first = a.q_begin + tile * kQkTile;   // block row of this tile's first query
-  const int q_end = min(a.q_begin + a.q_count, a.n);
-  // decoder: key blocks that begin behind the tile's last query hold no key any of its queries
-  // attends -- they are not computed (their pieces of the outputs are written as zeros)
-  const int nb = DEC ? min(n_blocks, min(q_first + kQkTile - 1, q_end - 1) / blk_keys + 1) : n_blocks;
-
-  int q_row[kQkQB];
-  int64_t q_off[kQkQB];
-#pragma unroll
-  for (int qb = 0; qb < kQkQB; ++qb) {
-    q_row[qb] = q_first + qb * 16 + l16;
-    q_off[qb] = (int64_t)min(q_row[qb], a.n - 1) * a.sn + lg * 8;
-  }
-
-  // Operands of head h and key block blk (rows clamped to valid ones), and the logits between this
-  // tile's queries and this wavefront's keys of the block (keys past the sequence read as -inf).
-  // The operands of the next (head, block) are loaded right after the matrix instructions of the
-  // current one, so that they arrive while its softmax is computed.
-  bf16x8_t kf[KBU][KS], qf[kQkQB][KS];
-  auto load_ops = [&](int h, int blk) {
-    const bf16_t* Qh = a.Q + b * a.sb + (int64_t)h * a.sh;
-    const bf16_t* Kh = a.K + b * a.sb + (int64_t)h * a.sh;
-    const int k0 = blk * blk_keys + key_base;
-#pragma unroll
-    for (int kb = 0; kb < KBU; ++kb) {
-      const int64_t off = (int64_t)min(k0 + kb * 16 + l16, a.n - 1) * a.sn + lg * 8;
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) __builtin_memcpy(&kf[kb][ks], Kh + off + ks * 32, 16);
-    }
-#pragma unroll
-    for (int qb = 0; qb < kQkQB; ++qb)
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) __builtin_memcpy(&qf[qb][ks], Qh + q_off[qb] + ks * 32, 16);
-  };
-  auto logits = [&](int blk, f32x4_t (&S)[KBU][kQkQB], int h_next, int blk_next) {
-    const int k0 = blk * blk_keys + key_base;
-#pragma unroll
-    for (int kb = 0; kb < KBU; ++kb)
-#pragma unroll
-      for (int qb = 0; qb < kQkQB; ++qb) {
-        S[kb][qb] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
-          S[kb][qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[kb][ks], qf[qb][ks], S[kb][qb], 0, 0, 0);
-      }
-    load_ops(h_next, blk_next);
-    issue_fence();                                   // the loads go out here, not where they are first used
-    if (k0 + kbu * 16 > a.n) {                       // scalar: only the last wavefronts of the last block
-#pragma unroll
-      for (int kb = 0; kb < KBU; ++kb)
-#pragma unroll
-        for (int v = 0; v < 4; ++v)
-          if (k0 + kb * 16 + lg * 4 + v >= a.n) {
-#pragma unroll
-            for (int qb = 0; qb < kQkQB; ++qb) S[kb][qb][v] = NEG;
-          }
-    }
-    if (DEC && k0 + kbu * 16 - 1 > q_first) {         // scalar: some key of this wavefront may lie behind some query
-#pragma unroll
-      for (int kb = 0; kb < KBU; ++kb)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const int key = k0 + kb * 16 + lg * 4 + v;
-#pragma unroll
-          for (int qb = 0; qb < kQkQB; ++qb)
-            if (key > q_row[qb]) S[kb][qb][v] = NEG;
-        }
     }
   };
-
-  // ---- sweep 1: (reference, 1 / sum) of every head and query ---------------------------------------
-  load_ops(h_lo, 0);
-#pragma unroll 1
-  for (int h = h_lo; h < h_hi; ++h) {
-    float mref[kQkQB], lsum[kQkQB];
+  // outputs of KB x QB blocks from query v0 and visual key ik0 on, of the sums over the heads
+  auto write_out = [&](auto kbn, auto qbn, int ik0, const auto& sums) __attribute__((always_inline)) {
+    constexpr int KB = decltype(kbn)::value, QB = decltype(qbn)::value;
+    const float invH = 1.0f / (float)a.H;
+    const int qt = v0 / kQkTile;
+    const bool recv = a.recv_part && qt < a.n_tiles;    // uniform
 #pragma unroll
-    for (int qb = 0; qb < kQkQB; ++qb) { mref[qb] = NEG; lsum[qb] = 0.0f; }
-#pragma unroll 1
-    for (int blk = 0; blk < nb; ++blk) {
-      f32x4_t S[KBU][kQkQB];
-      {
-        // next: the following block of this head, then block 0 of the next head; after the last of
-        // sweep 1 the first of sweep 2 (head 0, block 0)
-        const bool last_blk = blk + 1 == nb;
-        logits(blk, S, last_blk ? (h + 1 < h_hi ? h + 1 : h_lo) : h, last_blk ? 0 : blk + 1);
-      }
-      float mw[kQkQB];
-#pragma unroll
-      for (int qb = 0; qb < kQkQB; ++qb) {
-        mw[qb] = NEG;
-#pragma unroll
-        for (int kb = 0; kb < KBU; ++kb)
-#pragma unroll
-          for (int v = 0; v < 4; ++v) mw[qb] = fmaxf(mw[qb], S[kb][qb][v]);
-      }
-      {
-        float o[kQkQB];
-#pragma unroll
-        for (int qb = 0; qb < kQkQB; ++qb) o[qb] = __shfl_xor(mw[qb], 16, kWave);
-#pragma unroll
-        for (int qb = 0; qb < kQkQB; ++qb) mw[qb] = fmaxf(mw[qb], o[qb]);
-#pragma unroll
-        for (int qb = 0; qb < kQkQB; ++qb) o[qb] = __shfl_xor(mw[qb], 32, kWave);
-#pragma unroll
-        for (int qb = 0; qb < kQkQB; ++qb) mw[qb] = fmaxf(mw[qb], o[qb]);
-      }
-#pragma unroll
-      for (int qb = 0; qb < kQkQB; ++qb) {
-        // the block's maximum in units of log2, rounded up to a whole number; -inf: no key of it here
-        const float mc = mw[qb] > NEG ? ceilf(mw[qb] * a.scale_log2e) : NEG;
-        const float ref = fmaxf(mref[qb], mc);
-        const bool some = ref > NEG;                 // a key of this wavefront has been seen by now
-        lsum[qb] *= some && mref[qb] > NEG ? __builtin_amdgcn_exp2f(fmaxf(mref[qb] - ref, -150.0f)) : 0.0f;
-        mref[qb] = ref;
-        const float sub = some ? ref : 0.0f;
-#pragma unroll
-        for (int kb = 0; kb < KBU; ++kb)
-#pragma unroll
-          for (int v = 0; v < 4; ++v) lsum[qb] += __builtin_amdgcn_exp2f(fmaf(S[kb][qb][v], a.scale_log2e, -sub));
-      }
-    }
-    {
-      float o[kQkQB];
-#pragma unroll
-      for (int qb = 0; qb < kQkQB; ++qb) o[qb] = __shfl_xor(lsum[qb], 16, kWave);
-#pragma unroll
-      for (int qb = 0; qb < kQkQB; ++qb) lsum[qb] += o[qb];
-#pragma unroll
-      for (int qb = 0; qb < kQkQB; ++qb) o[qb] = __shfl_xor(lsum[qb], 32, kWave);
-#pragma unroll
-      for (int qb = 0; qb < kQkQB; ++qb) lsum[qb] += o[qb];
-    }
-    if (lg == 0) {
-#pragma unroll
-      for (int qb = 0; qb < kQkQB; ++qb) {
-        xmax[wv][qb * 16 + l16] = mref[qb];
-        xsum[wv][qb * 16 + l16] = lsum[qb];
-      }
-    }
-    __syncthreads();
-    if ((int)threadIdx.x < kQkTile) {
-      const int qi = threadIdx.x;
-      float m = NEG;
-#pragma unroll
-      for (int w = 0; w < kQkWaves; ++w) m = fmaxf(m, xmax[w][qi]);               // finite: key 0 is valid
-      float l = 0.0f;
-#pragma unroll
-      for (int w = 0; w < kQkWaves; ++w)                                          // wavefronts in order
-        l += xmax[w][qi] > NEG ? xsum[w][qi] * __builtin_amdgcn_exp2f(fmaxf(xmax[w][qi] - m, -150.0f)) : 0.0f;
-      norm[((h - h_lo) * kQkTile + qi) * 2] = m;
-      norm[((h - h_lo) * kQkTile + qi) * 2 + 1] = 1.0f / l;
-    }
-    __syncthreads();              // the pairs are read back below; the exchange slots are written again by the next head
-  }
-
-  // ---- sweep 2: probabilities, head mean, outputs, key block by key block --------------------------
-  const float invH = 1.0f / (float)a.H;
-#pragma unroll 1
-  for (int blk = 0; blk < n_blocks; ++blk) {
-    f32x4_t P[KBU][kQkQB];
-#pragma unroll
-    for (int kb = 0; kb < KBU; ++kb)
-#pragma unroll
-      for (int qb = 0; qb < kQkQB; ++qb) P[kb][qb] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll 1
-    for (int h = h_lo; h < (blk < nb ? h_hi : h_lo); ++h) {
-      f32x4_t S[KBU][kQkQB];
-      {
-        // next: the following head of this block, then the first head of the next block (past the end: the last again)
-        const bool last_h = h + 1 == h_hi;
-        logits(blk, S, last_h ? h_lo : h + 1, last_h ? min(blk + 1, nb - 1) : blk);
-      }
-#pragma unroll
-      for (int qb = 0; qb < kQkQB; ++qb) {
-        const float m = norm[((h - h_lo) * kQkTile + qb * 16 + l16) * 2];
-        const float inv = norm[((h - h_lo) * kQkTile + qb * 16 + l16) * 2 + 1];
-#pragma unroll
-        for (int kb = 0; kb < KBU; ++kb)
-#pragma unroll
-          for (int v = 0; v < 4; ++v)
-            P[kb][qb][v] = fmaf(__builtin_amdgcn_exp2f(fmaf(S[kb][qb][v], a.scale_log2e, -m)), inv, P[kb][qb][v]);
-      }
-    }
-#pragma unroll
-    for (int kb = 0; kb < KBU; ++kb) {
+    for (int kb = 0; kb < KB; ++kb) {
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        const int key = blk * blk_keys + key_base + kb * 16 + lg * 4 + v;
-        const int ik = key - a.vis0;                                  // visual key index
-        const bool k_vis = key < a.n && ik >= 0 && ik < a.N;
-        float cs = 0.0f;                                              // received from this tile's visual queries
+        const int ik = ik0 + kb * 16 + lg * 4 + v;      // visual key
+        const bool k_vis = ik < a.N;
+        double cs = 0.0;                                // received from this tile's visual queries
 #pragma unroll
-        for (int qb = 0; qb < kQkQB; ++qb) {
-          const int q = q_row[qb];
-          const int jq = q - a.vis0;                                  // visual query index
-          const bool q_vis = q < q_end && jq >= 0 && jq < a.N;
-          const int mq = q - a.text0;                                 // text query index
-          const bool q_txt = DEC && a.ttext && q < q_end && mq >= 0 && mq < a.M;
-          if (a.groups > 1) {            // uniform: head sums of this group, combined by qk_combine_kernel
-            const float ps = P[kb][qb][v];
-            const int64_t gb = (int64_t)grp * a.B + b;
-            if (a.abar && q_vis && k_vis) a.part_map[(gb * a.N + ik) * a.map_pitch + jq] = ps;
-            if (q == a.cls_r && k_vis) a.part_cls[gb * a.N + ik] = ps;
-            if (q_txt && k_vis) a.part_text[(gb * a.N + ik) * a.M + mq] = ps;
-            cs += q_vis ? ps : 0.0f;
-            continue;
+        for (int qb = 0; qb < QB; ++qb) {
+          const int vq = v0 + qb * 16 + l16;
+          float pm = sums[kb][qb][v] * invH;            // head-mean probability
+          if (DEC && a.vis0 + ik > a.row(vq)) pm = 0.0f;     // a key behind its query
+          const bool q_vis = vq < a.n_visq;
+          if (k_vis && q_vis && a.abar) a.abar[(b * a.N + ik) * a.map_pitch + vq] = pm;
+          if (k_vis && !q_vis && vq < a.nq) {
+            if (DEC) a.ttext[(b * a.N + ik) * a.M + (vq - a.n_visq)] = (double)pm;
+            else a.cls[b * a.N + ik] = (double)pm;
           }
-          const float pm = P[kb][qb][v] * invH;                       // head-mean probability P[q][key]
-          if (a.abar && q_vis && k_vis) a.abar[(b * a.N + ik) * a.map_pitch + jq] = pm;
-          if (q == a.cls_r && k_vis) a.cls[b * a.N + ik] = (double)pm;
-          if (q_txt && k_vis) a.ttext[(b * a.N + ik) * a.M + mq] = (double)pm;
-          cs += q_vis ? pm : 0.0f;
+          cs += q_vis ? (double)pm : 0.0;
         }
-#pragma unroll
-        for (int off = 8; off > 0; off >>= 1) cs += __shfl_xor(cs, off, kWave);
-        if (a.recv_part && l16 == 0 && k_vis) {
-          if (a.groups > 1) a.part_recv[(((int64_t)grp * a.B + b) * a.n_tiles + tile) * a.N + ik] = cs;
-          else a.recv_part[(b * a.n_tiles + tile) * a.N + ik] = (double)cs;
+        if (recv) {
+          // sum over the 16 lanes that hold the tile's other queries of this key (a fixed tree)
+          cs += dpp_move<0xB1>(cs);
+          cs += dpp_move<0x4E>(cs);
+          cs += dpp_move<0x141>(cs);
+          cs += dpp_move<0x140>(cs);
+          if (l16 == 0 && k_vis) a.recv_part[(b * a.n_tiles + qt) * a.N + ik] = cs;
         }
       }
     }
+  };
+
+  if (narrow) {
+    // The wavefronts take consecutive shares of the heads,
+    // operands straight from memory, and their sums are added in order.
+    constexpr int KB = kQkKeys / 16, W = Shape::kThreads / kWave;
+    f32x4_t P1[KB][1];
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb) P1[kb][0] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+    const int hs = (a.H + W - 1) / W, lo = min(wv * hs, a.H), hi = min(lo + hs, a.H);
+    if (lo < hi && !wg_dead) {
+      const int v = min(v0 + l16, a.nq - 1);
+      const bf16_t* q_at = a.Q + b * a.sb + (int64_t)a.row(v) * a.sn + lg * 8;
+      const bf16_t* k_at[KB];
+#pragma unroll
+      for (int kb = 0; kb < KB; ++kb) k_at[kb] = a.K + b * a.sb + (int64_t)(a.vis0 + min(wk0 + kb * 16 + l16, a.N - 1)) * a.sn + lg * 8;
+      bf16x8_t qf[KS], kf[KB][KS];
+      float2 nf;
+      auto load_head = [&](int h) {
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+          __builtin_memcpy(&qf[ks], q_at + (int64_t)h * a.sh + ks * 32, 16);
+#pragma unroll
+          for (int kb = 0; kb < KB; ++kb) __builtin_memcpy(&kf[kb][ks], k_at[kb] + (int64_t)h * a.sh + ks * 32, 16);
+        }
+        nf = a.norm[(bi * a.H + h) * a.nq + v];
+      };
+      load_head(lo);
+#pragma unroll 1
+      for (int h = lo; h < hi; ++h) {
+        f32x4_t S[KB];
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb) {
+          S[kb] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+          for (int ks = 0; ks < KS; ++ks) S[kb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[kb][ks], qf[ks], S[kb], 0, 0, 0);
+        }
+        const float2 n = nf;
+        load_head(min(h + 1, hi - 1));
+        issue_fence();
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+          for (int v4 = 0; v4 < 4; ++v4)
+            P1[kb][0][v4] = fmaf(__builtin_amdgcn_exp2f(fmaf(S[kb][v4], a.scale_log2e, -n.x)), n.y, P1[kb][0][v4]);
+      }
+    }
+    f32x4_t* sums = (f32x4_t*)stage_m;
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb)
+      if (wv > 0) sums[((wv - 1) * KB + kb) * kWave + lane] = P1[kb][0];
+    __syncthreads();
+    if (wv != 0) return;
+    for (int w = 0; w < W - 1; ++w)
+#pragma unroll
+      for (int kb = 0; kb < KB; ++kb) P1[kb][0] += sums[(w * KB + kb) * kWave + lane];
+    write_out(std::integral_constant<int, KB>{}, std::integral_constant<int, 1>{}, wk0, P1);
+    return;
   }
+
+  if (!wg_dead) heads();                                // uniform in the workgroup
+  if constexpr (SPLIT) {
+    f32x4_t* sums = (f32x4_t*)stage_m;                // (the staging areas are free)
+#pragma unroll
+    for (int step = Shape::kShares / 2; step >= 1; step /= 2) {
+      f32x4_t* slot = sums + (wv % (kQkCols * step)) * kQkMB * kQkQB * kWave + lane;
+      if (share >= step && share < 2 * step) {
+#pragma unroll
+        for (int kb = 0; kb < kQkMB; ++kb)
+#pragma unroll
+          for (int qb = 0; qb < kQkQB; ++qb) slot[(kb * kQkQB + qb) * kWave] = P[kb][qb];
+      }
+      __syncthreads();
+      if (share < step) {
+#pragma unroll
+        for (int kb = 0; kb < kQkMB; ++kb)
+#pragma unroll
+          for (int qb = 0; qb < kQkQB; ++qb) P[kb][qb] += slot[(kb * kQkQB + qb) * kWave];
+      }
+      __syncthreads();
+    }
+    if (share != 0) return;
+  }
+  if (v0 < a.nq) write_out(std::integral_constant<int, kQkMB>{}, std::integral_constant<int, kQkQB>{}, ik0, P);
 }
 
-// The groups' head sums added in group order and divided by H: one thread per output element.
-// The grid is the four outputs one after the other (map, text profiles, column partials, [CLS]
-// row), each with exactly the workgroups it needs (an empty workgroup still costs its start).
-struct QkCombineBlocks { int map, text, recv, cls; };
-__global__ __launch_bounds__(256) void qk_combine_kernel(QkArgs a, QkCombineBlocks nb) {
-  int blk = blockIdx.x, part = 0;
-  if (blk >= nb.map) { blk -= nb.map; part = 1; if (blk >= nb.text) { blk -= nb.text; part = 2; if (blk >= nb.recv) { blk -= nb.recv; part = 3; } } }
-  const int64_t i = (int64_t)blk * blockDim.x + threadIdx.x;
-  const float invH = 1.0f / (float)a.H;
-  auto total = [&](const float* part, int64_t at, int64_t stride) {
-    float t = 0.0f;
-    for (int g = 0; g < a.groups; ++g) t += part[at + g * stride];
-    return t * invH;
+template <int KS, bool DEC>
+static void launch_qk(QkArgs a, hipStream_t s) {
+  constexpr int CH = (KS > 2 ? 2 : KS) * 4;
+  const int tiles = (a.nq + kQkTile - 1) / kQkTile;
+  a.q_groups = (tiles + kQkWaves - 1) / kQkWaves;
+  hipLaunchKernelGGL((qk_norm_kernel<KS, DEC>), dim3(xcd_padded_total(a.nb * a.H * a.q_groups)), dim3(kQkWaves * kWave), 0, s, a);
+  auto mean = [&](auto kern, auto shape) {
+    using Shape = decltype(shape);
+    // two stages of (queries + keys) rows, in whole rounds of the loader; one pair per share of the heads
+    constexpr int kLoaders = Shape::kRows * kQkCols * kWave / CH;
+    constexpr int kStageRows = (Shape::kRows * kQkTile + kQkKeys + kLoaders - 1) / kLoaders * kLoaders;
+    constexpr size_t kLds = 2 * (size_t)kStageRows * CH * sizeof(u32x4_t) * Shape::kShares;
+    if (kLds > 32768)
+      (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLds);
+    a.q_groups = (tiles + Shape::kRows - 1) / Shape::kRows;
+    hipLaunchKernelGGL(kern, dim3(xcd_padded_total(a.nb * a.q_groups * a.k_tiles)), dim3(Shape::kThreads), kLds, s, a);
   };
-  if (part == 0) {
-    if (!a.abar || i >= (int64_t)a.B * a.N * a.N) return;
-    const int64_t at = (i / a.N) * a.map_pitch + i % a.N;           // [b][key][query < N]
-    a.abar[at] = total(a.part_map, at, (int64_t)a.B * a.N * a.map_pitch);
-  } else if (part == 1) {
-    if (!a.ttext || i >= (int64_t)a.B * a.N * a.M) return;
-    a.ttext[i] = (double)total(a.part_text, i, (int64_t)a.B * a.N * a.M);
-  } else if (part == 2) {
-    if (!a.recv_part || i >= (int64_t)a.B * a.n_tiles * a.N) return;
-    a.recv_part[i] = (double)total(a.part_recv, i, (int64_t)a.B * a.n_tiles * a.N);
-  } else {
-    if (a.cls_r < 0 || i >= (int64_t)a.B * a.N) return;
-    a.cls[i] = (double)total(a.part_cls, i, (int64_t)a.B * a.N);
-  }
+  // Fewer than one workgroup of the wide form per compute unit: the heads of a tile are split instead
+  // (one image of 577 tokens: step 96 us before, 46 us so).
+  const bool split = (int64_t)a.nb * ((tiles + QkMeanShape<false>::kRows - 1) / QkMeanShape<false>::kRows) * a.k_tiles < 256;
+  if (split) mean(qk_mean_kernel<KS, DEC, true>, QkMeanShape<true>{});
+  else mean(qk_mean_kernel<KS, DEC, false>, QkMeanShape<false>{});
 }
 
 void launch_attn_qk(const ficoco_problem& p, const Plan& pl, char* ws, hipStream_t s) {
+  const bool L = p.variant == FICOCO_VARIANT_L;
   QkArgs a{};
   a.Q = (const bf16_t*)p.Q; a.K = (const bf16_t*)p.K;
   a.sb = p.qk_stride_b; a.sh = p.qk_stride_h; a.sn = p.qk_stride_n;
   a.H = p.H; a.n = p.qk_n; a.N = p.N;
   a.vis0 = p.vis_begin - p.qk_begin;
-  a.cls_r = p.sem_src == FICOCO_G_CLS_ATTN ? p.cls_index - p.qk_begin : -1;
+  a.nq = pl.qk_nq;
+  a.n_visq = pl.qk_visq;
+  a.x0 = L ? a.vis0 + p.N : p.cls_index - p.qk_begin;
   a.scale_log2e = p.qk_scale * 1.4426950408889634f;
+  a.norm = (float2*)(ws + pl.qk_norm);
   a.abar = (p.corr_src == FICOCO_C_ATTN && pl.n_disc > 0) ? (float*)(ws + pl.abar) : nullptr;
   a.map_pitch = pl.map_pitch;
-  a.recv_part = (double*)(ws + pl.recv_part);
+  a.recv_part = p.red_src == FICOCO_R_ATTN_RECV ? (double*)(ws + pl.recv_part) : nullptr;
   a.cls = (double*)(ws + pl.cls);
-  a.n_tiles = pl.n_chunks; a.B = p.B;
-  a.q_begin = 0; a.q_count = p.qk_n;
-  const bool L = p.variant == FICOCO_VARIANT_L;
-  if (L) {                            // decoder: causal; the text queries follow the visual span
-    const bool need_vv = p.red_src == FICOCO_R_ATTN_RECV || p.corr_src == FICOCO_C_ATTN;
-    a.text0 = a.vis0 + p.N;
-    a.M = p.M;
-    a.ttext = (double*)(ws + pl.ttext);
-    a.q_begin = need_vv ? a.vis0 : a.text0;
-    a.q_count = need_vv ? p.N + p.M : p.M;
-    if (!need_vv) a.recv_part = nullptr;
-  }
-  const dim3 grid(xcd_padded_total(a.n_tiles * a.B)), block(kQkWaves * kWave);
-  if (L || p.qk_n > kQkMaxKeys) {     // keys in blocks, two sweeps
-    // key groups per wavefront that cut the keys evenly over as many blocks as blocks of 640 would take
-    const int blocks = (p.qk_n + kQkMaxKeys - 1) / kQkMaxKeys;
-    // (heads of 128 always take three: with five the kernel spills 41 registers)
-    const bool three = p.d_head == 128 || (p.qk_n + blocks * kQkWaves * 16 - 1) / (blocks * kQkWaves * 16) <= 3;
-    a.groups = pl.qk_groups;
-    a.heads_per_group = (p.H + a.groups - 1) / a.groups;
-    if (a.groups > 1) {
-      float* part = (float*)(ws + pl.qk_part);
-      a.part_map = part;
-      part += a.abar ? (size_t)a.groups * p.B * p.N * pl.map_pitch : 0;
-      a.part_text = part;
-      part += a.ttext ? (size_t)a.groups * p.B * p.N * p.M : 0;
-      a.part_recv = part;
-      part += (size_t)a.groups * p.B * a.n_tiles * p.N;
-      a.part_cls = part;
-    }
-    const dim3 grid2(xcd_padded_total(a.n_tiles * a.B * a.groups));
-    const size_t lds = (size_t)a.heads_per_group * kQkTile * 2 * sizeof(float);
-    auto go = [&](auto kern) { hipLaunchKernelGGL(kern, grid2, block, lds, s, a); };
-    const int ks = p.d_head / 32;       // (heads of 128 always take three key groups)
-    if (L) {
-      if (ks == 1) { if (three) go(attn_qk_long_kernel<1, 3, true>); else go(attn_qk_long_kernel<1, kQkKB, true>); }
-      else if (ks == 2) { if (three) go(attn_qk_long_kernel<2, 3, true>); else go(attn_qk_long_kernel<2, kQkKB, true>); }
-      else go(attn_qk_long_kernel<4, 3, true>);
-    } else {
-      if (ks == 1) { if (three) go(attn_qk_long_kernel<1, 3, false>); else go(attn_qk_long_kernel<1, kQkKB, false>); }
-      else if (ks == 2) { if (three) go(attn_qk_long_kernel<2, 3, false>); else go(attn_qk_long_kernel<2, kQkKB, false>); }
-      else go(attn_qk_long_kernel<4, 3, false>);
-    }
-    if (a.groups > 1) {
-      auto blocks = [](int64_t n) { return (int)((n + 255) / 256); };
-      QkCombineBlocks nb;
-      nb.map = a.abar ? blocks((int64_t)p.B * p.N * p.N) : 0;
-      nb.text = a.ttext ? blocks((int64_t)p.B * p.N * p.M) : 0;
-      nb.recv = a.recv_part ? blocks((int64_t)p.B * a.n_tiles * p.N) : 0;
-      nb.cls = a.cls_r >= 0 ? blocks((int64_t)p.B * p.N) : 0;
-      const int all = nb.map + nb.text + nb.recv + nb.cls;
-      if (all > 0) hipLaunchKernelGGL(qk_combine_kernel, dim3(all), dim3(256), 0, s, a, nb);
-    }
-    return;
-  }
-  switch (p.d_head / 32) {
-    case 1: hipLaunchKernelGGL(attn_qk_kernel<1>, grid, block, 0, s, a); break;
-    case 2: hipLaunchKernelGGL(attn_qk_kernel<2>, grid, block, 0, s, a); break;
-    default: hipLaunchKernelGGL(attn_qk_kernel<4>, grid, block, 0, s, a); break;
+  if (L) { a.ttext = (double*)(ws + pl.ttext); a.M = p.M; }
+  a.n_tiles = pl.n_chunks;
+  a.k_tiles = (p.N + kQkKeys - 1) / kQkKeys;
+  if (a.nq == 0) return;
+  const int ks = p.d_head / 32;
+  for (int b0 = 0; b0 < p.B; b0 += pl.qk_images) {    // as many images at a time as the normalisers have room for
+    a.b0 = b0;
+    a.nb = std::min(pl.qk_images, p.B - b0);
+    if (L) { if (ks == 1) launch_qk<1, true>(a, s); else if (ks == 2) launch_qk<2, true>(a, s); else launch_qk<4, true>(a, s); }
+    else { if (ks == 1) launch_qk<1, false>(a, s); else if (ks == 2) launch_qk<2, false>(a, s); else launch_qk<4, false>(a, s); }
   }
 }
 

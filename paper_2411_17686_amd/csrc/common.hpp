@@ -66,8 +66,10 @@ struct Plan {
   int fixed_k;           // >= 0: targets per discarded token fixed by the caller (0: no edges), -1: adaptive
   bool extra_token;      // the additional token of the convergent form is written
   bool qk;               // the maps are formed from queries and keys on the fly (attn_qk.hip)
-  int qk_groups;         // two-sweep form: workgroups per query tile, each with a share of the heads (1: no split)
-  size_t qk_part;        // float: the groups' head sums of map, text profiles, column partials, [CLS] row (qk_groups > 1)
+  int qk_nq, qk_visq;    // query rows that form needs, and how many of them are visual (all or none)
+  int qk_images;         // images whose row normalisers the workspace holds at a time
+  size_t qk_norm;        // float2 [qk_images][H][qk_nq] row normalisers
+  size_t qk_norm_bytes;
   bool use_gram;         // cosine correlation proposed by the MFMA tile kernel
   int gram_splits, gram_st_per_split;   // K ranges of that kernel and their length in 32-feature stages
   int f_chunks, f_rows_per_wg, Df;
@@ -84,9 +86,11 @@ int make_plan(const ficoco_problem& p, Plan& plan, const char** why);
 // feature stage's launch)
 void launch_attn_reduce(const ficoco_problem& p, const Plan& pl, char* ws, hipStream_t s, bool text_elsewhere = false);
 void launch_attn_qk(const ficoco_problem& p, const Plan& pl, char* ws, hipStream_t s);
-constexpr int kQkTile = 48;        // query rows per workgroup of the query/key form
-constexpr int kQkMaxKeys = 640;    // keys it holds in registers (longer blocks: the keys in blocks of this size, two sweeps)
-constexpr int kQkLongMaxHeads = 64; // heads whose softmax normalisers that form keeps in LDS
+constexpr int kQkTile = 48;        // query rows of a unit of the query/key form (its column partials are one per tile)
+constexpr int kQkMaxKeys = 640;    // with more keys than this, and for FiCoCo-L, at most ...
+constexpr int kQkLongMaxHeads = 64; // ... this many heads are taken
+// The row normalisers are kept for as many images at a time as fit in this many bytes (at least one).
+constexpr size_t kQkNormBytes = (size_t)8 << 20;
 // with_text: the launch of the row-norm kernel also forms the text profiles and the launch of the
 // column-sum kernel their statistics (with_cmax: the column maxima too), see text_with_features
 void launch_features(const ficoco_problem& p, const Plan& pl, char* ws, hipStream_t s, bool with_text = false,

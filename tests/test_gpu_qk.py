@@ -194,3 +194,58 @@ def test_unsupported_shapes_are_refused(ctx):
     with pytest.raises(fc.FicocoError) as e:
         fc.workspace_bytes(p)
     assert e.value.code == fc.EUNSUPPORTED
+
+
+@pytest.mark.parametrize("B,grid,H,d", [(1, 3, 2, 64), (2, 4, 9, 32), (1, 12, 3, 128), (2, 12, 8, 64), (16, 24, 3, 32), (40, 10, 2, 64),
+                                        (3, 21, 5, 128)])
+def test_query_tiles_and_head_shares(ctx, B, grid, H, d):
+    """Edges of the two kernels' tiles (48 query rows, 96 and 192 side by side, 64 keys): one block of
+    queries in all, the [CLS] query alone behind whole tiles, fewer heads than shares, more than a
+    share's; few tiles (heads split over wavefronts) and many (not)."""
+    full = _case(ctx, 300 + B + grid, B, grid, 72, H, d, "bf16", max(1, grid * grid // 3), 1.0)
+    assert full >= (B + 1) // 2
+
+
+@pytest.mark.parametrize("grid,H,d,where", [(24, 2, 64, 500), (24, 2, 64, 40), (12, 3, 32, 144), (30, 1, 128, 33), (3, 2, 64, 9)])
+def test_logits_far_above_those_of_the_first_keys(ctx, grid, H, d, where):
+    """Rows whose largest logit lies 100 to 300 (units of e) above those of the keys the softmax
+    reference is taken from: nearly all attention goes to that key, on queries of either sign."""
+    cfg = synth.ficoco_v_single(seed=77, B=1, grid=grid, D=72, H=1, centres=8, dtype="bf16", n_keep=grid * grid // 2)
+    Q, K = draw_qk(78, 1, H, cfg["N"] + 1, d, 1.0)
+    K[:, :, where] = (K[:, :, where].float() * 40.0).to(torch.bfloat16)
+    Q = (Q.float() * 8.0).to(torch.bfloat16)
+    out = run_qk(ctx, cfg, Q, K)
+    ref = O.v_step_qk(O.widen(synth.to_numpy(cfg["X"][0])), O.widen(synth.to_numpy(Q[0])), O.widen(synth.to_numpy(K[0])),
+                      float(d) ** -0.5, cls_index=0, vis_begin=1, N=cfg["N"], n_keep=cfg["n_keep"], lam=cfg["lam"],
+                      eps=cfg["eps"], grid=cfg["grid"], window=2, coef=2.0)
+    # logits up to a few hundred are rounded to 2^-24 of themselves in single precision: probabilities to about 3e-5
+    assert np.all(np.isfinite(out["scores"][0]))
+    assert np.max(np.abs(out["scores"][0] - ref["scores"])) <= 6e-5 * np.max(np.abs(ref["scores"]))
+
+
+def test_images_in_rounds_and_rows_beyond_the_text(ctx):
+    """More images than the row normalisers have room for at a time (40 x 64 heads x 601 queries:
+    two rounds), compared with the same images one by one."""
+    B, grid, H, d = 40, 24, 64, 32
+    cfg = synth.ficoco_v_single(seed=5, B=B, grid=grid, D=8, H=1, centres=8, dtype="bf16", n_keep=100)
+    Q, K = draw_qk(6, B, H, cfg["N"] + 1, d, 1.0)
+    out = run_qk(ctx, cfg, Q, K)
+    for b in (0, 26, 27, 28, 39):
+        one = dict(cfg, X=cfg["X"][b:b + 1], B=1)
+        alone = run_qk(ctx, one, Q[b:b + 1], K[b:b + 1])
+        # (one image alone has its heads split over wavefronts: sums in another order)
+        np.testing.assert_allclose(out["scores"][b], alone["scores"][0], rtol=0, atol=2e-6 * np.max(np.abs(alone["scores"][0])))
+        assert len(np.setdiff1d(out["keep"][b], alone["keep"][0])) <= 1
+
+
+def test_static_scratch_takes_what_it_took(ctx):
+    """The allocation-free entry point's limit does not count the row normalisers of this form."""
+    cfg = synth.ficoco_v_single(seed=9, B=16, grid=24, D=64, H=1, centres=8, dtype="bf16", n_keep=384)
+    Q, K = draw_qk(10, 16, 64, 577, 32, 1.0)
+    Xd, Qd, Kd = cfg["X"].to("cuda"), Q.to("cuda"), K.to("cuda")
+    p = fc.make_problem(Xd, variant=fc.VARIANT_V, vis_begin=1, N=576, n_keep=384, cls_index=0, grid=(1, 24, 24), window=2,
+                        Q=Qd, K=Kd, qk_begin=0)
+    a, b = fc.Buffers(p, "cuda", Xd.dtype), fc.Buffers(p, "cuda", Xd.dtype)
+    fc.ficoco_v_step(ctx, p, a)
+    fc.ficoco_v_step_static(ctx, p, b)
+    assert torch.equal(a.X_out, b.X_out) and torch.equal(a.scores, b.scores) and torch.equal(a.keep_idx, b.keep_idx)
