@@ -13,6 +13,8 @@
 #include "common.hpp"
 #include "gram_tile.hpp"
 
+#include <algorithm>
+
 namespace ficoco {
 
 enum CorrMode { kAttnV = 0, kAttnL = 1, kCosV = 2, kCosL = 3 };
@@ -39,6 +41,7 @@ struct CorrArgs {
   int ct_splits;
   double* cmax;          // [B][M]
   float delta;           // bound of |ct - exact dot|
+  int top_k;             // > 0: a row whose top_k-th largest value is clear of the rest has exactly the top_k as targets
   int fixed_k;           // > 0: ablation "fixed K" (sel_m = K, sel_g = 0): of the values equal to the threshold only
                          // the lowest positions are taken, K targets in all; -1: every value >= threshold
   double* gap;           // correlation-gap diagnostic output [B][n_disc] (its own kernel)
@@ -436,6 +439,10 @@ constexpr int kCandChunk = kCandKeep * kWave;    // targets per pass over the ro
 static_assert(kCandChunk <= kCandPad, "the block's padding covers one pass");
 constexpr int kCandBatch = 4;                    // targets evaluated exactly at a time
 
+// Bound by each wavefront's chain of dependent loads and, at 1152 targets per row, by the vector unit.
+// Rows whose targets are clear from the approximate values skip the exact dot products (K = 1) or take
+// them of the K targets only, and the largest values are kept by medians: 31.6 -> 18.1 us at 8 x 432 rows
+// of 144 targets and 4096 features (K = 1), 32.5 -> 27.4 us at 8064 rows of 1152 (K = 3, 1024 features).
 // Compiled for four wavefronts per SIMD (128 registers; it would take 132): the decoder shape has
 // 3456 discarded rows, one wavefront each, and the chip holds 3072 of them at three per SIMD.
 template <int MC>   // lower bounds kept per lane (>= sel_m: one lane may hold the m largest of the row)
@@ -537,7 +544,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void c
     }
   };
 
-  // lower bounds: per-lane top list, then m pops of the wavefront maximum -> lambda
+  // The largest approximate values: a descending list per lane (one median per entry and value), then m
+  // pops of the wavefront maximum; the m-th as a lower bound of an exact value is lambda.
   float top[MC];
 #pragma unroll
   for (int k = 0; k < MC; ++k) top[k] = NEGF;
@@ -546,19 +554,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void c
 #pragma unroll
     for (int u = 0; u < kCandKeep; ++u) {
       if (c0 + u * kWave >= n) break;           // uniform: slots past the row hold nothing
-      float lo = val[u] == NEGF ? NEGF : gam * fmaxf(val[u] - delta, 0.0f);
-      if (lo > top[MC - 1]) {
 #pragma unroll
-        for (int k = 0; k < MC; ++k) {
-          const bool sw = lo > top[k];
-          const float t = top[k];
-          top[k] = sw ? lo : t;
-          lo = sw ? t : lo;
-        }
-      }
+      for (int k = MC - 1; k > 0; --k) top[k] = __builtin_amdgcn_fmed3f(top[k - 1], top[k], val[u]);
+      top[0] = fmaxf(top[0], val[u]);
     }
   }
-  float lambda = NEGF;
+  auto lower = [&](float v) { return v == NEGF ? NEGF : gam * fmaxf(v - delta, 0.0f); };     // (grows with v)
+  float lambda = NEGF, lambda_k = NEGF;
   for (int r = 0; r < a.sel_m; ++r) {
     const float mx = wave_max(top[0]);
     const unsigned long long who = __ballot(top[0] == mx);
@@ -567,24 +569,46 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void c
       for (int k = 0; k + 1 < MC; ++k) top[k] = top[k + 1];
       top[MC - 1] = NEGF;
     }
-    lambda = mx;
+    lambda = lower(mx);
+    if (r + 1 == a.top_k) lambda_k = lambda;
   }
-  // candidates in ascending target order (a row of one pass is still in registers)
+  // Smallest approximate value whose upper bound, gam * max(v + delta, 0) * 1.000001 + extra, reaches
+  // `least`: rounded down by more than the roundings on the way can add up to.  (Absent targets hold
+  // -inf and never qualify.)
+  auto qualifying = [&](float least) {
+    const float want = least - extra - 4e-7f * (fabsf(least) + extra);
+    if (!(want > 0.0f)) return -3.0e38f;
+    const float v = want / (gam * 1.000001f);
+    return v - v * 4e-7f - delta * 1.000001f;
+  };
+  // Candidates in ascending target order (a row of one pass is still in registers): targets whose upper
+  // bound reaches a lower bound.  First try: if exactly top_k targets reach the top_k-th largest
+  // lower bound (less a margin), every other value of the row lies below theirs by more than the
+  // margin: tau falls into that gap and the targets are known without a single exact value.  One
+  // target's weight is one whatever its value (positive: its lower bound is); several need their
+  // values, but nobody else's.  Otherwise every target that could be among the sel_m largest.
   int n_cand = 0;
-  for (int c0 = 0; c0 < n; c0 += kCandChunk) {
-    if (n > kCandChunk) load_pass(c0);
+  bool known = false;
+#pragma unroll 1
+  for (int attempt = a.top_k > 0 && lambda_k > 0.0f ? 0 : 1; attempt < 2 && !known; ++attempt) {     // uniform
+    const float least = qualifying(attempt == 0 ? lambda_k * 0.99999f : lambda);
+    n_cand = 0;
+    for (int c0 = 0; c0 < n; c0 += kCandChunk) {
+      if (n > kCandChunk) load_pass(c0);
 #pragma unroll
-    for (int u = 0; u < kCandKeep; ++u) {
-      if (c0 + u * kWave >= n) break;           // uniform
-      const int jj = c0 + u * kWave + lane;
-      const bool is = jj < n && gam * fmaxf(val[u] + delta, 0.0f) * 1.000001f + extra >= lambda;
-      const unsigned long long m = __ballot(is);
-      if (is) {
-        const int slot = n_cand + __popcll(m & ((1ULL << lane) - 1ULL));
-        if (slot < kCandCap) cand_j[wv][slot] = jj;
+      for (int u = 0; u < kCandKeep; ++u) {
+        if (c0 + u * kWave >= n) break;           // uniform
+        const bool is = val[u] >= least;
+        const unsigned long long m = __ballot(is);
+        if (m == 0) continue;                     // uniform
+        if (is) {
+          const int slot = n_cand + __popcll(m & ((1ULL << lane) - 1ULL));
+          if (slot < kCandCap) cand_j[wv][slot] = c0 + u * kWave + lane;
+        }
+        n_cand += __popcll(m);
       }
-      n_cand += __popcll(m);
     }
+    known = attempt == 0 && n_cand == a.top_k;
   }
   if (n_cand > kCandCap) {       // uniform per wavefront
     corr_row_exact(a, b, row, lane);
@@ -594,8 +618,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void c
   const double NEG = -__builtin_huge_val();
   const int myjj = lane < n_cand ? cand_j[wv][lane] : -1;
   const int myj = myjj >= 0 ? T[myjj] : -1;
-  double myv = NEG;
-  for (int c = 0; c < n_cand; c += kCandBatch) {
+  double myv = known && lane == 0 ? 1.0 : NEG;     // (a single target: any positive value gives weight one)
+  for (int c = 0; c < (known && a.top_k == 1 ? 0 : n_cand); c += kCandBatch) {
     int j[kCandBatch];
     bool ok[kCandBatch];
 #pragma unroll
@@ -629,7 +653,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void c
   const int tie_quota = a.fixed_k > 0 ? a.sel_m - n_gt : 0x7fffffff;
   const bool is_eq = myjj >= 0 && myv == tau;
   const int eq_rank = __popcll(__ballot(is_eq) & ((1ULL << lane) - 1ULL));   // candidates are in ascending target order
-  unsigned long long hit = __ballot(myjj >= 0 && (myv > tau || (is_eq && eq_rank < tie_quota)));
+  unsigned long long hit = __ballot(myjj >= 0 && (known || myv > tau || (is_eq && eq_rank < tie_quota)));
   const unsigned long long hit_all = hit;
   const int cnt = __popcll(hit);
   const int my_pos = __popcll(hit & ((1ULL << lane) - 1ULL));
@@ -931,7 +955,12 @@ void launch_correlate(const ficoco_problem& p, const Plan& pl, char* ws, const i
   a.cmax = (double*)(ws + pl.cmax);
   a.fixed_k = pl.fixed_k;
   a.ct_splits = pl.gram_splits;
-  a.delta = (float)(pl.Df + 4 * pl.gram_splits) * 2.384185791015625e-07f;   // (Df + 4 splits) * 2^-22
+  // Every step of an accumulation adds at most 2^-22 of the sum of its terms' magnitudes; the magnitudes of
+  // all K ranges together add up to at most |x||y|, so the length that counts is that of one range.
+  a.delta = (float)(std::min(pl.Df, pl.gram_st_per_split * kGramStage) + 4 * pl.gram_splits) * 2.384185791015625e-07f;
+  // J_i is the top_k largest values where the next one is clear of them: the threshold lies strictly
+  // between v[f] and v[f+1] (g well inside (0, 1)), or at v[f] itself (g = 0, fixed K)
+  a.top_k = pl.sel_g == 0.0 ? pl.sel_m : (pl.sel_g > 1e-6 && pl.sel_g < 1.0 - 1e-6) ? pl.sel_m - 1 : 0;
   if (fused && pair_records(p, pl)) a.pair_tab = (PairRec*)(ws + pl.pair_tab);
   if (fused && edges_inverted(pl)) {
     a.share_cnt = (int32_t*)(ws + pl.share_cnt);
