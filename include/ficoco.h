@@ -353,8 +353,9 @@ int ficoco_l_step(ficoco_ctx *ctx, const ficoco_problem *p, void *ws, size_t ws_
  * ficoco_v_step without `ws` / `ws_bytes`: the step's workspace is a static device array of
  * FICOCO_STATIC_SCRATCH_BYTES inside the library (one copy per GPU, held until the process
  * ends).  The call allocates and frees nothing and launches the same kernels.
- *   - A problem whose ficoco_workspace_bytes exceeds FICOCO_STATIC_SCRATCH_BYTES (up to 8 MiB of
- *     softmax normalisers of the query/key form not counted) is rejected
+ *   - A problem whose ficoco_workspace_bytes exceeds FICOCO_STATIC_SCRATCH_BYTES (the softmax
+ *     normalisers of the query/key form, up to 8 MiB, and the source lists of the preserved
+ *     tokens, up to 8 MiB, not counted) is rejected
  *     with FICOCO_ENOMEM before anything is launched (the batched 576-token ViT shape,
  *     B = 16, needs about 25 MB and fits).
  *   - All calls on one GPU share that GPU's array: calls that overlap in time on one GPU

@@ -13,9 +13,9 @@
 // on holds its own copy for the life of the process.  Host code never passes the array's name to
 // a kernel (on the host it is a stand-in symbol, not a device address): ficoco_create asks the
 // runtime for the array's address on the ctx's device and keeps it in g_static_ws.
-// Behind FICOCO_STATIC_SCRATCH_BYTES there is room for the row normalisers of the query/key form,
-// which that limit does not count.
-constexpr size_t kStaticScratchBytes = FICOCO_STATIC_SCRATCH_BYTES + ficoco::kQkNormBytes;
+// Behind FICOCO_STATIC_SCRATCH_BYTES there is room for the row normalisers of the query/key form and for
+// the targets' lists, which that limit does not count.
+constexpr size_t kStaticScratchBytes = FICOCO_STATIC_SCRATCH_BYTES + ficoco::kQkNormBytes + 2 * ficoco::kBucketBytes;
 static __device__ __align__(256) unsigned char g_static_scratch[kStaticScratchBytes];
 constexpr int kMaxDevices = 64;
 static void* g_static_ws[kMaxDevices];    // per device, filled by ficoco_create (written once per device with the same value)
@@ -245,16 +245,27 @@ int make_plan(const ficoco_problem& p, Plan& pl, const char** why) {
   pl.tgt_alpha = take(B * (size_t)pl.n_disc * p.k_max * sizeof(double));
   pl.hub_list = take(B * (size_t)p.n_keep * sizeof(int32_t));
   pl.hub_cnt = take(B * sizeof(int32_t));
-  pl.share_cnt = take(edges_inverted(pl) ? B * (size_t)invert_groups(pl) * p.n_keep * sizeof(int32_t) : 0);
-  pl.pair_tab = take(pair_records(p, pl) ? B * (size_t)pl.n_disc * sizeof(PairRec) : 0);
+  if (pl.n_disc > 0) {
+    const size_t targets = B * (size_t)p.n_keep, entry = sizeof(int32_t) + sizeof(double);
+    // (shorter lists leave more targets to the edge lists; below a quarter / an eighth nothing is gained)
+    const int least = edges_inverted(pl) ? kBucketCapLong / 8 : kBucketCap / 4;
+    pl.bkt_cap = edges_inverted(pl) ? kBucketCapLong : kBucketCap;
+    while (pl.bkt_cap >= least && targets * pl.bkt_cap * entry > kBucketBytes) pl.bkt_cap /= 2;
+    if (pl.bkt_cap < least) pl.bkt_cap = 0;
+    const size_t before = off;
+    pl.bkt_cnt = take(pl.bkt_cap ? targets * sizeof(int32_t) : 0);
+    pl.bkt_src = take(targets * pl.bkt_cap * sizeof(int32_t));
+    pl.bkt_w = take(targets * pl.bkt_cap * sizeof(double));
+    pl.beyond += off - before;
+  }
   if (qk) {
     // equal rounds of as many images as have room
     const size_t per = (size_t)p.H * pl.qk_nq * sizeof(float2);
     const size_t most = std::max<size_t>(1, kQkNormBytes / std::max<size_t>(per, 1));
     const size_t rounds = (B + most - 1) / most;
     pl.qk_images = (int)((B + rounds - 1) / rounds);
-    pl.qk_norm_bytes = align_up(per * pl.qk_images);
-    pl.qk_norm = take(pl.qk_norm_bytes);
+    pl.qk_norm = take(per * pl.qk_images);
+    pl.beyond += align_up(per * pl.qk_images);
   }
   pl.rowbuf = take(pl.dense_rows ? B * (size_t)pl.n_disc * p.n_keep * sizeof(double) : 0);
   pl.use_gram = p.corr_src == FICOCO_C_COSINE && !pl.dense_rows && pl.Df % 8 == 0 && p.k_max <= 64 &&
@@ -559,7 +570,7 @@ int ficoco_v_step_static(ficoco_ctx* ctx, const ficoco_problem* p, void* X_out, 
   const char* why;
   const int rc = make_plan(*p, pl, &why);
   if (rc != FICOCO_OK) return fail(ctx, rc, fn, why);
-  if (pl.total - pl.qk_norm_bytes > FICOCO_STATIC_SCRATCH_BYTES || pl.total > kStaticScratchBytes)
+  if (pl.total - pl.beyond > FICOCO_STATIC_SCRATCH_BYTES || pl.total > kStaticScratchBytes)
     return fail(ctx, FICOCO_ENOMEM, fn, "the step's workspace exceeds the 32 MiB static scratch: use ficoco_v_step with a caller workspace");
   void* ws = ctx->device < kMaxDevices ? g_static_ws[ctx->device] : nullptr;
   if (!ws) return fail(ctx, FICOCO_EHIP, fn, "no static scratch on this device");

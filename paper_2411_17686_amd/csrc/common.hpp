@@ -52,8 +52,11 @@ struct Plan {
   size_t tgt_src;        // int32  [B][N^S*k_max] discarded token index per edge, by target
   size_t tgt_alpha;      // double [B][N^S*k_max]
   size_t hub_list, hub_cnt;   // int32 [B][n_keep], [B]: preserved tokens with long buckets (inverted lists only)
-  size_t share_cnt;      // int32  [B][invert_groups][n_keep]  edges per target from each share of the discarded rows (fused step, inverted lists)
-  size_t pair_tab;       // PairRec [B][N^S]     first two edges of every discarded row (fused step, lists not inverted)
+  int bkt_cap;           // fused step: edges kept per target while the lists are written (0: none)
+  size_t bkt_cnt;        // int32  [B][n_keep]            edges per target
+  size_t bkt_src;        // int32  [B][n_keep][bkt_cap]   their sources (bucket_entry), in order of arrival
+  size_t bkt_w;          // double [B][n_keep][bkt_cap]   their weights
+  size_t beyond;         // bytes of the regions that the limit of the static scratch does not count (qk_norm, bkt_*)
   size_t rowbuf;         // double [B][N^S][n_keep] (dense_rows only)
   size_t ct;             // float  [splits][B][N^S][n_keep]  approximate cosines (matrix-core path)
   size_t cmax;           // double [B][M]
@@ -69,7 +72,6 @@ struct Plan {
   int qk_nq, qk_visq;    // query rows that form needs, and how many of them are visual (all or none)
   int qk_images;         // images whose row normalisers the workspace holds at a time
   size_t qk_norm;        // float2 [qk_images][H][qk_nq] row normalisers
-  size_t qk_norm_bytes;
   bool use_gram;         // cosine correlation proposed by the MFMA tile kernel
   int gram_splits, gram_st_per_split;   // K ranges of that kernel and their length in 32-feature stages
   int f_chunks, f_rows_per_wg, Df;
@@ -131,33 +133,29 @@ void launch_gather(const ficoco_problem& p, const Plan& pl, const int32_t* keep_
                    int64_t sb, int64_t sn, int row_bytes, void* out, hipStream_t s);
 void launch_corr_gap(const ficoco_problem& p, const Plan& pl, char* ws, const int32_t* discard_idx,
                      const int32_t* keep_idx, double* gap, hipStream_t s);
-// targets_counted: the call follows the correlate stage of the same fused step, which counted the
-// edges per target and share of rows (inverted lists) or wrote the pair records (scanning merge)
-// while it wrote the lists; otherwise the compress stage works from the lists it is given alone
+// targets_listed: the call follows the correlate stage of the same fused step, which filled the
+// targets' lists; otherwise the compress stage works from the edge lists it is given alone
 void launch_compress(const ficoco_problem& p, const Plan& pl, char* ws, const int32_t* discard_idx,
                      const int32_t* keep_idx, const int32_t* edge_cnt, const int32_t* edge_tgt,
                      const double* edge_alpha, void* X_out, int32_t* pos_out,
-                     hipStream_t s, bool targets_counted = false);
-// Above kMatchMaxRows discarded tokens the compress stage first buckets the edges by target
-// (compress.hip).  The discarded rows are cut into invert_groups() shares of invert_share_rows()
-// consecutive rows, one workgroup of the bucketing kernel per share.  In a fused step the filter
-// stage clears a counter per (share, target) and the correlate stage adds one per edge it writes,
-// so the bucketing kernel starts from the counts instead of reading every list in every workgroup.
-// Up to kMatchMaxRows discarded tokens every workgroup of the merge stages the image's edges in LDS:
-// count, source token and the first two (target, weight) pairs of each discarded row.  Gathered
-// from the lists (rows of k_max slots) that is two or three cache lines per four rows and several
-// strided loads per thread, in every workgroup; in a fused step the correlate stage therefore also
-// writes those fields as one 32-byte record per row, which the merge reads with whole-line loads.
-struct alignas(16) PairRec {
-  int32_t cnt, src, t0, t1;
-  double a0, a1;
-};
-static_assert(sizeof(PairRec) == 32, "two 16-byte loads per record");
+                     hipStream_t s, bool targets_listed = false);
+// In a fused step the correlate stage drops every edge into the list of its target (bkt_*: a counter that
+// the filter stage clears, and up to bkt_cap (source, weight) pairs in order of arrival), and the
+// merge takes a row's sources from there.  Targets with more sources than a list holds work from the
+// edge lists; above kMatchMaxRows those with more than kHubMin sources are listed as they appear (hub_list).
+// A staged compress call has the edge lists alone: up to kMatchMaxRows discarded tokens
+// every workgroup of the merge scans the image's lists in LDS, above that they are first bucketed by
+// target (compress.hip), the discarded rows cut into invert_groups() shares of invert_share_rows()
+// consecutive rows, one workgroup of the bucketing kernel per share.
 constexpr int kMatchMaxRows = 1024;
 constexpr int kInvertRows = 512;
-inline bool pair_records(const ficoco_problem& p, const Plan& pl) {     // (lists of at most 64 entries: one wavefront holds a row's edges)
-  return pl.n_disc > 0 && pl.n_disc <= kMatchMaxRows && p.k_max <= 64 && pl.fixed_k != 0;
-}
+constexpr int kHubMin = 32;        // targets with more sources than this are merged by a whole workgroup
+// Entries per target up to kMatchMaxRows discarded tokens and above: as many as a wavefront, and a workgroup, puts in
+// order.  (16 for the former: 37 us instead of 19 where two dozen of 144 targets have 17 to 29 sources.)
+constexpr int kBucketCap = 32, kBucketCapLong = 256;
+constexpr size_t kBucketBytes = (size_t)8 << 20;         // at most, for all images together: larger batches keep fewer
+static_assert(kMaxSelectN <= (1 << 16), "row and token of an entry");
+__host__ __device__ __forceinline__ int bucket_entry(int row, int token) { return row << 16 | token; }   // ascending like the rows
 inline bool edges_inverted(const Plan& pl) { return pl.n_disc > kMatchMaxRows; }
 inline int invert_groups(const Plan& pl) { return (pl.n_disc + kInvertRows - 1) / kInvertRows; }
 inline int invert_share_rows(const Plan& pl) {
@@ -344,6 +342,20 @@ __device__ __forceinline__ int block_scan_inclusive(int v, int* scratch, int* to
   *total = tot;
   __syncthreads();
   return incl + before;
+}
+
+// The nearest float of a double lies on the same side of every midpoint between two bfloat16 as the
+// double itself, unless it IS such a midpoint (its low half reads 0x8000; denormals are kept, so the
+// same holds there).
+__device__ __forceinline__ bool bf16_midpoint(float f) { return (__float_as_uint(f) & 0xffffu) == 0x8000u; }
+// `off`: any double with the sign of value - midpoint, zero for a tie: one step off the midpoint on that side
+__device__ __forceinline__ float off_midpoint(float f, double off) {
+  const uint32_t u = __float_as_uint(f);
+  return off == 0.0 ? f : __uint_as_float((off > 0.0) == ((u >> 31) == 0u) ? u + 1u : u - 1u);
+}
+__device__ __forceinline__ uint32_t bf16_bits(float f) {  // nearest bfloat16 of a float, ties to even, in the high half
+  const uint32_t u = __float_as_uint(f);
+  return u + 0x7fffu + ((u >> 16) & 1u);
 }
 
 // Round a double to the nearest bfloat16, ties to even, straight from double (no

@@ -29,22 +29,17 @@ struct InvertArgs {
   double* tgt_alpha;
   int32_t* hub_list;   // [B][n_keep]  preserved tokens with more than kHubMin sources (any order)
   int32_t* hub_cnt;    // [B]
-  const int32_t* share_cnt;   // [B][gridDim.x][n_keep] edges per (share of rows, target) counted by the correlate stage, or null
   int share_rows;      // discarded rows per workgroup
 };
 
-constexpr int kHubMin = 32;        // buckets longer than this are merged by a whole workgroup
-
-// Buckets the edges of one image by target.  gridDim.x workgroups share an image, each owning
-// share_rows consecutive discarded rows.  Every workgroup needs, per target, the number of edges
-// of the whole image and the number from rows before its own share: the prefix sum of the former
-// gives the bucket offsets, and offset + "before" is where this workgroup's own rows start inside
-// each bucket.  Then it scatters its rows.  The two numbers come from the counters the correlate
-// stage kept per (share, target) while it wrote the lists (share_cnt, a fused step), or else from
-// a pass of every workgroup over ALL lists of the image into an LDS histogram (it needs no
-// exchange between workgroups and nothing cleared beforehand).  Bucket regions per workgroup
-// are fixed either way; only the order inside a region depends on scheduling (the merge orders
-// buckets itself).
+// Buckets the edges of one image by target (a staged compress call, whose lists are the caller's).
+// gridDim.x workgroups share an image, each owning share_rows consecutive discarded rows.  Every
+// workgroup needs, per target, the number of edges of the whole image and the number from rows
+// before its own share: the prefix sum of the former gives the bucket offsets, and offset + "before"
+// is where this workgroup's own rows start inside each bucket.  So each makes a pass over ALL lists
+// of the image into an LDS histogram (no exchange between workgroups, nothing cleared beforehand),
+// then scatters its rows.  Bucket regions per workgroup are fixed; only the order inside a region
+// depends on scheduling (the merge orders buckets itself).
 template <int CH>   // consecutive list slots one thread loads at a time: 4 (rows of 4k slots, 16-byte aligned lists) or 1
 __global__ __launch_bounds__(kSelectThreads) void invert_edges_kernel(InvertArgs a) {
   extern __shared__ int lds_i[];
@@ -66,57 +61,34 @@ __global__ __launch_bounds__(kSelectThreads) void invert_edges_kernel(InvertArgs
       v[0] = tgt[f];
     }
   };
-  if (a.share_cnt) {             // counted while the lists were written: add the shares up
-    const int32_t* sc = a.share_cnt + b * (int64_t)gridDim.x * n;
-    constexpr int kShareBatch = 8;      // counters one thread has in flight together
-    const int shares = gridDim.x, mine = blockIdx.x;
-    for (int j = tid; j < n; j += nt) {
-      int all = 0, before = 0;
-      for (int s0 = 0; s0 < shares; s0 += kShareBatch) {
-        int c[kShareBatch];
+  // Count pass over every slot of the image.  Consecutive threads take consecutive slots, so a
+  // wavefront's load covers whole cache lines (a thread per row would touch every line of the
+  // lists once per slot position); kInvertBatch loads per thread are in flight together.
+  for (int j = tid; j <= n; j += nt) cnt[j] = 0;
+  for (int j = tid; j < n; j += nt) cursor[j] = 0;
+  __syncthreads();
+  constexpr int kInvertBatch = CH == 4 ? 8 : 16;     // loads of list slots one thread has in flight together
+  const int n_chunks = a.n_disc * a.k_max / CH;
+  for (int c0 = tid; c0 < n_chunks; c0 += nt * kInvertBatch) {
+    int v[kInvertBatch][CH], have[kInvertBatch], row[kInvertBatch];
 #pragma unroll
-        for (int u = 0; u < kShareBatch; ++u) c[u] = sc[(int64_t)min(s0 + u, shares - 1) * n + j];   // clamped: always a valid address
-        issue_fence();
-#pragma unroll
-        for (int u = 0; u < kShareBatch; ++u) {
-          if (s0 + u < shares) all += c[u];
-          if (s0 + u < mine) before += c[u];
-        }
-      }
-      cnt[j] = all;
-      cursor[j] = before;
+    for (int u = 0; u < kInvertBatch; ++u) {
+      const int f = min(c0 + u * nt, n_chunks - 1) * CH;   // clamped: always a valid address
+      row[u] = f / a.k_max;
+      have[u] = min(a.edge_cnt[rbase + row[u]], a.k_max) - (f - row[u] * a.k_max);   // list entries from slot f on
+      load_slots(f, v[u]);
     }
-    if (tid == 0) cnt[n] = 0;
-  } else {
-    // Count pass over every slot of the image.  Consecutive threads take consecutive slots, so a
-    // wavefront's load covers whole cache lines (a thread per row would touch every line of the
-    // lists once per slot position); kInvertBatch loads per thread are in flight together.
-    for (int j = tid; j <= n; j += nt) cnt[j] = 0;
-    for (int j = tid; j < n; j += nt) cursor[j] = 0;
-    __syncthreads();
-    constexpr int kInvertBatch = CH == 4 ? 8 : 16;     // loads of list slots one thread has in flight together
-    const int n_chunks = a.n_disc * a.k_max / CH;
-    for (int c0 = tid; c0 < n_chunks; c0 += nt * kInvertBatch) {
-      int v[kInvertBatch][CH], have[kInvertBatch], row[kInvertBatch];
+    issue_fence();
 #pragma unroll
-      for (int u = 0; u < kInvertBatch; ++u) {
-        const int f = min(c0 + u * nt, n_chunks - 1) * CH;   // clamped: always a valid address
-        row[u] = f / a.k_max;
-        have[u] = min(a.edge_cnt[rbase + row[u]], a.k_max) - (f - row[u] * a.k_max);   // list entries from slot f on
-        load_slots(f, v[u]);
-      }
-      issue_fence();
+    for (int u = 0; u < kInvertBatch; ++u) {
+      if (c0 + u * nt >= n_chunks) break;
+      const bool before = row[u] < r_lo;
 #pragma unroll
-      for (int u = 0; u < kInvertBatch; ++u) {
-        if (c0 + u * nt >= n_chunks) break;
-        const bool before = row[u] < r_lo;
-#pragma unroll
-        for (int q = 0; q < CH; ++q) {
-          const int j = v[u][q];
-          if (q < have[u] && j >= 0 && j < n) {
-            atomicAdd(&cnt[j], 1);
-            if (before) atomicAdd(&cursor[j], 1);
-          }
+      for (int q = 0; q < CH; ++q) {
+        const int j = v[u][q];
+        if (q < have[u] && j >= 0 && j < n) {
+          atomicAdd(&cnt[j], 1);
+          if (before) atomicAdd(&cursor[j], 1);
         }
       }
     }
@@ -198,7 +170,10 @@ struct MergeArgs {
   int32_t* pos_out;
   const int32_t* hub_list;   // bucket mode: targets with more than kHubMin sources ...
   const int32_t* hub_cnt;    // ... and their number; null: no such split
-  const PairRec* pair_tab;   // [B][n_disc] the staged fields of every discarded row as one record (fused step), or null
+  const int32_t* bkt_cnt;    // the targets' lists (fused step; see common.hpp)
+  const int32_t* bkt_src;
+  const double* bkt_w;
+  int bkt_cap;
   int average;      // ablation "average compression": every weight counts as one
   int extra_row;    // output row of the additional token of the convergent form (mean of the discarded tokens), or -1
 };
@@ -216,8 +191,39 @@ constexpr int kMergeWaves = 8;    // wavefronts (= output row spans) per workgro
 // (kMatchMaxRows, common.hpp: above that many discarded tokens the edge lists are inverted first)
 static_assert(kMatchMaxRows % (kMergeWaves * kWave) == 0, "a workgroup stages the edge table in whole rounds");
 constexpr int kMatchCap = 64;     // scanning mode: sources of one target kept in LDS
-constexpr int kBucketCap = 256;   // inverted lists: bucket entries put in order in LDS
-constexpr int kBucketPer = kBucketCap / kWave;
+constexpr int kInvertedCap = 256; // inverted lists: bucket entries put in order in LDS
+constexpr int kBucketPer = kInvertedCap / kWave;
+
+// num / den of eight elements, each quotient rounded to double and then to the token type.  With rden the
+// correctly rounded 1 / den, num * rden lies within two units in the last place of the quotient and
+// two residual corrections make it the correctly rounded one (Markstein): five instructions per
+// element where a division takes a dozen (den is 1 to a few thousand: no exponent is near its ends).
+// The rounding to bfloat16 goes by way of the nearest float.
+__device__ __forceinline__ double quotient(double num, double den, double rden) {
+  double q = num * rden;
+  q = __builtin_fma(__builtin_fma(-q, den, num), rden, q);
+  return __builtin_fma(__builtin_fma(-q, den, num), rden, q);
+}
+__device__ __forceinline__ void store_quotients(bf16_t* out, const double (&num)[kVec], double den, double rden) {
+  float f[kVec];
+#pragma unroll
+  for (int k = 0; k < kVec; ++k) {
+    const double q = quotient(num[k], den, rden);
+    f[k] = (float)q;
+    if (bf16_midpoint(f[k])) f[k] = off_midpoint(f[k], q - (double)f[k]);
+  }
+  uint32_t h[kVec];
+#pragma unroll
+  for (int k = 0; k < kVec; ++k) h[k] = bf16_bits(f[k]) >> 16;
+  const uint4 o = make_uint4(h[0] | h[1] << 16, h[2] | h[3] << 16, h[4] | h[5] << 16, h[6] | h[7] << 16);
+  __builtin_memcpy(out, &o, sizeof(o));
+}
+__device__ __forceinline__ void store_quotients(float* out, const double (&num)[kVec], double den, double rden) {
+  float f[kVec];
+#pragma unroll
+  for (int k = 0; k < kVec; ++k) f[k] = (float)quotient(num[k], den, rden);
+  __builtin_memcpy(out, f, sizeof(f));
+}
 
 // Accumulate w * X[src] into num (this lane's slices of the feature span starting at d0).
 template <typename T, int SLICE>
@@ -353,7 +359,7 @@ __device__ __forceinline__ EdgeTable edge_table(char* base, int n_disc) {
 // LDS carve-up of merge_rows_kernel, shared by the kernel and its launcher.
 template <bool MATCH, int SLICE, int WPU>
 struct MergeLds {
-  static constexpr int kCap = MATCH ? kMatchCap : kBucketCap;
+  static constexpr int kCap = MATCH ? kMatchCap : kInvertedCap;
   static constexpr int kUnits = kMergeWaves / WPU;
   static constexpr size_t kLists = (size_t)kMergeWaves * kCap * 12;
   static constexpr size_t kPartDoubles = WPU > 1 ? (size_t)kUnits * (WPU - 1) * SLICE * kVec * kWave : 0;
@@ -419,18 +425,7 @@ __device__ __forceinline__ int merge_unit(const MergeArgs& a, char* lds_m, int b
   constexpr int kStage = MATCH ? kMatchMaxRows / (kMergeWaves * kWave) : 1;   // edge-table rows per thread
   int st_cnt[kStage], st_src[kStage], st_t0[kStage], st_t1[kStage];
   double st_a0[kStage], st_a1[kStage];
-  if (MATCH && a.n_disc > 0 && a.pair_tab) {       // uniform: one record per row, two whole-line loads
-#pragma unroll
-    for (int q = 0; q < kStage; ++q) {
-      const int row = min((int)threadIdx.x + q * kMergeWaves * kWave, a.n_disc - 1);   // clamped: a valid row
-      const PairRec* rec = a.pair_tab + (b * a.n_disc + row);
-      const int4 head = *reinterpret_cast<const int4*>(rec);
-      const double2 wts = *reinterpret_cast<const double2*>(&rec->a0);
-      st_cnt[q] = head.x; st_src[q] = head.y; st_t0[q] = head.z; st_t1[q] = head.w;
-      st_a0[q] = a.average ? 1.0 : wts.x;
-      st_a1[q] = a.average ? 1.0 : wts.y;
-    }
-  } else if (MATCH && a.n_disc > 0) {
+  if (MATCH && a.n_disc > 0) {
     const int e1 = min(1, a.k_max - 1);
 #pragma unroll
     for (int q = 0; q < kStage; ++q) {
@@ -686,14 +681,12 @@ __device__ __forceinline__ int merge_unit(const MergeArgs& a, char* lds_m, int b
       den += wden[2 * (unit_l * WPU + w)];
     }
   }
+  const double rden = 1.0 / den;
 #pragma unroll
   for (int u = 0; u < SLICE; ++u) {
     const int d = d0 + (u * kWave + lane) * kVec;
     if (full[u]) {
-      Pack8<T> o;
-#pragma unroll
-      for (int k = 0; k < kVec; ++k) store_token(&o.v[k], num[u][k] / den);
-      __builtin_memcpy(out + d, &o, sizeof(o));
+      store_quotients(out + d, num[u], den, rden);
     } else {
       for (int k = 0; k < kVec; ++k)
         if (d + k < a.D) store_token(out + d + k, num[u][k] / den);
@@ -825,11 +818,274 @@ __device__ __forceinline__ void write_pos_out(const MergeArgs& a, int blk) {
 }
 
 template <typename T, bool MATCH, int SLICE, int WPU>
-__global__ __launch_bounds__(kMergeWaves * kWave) void merge_rows_kernel(MergeArgs a) {
+__global__ __launch_bounds__(kMergeWaves * kWave) __attribute__((amdgpu_waves_per_eu(6))) void merge_rows_kernel(MergeArgs a) {
   extern __shared__ __attribute__((aligned(16))) char lds_m[];
   const int deferred = merge_unit<T, MATCH, SLICE, WPU>(a, lds_m, blockIdx.x);
   if (MATCH && WPU == 1) merge_hub_targets<T, SLICE>(a, lds_m, deferred);
   if (WPU == 1) write_pos_out<SLICE>(a, blockIdx.x);
+}
+
+// Fused step: the sources of a target come from its list, which the correlate stage filled, and
+// nothing but the row itself is left to wait for: index, list and count are one trip to memory, the
+// row and all its sources the second.  (Scanning the edge table that every workgroup staged in LDS
+// was a third, behind a barrier; buckets were a launch of their own.)  The list arrived in any order: its
+// entries are put in ascending order by rank counting across the wavefront.  A target with more than
+// kHubMin sources (or than its list holds) is left to a whole workgroup.  Returns their number.
+// Measured against that form: 15.4 -> 12.4 us at 16 x 385 rows of 1024, 24.7 -> 19.5 us at 8 x 243 rows of
+// 4096; above 1024 discarded tokens 31 -> 14 us (bucketing launch included) at 4 x 641 rows of 1024
+// and 32 -> 17.5 us at 1152, for 0.3 to 0.6 us more in the correlate stage.  A plain copy of the rows
+// takes 11.5 us in the first of these, the divisions 2 us.  Wide spans run at six wavefronts per SIMD
+// (the whole grid on the chip at once), narrow ones at five: at six they spill (6.2 us for 5.8 at
+// 99 rows of 1024, 17.9 for 14.0 at 4 x 641), at four too few are there (15.5).
+template <typename T, int SLICE>
+__device__ __forceinline__ int merge_listed_unit(const MergeArgs& a, char* lds_m, int blk) {
+  constexpr int kSpan = kWave * kVec * SLICE;
+  const int lane = threadIdx.x % kWave, wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  double* l_w = (double*)lds_m + wv * kMatchCap;
+  int* l_src = (int*)((double*)lds_m + kMergeWaves * kMatchCap) + wv * kMatchCap;
+  const int n_spans = (a.D + kSpan - 1) / kSpan;
+  const int unit = blk * kMergeWaves + wv;
+  const int64_t b = blockIdx.y;
+  const int r = unit / n_spans, d0 = (unit % n_spans) * kSpan;
+  if (r >= a.n_out || r == a.extra_row) return 0;       // the additional token is written by extra_token_kernel
+  const T* Xb = (const T*)a.X + b * a.xsb;
+  T* out = (T*)a.X_out + (b * a.n_out + r) * (int64_t)a.D;
+  int t = r, n_src = 0, my_src = 0x7fffffff;
+  double my_w = 0.0;
+  if (r >= a.vis_begin && r < a.vis_begin + a.n_keep) {  // uniform
+    const int64_t at = b * a.n_keep + (r - a.vis_begin);
+    const int e = min(lane, a.bkt_cap - 1);
+    const int tok = a.T[at];
+    n_src = a.bkt_cnt[at];
+    my_src = a.bkt_src[at * a.bkt_cap + e];
+    my_w = a.bkt_w[at * a.bkt_cap + e];
+    issue_fence();
+    t = a.vis_begin + min(max(tok, 0), a.N - 1);         // index sets are device data: stay inside the span
+    if (n_src > min(a.bkt_cap, kHubMin)) return n_src;
+  } else if (r >= a.vis_begin + a.n_keep) {
+    t = r + a.n_disc - (a.extra_row >= 0 ? 1 : 0);
+  }
+  const T* x = Xb + (int64_t)t * a.xsn;
+  bool full[SLICE];
+  Raw8<T> xr[SLICE];
+#pragma unroll
+  for (int u = 0; u < SLICE; ++u) {
+    full[u] = d0 + (u * kWave + lane) * kVec + kVec <= a.D;
+    if (full[u]) load_raw(x + d0 + (u * kWave + lane) * kVec, xr[u]);
+  }
+  if (n_src <= 0) {                                      // nothing merged into this row: exact copy
+#pragma unroll
+    for (int u = 0; u < SLICE; ++u) {
+      const int d = d0 + (u * kWave + lane) * kVec;
+      if (full[u]) __builtin_memcpy(out + d, &xr[u], sizeof(xr[u]));
+      else
+        for (int k = 0; k < kVec; ++k)
+          if (d + k < a.D) out[d + k] = x[d + k];
+    }
+    return 0;
+  }
+  my_src = lane < n_src ? my_src : 0x7fffffff;
+  int rank = 0;
+  for (int q = 0; q < n_src; ++q) rank += lane_value(my_src, q) < my_src ? 1 : 0;
+  if (lane < n_src) { l_src[rank] = my_src & 0xffff; l_w[rank] = a.average ? 1.0 : my_w; }
+  double num[SLICE][kVec];
+#pragma unroll
+  for (int u = 0; u < SLICE; ++u) {
+    const int d = d0 + (u * kWave + lane) * kVec;
+#pragma unroll
+    for (int k = 0; k < kVec; ++k) num[u][k] = 0.0;
+    if (full[u]) add_raw(xr[u], num[u]);
+    else
+      for (int k = 0; k < kVec; ++k) num[u][k] = d + k < a.D ? widen(x[d + k]) : 0.0;
+  }
+  double den = 1.0;
+  for (int e = 0; e < n_src; ++e) den += l_w[e];
+  const double rden = 1.0 / den;
+  add_sources<T, SLICE, 16>(a, Xb, l_src, l_w, n_src, d0, lane, full, num);
+#pragma unroll
+  for (int u = 0; u < SLICE; ++u) {
+    const int d = d0 + (u * kWave + lane) * kVec;
+    if (full[u]) {
+      store_quotients(out + d, num[u], den, rden);
+    } else {
+      for (int k = 0; k < kVec; ++k)
+        if (d + k < a.D) store_token(out + d + k, num[u][k] / den);
+    }
+  }
+  return 0;
+}
+
+// LDS of a workgroup that adds up the targets with more than kHubMin sources above kMatchMaxRows discarded tokens:
+// the wavefronts' lists, in their place afterwards the sums of seven wavefronts, then the sums of weights.
+template <int SLICE>
+struct HubLds {
+  static constexpr size_t kLists = (size_t)kMergeWaves * kInvertedCap * 12;
+  static constexpr size_t kParts = (size_t)(kMergeWaves - 1) * SLICE * kVec * kWave * 8;
+  static constexpr size_t kArea = kLists > kParts ? kLists : kParts;
+  static constexpr size_t kBytes = kArea + kMergeWaves * 8;
+  static_assert(kLists >= (size_t)kMergeWaves * kMatchCap * 12, "the one-wavefront units use the same area");
+};
+
+// Such a target: the discarded rows are cut into eight contiguous parts, each wavefront adds the sources
+// of its part in ascending order, and the eight sums are added in order.  The sources come from the
+// target's list, or, if that could not hold them all, from the edge lists of the part.
+template <typename T, int SLICE>
+__device__ __forceinline__ void merge_hub_parts(const MergeArgs& a, char* lds_m, int j, int d0, int n_all) {
+  const int lane = threadIdx.x % kWave, wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  double* l_w = (double*)lds_m + wv * kInvertedCap;
+  int* l_src = (int*)((double*)lds_m + kMergeWaves * kInvertedCap) + wv * kInvertedCap;
+  double* part = (double*)lds_m;                                 // [kMergeWaves-1][SLICE*kVec][64], once the lists are used
+  double* wden = (double*)(lds_m + HubLds<SLICE>::kArea);
+  const int64_t b = blockIdx.y, at = b * a.n_keep + j;
+  const T* Xb = (const T*)a.X + b * a.xsb;
+  const int part_rows = ((a.n_disc + kMergeWaves - 1) / kMergeWaves + kWave - 1) / kWave * kWave;
+  const int row_lo = min(wv * part_rows, a.n_disc), row_hi = min(row_lo + part_rows, a.n_disc);
+  bool full[SLICE];
+  double num[SLICE][kVec];
+#pragma unroll
+  for (int u = 0; u < SLICE; ++u) {
+    full[u] = d0 + (u * kWave + lane) * kVec + kVec <= a.D;
+#pragma unroll
+    for (int k = 0; k < kVec; ++k) num[u][k] = 0.0;
+  }
+  double den = 0.0;
+  if (wv == 0) {                                         // the row's own value is the first term
+    den = 1.0;
+    const T* x = Xb + (int64_t)(a.vis_begin + min(max(a.T[at], 0), a.N - 1)) * a.xsn;
+#pragma unroll
+    for (int u = 0; u < SLICE; ++u) {
+      const int d = d0 + (u * kWave + lane) * kVec;
+      if (full[u]) load8<T>(x + d, num[u]);
+      else
+        for (int k = 0; k < kVec; ++k) num[u][k] = d + k < a.D ? widen(x[d + k]) : 0.0;
+    }
+  }
+  auto add_list = [&](int n) {
+    for (int e = 0; e < n; ++e) den += l_w[e];
+    add_sources<T, SLICE, 16>(a, Xb, l_src, l_w, n, d0, lane, full, num);
+  };
+  if (n_all <= a.bkt_cap) {                              // uniform
+    int key[kBucketPer], rank[kBucketPer], n = 0;
+    double w[kBucketPer];
+#pragma unroll
+    for (int q = 0; q < kBucketPer; ++q) {
+      const int e = min(q * kWave + lane, n_all - 1);
+      key[q] = a.bkt_src[at * a.bkt_cap + e];
+      w[q] = a.average ? 1.0 : a.bkt_w[at * a.bkt_cap + e];
+      rank[q] = 0;
+    }
+#pragma unroll
+    for (int q = 0; q < kBucketPer; ++q) {
+      const int row = key[q] >> 16;
+      const bool mine = q * kWave + lane < n_all && row >= row_lo && row < row_hi;
+      const unsigned long long m = __ballot(mine);
+      if (mine) l_src[n + __popcll(m & ((1ULL << lane) - 1ULL))] = key[q];
+      else key[q] = -1;
+      n += __popcll(m);
+    }
+    for (int l = 0; l < n; ++l) {
+      const int v = l_src[l];
+#pragma unroll
+      for (int q = 0; q < kBucketPer; ++q) rank[q] += v < key[q] ? 1 : 0;
+    }
+#pragma unroll
+    for (int q = 0; q < kBucketPer; ++q)
+      if (key[q] >= 0) { l_src[rank[q]] = key[q] & 0xffff; l_w[rank[q]] = w[q]; }     // (all reads of the keys precede these writes)
+    if (n > 0) add_list(n);
+  } else {
+    for (int base = row_lo; base < row_hi; base += kWave) {
+      const int64_t rr = b * a.n_disc + min(base + lane, row_hi - 1);
+      const int cnt = base + lane < row_hi ? min(a.edge_cnt[rr], a.k_max) : 0;
+      bool hit = false;
+      double w = 1.0;
+      for (int e = 0; e < cnt; ++e)
+        if (a.edge_tgt[rr * a.k_max + e] == j) { hit = true; if (!a.average) w = a.edge_alpha[rr * a.k_max + e]; }
+      const unsigned long long m = __ballot(hit);
+      if (hit) {
+        const int slot = __popcll(m & ((1ULL << lane) - 1ULL));
+        l_src[slot] = a.S[rr];
+        l_w[slot] = w;
+      }
+      if (m) add_list(__popcll(m));
+    }
+  }
+  __syncthreads();                                       // every list is used up
+  if (wv > 0) {
+    double* dst = part + (size_t)(wv - 1) * SLICE * kVec * kWave + lane;
+#pragma unroll
+    for (int u = 0; u < SLICE; ++u)
+#pragma unroll
+      for (int k = 0; k < kVec; ++k) dst[(u * kVec + k) * kWave] = num[u][k];
+  }
+  if (lane == 0) wden[wv] = den;
+  __syncthreads();
+  if (wv == 0) {
+#pragma unroll 1
+    for (int w = 1; w < kMergeWaves; ++w) {
+      const double* src = part + (size_t)(w - 1) * SLICE * kVec * kWave + lane;
+#pragma unroll
+      for (int u = 0; u < SLICE; ++u)
+#pragma unroll
+        for (int k = 0; k < kVec; ++k) num[u][k] += src[(u * kVec + k) * kWave];
+      den += wden[w];
+    }
+    T* out = (T*)a.X_out + (b * a.n_out + a.vis_begin + j) * (int64_t)a.D;
+    const double rden = 1.0 / den;
+#pragma unroll
+    for (int u = 0; u < SLICE; ++u) {
+      const int d = d0 + (u * kWave + lane) * kVec;
+      if (full[u]) store_quotients(out + d, num[u], den, rden);
+      else
+        for (int k = 0; k < kVec; ++k)
+          if (d + k < a.D) store_token(out + d + k, num[u][k] / den);
+    }
+  }
+  __syncthreads();                                       // the sums in LDS are written again by the next target
+}
+
+// Up to kMatchMaxRows discarded tokens: the workgroup of a left target adds it from the edge table.
+template <typename T, int SLICE>
+__global__ __launch_bounds__(kMergeWaves * kWave) __attribute__((amdgpu_waves_per_eu(SLICE == 1 ? 5 : 6))) void merge_listed_kernel(MergeArgs a) {
+  extern __shared__ __attribute__((aligned(16))) char lds_m[];
+  const int deferred = merge_listed_unit<T, SLICE>(a, lds_m, blockIdx.x);
+  if (!__syncthreads_or(deferred)) return;
+  // the edge table of the image, from the lists
+  using Lds = MergeLds<true, SLICE, 1>;
+  const EdgeTable tb = edge_table(lds_m + Lds::kLists + Lds::kPartDoubles * 8 + Lds::kDen, a.n_disc);
+  const int64_t b = blockIdx.y;
+  const int e1 = min(1, a.k_max - 1);
+  for (int row = threadIdx.x; row < a.n_disc; row += kMergeWaves * kWave) {
+    const int64_t rr = b * a.n_disc + row;
+    tb.cnt[row] = min(a.edge_cnt[rr], a.k_max);
+    tb.src[row] = a.S[rr];
+    tb.t0[row] = a.edge_tgt[rr * a.k_max];
+    tb.t1[row] = a.edge_tgt[rr * a.k_max + e1];
+    tb.a0[row] = a.average ? 1.0 : a.edge_alpha[rr * a.k_max];
+    tb.a1[row] = a.average ? 1.0 : a.edge_alpha[rr * a.k_max + e1];
+  }
+  merge_hub_targets<T, SLICE>(a, lds_m, deferred);     // (begins with a barrier)
+}
+
+// Above: the first hub_blocks workgroups of an image take the left targets, which the correlate stage
+// listed: unit (target, span) u by workgroup u mod hub_blocks; the others eight one-wavefront units
+// each.  They come first because the long targets take longest: left to the workgroups of their
+// rows, several of them one after the other, the launch took 57 us at 1152 rows of 1024 and 8064 discarded
+// tokens.
+template <typename T, int SLICE>
+__global__ __launch_bounds__(kMergeWaves * kWave) __attribute__((amdgpu_waves_per_eu(5))) void merge_listed_long_kernel(MergeArgs a, int hub_blocks) {
+  extern __shared__ __attribute__((aligned(16))) char lds_m[];
+  if ((int)blockIdx.x >= hub_blocks) {
+    (void)merge_listed_unit<T, SLICE>(a, lds_m, blockIdx.x - hub_blocks);
+    return;
+  }
+  constexpr int kSpan = kWave * kVec * SLICE;
+  const int n_spans = (a.D + kSpan - 1) / kSpan;
+  const int64_t at = (int64_t)blockIdx.y * a.n_keep;
+  const int n_units = min(a.hub_cnt[blockIdx.y], a.n_keep) * n_spans;     // uniform
+  for (int u = blockIdx.x; u < n_units; u += hub_blocks) {
+    const int j = a.hub_list[at + u / n_spans];
+    merge_hub_parts<T, SLICE>(a, lds_m, j, u % n_spans * kSpan, a.bkt_cnt[at + j]);
+  }
 }
 
 // Bucket mode, both passes in one launch (no launch gap separates them): the first `hub_blocks`
@@ -921,12 +1177,24 @@ static void launch_merge_scan(const MergeArgs& m, int B, hipStream_t s) {
   const size_t lds = Lds::bytes(m.n_disc);
   const int units = m.n_out * n_spans;
   dim3 grid((units + Lds::kUnits - 1) / Lds::kUnits, B), block(kMergeWaves * kWave);
-  if (lds > 32768)
-    (void)hipFuncSetAttribute((const void*)merge_rows_kernel<T, true, SLICE, 1>,
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  hipLaunchKernelGGL((merge_rows_kernel<T, true, SLICE, 1>), grid, block, lds, s, m);
+  auto go = [&](auto kern) {
+    if (lds > 32768) (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    hipLaunchKernelGGL(kern, grid, block, lds, s, m);
+  };
+  if (m.bkt_cnt) go(merge_listed_kernel<T, SLICE>);
+  else go(merge_rows_kernel<T, true, SLICE, 1>);
 }
 
+// More discarded tokens than that, with the targets' lists.
+template <typename T>
+static void launch_merge_listed_long(const MergeArgs& m, int B, hipStream_t s) {
+  constexpr int kSpan = kWave * kVec;
+  const int n_spans = (m.D + kSpan - 1) / kSpan;
+  const int hub_blocks = std::min(m.n_keep * n_spans, std::max(64, 512 / B));
+  const int row_blocks = (m.n_out * n_spans + kMergeWaves - 1) / kMergeWaves;
+  hipLaunchKernelGGL((merge_listed_long_kernel<T, 1>), dim3(hub_blocks + row_blocks, B), dim3(kMergeWaves * kWave),
+                     HubLds<1>::kBytes, s, m, hub_blocks);
+}
 template <typename T, int SLICE>
 static void launch_merge_buckets(const MergeArgs& m, int B, hipStream_t s) {
   using L1 = MergeLds<false, SLICE, 1>;
@@ -946,9 +1214,9 @@ static void launch_merge_buckets(const MergeArgs& m, int B, hipStream_t s) {
 void launch_compress(const ficoco_problem& p, const Plan& pl, char* ws, const int32_t* discard_idx,
                      const int32_t* keep_idx, const int32_t* edge_cnt, const int32_t* edge_tgt,
                      const double* edge_alpha, void* X_out, int32_t* pos_out,
-                     hipStream_t s, bool targets_counted) {
-  const bool match = !edges_inverted(pl);
-  if (pl.n_disc > 0 && !match) {
+                     hipStream_t s, bool targets_listed) {
+  const bool match = !edges_inverted(pl), listed = targets_listed && pl.bkt_cap > 0;
+  if (pl.n_disc > 0 && !match && !listed) {
     InvertArgs a{};
     a.n_keep = p.n_keep; a.n_disc = pl.n_disc; a.k_max = p.k_max;
     a.edge_cnt = edge_cnt; a.edge_tgt = edge_tgt; a.edge_alpha = edge_alpha;
@@ -964,7 +1232,6 @@ void launch_compress(const ficoco_problem& p, const Plan& pl, char* ws, const in
     auto kern = quads ? invert_edges_kernel<4> : invert_edges_kernel<1>;
     if (lds > 32768)
       (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    a.share_cnt = targets_counted ? (const int32_t*)(ws + pl.share_cnt) : nullptr;
     a.share_rows = invert_share_rows(pl);
     hipLaunchKernelGGL(kern, dim3(invert_groups(pl), p.B), dim3(kSelectThreads), lds, s, a);
   }
@@ -979,7 +1246,16 @@ void launch_compress(const ficoco_problem& p, const Plan& pl, char* ws, const in
   m.edge_cnt = edge_cnt; m.edge_tgt = edge_tgt; m.edge_alpha = edge_alpha;
   m.pos = p.pos; m.pos_out = pos_out;
   m.average = p.compress_mode == FICOCO_COMPRESS_AVERAGE ? 1 : 0;
-  m.pair_tab = targets_counted && match && pair_records(p, pl) ? (const PairRec*)(ws + pl.pair_tab) : nullptr;
+  if (listed) {
+    m.bkt_cnt = (const int32_t*)(ws + pl.bkt_cnt);
+    m.bkt_src = (const int32_t*)(ws + pl.bkt_src);
+    m.bkt_w = (const double*)(ws + pl.bkt_w);
+    m.bkt_cap = pl.bkt_cap;
+  }
+  if (!match) {
+    m.hub_list = (const int32_t*)(ws + pl.hub_list);
+    m.hub_cnt = (const int32_t*)(ws + pl.hub_cnt);
+  }
   m.extra_row = pl.extra_token ? p.vis_begin + p.n_keep : -1;
   // Narrow spans (one 8-element vector per lane) double the number of wavefronts: taken when the
   // wide ones would not fill the chip.  Bucket mode has two kinds of workgroups in its one launch:
@@ -992,9 +1268,9 @@ void launch_compress(const ficoco_problem& p, const Plan& pl, char* ws, const in
   if (match) {
     if (bf16) { if (slice == 1) launch_merge_scan<bf16_t, 1>(m, p.B, s); else launch_merge_scan<bf16_t, 2>(m, p.B, s); }
     else { if (slice == 1) launch_merge_scan<float, 1>(m, p.B, s); else launch_merge_scan<float, 2>(m, p.B, s); }
+  } else if (listed) {
+    if (bf16) launch_merge_listed_long<bf16_t>(m, p.B, s); else launch_merge_listed_long<float>(m, p.B, s);
   } else {
-    m.hub_list = (const int32_t*)(ws + pl.hub_list);
-    m.hub_cnt = (const int32_t*)(ws + pl.hub_cnt);
     if (bf16) { if (slice == 1) launch_merge_buckets<bf16_t, 1>(m, p.B, s); else launch_merge_buckets<bf16_t, 2>(m, p.B, s); }
     else { if (slice == 1) launch_merge_buckets<float, 1>(m, p.B, s); else launch_merge_buckets<float, 2>(m, p.B, s); }
   }

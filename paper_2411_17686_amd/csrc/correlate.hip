@@ -45,25 +45,25 @@ struct CorrArgs {
   int fixed_k;           // > 0: ablation "fixed K" (sel_m = K, sel_g = 0): of the values equal to the threshold only
                          // the lowest positions are taken, K targets in all; -1: every value >= threshold
   double* gap;           // correlation-gap diagnostic output [B][n_disc] (its own kernel)
-  int32_t* share_cnt;    // [B][shares][n_keep] edges written per (share of discarded rows, target), cleared by the
-                         // filter stage of a fused step; null where the compress stage counts for itself
-  int shares, share_rows;
-  PairRec* pair_tab;     // [B][n_disc] first two edges of every row as one record (fused step, scanning merge), or null
+  int32_t* bkt_cnt;      // [B][n_keep] edges per target, cleared by the filter stage of a fused step, or null
+  int32_t* hub_list;     // [B][n_keep] targets with more than kHubMin sources, as they appear, or null ...
+  int32_t* hub_cnt;      // [B] ... and their number
+  int32_t* bkt_src;      // [B][n_keep][bkt_cap] the first of them: sources (bucket_entry) ...
+  double* bkt_w;         // ... and weights, in order of arrival (the merge orders them)
+  int bkt_cap;
 };
 
-// The record of discarded row `row` (source token i): written by one lane with two 16-byte stores.
-__device__ __forceinline__ void write_pair(const CorrArgs& a, int64_t b, int row, int cnt, int i, int t0, int t1,
-                                           double a0, double a1) {
-  PairRec r;
-  r.cnt = cnt; r.src = i; r.t0 = t0; r.t1 = t1; r.a0 = a0; r.a1 = a1;
-  a.pair_tab[b * a.n_disc + row] = r;
-}
-
-// One more edge from discarded row `row` to keep slot `tgt`: counted for the compress stage, which
-// buckets the edges by target (one workgroup per share of share_rows consecutive rows).
-__device__ __forceinline__ void count_edge(const CorrArgs& a, int64_t b, int row, int tgt) {
-  if (a.share_cnt && (unsigned)tgt < (unsigned)a.n_keep)
-    atomicAdd(&a.share_cnt[(b * a.shares + row / a.share_rows) * a.n_keep + tgt], 1);
+// One more edge, from discarded row `row` (token i) to keep slot `tgt` with weight `al`, for the
+// target's list that the compress stage of a fused step reads.
+__device__ __forceinline__ void emit_edge(const CorrArgs& a, int64_t b, int row, int i, int tgt, double al) {
+  if (a.bkt_cnt == nullptr || (unsigned)tgt >= (unsigned)a.n_keep) return;
+  const int64_t at = b * a.n_keep + tgt;
+  const int slot = atomicAdd(&a.bkt_cnt[at], 1);
+  if (slot < a.bkt_cap) {
+    a.bkt_src[at * a.bkt_cap + slot] = bucket_entry(row, i);
+    a.bkt_w[at * a.bkt_cap + slot] = al;
+  }
+  if (slot == kHubMin && a.hub_cnt) a.hub_list[b * a.n_keep + atomicAdd(&a.hub_cnt[b], 1)] = tgt;    // (once per target)
 }
 
 __device__ __forceinline__ double dot_bf16(const bf16_t* __restrict__ x, const bf16_t* __restrict__ y, int D) {
@@ -161,10 +161,7 @@ __device__ void corr_row_exact(const CorrArgs& a, const int64_t b, const int row
   const int i = a.S[b * a.n_disc + row];
   const int32_t* T = a.T + b * n;
   if ((unsigned)i >= (unsigned)a.N) {  // index sets are device data: never index with a bad one
-    if (lane == 0) {
-      a.edge_cnt[b * a.n_disc + row] = 0;
-      if (a.pair_tab) write_pair(a, b, row, 0, 0, 0, 0, 0.0, 0.0);
-    }
+    if (lane == 0) a.edge_cnt[b * a.n_disc + row] = 0;
     return;
   }
   const double* rowv = a.dense ? a.rowbuf + (b * a.n_disc + row) * n : nullptr;
@@ -256,20 +253,14 @@ __device__ void corr_row_exact(const CorrArgs& a, const int64_t b, const int row
       const double al = my_c / denom;
       a.edge_tgt[ebase + lane] = my_tgt;
       a.edge_alpha[ebase + lane] = al;
-      count_edge(a, b, row, my_tgt);
+      emit_edge(a, b, row, i, my_tgt, al);
     }
   } else if (live && lane == 0) {
     for (int e = 0; e < stored; ++e) {
       const double al = a.edge_alpha[ebase + e] / denom;
       a.edge_alpha[ebase + e] = al;
-      count_edge(a, b, row, a.edge_tgt[ebase + e]);
+      emit_edge(a, b, row, i, a.edge_tgt[ebase + e], al);
     }
-  }
-  if (a.pair_tab) {              // uniform (lists of at most 64 entries: lanes 0 and 1 hold the first two)
-    const double al = live && lane < stored ? my_c / denom : 0.0;
-    const int t0 = lane_value(my_tgt, 0), t1 = lane_value(my_tgt, 1);
-    const double a0 = lane_value(al, 0), a1 = lane_value(al, 1);
-    if (lane == 0) write_pair(a, b, row, live ? stored : 0, i, t0, t1, a0, a1);
   }
   if (lane == 0) {
     a.edge_cnt[b * a.n_disc + row] = live ? stored : 0;
@@ -456,10 +447,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void c
   const int i = a.S[b * a.n_disc + row];
   const int32_t* T = a.T + b * n;
   if ((unsigned)i >= (unsigned)a.N) {
-    if (lane == 0) {
-      a.edge_cnt[b * a.n_disc + row] = 0;
-      if (a.pair_tab) write_pair(a, b, row, 0, 0, 0, 0, 0.0, 0.0);
-    }
+    if (lane == 0) a.edge_cnt[b * a.n_disc + row] = 0;
     return;
   }
   // approximate direct term of the row: the matrix-core cosines, or (FiCoCo-L with the
@@ -654,7 +642,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void c
   const bool is_eq = myjj >= 0 && myv == tau;
   const int eq_rank = __popcll(__ballot(is_eq) & ((1ULL << lane) - 1ULL));   // candidates are in ascending target order
   unsigned long long hit = __ballot(myjj >= 0 && (known || myv > tau || (is_eq && eq_rank < tie_quota)));
-  const unsigned long long hit_all = hit;
   const int cnt = __popcll(hit);
   const int my_pos = __popcll(hit & ((1ULL << lane) - 1ULL));
   const bool mine = (hit >> lane) & 1ULL;
@@ -671,15 +658,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void c
     const double al = myv / denom;
     a.edge_tgt[ebase + my_pos] = myjj;
     a.edge_alpha[ebase + my_pos] = al;
-    count_edge(a, b, row, myjj);
-  }
-  if (a.pair_tab) {              // uniform; the lanes of the first two hits hold the first two edges
-    const double al = live && mine ? myv / denom : 0.0;
-    const unsigned long long rest = hit_all & (hit_all - 1);
-    const int l0 = hit_all ? __ffsll(hit_all) - 1 : 0, l1 = rest ? __ffsll(rest) - 1 : 0;
-    const int t0 = lane_value(myjj, l0), t1 = lane_value(myjj, l1);
-    const double a0 = lane_value(al, l0), a1 = lane_value(al, l1);
-    if (lane == 0) write_pair(a, b, row, live ? stored : 0, i, t0, t1, a0, a1);
+    emit_edge(a, b, row, i, myjj, al);
   }
   if (lane == 0) {
     a.edge_cnt[b * a.n_disc + row] = live ? stored : 0;
@@ -708,10 +687,7 @@ __global__ __launch_bounds__(256) void corr_attn_rows_kernel(CorrArgs a) {
   if (row >= a.n_disc) return;                 // whole wavefront leaves together
   const int i = a.S[b * a.n_disc + row];
   if ((unsigned)i >= (unsigned)a.N) {          // index sets are device data
-    if (lane == 0) {
-      a.edge_cnt[b * a.n_disc + row] = 0;
-      if (a.pair_tab) write_pair(a, b, row, 0, 0, 0, 0, 0.0, 0.0);
-    }
+    if (lane == 0) a.edge_cnt[b * a.n_disc + row] = 0;
     return;
   }
   const float* mrow = a.abar + (b * a.N + i) * a.map_pitch;
@@ -868,13 +844,7 @@ __global__ __launch_bounds__(256) void corr_attn_rows_kernel(CorrArgs a) {
     const double al = my_c / denom;
     a.edge_tgt[ebase + lane] = my_tgt;
     a.edge_alpha[ebase + lane] = al;
-    count_edge(a, b, row, my_tgt);
-  }
-  if (a.pair_tab) {              // uniform
-    const double al = live && lane < stored ? my_c / denom : 0.0;
-    const int t0 = lane_value(my_tgt, 0), t1 = lane_value(my_tgt, 1);
-    const double a0 = lane_value(al, 0), a1 = lane_value(al, 1);
-    if (lane == 0) write_pair(a, b, row, live ? stored : 0, i, t0, t1, a0, a1);
+    emit_edge(a, b, row, i, my_tgt, al);
   }
   if (lane == 0) {
     a.edge_cnt[b * a.n_disc + row] = live ? stored : 0;
@@ -961,11 +931,15 @@ void launch_correlate(const ficoco_problem& p, const Plan& pl, char* ws, const i
   // J_i is the top_k largest values where the next one is clear of them: the threshold lies strictly
   // between v[f] and v[f+1] (g well inside (0, 1)), or at v[f] itself (g = 0, fixed K)
   a.top_k = pl.sel_g == 0.0 ? pl.sel_m : (pl.sel_g > 1e-6 && pl.sel_g < 1.0 - 1e-6) ? pl.sel_m - 1 : 0;
-  if (fused && pair_records(p, pl)) a.pair_tab = (PairRec*)(ws + pl.pair_tab);
-  if (fused && edges_inverted(pl)) {
-    a.share_cnt = (int32_t*)(ws + pl.share_cnt);
-    a.shares = invert_groups(pl);
-    a.share_rows = invert_share_rows(pl);
+  if (fused && pl.bkt_cap > 0) {
+    a.bkt_cnt = (int32_t*)(ws + pl.bkt_cnt);
+    a.bkt_src = (int32_t*)(ws + pl.bkt_src);
+    a.bkt_w = (double*)(ws + pl.bkt_w);
+    a.bkt_cap = pl.bkt_cap;
+    if (edges_inverted(pl)) {
+      a.hub_list = (int32_t*)(ws + pl.hub_list);
+      a.hub_cnt = (int32_t*)(ws + pl.hub_cnt);
+    }
   }
   dim3 grid((pl.n_disc + 3) / 4, p.B), block(256);
   if (a.mode == kAttnV && !pl.dense_rows && p.k_max <= kWave) {

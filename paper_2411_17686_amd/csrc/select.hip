@@ -38,8 +38,9 @@ struct SelectArgs {
   int32_t* keep_idx;
   int32_t* slot_of;
   int32_t* overflow;        // zeroed here for the correlate stage (fused step only), may be null
-  int32_t* share_cnt;       // [B][share_n] edge counters of the correlate stage, zeroed here (fused step with inverted edge lists), or null
-  int share_n;
+  int32_t* edge_cnt;        // [B][n_keep] edge counters of the targets' lists, zeroed here (fused step), or null
+  int32_t* hub_cnt;         // [B] number of long targets listed there, zeroed here as well, or null
+  int n_keep;
   int32_t* pos_out;         // [B][n_keep] position ids of the preserved tokens (fused step: written here, beside keep_idx), or null
   // Exact re-evaluation of the cosine-derived terms for tokens whose decision is within the error
   // bound of the bulk evaluation (exact_r: the mean-cosine term, exact_g: the equivalent-token term)
@@ -687,8 +688,9 @@ __global__ __launch_bounds__(kSelectThreads) void select_kernel(SelectArgs a) {
   }
   if (!a.do_filter) return;
   if (a.overflow && tid == 0) a.overflow[b] = 0;
-  if (a.share_cnt)
-    for (int j = tid; j < a.share_n; j += nt) a.share_cnt[(int64_t)b * a.share_n + j] = 0;
+  if (a.hub_cnt && tid == 0) a.hub_cnt[b] = 0;
+  if (a.edge_cnt)
+    for (int j = tid; j < a.n_keep; j += nt) a.edge_cnt[(int64_t)b * a.n_keep + j] = 0;
   // ---- K*, flags and ordered compaction --------------------------------------------------------
   // Thread t owns the contiguous run [lo, hi) of tokens (at most kTokensPerThread of them).
   const int per = (N + nt - 1) / nt;
@@ -985,9 +987,10 @@ void launch_select(const ficoco_problem& p, const Plan& pl, char* ws, double* sc
   a.slot_of = (int32_t*)(ws + pl.slot_of);
   a.overflow = overflow;
   a.pos_out = do_filter ? pos_out : nullptr;
-  if (overflow && edges_inverted(pl)) {      // a fused step: the correlate stage counts its edges per target
-    a.share_cnt = (int32_t*)(ws + pl.share_cnt);
-    a.share_n = invert_groups(pl) * p.n_keep;
+  if (overflow && pl.bkt_cap > 0) {          // a fused step: the correlate stage fills the targets' lists
+    a.edge_cnt = (int32_t*)(ws + pl.bkt_cnt);
+    if (edges_inverted(pl)) a.hub_cnt = (int32_t*)(ws + pl.hub_cnt);
+    a.n_keep = p.n_keep;
   }
   const size_t lds = select_lds(p, penalty);
   const bool exact = a.exact_r || a.exact_g;
