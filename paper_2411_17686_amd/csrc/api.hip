@@ -250,10 +250,10 @@ int make_plan(const ficoco_problem& p, Plan& pl, const char** why) {
     // (shorter lists leave more targets to the edge lists; below a quarter / an eighth nothing is gained)
     const int least = edges_inverted(pl) ? kBucketCapLong / 8 : kBucketCap / 4;
     pl.bkt_cap = edges_inverted(pl) ? kBucketCapLong : kBucketCap;
-    while (pl.bkt_cap >= least && targets * pl.bkt_cap * entry > kBucketBytes) pl.bkt_cap /= 2;
+    while (pl.bkt_cap >= least && targets * (pl.bkt_cap * entry + edge_cnt_stride(pl) * sizeof(int32_t)) > kBucketBytes) pl.bkt_cap /= 2;
     if (pl.bkt_cap < least) pl.bkt_cap = 0;
     const size_t before = off;
-    pl.bkt_cnt = take(pl.bkt_cap ? targets * sizeof(int32_t) : 0);
+    pl.bkt_cnt = take(pl.bkt_cap ? targets * edge_cnt_stride(pl) * sizeof(int32_t) : 0);
     pl.bkt_src = take(targets * pl.bkt_cap * sizeof(int32_t));
     pl.bkt_w = take(targets * pl.bkt_cap * sizeof(double));
     pl.beyond += off - before;

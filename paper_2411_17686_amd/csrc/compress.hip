@@ -173,7 +173,7 @@ struct MergeArgs {
   const int32_t* bkt_cnt;    // the targets' lists (fused step; see common.hpp)
   const int32_t* bkt_src;
   const double* bkt_w;
-  int bkt_cap;
+  int bkt_cap, cnt_stride;
   int average;      // ablation "average compression": every weight counts as one
   int extra_row;    // output row of the additional token of the convergent form (mean of the discarded tokens), or -1
 };
@@ -856,7 +856,7 @@ __device__ __forceinline__ int merge_listed_unit(const MergeArgs& a, char* lds_m
     const int64_t at = b * a.n_keep + (r - a.vis_begin);
     const int e = min(lane, a.bkt_cap - 1);
     const int tok = a.T[at];
-    n_src = a.bkt_cnt[at];
+    n_src = a.bkt_cnt[at * a.cnt_stride];
     my_src = a.bkt_src[at * a.bkt_cap + e];
     my_w = a.bkt_w[at * a.bkt_cap + e];
     issue_fence();
@@ -1084,7 +1084,7 @@ __global__ __launch_bounds__(kMergeWaves * kWave) __attribute__((amdgpu_waves_pe
   const int n_units = min(a.hub_cnt[blockIdx.y], a.n_keep) * n_spans;     // uniform
   for (int u = blockIdx.x; u < n_units; u += hub_blocks) {
     const int j = a.hub_list[at + u / n_spans];
-    merge_hub_parts<T, SLICE>(a, lds_m, j, u % n_spans * kSpan, a.bkt_cnt[at + j]);
+    merge_hub_parts<T, SLICE>(a, lds_m, j, u % n_spans * kSpan, a.bkt_cnt[(at + j) * a.cnt_stride]);
   }
 }
 
@@ -1251,6 +1251,7 @@ void launch_compress(const ficoco_problem& p, const Plan& pl, char* ws, const in
     m.bkt_src = (const int32_t*)(ws + pl.bkt_src);
     m.bkt_w = (const double*)(ws + pl.bkt_w);
     m.bkt_cap = pl.bkt_cap;
+    m.cnt_stride = edge_cnt_stride(pl);
   }
   if (!match) {
     m.hub_list = (const int32_t*)(ws + pl.hub_list);

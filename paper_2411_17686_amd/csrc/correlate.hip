@@ -50,7 +50,7 @@ struct CorrArgs {
   int32_t* hub_cnt;      // [B] ... and their number
   int32_t* bkt_src;      // [B][n_keep][bkt_cap] the first of them: sources (bucket_entry) ...
   double* bkt_w;         // ... and weights, in order of arrival (the merge orders them)
-  int bkt_cap;
+  int bkt_cap, cnt_stride;
 };
 
 // One more edge, from discarded row `row` (token i) to keep slot `tgt` with weight `al`, for the
@@ -58,7 +58,7 @@ struct CorrArgs {
 __device__ __forceinline__ void emit_edge(const CorrArgs& a, int64_t b, int row, int i, int tgt, double al) {
   if (a.bkt_cnt == nullptr || (unsigned)tgt >= (unsigned)a.n_keep) return;
   const int64_t at = b * a.n_keep + tgt;
-  const int slot = atomicAdd(&a.bkt_cnt[at], 1);
+  const int slot = atomicAdd(&a.bkt_cnt[at * a.cnt_stride], 1);
   if (slot < a.bkt_cap) {
     a.bkt_src[at * a.bkt_cap + slot] = bucket_entry(row, i);
     a.bkt_w[at * a.bkt_cap + slot] = al;
@@ -936,6 +936,7 @@ void launch_correlate(const ficoco_problem& p, const Plan& pl, char* ws, const i
     a.bkt_src = (int32_t*)(ws + pl.bkt_src);
     a.bkt_w = (double*)(ws + pl.bkt_w);
     a.bkt_cap = pl.bkt_cap;
+    a.cnt_stride = edge_cnt_stride(pl);
     if (edges_inverted(pl)) {
       a.hub_list = (int32_t*)(ws + pl.hub_list);
       a.hub_cnt = (int32_t*)(ws + pl.hub_cnt);

@@ -40,7 +40,7 @@ struct SelectArgs {
   int32_t* overflow;        // zeroed here for the correlate stage (fused step only), may be null
   int32_t* edge_cnt;        // [B][n_keep] edge counters of the targets' lists, zeroed here (fused step), or null
   int32_t* hub_cnt;         // [B] number of long targets listed there, zeroed here as well, or null
-  int n_keep;
+  int n_keep, cnt_stride;
   int32_t* pos_out;         // [B][n_keep] position ids of the preserved tokens (fused step: written here, beside keep_idx), or null
   // Exact re-evaluation of the cosine-derived terms for tokens whose decision is within the error
   // bound of the bulk evaluation (exact_r: the mean-cosine term, exact_g: the equivalent-token term)
@@ -456,6 +456,10 @@ __global__ __launch_bounds__(kSelectThreads) void select_kernel(SelectArgs a) {
   const int b = blockIdx.x, tid = threadIdx.x, nt = blockDim.x;
   const int N = a.N;
   const bool exact_mode = EXACT && a.do_score && (a.exact_r || a.exact_g);    // uniform
+  // (first of all: nothing below waits for these stores)
+  if (a.hub_cnt && tid == 0) a.hub_cnt[b] = 0;
+  if (a.edge_cnt)
+    for (int j = tid; j < a.n_keep; j += nt) a.edge_cnt[((int64_t)b * a.n_keep + j) * a.cnt_stride] = 0;
   int32_t* ex_list = a.ex_list + (int64_t)b * N;
   auto is_exact = [&](int i) { return (exbits[i >> 5] >> (i & 31)) & 1u; };
   // marks token i; true if this call was the one that marked it (it then goes on the list)
@@ -688,9 +692,6 @@ __global__ __launch_bounds__(kSelectThreads) void select_kernel(SelectArgs a) {
   }
   if (!a.do_filter) return;
   if (a.overflow && tid == 0) a.overflow[b] = 0;
-  if (a.hub_cnt && tid == 0) a.hub_cnt[b] = 0;
-  if (a.edge_cnt)
-    for (int j = tid; j < a.n_keep; j += nt) a.edge_cnt[(int64_t)b * a.n_keep + j] = 0;
   // ---- K*, flags and ordered compaction --------------------------------------------------------
   // Thread t owns the contiguous run [lo, hi) of tokens (at most kTokensPerThread of them).
   const int per = (N + nt - 1) / nt;
@@ -991,6 +992,7 @@ void launch_select(const ficoco_problem& p, const Plan& pl, char* ws, double* sc
     a.edge_cnt = (int32_t*)(ws + pl.bkt_cnt);
     if (edges_inverted(pl)) a.hub_cnt = (int32_t*)(ws + pl.hub_cnt);
     a.n_keep = p.n_keep;
+    a.cnt_stride = edge_cnt_stride(pl);
   }
   const size_t lds = select_lds(p, penalty);
   const bool exact = a.exact_r || a.exact_g;
