@@ -38,6 +38,7 @@ struct SelectArgs {
   int32_t* keep_idx;
   int32_t* slot_of;
   int32_t* overflow;        // zeroed here for the correlate stage (fused step only), may be null
+  int win_rows, win_cols;   // windows per column and row of a grid (window > 0)
   int32_t* edge_cnt;        // [B][n_keep] edge counters of the targets' lists, zeroed here (fused step), or null
   int32_t* hub_cnt;         // [B] number of long targets listed there, zeroed here as well, or null
   int n_keep, cnt_stride;
@@ -456,10 +457,6 @@ __global__ __launch_bounds__(kSelectThreads) void select_kernel(SelectArgs a) {
   const int b = blockIdx.x, tid = threadIdx.x, nt = blockDim.x;
   const int N = a.N;
   const bool exact_mode = EXACT && a.do_score && (a.exact_r || a.exact_g);    // uniform
-  // (first of all: nothing below waits for these stores)
-  if (a.hub_cnt && tid == 0) a.hub_cnt[b] = 0;
-  if (a.edge_cnt)
-    for (int j = tid; j < a.n_keep; j += nt) a.edge_cnt[((int64_t)b * a.n_keep + j) * a.cnt_stride] = 0;
   int32_t* ex_list = a.ex_list + (int64_t)b * N;
   auto is_exact = [&](int i) { return (exbits[i >> 5] >> (i & 31)) & 1u; };
   // marks token i; true if this call was the one that marked it (it then goes on the list)
@@ -548,17 +545,24 @@ __global__ __launch_bounds__(kSelectThreads) void select_kernel(SelectArgs a) {
         if (a.red_src == FICOCO_R_ATTN_RECV) {
           // Column partials of the row chunks, added in chunk order.  32 loads are issued together
           // (one trip to memory per 32 chunks): past the last chunk the last one is loaded again and
-          // counted as zero, so that the batch stays straight-line code.
+          // counted as zero, so that the batch stays straight-line code.  What is left over is a batch of
+          // its own size: the one compute unit's path to the L2 carries the loads of all tokens.
           const double* p = a.recv_part + (int64_t)bq * a.n_chunks * N + i;
           double acc = 0.0;
-          for (int c = 0; c < a.n_chunks; c += 32) {
-            double v[32];
+          auto add = [&](auto batch, int c) {
+            constexpr int kBatch = decltype(batch)::value;
+            double v[kBatch];
 #pragma unroll
-            for (int u = 0; u < 32; ++u) v[u] = p[(int64_t)min(c + u, a.n_chunks - 1) * N];
+            for (int u = 0; u < kBatch; ++u) v[u] = p[(int64_t)min(c + u, a.n_chunks - 1) * N];
             issue_fence();
 #pragma unroll
-            for (int u = 0; u < 32; ++u) acc += c + u < a.n_chunks ? v[u] : 0.0;
-          }
+            for (int u = 0; u < kBatch; ++u) acc += c + u < a.n_chunks ? v[u] : 0.0;
+          };
+          int c = 0;
+          for (; a.n_chunks - c > 24; c += 32) add(std::integral_constant<int, 32>{}, c);
+          if (a.n_chunks - c > 16) add(std::integral_constant<int, 24>{}, c);
+          else if (a.n_chunks - c > 8) add(std::integral_constant<int, 16>{}, c);
+          else if (a.n_chunks - c > 0) add(std::integral_constant<int, 8>{}, c);
           R = acc / (double)N;
         } else if (a.red_src == FICOCO_R_VECTOR) {
           R = vec_head_mean(a.recv_vec, a.dtype, bq, a.H, N, i);
@@ -602,7 +606,7 @@ __global__ __launch_bounds__(kSelectThreads) void select_kernel(SelectArgs a) {
         __syncthreads();
         auto token_in = [&](int cell) { return table ? owner[cell] : (cell < N ? cell : -1); };
         const int W = a.window;
-        const int wr = (a.grid_h + W - 1) / W, wc = (a.grid_w + W - 1) / W;
+        const int wr = a.win_rows, wc = a.win_cols;
         const int n_win = a.grid_g * wr * wc;
         const float r_sub = 1.0f / (float)(wr * wc), r_wc = 1.0f / (float)wc;
         for (int w = tq; w < n_win; w += nt) {
@@ -611,6 +615,26 @@ __global__ __launch_bounds__(kSelectThreads) void select_kernel(SelectArgs a) {
           const int r0 = wrow * W, c0 = (rem - wrow * wc) * W;
           int best = -1;
           double best_s = 0.0;
+          if (!EXACT && W == 2) {
+            // The usual window: its four tokens' scores are read together, then compared in the order of the
+            // loop below (which waits for each of them in turn: 2.4 us at 24 x 24 cells, 1.8 like this).
+            const int at = (sub * a.grid_h + r0) * a.grid_w + c0;
+            const bool right = c0 + 1 < a.grid_w, low = r0 + 1 < a.grid_h;
+            const int cell[4] = {at, right ? at + 1 : at, low ? at + a.grid_w : at, right && low ? at + a.grid_w + 1 : at};
+            int t[4];
+            double v[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) t[q] = token_in(cell[q]);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) v[q] = s[max(t[q], 0)];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+              const bool in = t[q] >= 0 && (q & 1 ? right : true) && (q & 2 ? low : true);
+              if (in && (best < 0 || v[q] > best_s)) { best = t[q]; best_s = v[q]; }
+            }
+            if (best >= 0) s[best] = a.coef * best_s;     // windows are disjoint: no other reader
+            continue;
+          }
           for (int r = r0; r < min(r0 + W, a.grid_h); ++r)
             for (int c = c0; c < min(c0 + W, a.grid_w); ++c) {
               const int t = token_in((sub * a.grid_h + r) * a.grid_w + c);
@@ -692,6 +716,10 @@ __global__ __launch_bounds__(kSelectThreads) void select_kernel(SelectArgs a) {
   }
   if (!a.do_filter) return;
   if (a.overflow && tid == 0) a.overflow[b] = 0;
+  // (not before the loads of the terms, whose results would be waited for together with these stores)
+  if (a.hub_cnt && tid == 0) a.hub_cnt[b] = 0;
+  if (a.edge_cnt)
+    for (int j = tid; j < a.n_keep; j += nt) a.edge_cnt[((int64_t)b * a.n_keep + j) * a.cnt_stride] = 0;
   // ---- K*, flags and ordered compaction --------------------------------------------------------
   // Thread t owns the contiguous run [lo, hi) of tokens (at most kTokensPerThread of them).
   const int per = (N + nt - 1) / nt;
@@ -749,6 +777,32 @@ __global__ __launch_bounds__(kSelectThreads) void select_kernel(SelectArgs a) {
     }
   }
   const int n_keep = N - a.n_disc;
+  if (per > 1) {      // uniform
+    // Runs of tokens per thread: their places go through LDS (where the keys were), so that the stores cover
+    // whole lines (9216 tokens: 4.2 -> 2.2 us).
+    int* slot = (int*)lds_d;                             // [N]
+    uint16_t* list = (uint16_t*)(slot + N);              // [N]: preserved tokens, then discarded ones
+    for (int i = lo; i < hi; ++i) {                      // (every key was read before the scan's barriers)
+      const bool dis = dis_mask >> (i - lo) & 1u;
+      slot[i] = dis ? -1 : k_pos;
+      const int at = dis ? n_keep + d_pos : k_pos;
+      if (at < N) list[at] = (uint16_t)i;
+      d_pos += dis ? 1 : 0;
+      k_pos += dis ? 0 : 1;
+    }
+    __syncthreads();
+    for (int i = tid; i < N; i += nt) {
+      a.slot_of[(int64_t)b * N + i] = slot[i];
+      const int t = list[i];
+      if (i < n_keep) {
+        a.keep_idx[(int64_t)b * n_keep + i] = t;
+        if (a.pos_out) a.pos_out[(int64_t)b * n_keep + i] = a.pos ? a.pos[(int64_t)b * N + t] : t;
+      } else {
+        a.discard_idx[(int64_t)b * a.n_disc + i - n_keep] = t;
+      }
+    }
+    return;
+  }
   for (int i = lo; i < hi; ++i) {
     if (dis_mask & (1u << (i - lo))) {
       if (d_pos < a.n_disc) a.discard_idx[(int64_t)b * a.n_disc + d_pos] = i;
@@ -981,6 +1035,7 @@ void launch_select(const ficoco_problem& p, const Plan& pl, char* ws, double* sc
   a.pos = p.pos;
   a.grid_g = p.grid_g; a.grid_h = p.grid_h; a.grid_w = p.grid_w;
   a.window = penalty ? p.window : 0;
+  if (penalty) { a.win_rows = (p.grid_h + p.window - 1) / p.window; a.win_cols = (p.grid_w + p.window - 1) / p.window; }
   a.coef = (double)p.penalty_coef;
   a.scores = scores;
   a.n_disc = pl.n_disc;
