@@ -21,15 +21,12 @@ constexpr int kRowsAtOnce = 4;     // rows of one thread whose heads are added s
 constexpr int kHeadsAtOnce = 2;    // ... this many heads of each per batch of loads (more where the thread has fewer rows)
 
 
-// Three wavefronts per SIMD (170 registers): the four-row form keeps 32 double accumulators and 8
-// raw vectors per thread, and its grids hold about three wavefronts per SIMD anyway.
 template <typename T>
-__global__ __launch_bounds__(kReduceThreads) __attribute__((amdgpu_waves_per_eu(3))) void attn_reduce_kernel(AttnArgs a) {
-  extern __shared__ double lds[];
+__device__ __forceinline__ void attn_reduce_block(const AttnArgs& a, int block, double* lds) {
   // Workgroups that read neighbouring strips of the same rows share the cache lines at the
   // strip boundaries: they get consecutive logical ids, which run on the same XCD (one L2).
   const int total = a.n_chunks * a.col_strips * a.B;
-  const int logical = xcd_logical_id(blockIdx.x, total);
+  const int logical = xcd_logical_id(block, total);
   if (logical >= total) return;                   // padding workgroup (the whole block leaves)
   const int strip = logical % a.col_strips;
   const int chunk = (logical / a.col_strips) % a.n_chunks;
@@ -233,18 +230,50 @@ __global__ __launch_bounds__(kReduceThreads) __attribute__((amdgpu_waves_per_eu(
   }
 }
 
+// Three wavefronts per SIMD (170 registers): the four-row form keeps 32 double accumulators and 8
+// raw vectors per thread, and its grids hold about three wavefronts per SIMD anyway.
 template <typename T>
-__global__ __launch_bounds__(256) void text_reduce_kernel(AttnArgs a) {
-  text_reduce_block<T>(a, blockIdx.x, blockIdx.y, blockIdx.z);
+__global__ __launch_bounds__(kReduceThreads) __attribute__((amdgpu_waves_per_eu(3))) void attn_reduce_kernel(AttnArgs a) {
+  extern __shared__ double lds[];
+  attn_reduce_block<T>(a, blockIdx.x, lds);
 }
 
-static void launch_block(const AttnArgs& a, int B, int col_strips, bool bf16, hipStream_t s) {
+template <typename T>
+__global__ __launch_bounds__(256) void text_reduce_kernel(AttnArgs a) {
+  __shared__ TextTile tile[kTextTiles];
+  text_reduce_block<T>(a, blockIdx.x, blockIdx.y, blockIdx.z, tile);
+}
+
+// A decoder call with visual maps reads both blocks in one launch, the text block on its first
+// text_blocks workgroups (padded to whole rounds of the XCDs: the map's workgroups keep their places).  Alone
+// the text block is too small to fill the chip.  At 8 images x 32 heads x (576 + 64) x 576: 41.9 and 8.7 us
+// as two launches, 48.5 as one, the step 98.4 -> 96.0 us (a launch and its gap saved; the bytes take 37 us at
+// the rate of a large copy).  256 threads whatever a strip of the map needs: text workgroups of 192 gave 97.4.
+template <typename T>
+__global__ __launch_bounds__(kReduceThreads) __attribute__((amdgpu_waves_per_eu(3))) void attn_text_reduce_kernel(AttnArgs a, AttnArgs t, int tx, int ty, int text_blocks) {
+  extern __shared__ double lds[];
+  const int block = blockIdx.x;
+  if (block >= text_blocks) {
+    attn_reduce_block<T>(a, block - text_blocks, lds);
+  } else if (block < tx * ty * a.B) {                  // (padding otherwise)
+    text_reduce_block<T>(t, block % tx, block / tx % ty, block / (tx * ty), (TextTile*)lds);
+  }
+}
+
+// text: the text block's arguments, read in the same launch, or null
+static void launch_block(const ficoco_problem& p, const AttnArgs& a, const AttnArgs* text, int B, int col_strips, bool bf16, hipStream_t s) {
   AttnArgs g = a;
   g.col_strips = col_strips; g.B = B;
   dim3 grid(xcd_padded_total(a.n_chunks * col_strips * B)), block(std::min(kReduceThreads, (a.row_lanes * a.strip_groups + kWave - 1) / kWave * kWave));
   size_t lds = (size_t)a.row_lanes * a.strip_groups * kVec * sizeof(double);
   if (a.abar) lds += (size_t)a.strip_groups * kVec * (a.rows_per_wg + 1) * sizeof(float);   // the tile that is turned
-  if (bf16)
+  if (text) {
+    const dim3 tgrid = text_grid(p);
+    const int blocks = xcd_padded_total((int)(tgrid.x * tgrid.y * tgrid.z));
+    lds = std::max(lds, sizeof(TextTile) * kTextTiles);
+    auto kern = bf16 ? attn_text_reduce_kernel<bf16_t> : attn_text_reduce_kernel<float>;
+    hipLaunchKernelGGL(kern, dim3(grid.x + blocks), dim3(kReduceThreads), lds, s, g, *text, (int)tgrid.x, (int)tgrid.y, blocks);
+  } else if (bf16)
     hipLaunchKernelGGL(attn_reduce_kernel<bf16_t>, grid, block, lds, s, g);
   else
     hipLaunchKernelGGL(attn_reduce_kernel<float>, grid, block, lds, s, g);
@@ -255,6 +284,9 @@ void launch_attn_reduce(const ficoco_problem& p, const Plan& pl, char* ws, hipSt
   const bool want_recv = p.red_src == FICOCO_R_ATTN_RECV;
   const bool want_cls = p.sem_src == FICOCO_G_CLS_ATTN;
   const bool want_abar = p.corr_src == FICOCO_C_ATTN && pl.n_disc > 0;
+  AttnArgs t{};
+  bool text = p.A_text && p.variant == FICOCO_VARIANT_L && !text_elsewhere;
+  if (text) fill_text_args(p, pl, ws, t);
   if (p.A && (want_recv || want_cls || want_abar)) {
     AttnArgs a{};
     a.A = p.A; a.sb = p.a_stride_b; a.sh = p.a_stride_h; a.sq = p.a_stride_q;
@@ -274,13 +306,12 @@ void launch_attn_reduce(const ficoco_problem& p, const Plan& pl, char* ws, hipSt
     a.shift = pl.a_shift; a.map_pitch = pl.map_pitch;
     a.row_lanes = pl.row_lanes; a.strip_groups = pl.strip_groups;
     a.invH = 1.0 / (double)p.H;
-    launch_block(a, p.B, pl.col_strips, bf16, s);
+    launch_block(p, a, text ? &t : nullptr, p.B, pl.col_strips, bf16, s);
+    text = false;
   }
-  if (p.A_text && p.variant == FICOCO_VARIANT_L && !text_elsewhere) {
-    AttnArgs a{};
-    fill_text_args(p, pl, ws, a);
-    if (bf16) hipLaunchKernelGGL(text_reduce_kernel<bf16_t>, text_grid(p), dim3(256), 0, s, a);
-    else hipLaunchKernelGGL(text_reduce_kernel<float>, text_grid(p), dim3(256), 0, s, a);
+  if (text) {
+    if (bf16) hipLaunchKernelGGL(text_reduce_kernel<bf16_t>, text_grid(p), dim3(256), 0, s, t);
+    else hipLaunchKernelGGL(text_reduce_kernel<float>, text_grid(p), dim3(256), 0, s, t);
   }
 }
 

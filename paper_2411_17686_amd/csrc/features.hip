@@ -26,8 +26,9 @@ template <typename T, int KB>
 __global__ __launch_bounds__(256) void rows_text_kernel(FeatArgs a, AttnArgs t, int text_blocks, int tgx, int tgy,
                                                         int row_blocks) {
   if ((int)blockIdx.x < text_blocks) {
+    __shared__ TextTile tile[kTextTiles];
     const int q = blockIdx.x;
-    text_reduce_block<T>(t, q % tgx, (q / tgx) % tgy, q / (tgx * tgy));
+    text_reduce_block<T>(t, q % tgx, (q / tgx) % tgy, q / (tgx * tgy), tile);
     return;
   }
   const int rb = (int)blockIdx.x - text_blocks;

@@ -1,6 +1,6 @@
 // Text-query block of FiCoCo-L: the body of the kernel that forms the tokens' text profiles, shared
-// by attn_reduce.hip (its own launch) and features.hip (the fused step lets it ride in the launch
-// of the row-norm kernel, which does not depend on it).
+// by attn_reduce.hip (the launch that reads the maps, or its own) and features.hip (the fused step lets
+// it ride in the launch of the row-norm kernel, which does not depend on it).
 #pragma once
 #include "common.hpp"
 
@@ -39,10 +39,11 @@ inline dim3 text_grid(const ficoco_problem& p);
 // turned in LDS, and each thread then writes the 8 rows of one column as one 64-byte piece.
 constexpr int kTextHeadBatch = 16;
 constexpr int kTextRows = 8;
+using TextTile = double[kTextRows + 1];           // one column's rows; +1: the rows of one column in different banks
 constexpr int kTextGroups = 256 / kTextRows;      // 8-column groups per workgroup
+constexpr int kTextTiles = kTextGroups * kVec;    // the LDS it needs: TextTile[kTextTiles]
 template <typename T>
-__device__ __forceinline__ void text_reduce_block(const AttnArgs& a, int chunk, int strip, int64_t b) {
-  __shared__ double tile[kTextGroups * kVec][kTextRows + 1];     // +1: rows of one column in different banks
+__device__ __forceinline__ void text_reduce_block(const AttnArgs& a, int chunk, int strip, int64_t b, TextTile* tile) {
   const int tid = threadIdx.x;
   const int cg = tid % kTextGroups, rl = tid / kTextGroups;
   const int row = chunk * kTextRows + rl;
