@@ -305,7 +305,8 @@ int ficoco_correlation_gap(ficoco_ctx *ctx, const ficoco_problem *p, void *ws, s
 /*
  * Compress (Eq. 2, self-preserving compression; last lines of Algorithm 1/2): every
  * preserved visual token becomes (X_j + sum_i alpha_ij X_i) / (1 + sum_i alpha_ij), sources
- * added in ascending order; discarded tokens are dropped and every other token of the
+ * added in ascending order (with more than 1024 discarded tokens, 33 to 256 sources: in eight parts of
+ * consecutive discarded tokens, the parts' sums added in order); discarded tokens are dropped and every other token of the
  * sequence is copied unchanged, order preserved.
  *   X_out   [B][ficoco_out_rows][D] dtype, out (dense); compress_mode / k_mode select the
  *           ablation variants (average weights; the additional token of the convergent form).

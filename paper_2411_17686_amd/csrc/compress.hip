@@ -13,6 +13,8 @@
 // ascending source order before it adds, so the result never depends on scheduling.
 #include "common.hpp"
 
+#include <type_traits>
+
 // Products and sums of Eq. 2 are rounded separately everywhere in this file (no fused multiply-add):
 // the weighted sums are then the very doubles the plain statement of the equation produces.
 #pragma clang fp contract(off)
@@ -695,107 +697,149 @@ __device__ __forceinline__ int merge_unit(const MergeArgs& a, char* lds_m, int b
   return 0;
 }
 
+// One or two elements as loaded (two bfloat16 in one register; one in a register of its own: two loads into the
+// halves of one register wait for each other), and element e of them as double.
+template <typename T, int SLICE> struct RawSlice;
+template <> struct RawSlice<bf16_t, 1> { uint32_t u; };
+template <> struct RawSlice<bf16_t, 2> { uint32_t u; };
+template <> struct RawSlice<float, 1> { float u[1]; };
+template <> struct RawSlice<float, 2> { float u[2]; };
+__device__ __forceinline__ void load_slice(const bf16_t* p, RawSlice<bf16_t, 1>& r) { r.u = *p; }
+__device__ __forceinline__ void load_slice(const bf16_t* p, RawSlice<bf16_t, 2>& r) { __builtin_memcpy(&r.u, p, 4); }
+template <int SLICE>
+__device__ __forceinline__ void load_slice(const float* p, RawSlice<float, SLICE>& r) { __builtin_memcpy(r.u, p, sizeof(r.u)); }
+__device__ __forceinline__ double slice_value(const RawSlice<bf16_t, 1>& r, int) { return (double)__uint_as_float(r.u << 16); }
+__device__ __forceinline__ double slice_value(const RawSlice<bf16_t, 2>& r, int e) {
+  return (double)__uint_as_float(e == 0 ? r.u << 16 : r.u & 0xffff0000u);
+}
+template <int SLICE>
+__device__ __forceinline__ double slice_value(const RawSlice<float, SLICE>& r, int e) { return (double)r.u[e]; }
+
+// A target whose sources a whole workgroup adds in ONE ascending sum: the discarded rows are taken 512 at a
+// time, every wavefront looks at 64 of them (whether a row names the target: fetch(row) loads what
+// named(fetched, row, w, token) needs), the hits are packed in ascending row order into one list (the LDS of the
+// per-wavefront lists), and every wavefront then adds the whole list to its own 64 * SLICE features of the span from
+// d0 on; what the next 512 rows need is loaded under that.  Bound by the trips to memory of the one wavefront that
+// owns a feature.  At 2178 sources (4 x 641 rows of 1024) the launch takes 172 us (eight partial sums, which
+// are not the ascending sum: 104; a search for the next source each time: 8400); with the rows'
+// addresses in vector registers and every entry tested for the list's end 290.  More loads in flight than kBatch
+// spill.  At 16 x 385 rows, one target of 155 sources: step 62.0 -> 53.4 us; one image, 358 sources: 108 -> 74 us.
+template <typename T, int SLICE, typename F, typename G>
+__device__ __forceinline__ void merge_ascending(const MergeArgs& a, char* lds_m, int j, int d0, F fetch, G named) {
+  constexpr int kChunk = kMergeWaves * kWave;
+  constexpr int kBatch = sizeof(T) == 2 ? 16 * SLICE : 16 / SLICE;     // row loads in flight
+  __shared__ int hit_n[kMergeWaves];
+  const int lane = threadIdx.x % kWave, wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  double* s_w = (double*)lds_m;                          // [kMergeWaves * kWave]: one hit per row looked at
+  int* s_src = (int*)((double*)lds_m + kMergeWaves * kWave);
+  const int64_t b = blockIdx.y;
+  const T* Xb = (const T*)a.X + b * a.xsb + (int64_t)a.vis_begin * a.xsn;
+  const int dl = d0 + (wv * kWave + lane) * SLICE;
+  const bool whole = dl + SLICE <= a.D;
+  auto next = fetch(wv * kWave + lane);
+  const int tok = min(max(a.T[b * a.n_keep + j], 0), a.N - 1);
+  const T* x = Xb + (int64_t)tok * a.xsn;
+  T* out = (T*)a.X_out + (b * a.n_out + a.vis_begin + j) * (int64_t)a.D;
+  double num[SLICE];
+#pragma unroll
+  for (int e = 0; e < SLICE; ++e) num[e] = dl + e < a.D ? widen(x[dl + e]) : 0.0;
+  double den = 1.0;
+  for (int c0 = 0; c0 < a.n_disc; c0 += kChunk) {
+    const int row = c0 + wv * kWave + lane;
+    double w = 0.0;
+    int src = 0;
+    const bool hit = named(next, row, w, src);
+    const unsigned long long m = __ballot(hit);
+    if (lane == 0) hit_n[wv] = __popcll(m);
+    __syncthreads();
+    int off = 0, n_list = 0;
+#pragma unroll
+    for (int q = 0; q < kMergeWaves; ++q) {
+      const int c = hit_n[q];
+      off += q < wv ? c : 0;
+      n_list += c;
+    }
+    n_list = __builtin_amdgcn_readfirstlane(n_list);
+    if (hit) {
+      const int slot = off + __popcll(m & ((1ULL << lane) - 1ULL));
+      s_src[slot] = min(max(src, 0), a.N - 1);           // device data: stay inside the span
+      s_w[slot] = w;
+    }
+    __syncthreads();
+    next = fetch(row + kChunk);
+    issue_fence();
+    // Straight-line batches as in add_sources; a lane without its whole features reads the row's first ones and
+    // drops them.  One lane's entry each, handed round by lane number: the rows' addresses are scalars.
+    const int at = whole ? dl : 0;
+    auto add_batch = [&](auto batch, int e0, bool last) __attribute__((always_inline)) {
+      constexpr int kB = decltype(batch)::value;
+      const int my_src = s_src[min(e0 + lane % kB, n_list - 1)];
+      const double my_w = s_w[min(e0 + lane % kB, n_list - 1)];
+      RawSlice<T, SLICE> v[kB];
+      if (a.D >= SLICE) {                                // uniform (otherwise no lane is whole)
+#pragma unroll
+        for (int q = 0; q < kB; ++q) load_slice(Xb + (int64_t)lane_value(my_src, q) * a.xsn + at, v[q]);
+      }
+      issue_fence();
+#pragma unroll
+      for (int q = 0; q < kB; ++q) {
+        const double wq = lane_value(my_w, q);
+        const bool in = !last || e0 + q < n_list;        // past the end: the last row again, not counted
+        den += in ? wq : 0.0;
+#pragma unroll
+        for (int e = 0; e < SLICE; ++e) {
+          const double t = wq * slice_value(v[q], e);
+          num[e] += SLICE == 1 ? (in ? t : 0.0) : whole && in ? t : 0.0;
+        }
+      }
+    };
+    int e0 = 0;
+#pragma unroll 1
+    for (; n_list - e0 >= kBatch; e0 += kBatch) add_batch(std::integral_constant<int, kBatch>{}, e0, false);
+#pragma unroll 1
+    for (; e0 < n_list; e0 += kBatch / 4) add_batch(std::integral_constant<int, kBatch / 4>{}, e0, true);
+    if (SLICE > 1 && !whole && dl < a.D) {               // the lane at the end of a row of odd width
+#pragma unroll 1
+      for (int q = 0; q < n_list; ++q) {
+        const T* xs = Xb + (int64_t)s_src[q] * a.xsn;
+        const double wq = s_w[q];
+#pragma unroll
+        for (int e = 0; e < SLICE; ++e)
+          if (dl + e < a.D) num[e] += wq * widen(xs[dl + e]);
+      }
+    }
+    __syncthreads();        // the list and the counts are written again by the next chunk or target
+  }
+#pragma unroll
+  for (int e = 0; e < SLICE; ++e)
+    if (dl + e < a.D) store_token(out + dl + e, num[e] / den);
+}
+
 // Scanning mode, targets with more than kHubMin sources (a token that most discarded tokens
 // attend to): the eight wavefronts of the workgroup that holds such a unit add it together once
-// their own units are done.  The discarded rows are taken 512 at a time: every wavefront scans
-// 64 of them, the hits are packed in ascending row order into one list (the LDS of the
-// per-wavefront lists), and every wavefront then adds the whole list, 16 row loads in flight,
-// to its own 64 * SLICE features of the span: the sum of every output element still runs over
-// ascending discarded rows.
+// their own units are done.
 template <typename T, int SLICE>
 __device__ __forceinline__ void merge_hub_targets(const MergeArgs& a, char* lds_m, int deferred) {
   using Lds = MergeLds<true, SLICE, 1>;
   static_assert(Lds::kCap == kWave, "the shared list holds one hit per scanned row");
   constexpr int kSpan = kWave * kVec * SLICE;
-  constexpr int kChunk = kMergeWaves * kWave;
-  constexpr int kBatch = 16;
   __shared__ int hub_n[kMergeWaves];
-  __shared__ int hit_n[kMergeWaves];
   const int lane = threadIdx.x % kWave, wv = threadIdx.x / kWave;
   if (lane == 0) hub_n[wv] = deferred;
   __syncthreads();            // every wavefront is done with its own list
-  double* s_w = (double*)lds_m;
-  int* s_src = (int*)((double*)lds_m + kMergeWaves * Lds::kCap);
   const EdgeTable tb = edge_table(lds_m + Lds::kLists + Lds::kPartDoubles * 8 + Lds::kDen, a.n_disc);
   const int n_spans = (a.D + kSpan - 1) / kSpan;
-  const int64_t b = blockIdx.y;
-  const int64_t ebase = b * (int64_t)a.n_disc * a.k_max;
-  const T* Xb = (const T*)a.X + b * a.xsb;
+  const int64_t ebase = (int64_t)blockIdx.y * a.n_disc * a.k_max;
   for (int u = 0; u < kMergeWaves; ++u) {
     if (hub_n[u] == 0) continue;                         // uniform over the workgroup
     const int unit = blockIdx.x * kMergeWaves + u;
-    const int r = unit / n_spans;
-    const int j = r - a.vis_begin;                       // a deferred unit is a preserved visual row
-    const int dl = (unit % n_spans) * kSpan + (wv * kWave + lane) * SLICE;
-    const bool whole = dl + SLICE <= a.D;
-    const int tok = min(max(a.T[b * a.n_keep + j], 0), a.N - 1);
-    const T* x = Xb + (int64_t)(a.vis_begin + tok) * a.xsn;
-    T* out = (T*)a.X_out + (b * a.n_out + r) * (int64_t)a.D;
-    double num[SLICE];
-#pragma unroll
-    for (int e = 0; e < SLICE; ++e) num[e] = dl + e < a.D ? widen(x[dl + e]) : 0.0;
-    double den = 1.0;
-    for (int c0 = 0; c0 < a.n_disc; c0 += kChunk) {
-      const int row = c0 + wv * kWave + lane;
-      double w = 0.0;
+    const int j = unit / n_spans - a.vis_begin;          // a deferred unit is a preserved visual row
+    merge_ascending<T, SLICE>(a, lds_m, j, (unit % n_spans) * kSpan, [](int) { return 0; }, [&](int, int row, double& w, int& src) {
       bool more;
       const bool hit = row_names_target<true>(a, tb, ebase, row, row < a.n_disc, j, w, more);
-      const unsigned long long m = __ballot(hit);
-      if (lane == 0) hit_n[wv] = __popcll(m);
-      __syncthreads();
-      int off = 0, n_list = 0;
-#pragma unroll
-      for (int q = 0; q < kMergeWaves; ++q) {
-        const int c = hit_n[q];
-        off += q < wv ? c : 0;
-        n_list += c;
-      }
-      if (hit) {
-        const int slot = off + __popcll(m & ((1ULL << lane) - 1ULL));
-        s_src[slot] = tb.src[row];
-        s_w[slot] = w;
-      }
-      __syncthreads();
-      auto row_of = [&](int e) {
-        const int i = min(max(s_src[e], 0), a.N - 1);      // device data: stay inside the span
-        return Xb + (int64_t)(a.vis_begin + i) * a.xsn;
-      };
-      if (a.D >= SLICE) {                                  // uniform; straight-line batches as in add_sources
-        const int off = whole ? dl : 0;
-#pragma unroll 1
-        for (int e0 = 0; e0 < n_list; e0 += kBatch) {
-          T v[kBatch][SLICE];
-#pragma unroll
-          for (int q = 0; q < kBatch; ++q)
-            __builtin_memcpy(&v[q][0], row_of(min(e0 + q, n_list - 1)) + off, sizeof(T) * SLICE);
-          issue_fence();
-#pragma unroll
-          for (int q = 0; q < kBatch; ++q) {
-            const bool in = e0 + q < n_list;               // past the end: the last row again, not counted
-            const double wq = s_w[min(e0 + q, n_list - 1)];
-            den += in ? wq : 0.0;
-#pragma unroll
-            for (int e = 0; e < SLICE; ++e) num[e] += whole && in ? wq * widen(v[q][e]) : 0.0;
-          }
-        }
-      } else {
-        for (int e0 = 0; e0 < n_list; ++e0) den += s_w[e0];
-      }
-      if (!whole && dl < a.D) {                            // the lane at the end of a row of odd width
-#pragma unroll 1
-        for (int e0 = 0; e0 < n_list; ++e0) {
-          const T* xs = row_of(e0);
-          const double wq = s_w[e0];
-#pragma unroll
-          for (int e = 0; e < SLICE; ++e)
-            if (dl + e < a.D) num[e] += wq * widen(xs[dl + e]);
-        }
-      }
-      __syncthreads();        // the list and the counts are written again by the next chunk or unit
-    }
-#pragma unroll
-    for (int e = 0; e < SLICE; ++e)
-      if (dl + e < a.D) store_token(out + dl + e, num[e] / den);
+      if (hit) src = tb.src[row];
+      return hit;
+    });
   }
 }
 
@@ -928,7 +972,8 @@ struct HubLds {
 
 // Such a target: the discarded rows are cut into eight contiguous parts, each wavefront adds the sources
 // of its part in ascending order, and the eight sums are added in order.  The sources come from the
-// target's list, or, if that could not hold them all, from the edge lists of the part.
+// target's list, or, if that could not hold them all, from the edge lists of the part.  (More than kInvertedCap
+// sources: merge_hub_ascending.  The same division as in merge_unit, so that the sums are the same.)
 template <typename T, int SLICE>
 __device__ __forceinline__ void merge_hub_parts(const MergeArgs& a, char* lds_m, int j, int d0, int n_all) {
   const int lane = threadIdx.x % kWave, wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -1043,6 +1088,32 @@ __device__ __forceinline__ void merge_hub_parts(const MergeArgs& a, char* lds_m,
   __syncthreads();                                       // the sums in LDS are written again by the next target
 }
 
+// More sources than the workgroup-per-target pass of a staged call puts in order: one ascending sum there, and
+// here, from the edge lists.
+template <typename T, int SLICE>
+__device__ __forceinline__ void merge_hub_ascending(const MergeArgs& a, char* lds_m, int j, int d0) {
+  static_assert(HubLds<SLICE>::kLists >= (size_t)kMergeWaves * kWave * 12, "the list of the rows looked at");
+  const int64_t rbase = (int64_t)blockIdx.y * a.n_disc;
+  const int e1 = min(1, a.k_max - 1);
+  struct Row { int cnt, src, t0, t1; double a0, a1; };   // count, token and the first two pairs of a row
+  auto fetch = [&](int row) {
+    const int64_t rr = rbase + min(row, a.n_disc - 1), at = rr * a.k_max;      // clamped: a valid row
+    return Row{a.edge_cnt[rr], a.S[rr], a.edge_tgt[at], a.edge_tgt[at + e1], a.edge_alpha[at], a.edge_alpha[at + e1]};
+  };
+  merge_ascending<T, SLICE>(a, lds_m, j, d0, fetch, [&](const Row& r, int row, double& w, int& src) {
+    const int cnt = row < a.n_disc ? min(r.cnt, a.k_max) : 0;
+    const int64_t at = (rbase + row) * a.k_max;
+    bool hit = false;
+    if (cnt > 0 && r.t0 == j) { hit = true; w = r.a0; }
+    if (cnt > 1 && r.t1 == j) { hit = true; w = r.a1; }
+    for (int e = 2; e < cnt; ++e)
+      if (a.edge_tgt[at + e] == j) { hit = true; w = a.edge_alpha[at + e]; }
+    if (a.average) w = 1.0;
+    src = r.src;
+    return hit;
+  });
+}
+
 // Up to kMatchMaxRows discarded tokens: the workgroup of a left target adds it from the edge table.
 template <typename T, int SLICE>
 __global__ __launch_bounds__(kMergeWaves * kWave) __attribute__((amdgpu_waves_per_eu(SLICE == 1 ? 5 : 6))) void merge_listed_kernel(MergeArgs a) {
@@ -1083,8 +1154,9 @@ __global__ __launch_bounds__(kMergeWaves * kWave) __attribute__((amdgpu_waves_pe
   const int64_t at = (int64_t)blockIdx.y * a.n_keep;
   const int n_units = min(a.hub_cnt[blockIdx.y], a.n_keep) * n_spans;     // uniform
   for (int u = blockIdx.x; u < n_units; u += hub_blocks) {
-    const int j = a.hub_list[at + u / n_spans];
-    merge_hub_parts<T, SLICE>(a, lds_m, j, u % n_spans * kSpan, a.bkt_cnt[(at + j) * a.cnt_stride]);
+    const int j = a.hub_list[at + u / n_spans], n_all = a.bkt_cnt[(at + j) * a.cnt_stride];     // uniform
+    if (n_all > kInvertedCap) merge_hub_ascending<T, SLICE>(a, lds_m, j, u % n_spans * kSpan);
+    else merge_hub_parts<T, SLICE>(a, lds_m, j, u % n_spans * kSpan, n_all);
   }
 }
 

@@ -89,3 +89,26 @@ def test_extreme_tokens(ctx, dtype, scale):
     want = P.O.widen(P.O.round_to_dtype(ref["X_out"], dtype))
     assert np.array_equal(P.O.widen(out["X_out"][0]), want)
     assert torch.isfinite(X.double()).all()
+
+
+@pytest.mark.parametrize("mode", [fc.COMPRESS_SELF, fc.COMPRESS_AVERAGE])
+@pytest.mark.parametrize("grid,D", [(48, 515), (33, 24), (48, 5)])
+def test_one_ascending_sum_beyond_256_sources(ctx, grid, D, mode):
+    """Above 1024 discarded tokens a target with more than 256 sources is one sum over ascending sources, in a
+    fused step as in a staged call.  Every row names all three targets with the same weight, and every
+    second source is a large number or its negative: what is left of the others depends on the order."""
+    cfg = synth.ficoco_v_single(seed=61, B=1, grid=grid, D=D, H=1, centres=9, dtype="f32", n_keep=3)
+    cfg["A"][:] = 0.125
+    kw = dict(corr_src=fc.C_ATTN, k_mode=fc.K_FIXED, fixed_k=3, window=0, compress_mode=mode)
+    S = P.oracle_v(cfg, cfg["A"], 0, **kw)["S"]
+    assert len(S) > 1024
+    X = cfg["X"].clone() * 1000.0
+    pairs = len(S) // 4
+    X[0, 1 + S[0:4 * pairs:4]] = 2.0 ** 60
+    X[0, 1 + S[2:4 * pairs:4]] = -2.0 ** 60
+    ref = P.oracle_v(cfg, cfg["A"], 0, X=X, **kw)
+    assert sources(ref) == {len(S)}
+    want = P.O.widen(P.O.round_to_dtype(ref["X_out"], "f32"))
+    for staged in (True, False):
+        out, _ = P.run_v(cfg, cfg["A"], X=X, ctx=ctx, k_max=4, staged=staged, **kw)
+        assert np.array_equal(P.O.widen(out["X_out"][0]), want), "staged" if staged else "fused"
