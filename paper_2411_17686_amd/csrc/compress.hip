@@ -200,11 +200,19 @@ constexpr int kBucketPer = kInvertedCap / kWave;
 // correctly rounded 1 / den, num * rden lies within two units in the last place of the quotient and
 // two residual corrections make it the correctly rounded one (Markstein): five instructions per
 // element where a division takes a dozen (den is 1 to a few thousand: no exponent is near its ends).
-// The rounding to bfloat16 goes by way of the nearest float.
+// An infinity has a NaN for its residual: seen in the sum of the eight, and put right there (a test per
+// element costs 0.6 us of 9 at 16 x 385 rows of 1024).  The rounding to bfloat16 goes by way of the nearest float.
 __device__ __forceinline__ double quotient(double num, double den, double rden) {
   double q = num * rden;
   q = __builtin_fma(__builtin_fma(-q, den, num), rden, q);
   return __builtin_fma(__builtin_fma(-q, den, num), rden, q);
+}
+__device__ __forceinline__ void keep_infinities(float (&f)[kVec], const double (&num)[kVec]) {
+  const float any = ((f[0] + f[1]) + (f[2] + f[3])) + ((f[4] + f[5]) + (f[6] + f[7]));
+  if (any != any) {
+#pragma unroll
+    for (int k = 0; k < kVec; ++k) f[k] = __builtin_isinf(num[k]) ? (float)num[k] : f[k];
+  }
 }
 __device__ __forceinline__ void store_quotients(bf16_t* out, const double (&num)[kVec], double den, double rden) {
   float f[kVec];
@@ -214,6 +222,7 @@ __device__ __forceinline__ void store_quotients(bf16_t* out, const double (&num)
     f[k] = (float)q;
     if (bf16_midpoint(f[k])) f[k] = off_midpoint(f[k], q - (double)f[k]);
   }
+  keep_infinities(f, num);
   uint32_t h[kVec];
 #pragma unroll
   for (int k = 0; k < kVec; ++k) h[k] = bf16_bits(f[k]) >> 16;
@@ -224,6 +233,7 @@ __device__ __forceinline__ void store_quotients(float* out, const double (&num)[
   float f[kVec];
 #pragma unroll
   for (int k = 0; k < kVec; ++k) f[k] = (float)quotient(num[k], den, rden);
+  keep_infinities(f, num);
   __builtin_memcpy(out, f, sizeof(f));
 }
 

@@ -112,3 +112,27 @@ def test_one_ascending_sum_beyond_256_sources(ctx, grid, D, mode):
     for staged in (True, False):
         out, _ = P.run_v(cfg, cfg["A"], X=X, ctx=ctx, k_max=4, staged=staged, **kw)
         assert np.array_equal(P.O.widen(out["X_out"][0]), want), "staged" if staged else "fused"
+
+
+@pytest.mark.parametrize("staged", [False, True])
+@pytest.mark.parametrize("grid,n_keep,D,dtype", [(16, 90, 72, "bf16"), (16, 90, 72, "f32"), (36, 200, 1032, "bf16"), (36, 200, 40, "f32")])
+def test_infinities(ctx, grid, n_keep, D, dtype, staged):
+    """Infinite features of merged tokens stay infinite (of one sign) or become NaN (of both), as the sums and the
+    division of Eq. 2 give them."""
+    B = 1
+    cfg = synth.ficoco_v_single(seed=67, B=B, grid=grid, D=D, H=2, centres=9, dtype=dtype, n_keep=n_keep)
+    X = cfg["X"].clone()
+    X[0, 1::7, 0::8] = float("inf")
+    X[0, 2::11, 1::8] = -float("inf")
+    X[0, 3::9, 2::8] = float("inf")
+    X[0, 4::9, 2::8] = -float("inf")
+    kw = dict(corr_src=fc.C_ATTN, window=2)
+    out, _ = P.run_v(cfg, cfg["A"], X=X, ctx=ctx, staged=staged, **kw)
+    with np.errstate(invalid="ignore"):
+        ref = P.oracle_v(cfg, cfg["A"], 0, X=X, **kw)
+    got, want = P.O.widen(out["X_out"][0]), ref["X_out"]
+    inf = np.isinf(want)
+    assert inf.any() and np.isnan(want).any()
+    assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(got[inf], want[inf])
+    done = np.isfinite(want)
+    assert np.array_equal(got[done], P.O.widen(P.O.round_to_dtype(want, dtype))[done])
