@@ -41,7 +41,7 @@ constexpr int64_t kWgTarget = 1024;
 
 static size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
 
-int make_plan(const ficoco_problem& p, Plan& pl, const char** why) {
+int make_plan(const ficoco_problem& p, Plan& pl, const char** why, size_t scratch) {
   static const char* kNone = "";
   *why = kNone;
   std::memset(&pl, 0, sizeof(pl));
@@ -245,19 +245,6 @@ int make_plan(const ficoco_problem& p, Plan& pl, const char** why) {
   pl.tgt_alpha = take(B * (size_t)pl.n_disc * p.k_max * sizeof(double));
   pl.hub_list = take(B * (size_t)p.n_keep * sizeof(int32_t));
   pl.hub_cnt = take(B * sizeof(int32_t));
-  if (pl.n_disc > 0) {
-    const size_t targets = B * (size_t)p.n_keep, entry = sizeof(int32_t) + sizeof(double);
-    // (shorter lists leave more targets to the edge lists; below a quarter / an eighth nothing is gained)
-    const int least = edges_inverted(pl) ? kBucketCapLong / 8 : kBucketCap / 4;
-    pl.bkt_cap = edges_inverted(pl) ? kBucketCapLong : kBucketCap;
-    while (pl.bkt_cap >= least && targets * (pl.bkt_cap * entry + edge_cnt_stride(pl) * sizeof(int32_t)) > kBucketBytes) pl.bkt_cap /= 2;
-    if (pl.bkt_cap < least) pl.bkt_cap = 0;
-    const size_t before = off;
-    pl.bkt_cnt = take(pl.bkt_cap ? targets * edge_cnt_stride(pl) * sizeof(int32_t) : 0);
-    pl.bkt_src = take(targets * pl.bkt_cap * sizeof(int32_t));
-    pl.bkt_w = take(targets * pl.bkt_cap * sizeof(double));
-    pl.beyond += off - before;
-  }
   if (qk) {
     // equal rounds of as many images as have room
     const size_t per = (size_t)p.H * pl.qk_nq * sizeof(float2);
@@ -293,6 +280,32 @@ int make_plan(const ficoco_problem& p, Plan& pl, const char** why) {
   pl.ex_u = take(exact_terms ? B * 8 * (size_t)pl.Df * sizeof(double) : 0);
   pl.ex_g = take(exact_terms ? B * 8 * N * sizeof(double) : 0);
   pl.ex_list = take(exact_terms ? B * N * sizeof(int32_t) : 0);
+  if (pl.n_disc > 0) {
+    // The targets' lists.  A caller's workspace has room for them whatever the batch is (at 384 of 576 tokens
+    // they are a tenth of the head-mean map): bounded by what all images together may take, they ended at
+    // B = 219 there, and what they gain with them (256 images of one head 302 us without, 280 with them; 32 x
+    // 2881 tokens 740 and 658).  Up to kMatchMaxRows discarded tokens half as many entries do where a target has no more
+    // than one source on average, or two by attention, whose counts spread less than those of like tokens
+    // (64 images of one head, 0.5 sources: 84.0 us with 32 entries, 78.5 with 16; 256 images, 2 sources: 288
+    // and 282; 16 images, 19 sources: 212 and 365).  In a scratch of given size the lists take what the rest
+    // leaves; below a quarter / an eighth of the full length nothing is gained.
+    const size_t targets = (size_t)p.n_keep, entry = sizeof(int32_t) + sizeof(double);
+    const bool is_long = edges_inverted(pl);
+    const int least = is_long ? kBucketCapLong / 8 : kBucketCap / 4;
+    auto image_bytes = [&](int cap) { return targets * (cap * entry + edge_cnt_stride(pl) * sizeof(int32_t)); };
+    const int per_row = pl.fixed_k >= 0 ? pl.fixed_k : std::max(pl.sel_m - 1, 1);      // targets of a row
+    const bool few = (int64_t)pl.n_disc * per_row <= (p.corr_src == FICOCO_C_ATTN ? 2 : 1) * (int64_t)p.n_keep;
+    int cap = is_long ? kBucketCapLong : std::min(few ? kBucketCap / 2 : kBucketCap, (pl.n_disc + 7) / 8 * 8);
+    while (cap > least && image_bytes(cap) > kBucketBytes) cap /= 2;
+    const size_t used = off + 3 * 256;                // (each region is rounded up)
+    while (cap >= least && (used > scratch || B * image_bytes(cap) > scratch - used)) cap /= 2;
+    pl.bkt_cap = cap >= least ? cap : 0;
+    const size_t before = off;
+    pl.bkt_cnt = take(pl.bkt_cap ? B * targets * edge_cnt_stride(pl) * sizeof(int32_t) : 0);
+    pl.bkt_src = take(B * targets * pl.bkt_cap * sizeof(int32_t));
+    pl.bkt_w = take(B * targets * pl.bkt_cap * sizeof(double));
+    pl.beyond += off - before;
+  }
   pl.total = off;
   return FICOCO_OK;
 }
@@ -327,13 +340,13 @@ static size_t x_out_extent(const ficoco_problem& p, const Plan& pl) {
 }
 
 static int prepare(ficoco_ctx* ctx, const ficoco_problem* p, const void* ws, size_t ws_bytes,
-                   Plan& pl, const char* fn) {
+                   Plan& pl, const char* fn, size_t scratch = SIZE_MAX) {
   if (!ctx) return FICOCO_EINVAL;
   if (!p) return fail(ctx, FICOCO_EINVAL, fn, "problem is NULL");
   const int dev_rc = check_device(ctx, fn);
   if (dev_rc != FICOCO_OK) return dev_rc;
   const char* why;
-  const int rc = make_plan(*p, pl, &why);
+  const int rc = make_plan(*p, pl, &why, scratch);
   if (rc != FICOCO_OK) return fail(ctx, rc, fn, why);
   if (!ws || ((uintptr_t)ws & 255)) return fail(ctx, FICOCO_EINVAL, fn, "workspace is NULL or not 256-byte aligned");
   if (ws_bytes < pl.total) return fail(ctx, FICOCO_ENOMEM, fn, "workspace smaller than ficoco_workspace_bytes()");
@@ -349,12 +362,12 @@ static int finish(ficoco_ctx* ctx, const char* fn) {
 static int run_step(ficoco_ctx* ctx, const ficoco_problem* p0, int variant, void* ws, size_t ws_bytes,
                     void* X_out, int32_t* pos_out, int32_t* keep_idx, int32_t* discard_idx,
                     int32_t* edge_cnt, int32_t* edge_tgt, double* edge_alpha, double* scores,
-                    int32_t* overflow, void* stream, const char* fn) {
+                    int32_t* overflow, void* stream, const char* fn, size_t scratch = SIZE_MAX) {
   if (!ctx) return FICOCO_EINVAL;
   if (!p0) return fail(ctx, FICOCO_EINVAL, fn, "problem is NULL");
   if (p0->variant != variant) return fail(ctx, FICOCO_EINVAL, fn, "problem.variant does not match the entry point");
   Plan pl;
-  const int rc = prepare(ctx, p0, ws, ws_bytes, pl, fn);
+  const int rc = prepare(ctx, p0, ws, ws_bytes, pl, fn, scratch);
   if (rc != FICOCO_OK) return rc;
   if (!X_out || !keep_idx || !scores || !overflow ||
       (pl.n_disc > 0 && (!discard_idx || !edge_cnt || !edge_tgt || !edge_alpha)))
@@ -568,14 +581,14 @@ int ficoco_v_step_static(ficoco_ctx* ctx, const ficoco_problem* p, void* X_out, 
   if (!p) return fail(ctx, FICOCO_EINVAL, fn, "problem is NULL");
   Plan pl;
   const char* why;
-  const int rc = make_plan(*p, pl, &why);
+  const int rc = make_plan(*p, pl, &why, kStaticScratchBytes);
   if (rc != FICOCO_OK) return fail(ctx, rc, fn, why);
   if (pl.total - pl.beyond > FICOCO_STATIC_SCRATCH_BYTES || pl.total > kStaticScratchBytes)
     return fail(ctx, FICOCO_ENOMEM, fn, "the step's workspace exceeds the 32 MiB static scratch: use ficoco_v_step with a caller workspace");
   void* ws = ctx->device < kMaxDevices ? g_static_ws[ctx->device] : nullptr;
   if (!ws) return fail(ctx, FICOCO_EHIP, fn, "no static scratch on this device");
   return run_step(ctx, p, FICOCO_VARIANT_V, ws, kStaticScratchBytes, X_out, pos_out, keep_idx, discard_idx,
-                  edge_cnt, edge_tgt, edge_alpha, scores, overflow, stream, fn);
+                  edge_cnt, edge_tgt, edge_alpha, scores, overflow, stream, fn, kStaticScratchBytes);
 }
 
 int ficoco_l_step(ficoco_ctx* ctx, const ficoco_problem* p, void* ws, size_t ws_bytes, void* X_out,

@@ -78,7 +78,8 @@ struct Plan {
   size_t total;
 };
 
-int make_plan(const ficoco_problem& p, Plan& plan, const char** why);
+// scratch: bytes the whole workspace may have at most, as far as the lists of the targets can be cut down to it
+int make_plan(const ficoco_problem& p, Plan& plan, const char** why, size_t scratch = SIZE_MAX);
 
 // One edge of the correlate stage in the form the merge kernel scans: target slot, source
 // visual token, weight.  16 bytes, one load.
@@ -153,7 +154,7 @@ constexpr int kHubMin = 32;        // targets with more sources than this are me
 // Entries per target up to kMatchMaxRows discarded tokens and above: as many as a wavefront, and a workgroup, puts in
 // order.  (16 for the former: 37 us instead of 19 where two dozen of 144 targets have 17 to 29 sources.)
 constexpr int kBucketCap = 32, kBucketCapLong = 256;
-constexpr size_t kBucketBytes = (size_t)8 << 20;         // at most, for all images together: larger batches keep fewer
+constexpr size_t kBucketBytes = (size_t)8 << 20;         // at most, for one image: more targets keep fewer
 static_assert(kMaxSelectN <= (1 << 16), "row and token of an entry");
 __host__ __device__ __forceinline__ int bucket_entry(int row, int token) { return row << 16 | token; }   // ascending like the rows
 inline bool edges_inverted(const Plan& pl) { return pl.n_disc > kMatchMaxRows; }

@@ -111,3 +111,15 @@ def test_product_path_has_no_oracle_import():
     for f in os.listdir(os.path.join(ROOT, "oracle")):
         if f.endswith(".py"):
             assert "paper_2411_17686_amd" not in open(os.path.join(ROOT, "oracle", f)).read()
+
+
+@pytest.mark.parametrize("N,n_keep,B", [(576, 384, 240), (576, 144, 400), (2880, 640, 32)])
+def test_workspace_per_image_does_not_shrink_with_the_batch(N, n_keep, B):
+    """The lists of sources that the merge of a fused step works from are there at every batch size."""
+    def need(batch):
+        p = _valid_problem()
+        p.B, p.N, p.n_tot, p.vis_begin, p.n_keep, p.cls_index, p.window = batch, N, N, 0, n_keep, -1, 0
+        p.recv_vec, p.sem_vec, p.red_src, p.sem_src, p.corr_src = 4096, 8192, fc.R_VECTOR, fc.G_VECTOR, fc.C_COSINE
+        p.k_max = 65                     # (no matrix-core block, whose cuts depend on the batch)
+        return fc.workspace_bytes(p)
+    assert need(B) >= B * (need(1) - 64 * 256)      # (regions are rounded up to 256 bytes)

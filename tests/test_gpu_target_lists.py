@@ -1,7 +1,7 @@
 """The lists of sources per target that the correlate stage of a fused step fills for the merge: targets with
 fewer, exactly as many and more sources than a wavefront merges by itself (32) or a list holds (32 up to
-1024 discarded tokens, 256 above), ragged widths, every way of weighting, the shorter lists of large
-batches, and tokens down to the subnormal range."""
+1024 discarded tokens, 256 above), ragged widths, every way of weighting, large batches, and tokens down to
+the subnormal range."""
 import numpy as np
 import pytest
 import torch
@@ -63,8 +63,7 @@ def test_rows_with_many_targets(ctx):
 @pytest.mark.parametrize("B,grid,n_keep", [(50, 23, 400), (100, 23, 400), (200, 23, 400), (240, 23, 400),
                                            (24, 36, 200), (60, 36, 200), (120, 36, 200)])
 def test_large_batches(ctx, B, grid, n_keep):
-    """Lists of 32, 16, 8 and no entries, of 128, 32 and none: the same bytes as from the edge lists (a sum of
-    more than 256 sources may be split differently, but no target has that many)."""
+    """Batches whose lists take many times 8 MiB: the same bytes as from the edge lists."""
     cfg = synth.ficoco_v_single(seed=53, B=2, grid=grid, D=24, H=1, centres=9, dtype="bf16", n_keep=n_keep)
     rep = (B + 1) // 2
     X, A = cfg["X"].repeat(rep, 1, 1)[:B].contiguous(), cfg["A"].repeat(rep, 1, 1, 1)[:B].contiguous()
