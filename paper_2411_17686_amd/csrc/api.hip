@@ -291,17 +291,25 @@ int make_plan(const ficoco_problem& p, Plan& pl, const char** why, size_t scratc
     // leaves; below a quarter / an eighth of the full length nothing is gained.
     const size_t targets = (size_t)p.n_keep, entry = sizeof(int32_t) + sizeof(double);
     const bool is_long = edges_inverted(pl);
-    const int least = is_long ? kBucketCapLong / 8 : kBucketCap / 4;
-    auto image_bytes = [&](int cap) { return targets * (cap * entry + edge_cnt_stride(pl) * sizeof(int32_t)); };
     const int per_row = pl.fixed_k >= 0 ? pl.fixed_k : std::max(pl.sel_m - 1, 1);      // targets of a row
-    const bool few = (int64_t)pl.n_disc * per_row <= (p.corr_src == FICOCO_C_ATTN ? 2 : 1) * (int64_t)p.n_keep;
+    const int64_t edges = (int64_t)pl.n_disc * per_row;
+    // The adds to counters of one cache line queue, about 11 ns each (16 images with one preserved token of 576,
+    // whose counters share a line: 109 us for the correlate stage, 9 without the adds).  Where the targets
+    // have four sources or more on average, and above kMatchMaxRows, each counter has 64 bytes of its own: step with
+    // the counters packed and apart 217.8 and 131.7 us there, 94.0 and 79.8 at 16 preserved, 46.7 and 40.9 at
+    // 32, 39.3 and 39.0 at 96 (5 sources); 8064 rows with 1152 targets 34 and 28 us for the stage.  Below, the filter
+    // and the merge, which write and read the lines, lose what the adds gain (40.0 and 40.3 at 144, 3 sources).
+    pl.cnt_stride = is_long || edges >= 4 * (int64_t)p.n_keep ? 16 : 1;
+    const int least = is_long ? kBucketCapLong / 8 : kBucketCap / 4;
+    auto image_bytes = [&](int cap) { return targets * (cap * entry + pl.cnt_stride * sizeof(int32_t)); };
+    const bool few = edges <= (p.corr_src == FICOCO_C_ATTN ? 2 : 1) * (int64_t)p.n_keep;
     int cap = is_long ? kBucketCapLong : std::min(few ? kBucketCap / 2 : kBucketCap, (pl.n_disc + 7) / 8 * 8);
     while (cap > least && image_bytes(cap) > kBucketBytes) cap /= 2;
     const size_t used = off + 3 * 256;                // (each region is rounded up)
     while (cap >= least && (used > scratch || B * image_bytes(cap) > scratch - used)) cap /= 2;
     pl.bkt_cap = cap >= least ? cap : 0;
     const size_t before = off;
-    pl.bkt_cnt = take(pl.bkt_cap ? B * targets * edge_cnt_stride(pl) * sizeof(int32_t) : 0);
+    pl.bkt_cnt = take(pl.bkt_cap ? B * targets * pl.cnt_stride * sizeof(int32_t) : 0);
     pl.bkt_src = take(B * targets * pl.bkt_cap * sizeof(int32_t));
     pl.bkt_w = take(B * targets * pl.bkt_cap * sizeof(double));
     pl.beyond += off - before;

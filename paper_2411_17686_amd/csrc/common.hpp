@@ -53,7 +53,8 @@ struct Plan {
   size_t tgt_alpha;      // double [B][N^S*k_max]
   size_t hub_list, hub_cnt;   // int32 [B][n_keep], [B]: preserved tokens with long buckets (inverted lists only)
   int bkt_cap;           // fused step: edges kept per target while the lists are written (0: none)
-  size_t bkt_cnt;        // int32  [B][n_keep]            edges per target
+  int cnt_stride;        // counters are this many int32 apart
+  size_t bkt_cnt;        // int32  [B][n_keep][cnt_stride] edges per target
   size_t bkt_src;        // int32  [B][n_keep][bkt_cap]   their sources (bucket_entry), in order of arrival
   size_t bkt_w;          // double [B][n_keep][bkt_cap]   their weights
   size_t beyond;         // bytes of the regions that the limit of the static scratch does not count (qk_norm, bkt_*)
@@ -158,10 +159,6 @@ constexpr size_t kBucketBytes = (size_t)8 << 20;         // at most, for one ima
 static_assert(kMaxSelectN <= (1 << 16), "row and token of an entry");
 __host__ __device__ __forceinline__ int bucket_entry(int row, int token) { return row << 16 | token; }   // ascending like the rows
 inline bool edges_inverted(const Plan& pl) { return pl.n_disc > kMatchMaxRows; }
-// Above kMatchMaxRows each counter has 64 bytes of its own: the adds to one cache line queue (8064 rows' edges to 1152 targets:
-// 34 us for the stage with the counters packed, 28 like this).  Below the stage gains nothing and the filter and
-// the merge, which write and read the lines, lose half a microsecond.
-inline int edge_cnt_stride(const Plan& pl) { return edges_inverted(pl) ? 16 : 1; }
 inline int invert_groups(const Plan& pl) { return (pl.n_disc + kInvertRows - 1) / kInvertRows; }
 inline int invert_share_rows(const Plan& pl) {
   const int g = invert_groups(pl);

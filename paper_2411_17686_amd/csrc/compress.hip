@@ -1333,7 +1333,7 @@ void launch_compress(const ficoco_problem& p, const Plan& pl, char* ws, const in
     m.bkt_src = (const int32_t*)(ws + pl.bkt_src);
     m.bkt_w = (const double*)(ws + pl.bkt_w);
     m.bkt_cap = pl.bkt_cap;
-    m.cnt_stride = edge_cnt_stride(pl);
+    m.cnt_stride = pl.cnt_stride;
   }
   if (!match) {
     m.hub_list = (const int32_t*)(ws + pl.hub_list);

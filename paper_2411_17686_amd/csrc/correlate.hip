@@ -936,7 +936,7 @@ void launch_correlate(const ficoco_problem& p, const Plan& pl, char* ws, const i
     a.bkt_src = (int32_t*)(ws + pl.bkt_src);
     a.bkt_w = (double*)(ws + pl.bkt_w);
     a.bkt_cap = pl.bkt_cap;
-    a.cnt_stride = edge_cnt_stride(pl);
+    a.cnt_stride = pl.cnt_stride;
     if (edges_inverted(pl)) {
       a.hub_list = (int32_t*)(ws + pl.hub_list);
       a.hub_cnt = (int32_t*)(ws + pl.hub_cnt);

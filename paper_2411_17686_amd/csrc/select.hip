@@ -1047,7 +1047,7 @@ void launch_select(const ficoco_problem& p, const Plan& pl, char* ws, double* sc
     a.edge_cnt = (int32_t*)(ws + pl.bkt_cnt);
     if (edges_inverted(pl)) a.hub_cnt = (int32_t*)(ws + pl.hub_cnt);
     a.n_keep = p.n_keep;
-    a.cnt_stride = edge_cnt_stride(pl);
+    a.cnt_stride = pl.cnt_stride;
   }
   const size_t lds = select_lds(p, penalty);
   const bool exact = a.exact_r || a.exact_g;

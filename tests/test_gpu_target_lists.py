@@ -135,3 +135,14 @@ def test_infinities(ctx, grid, n_keep, D, dtype, staged):
     assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(got[inf], want[inf])
     done = np.isfinite(want)
     assert np.array_equal(got[done], P.O.widen(P.O.round_to_dtype(want, dtype))[done])
+
+
+@pytest.mark.parametrize("grid,n_keep,fixed_k", [(10, 20, 1), (10, 21, 1), (20, 1, 1), (20, 3, 2), (12, 48, 2), (12, 49, 2)])
+def test_counters_packed_and_apart(ctx, grid, n_keep, fixed_k):
+    """Four sources per target on average and more: the counters of the lists are 64 bytes apart, below that
+    packed; here 4, just below, hundreds with one counter an image, and 4 and just below with two targets a row."""
+    cfg = synth.ficoco_v_single(seed=71, B=3, grid=grid, D=40, H=2, centres=9, dtype="bf16", n_keep=n_keep)
+    kw = dict(corr_src=fc.C_ATTN, k_mode=fc.K_FIXED, fixed_k=fixed_k, window=2)
+    out, _ = P.run_v(cfg, cfg["A"], ctx=ctx, k_max=4, **kw)
+    for b in range(3):
+        P.compare_image(out, b, P.oracle_v(cfg, cfg["A"], b, **kw), "bf16", 1, True)
