@@ -351,12 +351,13 @@ int ficoco_l_step(ficoco_ctx *ctx, const ficoco_problem *p, void *ws, size_t ws_
 /*
  * ficoco_v_step for callers that cannot allocate or hand over a workspace: code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments and results as
- * ficoco_v_step without `ws` / `ws_bytes`: the step's workspace is a static device array of
- * FICOCO_STATIC_SCRATCH_BYTES inside the library (one copy per GPU, held until the process
- * ends).  The call allocates and frees nothing and launches the same kernels.
- *   - A problem whose ficoco_workspace_bytes exceeds FICOCO_STATIC_SCRATCH_BYTES (the softmax
- *     normalisers of the query/key form, up to 8 MiB, and the source lists of the preserved
- *     tokens, up to 8 MiB, not counted) is rejected
+ * ficoco_v_step without `ws` / `ws_bytes`: the step's workspace is a static device array inside the
+ * library (one copy per GPU, held until the process ends): FICOCO_STATIC_SCRATCH_BYTES and 16 MiB
+ * more for the softmax normalisers of the query/key form and the lists of the preserved tokens'
+ * sources.  The call allocates and frees nothing and launches the same kernels.
+ *   - A problem whose ficoco_workspace_bytes is at most FICOCO_STATIC_SCRATCH_BYTES is accepted.  Of a
+ *     larger one the normalisers and the lists are not counted (the lists are shortened to what is
+ *     left, which costs time, never results): it is rejected if the rest exceeds the limit,
  *     with FICOCO_ENOMEM before anything is launched (the batched 576-token ViT shape,
  *     B = 16, needs about 25 MB and fits).
  *   - All calls on one GPU share that GPU's array: calls that overlap in time on one GPU

@@ -14,8 +14,9 @@
 // a kernel (on the host it is a stand-in symbol, not a device address): ficoco_create asks the
 // runtime for the array's address on the ctx's device and keeps it in g_static_ws.
 // Behind FICOCO_STATIC_SCRATCH_BYTES there is room for the row normalisers of the query/key form and for
-// the targets' lists, which that limit does not count.
-constexpr size_t kStaticScratchBytes = FICOCO_STATIC_SCRATCH_BYTES + ficoco::kQkNormBytes + 2 * ficoco::kBucketBytes;
+// the targets' lists, which that limit does not count (the lists are cut down to what is left).
+constexpr size_t kStaticScratchBytes = FICOCO_STATIC_SCRATCH_BYTES + ficoco::kQkNormBytes + ficoco::kBucketBytes;
+static_assert(kStaticScratchBytes == (size_t)48 << 20, "the size that ficoco.h states");
 static __device__ __align__(256) unsigned char g_static_scratch[kStaticScratchBytes];
 constexpr int kMaxDevices = 64;
 static void* g_static_ws[kMaxDevices];    // per device, filled by ficoco_create (written once per device with the same value)

@@ -61,3 +61,29 @@ def test_static_scratch_rejects_a_step_that_does_not_fit():
     torch.cuda.synchronize()
     del keep_alive
     ctx.close()
+
+
+def test_static_scratch_shortens_the_lists_it_has_no_room_for():
+    """1300 images of 64 tokens: the workspace without the lists of sources (28 MiB) is within the limit, the full lists
+    (22 MiB) do not fit the array and are cut in half; targets with more sources than that among them."""
+    ctx = fc.Context(0)
+    B = 1300
+    cfg = synth.ficoco_v_single(seed=24, B=2, grid=8, D=16, H=1, centres=4, dtype="bf16", n_keep=39)
+    cfg["A"][:, :, 30] = 0.5                                # query 30 attends to all alike: every row names it
+    cfg["X"] = cfg["X"].repeat(B // 2, 1, 1)
+    Xd, Ad = cfg["X"].cuda(), cfg["A"].repeat(B // 2, 1, 1, 1).cuda()
+    p = fc.make_problem(Xd, variant=fc.VARIANT_V, vis_begin=1, N=64, n_keep=39, A=Ad, cls_index=0, grid=(1, 8, 8), window=2,
+                        penalty_coef=cfg["coef"], w_score=cfg["lam"], eps=cfg["eps"], k_max=8, k_mode=fc.K_FIXED, fixed_k=8)
+    lists = B * 39 * (32 * 12 + 64)
+    assert fc.workspace_bytes(p) > fc.STATIC_SCRATCH_BYTES + (16 << 20) > fc.workspace_bytes(p) - lists // 2
+    want, got = fc.Buffers(p, "cuda", Xd.dtype), fc.Buffers(p, "cuda", Xd.dtype)
+    fc.ficoco_v_step(ctx, p, want)
+    fc.ficoco_v_step_static(ctx, p, got)
+    want, got = P.gpu_outputs(want), P.gpu_outputs(got)
+    for k in ("X_out", "keep", "cnt", "tgt", "alpha", "scores", "overflow"):
+        assert np.array_equal(got[k], want[k]), k
+    refs = [P.oracle_v(cfg, cfg["A"], b, k_mode=fc.K_FIXED, fixed_k=8) for b in range(2)]
+    assert max(np.bincount(np.concatenate(r["J"])).max() for r in refs) > 16
+    for b in (0, 1, B - 1):
+        P.compare_image(got, b, refs[b % 2], "bf16", 1, True)
+    ctx.close()
