@@ -249,6 +249,9 @@ __global__ __launch_bounds__(256) void text_reduce_kernel(AttnArgs a) {
 // the text block is too small to fill the chip.  At 8 images x 32 heads x (576 + 64) x 576: 41.9 and 8.7 us
 // as two launches, 48.5 as one, the step 98.4 -> 96.0 us (a launch and its gap saved; the bytes take 37 us at
 // the rate of a large copy).  256 threads whatever a strip of the map needs: text workgroups of 192 gave 97.4.
+// In float32 the text form's 162 registers leave the map three wavefronts per SIMD instead of four.  The one launch is
+// still the faster (step, one launch against two: 8 x 32 heads x 640 x 576 144 and 145 us, 2 such images 54 and
+// 59, 8 x 32 x 656 x 400 88 and 95, one image 46 and 51); at four, with spills, it is not (151, 58, 105, 51).
 template <typename T>
 __global__ __launch_bounds__(kReduceThreads) __attribute__((amdgpu_waves_per_eu(3))) void attn_text_reduce_kernel(AttnArgs a, AttnArgs t, int tx, int ty, int text_blocks) {
   extern __shared__ double lds[];

@@ -888,9 +888,10 @@ __global__ __launch_bounds__(kMergeWaves * kWave) __attribute__((amdgpu_waves_pe
 // Measured against that form: 15.4 -> 12.4 us at 16 x 385 rows of 1024, 24.7 -> 19.5 us at 8 x 243 rows of
 // 4096; above 1024 discarded tokens 31 -> 14 us (bucketing launch included) at 4 x 641 rows of 1024
 // and 32 -> 17.5 us at 1152, for 0.3 to 0.6 us more in the correlate stage.  A plain copy of the rows
-// takes 11.5 us in the first of these, the divisions 2 us.  Wide spans run at six wavefronts per SIMD
-// (the whole grid on the chip at once), narrow ones at five: at six they spill (6.2 us for 5.8 at
-// 99 rows of 1024, 17.9 for 14.0 at 4 x 641), at four too few are there (15.5).
+// takes 11.5 us in the first of these, the divisions 2 us.  Wide bfloat16 spans run at six wavefronts per SIMD
+// (the whole grid on the chip at once), the others at five: at six they spill (6.2 us for 5.8 at
+// 99 rows of 1024, 17.9 for 14.0 at 4 x 641; float32, 8 x 243 rows of 4096: step 143.9 and 140.7), at four too few are
+// there (15.5).
 template <typename T, int SLICE>
 __device__ __forceinline__ int merge_listed_unit(const MergeArgs& a, char* lds_m, int blk) {
   constexpr int kSpan = kWave * kVec * SLICE;
@@ -1126,7 +1127,7 @@ __device__ __forceinline__ void merge_hub_ascending(const MergeArgs& a, char* ld
 
 // Up to kMatchMaxRows discarded tokens: the workgroup of a left target adds it from the edge table.
 template <typename T, int SLICE>
-__global__ __launch_bounds__(kMergeWaves * kWave) __attribute__((amdgpu_waves_per_eu(SLICE == 1 ? 5 : 6))) void merge_listed_kernel(MergeArgs a) {
+__global__ __launch_bounds__(kMergeWaves * kWave) __attribute__((amdgpu_waves_per_eu(SLICE == 1 || sizeof(T) == 4 ? 5 : 6))) void merge_listed_kernel(MergeArgs a) {
   extern __shared__ __attribute__((aligned(16))) char lds_m[];
   const int deferred = merge_listed_unit<T, SLICE>(a, lds_m, blockIdx.x);
   if (!__syncthreads_or(deferred)) return;
