@@ -52,6 +52,7 @@ struct QkArgs {
   int n_tiles;          // query tiles that hold visual queries
   int b0, nb;           // images of this launch
   int q_groups, k_tiles; // workgroups of one image: query tiles or groups of them, key tiles
+  bool share_keys;      // row normalisers: one query tile per workgroup, whose wavefronts share its keys
   __device__ __forceinline__ int row(int v) const { return v < n_visq ? vis0 + v : x0 + (v - n_visq); }
 };
 
@@ -71,7 +72,7 @@ __device__ __forceinline__ int lds_chunk(int r, int c) { return r * CH + (c ^ ((
 
 // ---- row normalisers ---------------------------------------------------------------------------
 // A workgroup takes 4 x 48 queries of one head and walks its keys 64 at a time, the next 64 being
-// loaded while the current ones are added.  The exponentials are taken relative to a whole number
+// loaded while the current ones are added (few workgroups: 48 queries, the keys shared by its wavefronts).  The exponentials are taken relative to a whole number
 // (units of log2) at the largest logit of the first 32 keys, not of the whole row: any reference
 // serves as long as nothing overflows, and then the sums need no running maximum.  A row whose sum
 // does overflow (its largest logit more than ~70 above those of the first 32 keys) is seen in the
@@ -88,9 +89,10 @@ __global__ __launch_bounds__(kQkWaves * kWave) __attribute__((amdgpu_waves_per_e
   if (unit >= units) return;
   const int tid = threadIdx.x, lane = tid % kWave, l16 = lane % 16, lg = lane / 16;
   const int wv = __builtin_amdgcn_readfirstlane(tid / kWave);
-  const int w0 = (unit % a.q_groups) * kQkWaves * kQkTile;
-  const bool narrow = a.nq - w0 <= 16;     // one block of queries in all (the [CLS] query behind 576 visual ones): the wavefronts share its keys
-  const int v0 = narrow ? w0 : w0 + wv * kQkTile;
+  const int w0 = (unit % a.q_groups) * (a.share_keys ? 1 : kQkWaves) * kQkTile;
+  const bool narrow = a.nq - w0 <= 16;     // one block of queries in all (the [CLS] query behind 576 visual ones)
+  const bool share_keys = a.share_keys || narrow;
+  const int v0 = share_keys ? w0 : w0 + wv * kQkTile;
   const int h = (unit / a.q_groups) % a.H;
   const int64_t bi = unit / (a.q_groups * a.H);
   const float NEG = -__builtin_huge_valf();
@@ -210,30 +212,40 @@ __global__ __launch_bounds__(kQkWaves * kWave) __attribute__((amdgpu_waves_per_e
     };
   };
   bool over = false;
-  if (narrow) {
-    // each wavefront every fourth 32 keys, with a reference of its own; the four sums are combined in order
-    const std::integral_constant<int, 1> one{};
-    __shared__ float part_ref[kQkWaves][16];
-    __shared__ double part_sum[kQkWaves][16];
+  // Each wavefront every fourth 32 keys, with a reference of its own; the four sums are combined in order.
+  __shared__ float part_ref[kQkWaves][kQkTile];
+  __shared__ double part_sum[kQkWaves][kQkTile];
+  auto shared_keys = [&](auto qbn) __attribute__((always_inline)) {
+    constexpr int QB = decltype(qbn)::value;
     const int first = wv * kQkKB * 16;
 #pragma unroll 1
     for (int k0 = first; k0 < k_end; k0 += kQkWaves * kQkKB * 16) {
-      logits(one, direct(k0));
-      if (k0 == first) { max_of(one, k0); set_ref(one); }     // (-inf where none of them counts: then none of the later ones does)
-      add_chunk(one, k0);
+      logits(qbn, direct(k0));
+      if (k0 == first) { max_of(qbn, k0); set_ref(qbn); }     // (-inf where none of them counts: then none of the later ones does)
+      add_chunk(qbn, k0);
     }
     across();
-    if (lg == 0) { part_ref[wv][l16] = ref[0]; part_sum[wv][l16] = sum[0]; }
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb)
+      if (lg == 0) { part_ref[wv][qb * 16 + l16] = ref[qb]; part_sum[wv][qb * 16 + l16] = sum[qb]; }
     __syncthreads();
     if (wv != 0) return;
-    for (int w = 0; w < kQkWaves; ++w) ref[0] = fmaxf(ref[0], part_ref[w][l16]);
-    sum[0] = 0.0;
-    for (int w = 0; w < kQkWaves; ++w) {
-      const float r = part_ref[w][l16];
-      const double t = part_sum[w][l16];
-      over |= !(t < 0x1p100);
-      sum[0] += r > NEG ? ldexp(t, (int)fmaxf(r - ref[0], -3000.0f)) : 0.0;
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+      for (int w = 0; w < kQkWaves; ++w) ref[qb] = fmaxf(ref[qb], part_ref[w][qb * 16 + l16]);
+      sum[qb] = 0.0;
+      for (int w = 0; w < kQkWaves; ++w) {
+        const float r = part_ref[w][qb * 16 + l16];
+        const double t = part_sum[w][qb * 16 + l16];
+        over |= !(t < 0x1p100);
+        sum[qb] += r > NEG ? ldexp(t, (int)fmaxf(r - ref[qb], -3000.0f)) : 0.0;
+      }
     }
+  };
+  if (share_keys) {                                  // uniform in the workgroup
+    if (narrow) shared_keys(std::integral_constant<int, 1>{});
+    else shared_keys(all);
+    if (wv != 0) return;
   } else {
     load_stage(0);
     store_stage(0);
@@ -290,7 +302,8 @@ __global__ __launch_bounds__(kQkWaves * kWave) __attribute__((amdgpu_waves_per_e
 // barriers.  Measured at 4 x 2881 tokens, 16 heads of 64 / 16 x 577, 16 of 64 / 8 x 675 causal, 32
 // of 128: operands straight from memory 314 / 70 / 99 us; staged, 192 x 64 by eight wavefronts, each head
 // on its own 180 / 44 / 56; the next head's matrix instructions under this head's exponentials, 96 x 64 by
-// four wavefronts (three workgroups on a compute unit instead of two) 170 / 40 / 51.
+// four wavefronts (three workgroups on a compute unit instead of two) 170 / 40 / 51.  With heads of 32 four fit if the
+// registers are held to 128 (131 otherwise): step of 16 x 577 tokens, 16 heads 77.9 -> 74.1 us, one head 46.0 -> 43.3.
 constexpr int kQkBand = 8;                          // key tiles side by side in the order of the workgroups
 constexpr int kQkCols = 2;                          // wavefronts side by side on the keys
 constexpr int kQkMB = kQkKeys / 16 / kQkCols;       // 16-key blocks of a wavefront
@@ -300,7 +313,7 @@ template <bool SPLIT> struct QkMeanShape {
   static constexpr int kThreads = kRows * kQkCols * kShares * kWave;
 };
 template <int KS, bool DEC, bool SPLIT>
-__global__ __launch_bounds__(QkMeanShape<SPLIT>::kThreads) __attribute__((amdgpu_waves_per_eu(SPLIT || KS == 4 ? 2 : 3))) void qk_mean_kernel(QkArgs a) {
+__global__ __launch_bounds__(QkMeanShape<SPLIT>::kThreads) __attribute__((amdgpu_waves_per_eu(SPLIT || KS == 4 ? 2 : KS == 1 ? 4 : 3))) void qk_mean_kernel(QkArgs a) {
   constexpr int KSS = KS > 2 ? 2 : KS, NST = KS / KSS, CH = KSS * 4;     // 32-feature steps of a stage, stages of a head
   using Shape = QkMeanShape<SPLIT>;
   constexpr int QR = Shape::kRows * kQkTile;                              // query rows of a stage
@@ -557,6 +570,13 @@ static void launch_qk(QkArgs a, hipStream_t s) {
   constexpr int CH = (KS > 2 ? 2 : KS) * 4;
   const int tiles = (a.nq + kQkTile - 1) / kQkTile;
   a.q_groups = (tiles + kQkWaves - 1) / kQkWaves;
+  // Fewer than one workgroup per compute unit (for heads of 32, whose steps are short, four): one tile each, whose keys
+  // the wavefronts share.  Step of 16 x 577 tokens, whole tiles per wavefront and shared: one head of 64
+  // 52.7 and 47.6 us, three 55.5 and 54.8, four (256 workgroups) 57.4 and 59.5, twelve 76.6 and 88.4; heads of 32: one 49.5 and
+  // 45.9, eight 62.0 and 61.6, twelve 70.1 and 69.6.  One image of 577, one head 38.4 and 34.0; of 626, sixteen of 32
+  // 38.8 and 35.0.
+  a.share_keys = (int64_t)a.nb * a.H * a.q_groups < (KS == 1 ? 1024 : 256);
+  if (a.share_keys) a.q_groups = tiles;
   hipLaunchKernelGGL((qk_norm_kernel<KS, DEC>), dim3(xcd_padded_total(a.nb * a.H * a.q_groups)), dim3(kQkWaves * kWave), 0, s, a);
   auto mean = [&](auto kern, auto shape) {
     using Shape = decltype(shape);

@@ -206,6 +206,14 @@ def test_query_tiles_and_head_shares(ctx, B, grid, H, d):
     assert full >= (B + 1) // 2
 
 
+@pytest.mark.parametrize("B,grid,H,d", [(16, 24, 3, 64), (16, 24, 4, 64), (16, 14, 15, 32), (32, 14, 16, 32)])
+def test_keys_shared_by_the_wavefronts_or_not(ctx, B, grid, H, d):
+    """192 and 256 workgroups of the row normalisers with heads of 64, 480 and 1024 with heads of 32: below 256
+    and 1024 the wavefronts of a workgroup share the keys of a query tile."""
+    full = _case(ctx, 330 + B + H, B, grid, 72, H, d, "bf16", grid * grid // 3, 1.0)
+    assert full >= (B + 1) // 2
+
+
 @pytest.mark.parametrize("grid,H,d,where", [(24, 2, 64, 500), (24, 2, 64, 40), (12, 3, 32, 144), (30, 1, 128, 33), (3, 2, 64, 9)])
 def test_logits_far_above_those_of_the_first_keys(ctx, grid, H, d, where):
     """Rows whose largest logit lies 100 to 300 (units of e) above those of the keys the softmax
