@@ -111,8 +111,7 @@ def test_small_and_ragged_shapes(ctx, seed, grid, H, d, n_keep):
 
 
 def test_long_sequence_at_full_width_from_queries_and_keys(ctx):
-    """2304 patches + [CLS], 16 heads of 64, D = 1024, 640 preserved (the size class of BASELINE
-    config 2): four key blocks, the last of 385 keys."""
+    """2304 patches + [CLS], 16 heads of 64, D = 1024, 640 preserved."""
     full = _case(ctx, 42, 2, 48, 1024, 16, 64, "bf16", 640, 1.0)
     say("2304-patch shape from Q, K: %d of 2 images with every decision identical" % full)
 
@@ -120,9 +119,7 @@ def test_long_sequence_at_full_width_from_queries_and_keys(ctx):
 @pytest.mark.parametrize("seed,grid,H,d,n_keep", [(1, 27, 3, 64, 300), (2, 36, 2, 32, 500), (3, 31, 5, 128, 700),
                                                   (4, 40, 1, 64, 1000)])
 def test_sequences_longer_than_one_key_block(ctx, seed, grid, H, d, n_keep):
-    """More than 640 keys: the keys are taken in blocks of 640 in two sweeps (normalisers of every
-    head first, then the probabilities block by block).  730 keys: a second block of 90; 1297: a
-    third block of 17, most of whose wavefronts hold no key; 962 and 1601 with one to five heads."""
+    """730, 1297, 962 and 1601 keys with one to five heads: more keys than heads are unlimited for."""
     full = _case(ctx, 70 + seed, 2, grid, 72, H, d, ["f32", "bf16"][seed % 2], n_keep, 1.0)
     assert full >= 1
 
@@ -161,8 +158,7 @@ def _case_l(ctx, seed, B, n_sys, N, M, D, H, d, n_keep, red, corr, sigma=1.0, st
 @pytest.mark.parametrize("shape", [(3, 77, 9, 72, 3, 32, 31), (35, 576, 64, 128, 4, 64, 144), (5, 1300, 40, 72, 2, 128, 700),
                                    (0, 100, 1, 64, 1, 64, 50)])
 def test_decoder_step_from_queries_and_keys(ctx, shape, red, corr):
-    """89, 675 (the decoder shape of BASELINE config 3: two key blocks), 1345 and 101 positions; with
-    the visual-to-visual terms (tiles over the visual and the text queries) and without (text queries
+    """89, 675, 1345 and 101 positions; with the visual-to-visual terms (tiles over the visual and the text queries) and without (text queries
     alone); 1 to 64 text queries."""
     n_sys, N, M, D, H, d, n_keep = shape
     full = _case_l(ctx, 80 + N % 50, 2, n_sys, N, M, D, H, d, n_keep, red, corr)
@@ -185,7 +181,7 @@ def test_unsupported_shapes_are_refused(ctx):
         with pytest.raises(fc.FicocoError) as e:
             fc.workspace_bytes(p)
         assert e.value.code == fc.EUNSUPPORTED
-    # beyond 640 rows the normalisers of all heads are kept on chip: at most 64 heads
+    # beyond 640 rows: at most 64 heads
     cfg = synth.ficoco_v_single(seed=9, B=1, grid=26, D=8, H=1, centres=2, dtype="bf16", n_keep=8)
     Xd = cfg["X"].to("cuda")
     Q = torch.zeros(1, 65, 677, 32, dtype=torch.bfloat16, device="cuda")
@@ -231,19 +227,97 @@ def test_logits_far_above_those_of_the_first_keys(ctx, grid, H, d, where):
     assert np.max(np.abs(out["scores"][0] - ref["scores"])) <= 6e-5 * np.max(np.abs(ref["scores"]))
 
 
-def test_images_in_rounds_and_rows_beyond_the_text(ctx):
-    """More images than the row normalisers have room for at a time (40 x 64 heads x 601 queries:
-    two rounds), compared with the same images one by one."""
+def test_images_in_rounds(ctx):
+    """More images than the row normalisers have room for at a time (40 x 64 heads x 577 queries: two rounds of
+    20): scores, edges, weights and tokens on both sides of the border."""
     B, grid, H, d = 40, 24, 64, 32
     cfg = synth.ficoco_v_single(seed=5, B=B, grid=grid, D=8, H=1, centres=8, dtype="bf16", n_keep=100)
     Q, K = draw_qk(6, B, H, cfg["N"] + 1, d, 1.0)
     out = run_qk(ctx, cfg, Q, K)
-    for b in (0, 26, 27, 28, 39):
-        one = dict(cfg, X=cfg["X"][b:b + 1], B=1)
-        alone = run_qk(ctx, one, Q[b:b + 1], K[b:b + 1])
-        # (one image alone has its heads split over wavefronts: sums in another order)
-        np.testing.assert_allclose(out["scores"][b], alone["scores"][0], rtol=0, atol=2e-6 * np.max(np.abs(alone["scores"][0])))
-        assert len(np.setdiff1d(out["keep"][b], alone["keep"][0])) <= 1
+    full = 0
+    for b in (0, 19, 20, 39):
+        ref = O.v_step_qk(O.widen(synth.to_numpy(cfg["X"][b])), O.widen(synth.to_numpy(Q[b])), O.widen(synth.to_numpy(K[b])),
+                          float(d) ** -0.5, cls_index=0, vis_begin=1, N=cfg["N"], n_keep=100, lam=cfg["lam"],
+                          eps=cfg["eps"], grid=cfg["grid"], window=2, coef=2.0)
+        full += compare_under_margin_rule(out, b, ref, "bf16", 1)
+    assert full >= 3
+
+
+@pytest.mark.parametrize("B,N,M,red,corr,check", [
+    (130, 100, 40, fc.R_ATTN_RECV, fc.C_ATTN, (0, 64, 65, 129)),         # 140 queries of 64 heads: two rounds of 65
+    (560, 40, 30, fc.R_SIM_MEAN, fc.C_COSINE, (0, 279, 280, 559)),       # the text queries alone: two rounds of 280
+    (3, 60, 21, fc.R_ATTN_RECV, fc.C_ATTN, (0, 1, 2)),
+])
+def test_decoder_images_in_rounds_and_rows_beyond_the_text(ctx, B, N, M, red, corr, check):
+    """The causal form in rounds of images, with rows behind the text tokens that are no query of the step."""
+    n_sys, tail, H, d, D, n_keep = 3, 19, 64, 32, 16, N // 3
+    cfg = synth.ficoco_l_decoder(seed=15, B=B, n_sys=n_sys, N=N, M=M + tail, D=D, H=1, centres=8, n_keep=n_keep, with_vv=False)
+    Q, K = draw_qk(16, B, H, n_sys + N + M + tail, d, 1.0)
+    Q[:, :, n_sys + N + M:] = 100.0                          # (a query from there would be seen)
+    K[:, :, n_sys + N + M:] = 100.0
+    Xd, Qd, Kd = cfg["X"].to("cuda"), Q.to("cuda"), K.to("cuda")
+    p = fc.make_problem(Xd, variant=fc.VARIANT_L, vis_begin=n_sys, N=N, n_keep=n_keep, w_score=cfg["beta"],
+                        gamma=cfg["gamma"], eps=cfg["eps"], red_src=red, sem_src=fc.G_TEXT_ATTN, corr_src=corr,
+                        window=0, Q=Qd, K=Kd, qk_begin=0, M=M)
+    buf = fc.Buffers(p, "cuda", Xd.dtype)
+    fc.ficoco_l_step(ctx, p, buf)
+    out = P.gpu_outputs(buf)
+    del Xd, Qd, Kd
+    full = 0
+    for b in check:
+        ref = O.l_step_qk(O.widen(synth.to_numpy(cfg["X"][b])), O.widen(synth.to_numpy(Q[b])), O.widen(synth.to_numpy(K[b])),
+                          float(d) ** -0.5, vis_begin=n_sys, N=N, M=M, n_keep=n_keep, beta=cfg["beta"], gamma=cfg["gamma"],
+                          eps=cfg["eps"], red_src="attn" if red == fc.R_ATTN_RECV else "sim_mean",
+                          corr_src="attn" if corr == fc.C_ATTN else "cosine")
+        full += compare_under_margin_rule(out, b, ref, cfg["dtype"], n_sys)
+    assert full >= len(check) - 1
+
+
+@pytest.mark.parametrize("B,N,M,H,d,visual", [(1, 300, 7, 3, 64, False), (1, 260, 16, 3, 32, False), (1, 300, 17, 3, 64, False),
+                                              (1, 150, 60, 3, 128, True), (2, 290, 60, 64, 64, True)])
+def test_causal_logits_far_above_those_of_the_first_keys(ctx, B, N, M, H, d, visual):
+    """The decoder's causal form where a visual and a text key lie far above the first 32: rows that are done again
+    with their own maximum, and, for queries before such a key, probabilities beyond single precision that must not
+    be seen.  16 queries or fewer, one tile whose keys the wavefronts share, and whole tiles per wavefront (the
+    last).  Logits of a few hundred are rounded to 2^-24 of themselves: probabilities to about 3e-5, so decisions
+    are compared where the margin exceeds 1e-3."""
+    n_sys, D, n_keep = 4, 72, N // 3
+    cfg = synth.ficoco_l_decoder(seed=83, B=B, n_sys=n_sys, N=N, M=M, D=D, H=1, centres=8, n_keep=n_keep, with_vv=False)
+    Q, K = draw_qk(84, B, H, n_sys + N + M, d, 1.0)
+    for where in (n_sys + N - 20, n_sys + N + M // 2):
+        K[:, :, where] = (K[:, :, where].float() * 40.0).to(torch.bfloat16)
+    Q = (Q.float() * 8.0).to(torch.bfloat16)
+    x = (Q[0].float() @ K[0].float().transpose(1, 2)) * float(d) ** -0.5
+    first = torch.stack([x[:, n_sys + N:, c:c + 32].amax(2) for c in (0, 32, 64, 96)]).amin(0)
+    assert (x[:, n_sys + N:, n_sys + N - 20] - first).max() > 90     # (beyond 2^100 relative to any wavefront's reference)
+    Xd, Qd, Kd = cfg["X"].to("cuda"), Q.to("cuda"), K.to("cuda")
+    p = fc.make_problem(Xd, variant=fc.VARIANT_L, vis_begin=n_sys, N=N, n_keep=n_keep, w_score=cfg["beta"],
+                        gamma=cfg["gamma"], eps=cfg["eps"], red_src=fc.R_ATTN_RECV if visual else fc.R_SIM_MEAN,
+                        sem_src=fc.G_TEXT_ATTN, corr_src=fc.C_ATTN if visual else fc.C_COSINE, window=0, Q=Qd, K=Kd, qk_begin=0, M=M)
+    buf = fc.Buffers(p, "cuda", Xd.dtype)
+    fc.ficoco_l_step(ctx, p, buf)
+    out = P.gpu_outputs(buf)
+    del Xd, Qd, Kd
+    ref = O.l_step_qk(O.widen(synth.to_numpy(cfg["X"][0])), O.widen(synth.to_numpy(Q[0])), O.widen(synth.to_numpy(K[0])),
+                      float(d) ** -0.5, vis_begin=n_sys, N=N, M=M, n_keep=n_keep, beta=cfg["beta"], gamma=cfg["gamma"],
+                      eps=cfg["eps"], red_src="attn" if visual else "sim_mean", corr_src="attn" if visual else "cosine")
+    scale = np.max(np.abs(ref["scores"]))
+    assert np.max(np.abs(out["scores"][0] - ref["scores"])) <= 6e-5 * scale
+    assert np.all(np.isfinite(O.widen(out["X_out"][0])))
+    order = np.sort(ref["scores"])[::-1]
+    cut = 0.5 * (order[N - n_keep - 1] + order[N - n_keep])
+    far = np.abs(ref["scores"] - cut) > 1e-3 * scale
+    gone = np.zeros(N, bool)
+    gone[out["discard"][0]] = True
+    assert np.array_equal(gone[far], (ref["scores"] > cut)[far])
+    assert np.array_equal(out["discard"][0], ref["S"]), "the case is meant to have its cut in a gap"
+    C, tau = ref["C"], np.asarray(ref["tau"])[:, None]
+    clear = np.all((np.abs(C - tau) > 1e-3 * tau) | (C == tau), axis=1) & (tau[:, 0] > 0)
+    assert clear.sum() >= len(clear) // 4                   # (by the oracle alone: rows that the margin leaves)
+    for a in np.flatnonzero(clear):
+        J = ref["J"][a]
+        assert np.array_equal(out["tgt"][0, a, :out["cnt"][0, a]], J)
+        np.testing.assert_allclose(out["alpha"][0, a, :len(J)], ref["alpha"][a], rtol=2e-3)
 
 
 def test_static_scratch_takes_what_it_took(ctx):
