@@ -168,10 +168,12 @@ typedef struct {
    * vis_begin + N .. vis_begin + N + M - 1 and must lie inside the block; their rows give the
    * text profiles of Eq. 3 / Eq. 4, the visual rows the visual-to-visual terms where selected.  bfloat16 only (qk_dtype = FICOCO_BF16, whatever
    * `dtype` the tokens have), d_head in {32, 64, 128}; with qk_n > 640
-   * and for FiCoCo-L at most 64 heads: FICOCO_EUNSUPPORTED otherwise.  Logits, exponentials and row sums are single precision (bf16 products are exact
-   * in it), so scores and map entries agree with a double-precision evaluation to about 1e-6
-   * relative, not to the last bit: a top-K or threshold decision whose margin is below that may
-   * differ from one taken on double-precision values. */
+   * and for FiCoCo-L at most 64 heads: FICOCO_EUNSUPPORTED otherwise.  Logits and exponentials are
+   * single precision (bf16 products are exact in it, row and column sums double), so with logits
+   * of the order of ten scores and map entries agree with a double-precision evaluation to about
+   * 1e-6 relative, not to the last bit: a top-K or threshold decision whose margin is below that may
+   * differ from one taken on double-precision values.  The bound grows with the largest logit, which
+   * is itself rounded to 2^-24 of its size: about 3e-5 at a few hundred. */
   const void *Q; /* [B][H][qk_n][d_head], d_head contiguous */
   const void *K; /* same shape and strides */
   int64_t qk_stride_b, qk_stride_h, qk_stride_n;

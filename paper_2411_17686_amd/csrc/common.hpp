@@ -82,19 +82,19 @@ struct Plan {
 // scratch: bytes the whole workspace may have at most, as far as the lists of the targets can be cut down to it
 int make_plan(const ficoco_problem& p, Plan& plan, const char** why, size_t scratch = SIZE_MAX);
 
-// One edge of the correlate stage in the form the merge kernel scans: target slot, source
-// visual token, weight.  16 bytes, one load.
-
 // ---- launchers (all asynchronous on `s`) -----------------------------------------------
 // text_elsewhere: the text-profile kernel is not launched here (text_with_features: it rides in the
 // feature stage's launch)
 void launch_attn_reduce(const ficoco_problem& p, const Plan& pl, char* ws, hipStream_t s, bool text_elsewhere = false);
 void launch_attn_qk(const ficoco_problem& p, const Plan& pl, char* ws, hipStream_t s);
 constexpr int kQkTile = 48;        // query rows of a unit of the query/key form (its column partials are one per tile)
-constexpr int kQkMaxKeys = 640;    // with more keys than this, and for FiCoCo-L, at most ...
-constexpr int kQkLongMaxHeads = 64; // ... this many heads are taken
 // The row normalisers are kept for as many images at a time as fit in this many bytes (at least one).
 constexpr size_t kQkNormBytes = (size_t)8 << 20;
+// With more keys than kQkMaxKeys, and for FiCoCo-L, at most kQkLongMaxHeads heads are taken: one image of FiCoCo-V then
+// stays within those bytes whatever its length is, as the static scratch requires (640 keys would need 1600 heads
+// for as much), and FiCoCo-L, which has no static form, has the same limit.
+constexpr int kQkMaxKeys = 640, kQkLongMaxHeads = 64;
+static_assert((size_t)kQkLongMaxHeads * (kMaxSelectN + 1) * sizeof(float2) <= kQkNormBytes, "one image");
 // with_text: the launch of the row-norm kernel also forms the text profiles and the launch of the
 // column-sum kernel their statistics (with_cmax: the column maxima too), see text_with_features
 void launch_features(const ficoco_problem& p, const Plan& pl, char* ws, hipStream_t s, bool with_text = false,

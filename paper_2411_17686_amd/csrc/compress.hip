@@ -6,11 +6,13 @@
 //     (X_j + sum_i alpha_ij X_i) / (1 + sum_i alpha_ij)
 // accumulated in double precision in ascending i; rows without sources, and every token
 // outside the visual span, are copied bit for bit.  No floating-point atomics anywhere.
-// Where the sources come from: with few discarded tokens the workgroup stages the image's
-// per-source edge lists in LDS and every wavefront scans them for its target; otherwise
-// `invert_edges` first buckets the edges by target with an integer counting sort in LDS
-// (order inside a bucket is arbitrary) and the merging wavefront puts its bucket into
-// ascending source order before it adds, so the result never depends on scheduling.
+// Where the sources come from: in a fused step from the target's list, which the correlate stage filled in
+// any order and the merging wavefront (or, with many sources, workgroup) puts in ascending order
+// (`merge_listed`).  A staged call has the edge lists alone: with few discarded tokens the workgroup
+// stages them in LDS and every wavefront scans them for its target; otherwise `invert_edges` first
+// buckets the edges by target with an integer counting sort in LDS (order inside a bucket is
+// arbitrary) and the merging wavefront puts its bucket into ascending source order before it adds.
+// Either way the result never depends on scheduling.
 #include "common.hpp"
 
 #include <type_traits>
