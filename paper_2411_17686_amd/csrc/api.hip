@@ -286,9 +286,9 @@ int make_plan(const ficoco_problem& p, Plan& pl, const char** why, size_t scratc
     // they are a tenth of the head-mean map): bounded by what all images together may take, they ended at
     // B = 219 there, and what they gain with them (256 images of one head 302 us without, 280 with them; 32 x
     // 2881 tokens 740 and 658).  Up to kMatchMaxRows discarded tokens half as many entries do where a target has no more
-    // than one source on average, or two by attention, whose counts spread less than those of like tokens
-    // (64 images of one head, 0.5 sources: 84.0 us with 32 entries, 78.5 with 16; 256 images, 2 sources: 288
-    // and 282; 16 images, 19 sources: 212 and 365).  In a scratch of given size the lists take what the rest
+    // than two sources on average by attention (64 images of one head, 0.5 sources: 84.0 us with 32 entries, 78.5 with
+    // 16; 256 images, 2 sources: 288 and 282; 16 images, 19 sources: 212 and 365); the counts of like tokens spread
+    // more (cosine, 0.5 sources: the merge 12.4 and 15.1 us).  In a scratch of given size the lists take what the rest
     // leaves; below a quarter / an eighth of the full length nothing is gained.
     const size_t targets = (size_t)p.n_keep, entry = sizeof(int32_t) + sizeof(double);
     const bool is_long = edges_inverted(pl);
@@ -303,7 +303,7 @@ int make_plan(const ficoco_problem& p, Plan& pl, const char** why, size_t scratc
     pl.cnt_stride = is_long || edges >= 4 * (int64_t)p.n_keep ? 16 : 1;
     const int least = is_long ? kBucketCapLong / 8 : kBucketCap / 4;
     auto image_bytes = [&](int cap) { return targets * (cap * entry + pl.cnt_stride * sizeof(int32_t)); };
-    const bool few = edges <= (p.corr_src == FICOCO_C_ATTN ? 2 : 1) * (int64_t)p.n_keep;
+    const bool few = p.corr_src == FICOCO_C_ATTN && edges <= 2 * (int64_t)p.n_keep;
     int cap = is_long ? kBucketCapLong : std::min(few ? kBucketCap / 2 : kBucketCap, (pl.n_disc + 7) / 8 * 8);
     while (cap > least && image_bytes(cap) > kBucketBytes) cap /= 2;
     const size_t used = off + 3 * 256;                // (each region is rounded up)
