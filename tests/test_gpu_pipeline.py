@@ -2,8 +2,8 @@
 twelve fused steps in flight round-robin (bench.issue_steps, on bench.py's own inputs).  What every
 stream's buffers hold at the end must equal (a) the same step run alone on one stream, bit for bit,
 and (b) the CPU oracle, for one image of the input set that step read.  The other benchmark
-configurations (cosine correlation with bucketed edges, FiCoCo-L, maps formed from queries and keys
-with the head groups' partial sums in the workspace) are held to (a): every one of their kernels is
+configurations (cosine correlation with long lists of sources, FiCoCo-L, maps formed from queries and
+keys with their row normalisers in the workspace) are held to (a): every one of their kernels is
 compared with the oracle on one stream elsewhere, what is new here is that three workspaces of one
 context are in use at once."""
 import pytest
