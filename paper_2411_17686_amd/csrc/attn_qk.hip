@@ -78,23 +78,29 @@ __device__ __forceinline__ int lds_chunk(int r, int c) { return r * CH + (c ^ ((
 // does overflow (its largest logit more than ~70 above those of the first 32 keys) is seen in the
 // sum and done again with its own maximum.
 //
-// Bound by the vector unit: exponential, multiply-add and add per logit (VALU busy 66 % of the time at
-// 4 x 2881 tokens, 16 heads of 64: 116 us; with operands straight from memory 165-205 us).
+// Bound by the vector unit: exponential, multiply-add and add per logit, and by the matrix instructions, which hardly
+// run beside them (4 x 2881 tokens, 16 heads of 64: 112 us; with operands straight from memory 165-205 us).
 template <int KS, bool DEC>
 __global__ __launch_bounds__(kQkWaves * kWave) __attribute__((amdgpu_waves_per_eu(2))) void qk_norm_kernel(QkArgs a) {
   constexpr int CH = KS * 4, T = kQkWaves * kWave, RPI = T / CH, NL = kQkKeys / RPI;
   __shared__ u32x4_t stage[2][kQkKeys * CH];
-  const int units = a.nb * a.H * a.q_groups;
-  const int unit = xcd_logical_id(blockIdx.x, units);     // the workgroups of a head share an L2 (its keys)
-  if (unit >= units) return;
+  // The workgroups of a head share an L2 (its keys).  The last ones of the heads, if they are narrow, come behind all
+  // others: in their places between them they left every q_groups-th compute unit without work (a quarter of the chip at
+  // 16 x 577 tokens: 29.8 us, and 24.3 with the order of precedence below).
+  const bool last_narrow = a.nq - (a.q_groups - 1) * (a.share_keys ? 1 : kQkWaves) * kQkTile <= 16;
+  const int groups = a.q_groups - (last_narrow ? 1 : 0), units = a.nb * a.H * groups, first = xcd_padded_total(units);
+  const bool behind = (int)blockIdx.x >= first;
+  const int unit = xcd_logical_id(behind ? blockIdx.x - first : blockIdx.x, behind ? a.nb * a.H : units);
+  if (unit >= (behind ? a.nb * a.H : units)) return;
   const int tid = threadIdx.x, lane = tid % kWave, l16 = lane % 16, lg = lane / 16;
   const int wv = __builtin_amdgcn_readfirstlane(tid / kWave);
-  const int w0 = (unit % a.q_groups) * (a.share_keys ? 1 : kQkWaves) * kQkTile;
+  const int in_head = behind ? groups : unit % groups, head = behind ? unit : unit / groups;
+  const int w0 = in_head * (a.share_keys ? 1 : kQkWaves) * kQkTile;
   const bool narrow = a.nq - w0 <= 16;     // one block of queries in all (the [CLS] query behind 576 visual ones)
   const bool share_keys = a.share_keys || narrow;
   const int v0 = share_keys ? w0 : w0 + wv * kQkTile;
-  const int h = (unit / a.q_groups) % a.H;
-  const int64_t bi = unit / (a.q_groups * a.H);
+  const int h = head % a.H;
+  const int64_t bi = head / a.H;
   const float NEG = -__builtin_huge_valf();
   const bf16_t* Qh = a.Q + (a.b0 + bi) * a.sb + (int64_t)h * a.sh;
   const bf16_t* Kh = a.K + (a.b0 + bi) * a.sb + (int64_t)h * a.sh;
@@ -125,19 +131,19 @@ __global__ __launch_bounds__(kQkWaves * kWave) __attribute__((amdgpu_waves_per_e
     for (int i = 0; i < NL; ++i) stage[buf][lds_chunk<CH>(tid / CH + i * RPI, tid % CH)] = next[i];
   };
 
-  f32x4_t S[kQkKB][kQkQB];
-  // logits of 32 keys; `key_op(kb, ks)` gives this lane's operand
-  auto logits = [&](auto qbn, auto key_op) __attribute__((always_inline)) {
+  typedef f32x4_t Logits[kQkKB][kQkQB];      // of 32 keys
+  Logits S;
+  // `key_op(kb, ks)` gives this lane's operand
+  auto logits = [&](auto qbn, auto key_op, Logits& S) __attribute__((always_inline)) {
     constexpr int QB = decltype(qbn)::value;
 #pragma unroll
     for (int kb = 0; kb < kQkKB; ++kb) {
 #pragma unroll
-      for (int qb = 0; qb < QB; ++qb) S[kb][qb] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
       for (int ks = 0; ks < KS; ++ks) {
         const bf16x8_t kf = key_op(kb, ks);
 #pragma unroll
-        for (int qb = 0; qb < QB; ++qb) S[kb][qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, qf[qb][ks], S[kb][qb], 0, 0, 0);
+        for (int qb = 0; qb < QB; ++qb)
+          S[kb][qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, qf[qb][ks], ks == 0 ? f32x4_t{0.0f, 0.0f, 0.0f, 0.0f} : S[kb][qb], 0, 0, 0);
       }
     }
   };
@@ -164,18 +170,25 @@ __global__ __launch_bounds__(kQkWaves * kWave) __attribute__((amdgpu_waves_per_e
       ref[qb] = ceilf(ref[qb] * a.scale_log2e);
     }
   };
-  auto add_chunk = [&](auto qbn, int k0) __attribute__((always_inline)) {
+  auto add_whole = [&](auto qbn, const Logits& S) __attribute__((always_inline)) {
+    constexpr int QB = decltype(qbn)::value;
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+      float part;
+#pragma unroll
+      for (int kb = 0; kb < kQkKB; ++kb)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const float e = __builtin_amdgcn_exp2f(fmaf(S[kb][qb][v], a.scale_log2e, -ref[qb]));
+          part = kb == 0 && v == 0 ? e : part + e;
+        }
+      sum[qb] += (double)part;
+    }
+  };
+  auto add_chunk = [&](auto qbn, int k0, const Logits& S) __attribute__((always_inline)) {
     constexpr int QB = decltype(qbn)::value;
     if (k0 + kQkKB * 16 <= full_end) {               // uniform
-#pragma unroll
-      for (int qb = 0; qb < QB; ++qb) {
-        float part = 0.0f;
-#pragma unroll
-        for (int kb = 0; kb < kQkKB; ++kb)
-#pragma unroll
-          for (int v = 0; v < 4; ++v) part += __builtin_amdgcn_exp2f(fmaf(S[kb][qb][v], a.scale_log2e, -ref[qb]));
-        sum[qb] += (double)part;
-      }
+      add_whole(qbn, S);
     } else {
 #pragma unroll
       for (int kb = 0; kb < kQkKB; ++kb)
@@ -220,9 +233,9 @@ __global__ __launch_bounds__(kQkWaves * kWave) __attribute__((amdgpu_waves_per_e
     const int first = wv * kQkKB * 16;
 #pragma unroll 1
     for (int k0 = first; k0 < k_end; k0 += kQkWaves * kQkKB * 16) {
-      logits(qbn, direct(k0));
+      logits(qbn, direct(k0), S);
       if (k0 == first) { max_of(qbn, k0); set_ref(qbn); }     // (-inf where none of them counts: then none of the later ones does)
-      add_chunk(qbn, k0);
+      add_chunk(qbn, k0, S);
     }
     across();
 #pragma unroll
@@ -247,26 +260,39 @@ __global__ __launch_bounds__(kQkWaves * kWave) __attribute__((amdgpu_waves_per_e
     else shared_keys(all);
     if (wv != 0) return;
   } else {
+    // The oldest wavefront of a SIMD is served first (of the four on one at 4 x 2881 tokens they ended at 58, 80, 104
+    // and 128 us), and the last one is left alone with its trips through LDS and the matrix unit.  So the wavefronts with
+    // most keys left take precedence, down to an eighth of the keys (110 to 120 us then).  Causal maps: wavefronts differ
+    // in length and end one after the other anyway (47 us for 8 x 675 tokens, 54 with precedence).
+    int level = 4;
     load_stage(0);
     store_stage(0);
     __syncthreads();
 #pragma unroll 1
     for (int k0 = 0; k0 < wg_end; k0 += kQkKeys) {
+      const int left = k_end - k0, now = (left > a.n / 2 ? 1 : 0) + (left > a.n / 4 ? 1 : 0) + (left > a.n / 8 ? 1 : 0);
+      if (!DEC && now != level) {                      // uniform
+        level = now;
+        if (now == 3) __builtin_amdgcn_s_setprio(3);
+        else if (now == 2) __builtin_amdgcn_s_setprio(2);
+        else if (now == 1) __builtin_amdgcn_s_setprio(1);
+        else __builtin_amdgcn_s_setprio(0);
+      }
       const int buf = k0 / kQkKeys % 2;
       load_stage(k0 + kQkKeys);       // on their way while the current keys are added (past the end: the last row)
       issue_fence();
-      if (k0 < k_end) {
-        const bf16x8_t* st = (const bf16x8_t*)stage[buf];
+      const bf16x8_t* st = (const bf16x8_t*)stage[buf];
 #pragma unroll
-        for (int half = 0; half < 2; ++half) {
-          logits(all, [&](int kb, int ks) { return st[lds_chunk<CH>((half * kQkKB + kb) * 16 + l16, ks * 4 + lg)]; });
-          if (half == 0 && k0 == 0) { max_of(all, 0); set_ref(all); }
-          add_chunk(all, k0 + half * kQkKB * 16);
-        }
+      for (int half = 0; half < 2; ++half) {
+        if (k0 + half * kQkKB * 16 >= k_end) continue;   // uniform
+        logits(all, [&](int kb, int ks) { return st[lds_chunk<CH>((half * kQkKB + kb) * 16 + l16, ks * 4 + lg)]; }, S);
+        if (half == 0 && k0 == 0) { max_of(all, 0); set_ref(all); }
+        add_chunk(all, k0 + half * kQkKB * 16, S);
       }
       store_stage(1 - buf);
       __syncthreads();
     }
+    __builtin_amdgcn_s_setprio(0);
     if (!active) return;
     across();
 #pragma unroll
@@ -276,10 +302,10 @@ __global__ __launch_bounds__(kQkWaves * kWave) __attribute__((amdgpu_waves_per_e
 #pragma unroll
     for (int qb = 0; qb < kQkQB; ++qb) { ref[qb] = NEG; sum[qb] = 0.0; }
 #pragma unroll 1
-    for (int k0 = 0; k0 < k_end; k0 += kQkKB * 16) { logits(all, direct(k0)); max_of(all, k0); }
+    for (int k0 = 0; k0 < k_end; k0 += kQkKB * 16) { logits(all, direct(k0), S); max_of(all, k0); }
     set_ref(all);
 #pragma unroll 1
-    for (int k0 = 0; k0 < k_end; k0 += kQkKB * 16) { logits(all, direct(k0)); add_chunk(all, k0); }
+    for (int k0 = 0; k0 < k_end; k0 += kQkKB * 16) { logits(all, direct(k0), S); add_chunk(all, k0, S); }
     across();
   }
 #pragma unroll
@@ -289,6 +315,26 @@ __global__ __launch_bounds__(kQkWaves * kWave) __attribute__((amdgpu_waves_per_e
   }
 }
 
+// The value of lane ^ 4: rows shifted by four lanes up for the first quad of a pair, down for the second.
+__device__ __forceinline__ int lane_xor_4(int v) {
+  const int up = __builtin_amdgcn_update_dpp(v, v, 0x104, 0xF, 0x5, false);      // row_shl:4 into quads 0 and 2
+  return __builtin_amdgcn_update_dpp(up, v, 0x114, 0xF, 0xA, false);             // row_shr:4 into quads 1 and 3
+}
+// Eight values of every lane, each summed over the 16 lanes of a row: the tree of the four steps lane ^ 1, ^ 2, ^ 4,
+// ^ 8.  Every step hands half of the values to the other lane of the pair, so lane l is left with value
+// 4 (l & 1) + (l & 2) + (l >> 2 & 1) alone: 15 additions instead of 32.
+__device__ __forceinline__ double row_sums_of_8(const double (&x)[8], int l16) {
+  auto pick = [](bool second, double a, double b) { return second ? b : a; };
+  double y[4], z[2];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) y[i] = pick(l16 & 1, x[i], x[i + 4]) + dpp_move<0xB1>(pick(l16 & 1, x[i + 4], x[i]));
+#pragma unroll
+  for (int i = 0; i < 2; ++i) z[i] = pick(l16 & 2, y[i], y[i + 2]) + dpp_move<0x4E>(pick(l16 & 2, y[i + 2], y[i]));
+  const double give = pick(l16 & 4, z[1], z[0]);
+  const double u = pick(l16 & 4, z[0], z[1]) + __hiloint2double(lane_xor_4(__double2hiint(give)), lane_xor_4(__double2loint(give)));
+  return u + dpp_move<0x128>(u);      // rotated by eight: lane ^ 8
+}
+
 // ---- probabilities, head mean, outputs -----------------------------------------------------------
 // A wavefront forms 48 queries x 32 visual keys of an image, the heads added in order in registers.
 // SPLIT = false: the four wavefronts of a workgroup sit two by two on 96 queries x 64 keys and
@@ -296,13 +342,15 @@ __global__ __launch_bounds__(kQkWaves * kWave) __attribute__((amdgpu_waves_per_e
 // take consecutive shares of the heads, each with a staging area of its own; their sums are added
 // pairwise (a fixed tree) in LDS.  Rows are staged 64 features at a time in two buffers, loaded into
 // registers two stages ahead; the exponentials of a head are computed beside the matrix
-// instructions and LDS reads of the next one.
+// instructions and LDS reads of the next one, in a fixed order.  The normalisers of a head come through LDS
+// as well (each wavefront reading its own took 30 % of the address unit's time).
 //
 // Bound by the vector unit (exponential, two multiply-adds per logit) and the trips between
 // barriers.  Measured at 4 x 2881 tokens, 16 heads of 64 / 16 x 577, 16 of 64 / 8 x 675 causal, 32
 // of 128: operands straight from memory 314 / 70 / 99 us; staged, 192 x 64 by eight wavefronts, each head
 // on its own 180 / 44 / 56; the next head's matrix instructions under this head's exponentials, 96 x 64 by
-// four wavefronts (three workgroups on a compute unit instead of two) 170 / 40 / 51.  With heads of 32 four fit if the
+// four wavefronts (three workgroups on a compute unit instead of two) 170 / 40 / 51; normalisers through LDS, whole
+// tiles written without tests, exponentials between the other instructions 154 / 33.5 / 49.  With heads of 32 four fit if the
 // registers are held to 128 (131 otherwise): step of 16 x 577 tokens, 16 heads 77.9 -> 74.1 us, one head 46.0 -> 43.3.
 constexpr int kQkBand = 8;                          // key tiles side by side in the order of the workgroups
 constexpr int kQkCols = 2;                          // wavefronts side by side on the keys
@@ -319,7 +367,7 @@ __global__ __launch_bounds__(QkMeanShape<SPLIT>::kThreads) __attribute__((amdgpu
   constexpr int QR = Shape::kRows * kQkTile;                              // query rows of a stage
   constexpr int T = Shape::kRows * kQkCols * kWave, RPI = T / CH;
   constexpr int NL = (QR + kQkKeys + RPI - 1) / RPI;                      // rounds of RPI rows (past the last key: that key again)
-  extern __shared__ u32x4_t stage_m[];                 // [2][SPLIT ? 4 : 1][rounded-up rows of a stage]
+  extern __shared__ u32x4_t stage_m[];                 // [2][SPLIT ? 4 : 1][rounded-up rows of a stage], then the queries' normalisers
   constexpr int kArea = NL * RPI * CH;
   const int units = a.nb * a.q_groups * a.k_tiles;
   const int unit = xcd_logical_id(blockIdx.x, units);
@@ -362,14 +410,23 @@ __global__ __launch_bounds__(QkMeanShape<SPLIT>::kThreads) __attribute__((amdgpu
       const int row = r < QR ? a.row(min(w0 + r, a.nq - 1)) : a.vis0 + min(wk0 + r - QR, a.N - 1);
       src[i] = (r < QR ? a.Q : a.K) + b * a.sb + (int64_t)row * a.sn + t % CH * 8;
     }
+    // (read before the loop: a scalar load on its way there makes every wait for LDS a wait for all of it)
+    float scale = a.scale_log2e;
+    asm volatile("" : "+s"(scale));
     const float2* nrm = a.norm + bi * a.H * a.nq;
+    const uint32_t nrm_at = (uint32_t)min(w0 + t, a.nq - 1);
     u32x4_t next[NL];
+    float2 next_nf;
+    float2* nf_area = (float2*)(stage_m + 2 * kBuf) + share * QR;    // [2][shares][QR]
     auto load_stage = [&](int h, int part) {
       const int64_t off = (int64_t)h * a.sh + part * KSS * 32;
+      if (part == 0) next_nf = (nrm + (int64_t)h * a.nq)[nrm_at];
 #pragma unroll
       for (int i = 0; i < NL; ++i) __builtin_memcpy(&next[i], src[i] + off, 16);
     };
-    auto store_stage = [&](int buf) {
+    // rows into buffer `buf`; a head's first stage brings its normalisers (nf_buf: the head's parity)
+    auto store_stage = [&](int buf, int part, int nf_buf) {
+      if (part == 0 && t < QR) nf_area[nf_buf * Shape::kShares * QR + t] = next_nf;
 #pragma unroll
       for (int i = 0; i < NL; ++i) area[buf * kBuf + lds_chunk<CH>(t / CH + i * RPI, t % CH)] = next[i];
     };
@@ -384,59 +441,83 @@ __global__ __launch_bounds__(QkMeanShape<SPLIT>::kThreads) __attribute__((amdgpu
     };
     // Head i: its logits into S, beside the exponentials of head i - 1 from Sp -- the matrix
     // instructions and the trips through LDS run under the vector work of the head before.
-    auto step = [&](int i, const f32x4_t (&Sp)[kQkMB][QB], const float2 (&np)[QB], f32x4_t (&S)[kQkMB][QB],
+    auto step = [&](int i, int par, const f32x4_t (&Sp)[kQkMB][QB], const float2 (&np)[QB], f32x4_t (&S)[kQkMB][QB],
                     float2 (&nf)[QB]) __attribute__((always_inline)) {
 #pragma unroll
       for (int part = 0; part < NST; ++part) {
-        const int buf = NST == 1 ? i % 2 : part % 2;
-        store_stage(1 - buf);                          // the stage after this one, loaded a step ago
-        if (part == 0) {
-#pragma unroll
-          for (int qb = 0; qb < QB; ++qb)
-            nf[qb] = (nrm + (int64_t)(h0 + min(i, last)) * a.nq)[(uint32_t)min(v0 + qb * 16 + l16, a.nq - 1)];
-        }
+        const int buf = NST == 1 ? par : part % 2;
+        store_stage(1 - buf, (part + 1) % NST, 1 - par);    // the stage after this one, loaded a step ago
         load_at(i + (part + 2) / NST, (part + 2) % NST);
         issue_fence();
         if (active) {                                  // uniform in the wavefront
           const bf16x8_t* st = (const bf16x8_t*)(area + buf * kBuf);
           bf16x8_t qf[QB][KSS], kf[kQkMB][KSS];
 #pragma unroll
-          for (int qb = 0; qb < QB; ++qb)
+          for (int ks = 0; ks < KSS; ++ks) {
 #pragma unroll
-            for (int ks = 0; ks < KSS; ++ks)
-              qf[qb][ks] = st[lds_chunk<CH>(v0 - w0 + qb * 16 + l16, ks * 4 + lg)];
+            for (int qb = 0; qb < QB; ++qb) qf[qb][ks] = st[lds_chunk<CH>(v0 - w0 + qb * 16 + l16, ks * 4 + lg)];
 #pragma unroll
-          for (int kb = 0; kb < kQkMB; ++kb)
-#pragma unroll
-            for (int ks = 0; ks < KSS; ++ks) kf[kb][ks] = st[lds_chunk<CH>(QR + ik0 - wk0 + kb * 16 + l16, ks * 4 + lg)];
-          if (i > 0 && i <= cnt) {                     // uniform
-#pragma unroll
-            for (int kb = 0; kb < kQkMB; ++kb)
-              if (NST == 1 || kb * NST / kQkMB == part) add(Sp, np, kb);
+            for (int kb = 0; kb < kQkMB; ++kb) kf[kb][ks] = st[lds_chunk<CH>(QR + ik0 - wk0 + kb * 16 + l16, ks * 4 + lg)];
           }
+          issue_fence();
+          // In this very order: an exponential to two other vector instructions, then a matrix instruction every
+          // second time.
+          constexpr int E = kQkMB * QB * 4 / NST, M = kQkMB * KSS * QB, kLead = 6;
+          const int e0 = part * E;
+          auto x_of = [&](int i) {
+            const int kb = i / (QB * 4), qb = i / 4 % QB, v = i % 4;
+            return fmaf(Sp[kb][qb][v], scale, -np[qb].x);
+          };
+          float x[2] = {x_of(e0), x_of(e0 + 1)}, e_prev = 0.0f;
+          issue_fence();
 #pragma unroll
-          for (int kb = 0; kb < kQkMB; ++kb)
+          for (int i = 0; i <= E; ++i) {
+            float e = 0.0f;
+            if (i < E) e = __builtin_amdgcn_exp2f(x[i % 2]);
+            if (i + 2 < E) x[i % 2] = x_of(e0 + i + 2);
+            if (i > 0) {
+              const int j = e0 + i - 1, kb = j / (QB * 4), qb = j / 4 % QB, v = j % 4;
+              P[kb][qb][v] = fmaf(e_prev, np[qb].y, P[kb][qb][v]);
+            }
 #pragma unroll
-            for (int ks = 0; ks < KSS; ++ks)
-#pragma unroll
-              for (int qb = 0; qb < QB; ++qb)
+            for (int m = 0; m < M; ++m)
+              if (kLead + m * (E - kLead) / M == i) {
+                const int ks = m / (kQkMB * QB), kb = m / QB % kQkMB, qb = m % QB;
                 S[kb][qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[kb][ks], qf[qb][ks], part == 0 && ks == 0 ? f32x4_t{0.0f, 0.0f, 0.0f, 0.0f} : S[kb][qb], 0, 0, 0);
+              }
+            issue_fence();
+            e_prev = e;
+          }
+          if (part == 0) {
+#pragma unroll
+            for (int qb = 0; qb < QB; ++qb) {
+              nf[qb] = nf_area[par * Shape::kShares * QR + v0 - w0 + qb * 16 + l16];
+              if (SPLIT && i >= cnt) nf[qb].y = 0.0f;  // (a shorter share: its last head again, not counted)
+            }
+          }
         }
         __syncthreads();
       }
     };
+    // (nothing before the first head: 2^-inf, times zero)
     f32x4_t Sa[kQkMB][QB], Sb[kQkMB][QB];
     float2 na[QB], nb[QB];
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+      nb[qb] = make_float2(__builtin_huge_valf(), 0.0f);
+#pragma unroll
+      for (int kb = 0; kb < kQkMB; ++kb) Sb[kb][qb] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+    }
     load_at(0, 0);
-    store_stage(0);
+    store_stage(0, 0, 0);
     load_at(1 / NST, 1 % NST);
     __syncthreads();
 #pragma unroll 1
     for (int i = 0; i < per; i += 2) {
-      step(i, Sb, nb, Sa, na);
-      if (i + 1 < per) step(i + 1, Sa, na, Sb, nb);
+      step(i, 0, Sb, nb, Sa, na);
+      if (i + 1 < per) step(i + 1, 1, Sa, na, Sb, nb);
     }
-    if (active && cnt == per) {
+    if (active) {
 #pragma unroll
       for (int kb = 0; kb < kQkMB; ++kb) {
         if (per % 2) add(Sa, na, kb); else add(Sb, nb, kb);
@@ -449,6 +530,31 @@ __global__ __launch_bounds__(QkMeanShape<SPLIT>::kThreads) __attribute__((amdgpu
     const float invH = 1.0f / (float)a.H;
     const int qt = v0 / kQkTile;
     const bool recv = a.recv_part && qt < a.n_tiles;    // uniform
+    // Whole blocks of visual queries that all count (all but the edges): no test per value, the rows' addresses in
+    // scalar registers, and the column sums of eight keys halved between the lanes step by step.
+    if constexpr (KB == 2) {
+      if (a.abar && recv && ik0 + KB * 16 <= a.N && v0 + QB * 16 <= a.n_visq && !(DEC && ik0 + KB * 16 - 1 > v0)) {     // uniform
+        double cs[KB * 4];
+        const uint32_t at = (uint32_t)(lg * 4 * a.map_pitch + l16);
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            float* row = a.abar + (b * a.N + ik0 + kb * 16 + v) * a.map_pitch + v0;
+            cs[kb * 4 + v] = 0.0;
+#pragma unroll
+            for (int qb = 0; qb < QB; ++qb) {
+              const float pm = sums[kb][qb][v] * invH;
+              row[at + qb * 16] = pm;
+              cs[kb * 4 + v] += (double)pm;
+            }
+          }
+        const double mine = row_sums_of_8(cs, l16);
+        const int i = (l16 & 1) * 4 + (l16 & 2) + (l16 >> 2 & 1);       // the key whose sum this lane holds
+        if (l16 < 8) a.recv_part[(b * a.n_tiles + qt) * a.N + ik0 + i / 4 * 16 + lg * 4 + i % 4] = mine;
+        return;
+      }
+    }
 #pragma unroll
     for (int kb = 0; kb < KB; ++kb) {
 #pragma unroll
@@ -577,13 +683,15 @@ static void launch_qk(QkArgs a, hipStream_t s) {
   // 38.8 and 35.0.
   a.share_keys = (int64_t)a.nb * a.H * a.q_groups < (KS == 1 ? 1024 : 256);
   if (a.share_keys) a.q_groups = tiles;
-  hipLaunchKernelGGL((qk_norm_kernel<KS, DEC>), dim3(xcd_padded_total(a.nb * a.H * a.q_groups)), dim3(kQkWaves * kWave), 0, s, a);
+  const bool narrow = a.nq - (a.q_groups - 1) * (a.share_keys ? 1 : kQkWaves) * kQkTile <= 16;      // (as the kernel sees it)
+  const int groups = a.q_groups - (narrow ? 1 : 0);
+  hipLaunchKernelGGL((qk_norm_kernel<KS, DEC>), dim3(xcd_padded_total(a.nb * a.H * groups) + (narrow ? xcd_padded_total(a.nb * a.H) : 0)), dim3(kQkWaves * kWave), 0, s, a);
   auto mean = [&](auto kern, auto shape) {
     using Shape = decltype(shape);
     // two stages of (queries + keys) rows, in whole rounds of the loader; one pair per share of the heads
     constexpr int kLoaders = Shape::kRows * kQkCols * kWave / CH;
     constexpr int kStageRows = (Shape::kRows * kQkTile + kQkKeys + kLoaders - 1) / kLoaders * kLoaders;
-    constexpr size_t kLds = 2 * (size_t)kStageRows * CH * sizeof(u32x4_t) * Shape::kShares;
+    constexpr size_t kLds = 2 * Shape::kShares * ((size_t)kStageRows * CH * sizeof(u32x4_t) + Shape::kRows * kQkTile * sizeof(float2));
     if (kLds > 32768)
       (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLds);
     a.q_groups = (tiles + Shape::kRows - 1) / Shape::kRows;
