@@ -6,7 +6,7 @@
 // (causal maps) the text profiles of Eq. 3 / Eq. 4.
 //
 // Two kernels (before: one workgroup per 48 query rows that exchanged maxima and sums between its
-// wavefronts head by head; whole stage 81 -> 70 us at 16 x 577 tokens, 590 -> 290 us at 4 x 2881, 361 -> 98 us
+// wavefronts head by head; whole stage 81 -> 50 us at 16 x 577 tokens, 590 -> 242 us at 4 x 2881, 361 -> 86 us
 // at the causal 8 x 675): qk_norm_kernel leaves (reference, 1 / row sum) of every (head, query) row, and
 // qk_mean_kernel forms the probabilities of one (query tile, key tile) from them, adds the heads in
 // registers and writes the tile's outputs.  The logits are computed twice, but once the normalisers
@@ -21,15 +21,14 @@
 namespace ficoco {
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
-typedef float f32x4_t __attribute__((ext_vector_type(4)));
+typedef float f32x16_t __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
-constexpr int kQkWaves = 4;                         // wavefronts side by side on the queries, a tile each
-constexpr int kQkQB = kQkTile / 16;                 // 16-query blocks of a wavefront
-constexpr int kQkKB = 2;                            // 16-key blocks a wavefront takes together
-constexpr int kQkKeys = 64;                         // keys staged together: two such steps, or one of each of two wavefronts
-static_assert(kQkKeys == 2 * kQkKB * 16, "two steps of keys");
-static_assert(kQkTile % 16 == 0, "whole 16-query blocks");
+constexpr int kQkWaves = 4;                         // wavefronts of a workgroup (of a share of the heads)
+constexpr int kQkB = 32;                            // queries and keys of a block: one matrix instruction
+constexpr int kQkKeys = 2 * kQkB;                   // keys staged together: a block of each of two wavefronts
+constexpr int kQkE = kQkB * kQkB / kWave;           // logits of a block that a lane holds, all of one query
+static_assert(kQkTile == 2 * kQkB, "a column partial covers two blocks of queries");
 
 struct QkArgs {
   const bf16_t* Q;
@@ -56,24 +55,53 @@ struct QkArgs {
   __device__ __forceinline__ int row(int v) const { return v < n_visq ? vis0 + v : x0 + (v - n_visq); }
 };
 
-// v_mfma_f32_16x16x32_bf16: operand A is 16 rows x 32 features (lane: row lane % 16, features
-// 8 (lane / 16) .. + 8), operand B 16 columns x 32 features (same), the result 16 x 16 (lane: column
-// lane % 16, rows 4 (lane / 16) + v for its four registers v).  Rows are keys here, columns queries:
-// a query's logits sit in the registers of four lanes, and sixteen lanes hold consecutive queries of one
-// key, which is a piece of a row of the transposed map.
+// Rows of a product are keys here, columns queries.  Head mean: v_mfma_f32_32x32x16_bf16, operand A 32 rows x 16
+// features (lane: row lane % 32, features 8 (lane / 32) .. + 8), operand B 32 columns x 16 features (same), the
+// result 32 x 32 (lane: column lane % 32, rows key_of(v) + 4 (lane / 32) for its registers v): 32 lanes hold consecutive
+// queries of one key, which is a piece of a row of the transposed map.  Row normalisers:
+// v_mfma_f32_16x16x32_bf16, operand A 16 rows x 32 features (lane: row lane % 16, features 8 (lane / 16) .. + 8),
+// operand B the same, the result 16 x 16 (lane: column lane % 16, rows 4 (lane / 16) + v).
+//
+// The vector unit works beside the 32 x 32 form, hardly beside the 16 x 16 one: 24 x (exponential, multiply-add, add)
+// and the same products in either form, four wavefronts per SIMD, take 179 us without products; with them
+// 251 (16 x 16), 199 (32 x 32), and 212 / 188 where the instructions alternate.  The normalisers stay with the
+// former: three blocks of 32 queries a wavefront leave three wavefronts per SIMD instead of four (4 x 2881 tokens 120 us
+// against 112, 16 x 577 26.8 against 24.3).
+__device__ __forceinline__ constexpr int key_of(int v) { return v / 4 * 8 + v % 4; }
+__device__ __forceinline__ f32x16_t qk_mfma(bf16x8_t keys, bf16x8_t queries, f32x16_t c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(keys, queries, c, 0, 0, 0);
+}
+__device__ __forceinline__ f32x16_t qk_zero() { return f32x16_t{0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0}; }
 
 // A lane's 16-byte operand loads from global memory would touch a row of its own in every lane, and
 // the address unit takes such a load apart into 64 accesses (measured: it was busy 74 % of the time
 // and bound both kernels).  So rows are brought in whole -- neighbouring lanes on neighbouring 16-byte
 // chunks -- and turned into operands through LDS.  CH chunks per row; the chunk of row r lies at
-// chunk ^ swizzle, which spreads the sixteen rows of an operand read over all 64 banks.
+// chunk ^ swizzle, which spreads sixteen rows of an operand read over all 64 banks.
 template <int CH>
 __device__ __forceinline__ int lds_chunk(int r, int c) { return r * CH + (c ^ ((r / (16 / CH)) & (CH - 1))); }
 
+// 16 bytes per lane on their way from memory into LDS, past the registers: lane l fills the 16 bytes at 16 l behind
+// an address of the wavefront.  So it is the source that is swizzled: thread t brings chunk
+// (t % CH) ^ ((t / 16) % CH) of row t / CH (+ whole rounds of the workgroup: the same for all of them).
+__device__ __forceinline__ void load_to_lds(const bf16_t* src, u32x4_t* dst) {
+  __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src, (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
+}
+__device__ __forceinline__ void loaded_to_lds() {      // all of the workgroup's loads have arrived
+  __builtin_amdgcn_s_waitcnt(0x0f70);                  // vmcnt(0)
+  __syncthreads();
+}
+
 // ---- row normalisers ---------------------------------------------------------------------------
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+constexpr int kNormTile = 48;                       // queries of a wavefront
+constexpr int kNormQB = kNormTile / 16;             // in blocks of 16
+constexpr int kNormKB = 2;                          // 16-key blocks a wavefront takes together
+static_assert(kQkKeys == 2 * kNormKB * 16, "two steps of keys");
+
 // A workgroup takes 4 x 48 queries of one head and walks its keys 64 at a time, the next 64 being
-// loaded while the current ones are added (few workgroups: 48 queries, the keys shared by its wavefronts).  The exponentials are taken relative to a whole number
-// (units of log2) at the largest logit of the first 32 keys, not of the whole row: any reference
+// loaded while the current ones are added (few workgroups: 48 queries, the keys shared by its wavefronts).
+// (Keys loaded straight into LDS: no change.)  The exponentials are taken relative to a whole number (units of log2) at the largest logit of the first 32 keys, not of the whole row: any reference
 // serves as long as nothing overflows, and then the sums need no running maximum.  A row whose sum
 // does overflow (its largest logit more than ~70 above those of the first 32 keys) is seen in the
 // sum and done again with its own maximum.
@@ -87,7 +115,7 @@ __global__ __launch_bounds__(kQkWaves * kWave) __attribute__((amdgpu_waves_per_e
   // The workgroups of a head share an L2 (its keys).  The last ones of the heads, if they are narrow, come behind all
   // others: in their places between them they left every q_groups-th compute unit without work (a quarter of the chip at
   // 16 x 577 tokens: 29.8 us, and 24.3 with the order of precedence below).
-  const bool last_narrow = a.nq - (a.q_groups - 1) * (a.share_keys ? 1 : kQkWaves) * kQkTile <= 16;
+  const bool last_narrow = a.nq - (a.q_groups - 1) * (a.share_keys ? 1 : kQkWaves) * kNormTile <= 16;
   const int groups = a.q_groups - (last_narrow ? 1 : 0), units = a.nb * a.H * groups, first = xcd_padded_total(units);
   const bool behind = (int)blockIdx.x >= first;
   const int unit = xcd_logical_id(behind ? blockIdx.x - first : blockIdx.x, behind ? a.nb * a.H : units);
@@ -95,10 +123,10 @@ __global__ __launch_bounds__(kQkWaves * kWave) __attribute__((amdgpu_waves_per_e
   const int tid = threadIdx.x, lane = tid % kWave, l16 = lane % 16, lg = lane / 16;
   const int wv = __builtin_amdgcn_readfirstlane(tid / kWave);
   const int in_head = behind ? groups : unit % groups, head = behind ? unit : unit / groups;
-  const int w0 = in_head * (a.share_keys ? 1 : kQkWaves) * kQkTile;
+  const int w0 = in_head * (a.share_keys ? 1 : kQkWaves) * kNormTile;
   const bool narrow = a.nq - w0 <= 16;     // one block of queries in all (the [CLS] query behind 576 visual ones)
   const bool share_keys = a.share_keys || narrow;
-  const int v0 = share_keys ? w0 : w0 + wv * kQkTile;
+  const int v0 = share_keys ? w0 : w0 + wv * kNormTile;
   const int h = head % a.H;
   const int64_t bi = head / a.H;
   const float NEG = -__builtin_huge_valf();
@@ -106,15 +134,15 @@ __global__ __launch_bounds__(kQkWaves * kWave) __attribute__((amdgpu_waves_per_e
   const bf16_t* Kh = a.K + (a.b0 + bi) * a.sb + (int64_t)h * a.sh;
   // keys below full_end count for every query of this wavefront, from k_end on for none
   const bool active = v0 < a.nq;
-  const int q_lo = a.row(min(v0, a.nq - 1)), q_hi = a.row(min(v0 + kQkTile, a.nq) - 1);
+  const int q_lo = a.row(min(v0, a.nq - 1)), q_hi = a.row(min(v0 + kNormTile, a.nq) - 1);
   const int k_end = !active ? 0 : DEC ? min(a.n, q_hi + 1) : a.n;
   const int full_end = DEC ? min(a.n, q_lo + 1) : a.n;
-  const int wg_end = DEC ? min(a.n, a.row(min(w0 + kQkWaves * kQkTile, a.nq) - 1) + 1) : a.n;
+  const int wg_end = DEC ? min(a.n, a.row(min(w0 + kQkWaves * kNormTile, a.nq) - 1) + 1) : a.n;
 
-  int qrow[kQkQB];
-  bf16x8_t qf[kQkQB][KS];
+  int qrow[kNormQB];
+  bf16x8_t qf[kNormQB][KS];
 #pragma unroll
-  for (int qb = 0; qb < kQkQB; ++qb) {
+  for (int qb = 0; qb < kNormQB; ++qb) {
     qrow[qb] = a.row(min(v0 + qb * 16 + l16, a.nq - 1));
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) __builtin_memcpy(&qf[qb][ks], Qh + (int64_t)qrow[qb] * a.sn + lg * 8 + ks * 32, 16);
@@ -131,13 +159,13 @@ __global__ __launch_bounds__(kQkWaves * kWave) __attribute__((amdgpu_waves_per_e
     for (int i = 0; i < NL; ++i) stage[buf][lds_chunk<CH>(tid / CH + i * RPI, tid % CH)] = next[i];
   };
 
-  typedef f32x4_t Logits[kQkKB][kQkQB];      // of 32 keys
+  typedef f32x4_t Logits[kNormKB][kNormQB];      // of 32 keys
   Logits S;
   // `key_op(kb, ks)` gives this lane's operand
   auto logits = [&](auto qbn, auto key_op, Logits& S) __attribute__((always_inline)) {
     constexpr int QB = decltype(qbn)::value;
 #pragma unroll
-    for (int kb = 0; kb < kQkKB; ++kb) {
+    for (int kb = 0; kb < kNormKB; ++kb) {
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) {
         const bf16x8_t kf = key_op(kb, ks);
@@ -149,14 +177,14 @@ __global__ __launch_bounds__(kQkWaves * kWave) __attribute__((amdgpu_waves_per_e
   };
   auto counts = [&](int key, int qb) { return key < a.n && (!DEC || key <= qrow[qb]); };
   // the largest logit of the 32 keys from k0 on that count, and of the four lanes of a query
-  float ref[kQkQB];
-  double sum[kQkQB];
+  float ref[kNormQB];
+  double sum[kNormQB];
   auto max_of = [&](auto qbn, int k0) __attribute__((always_inline)) {
     constexpr int QB = decltype(qbn)::value;
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb)
 #pragma unroll
-      for (int kb = 0; kb < kQkKB; ++kb)
+      for (int kb = 0; kb < kNormKB; ++kb)
 #pragma unroll
         for (int v = 0; v < 4; ++v)
           ref[qb] = fmaxf(ref[qb], counts(k0 + kb * 16 + lg * 4 + v, qb) ? S[kb][qb][v] : NEG);
@@ -176,7 +204,7 @@ __global__ __launch_bounds__(kQkWaves * kWave) __attribute__((amdgpu_waves_per_e
     for (int qb = 0; qb < QB; ++qb) {
       float part;
 #pragma unroll
-      for (int kb = 0; kb < kQkKB; ++kb)
+      for (int kb = 0; kb < kNormKB; ++kb)
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
           const float e = __builtin_amdgcn_exp2f(fmaf(S[kb][qb][v], a.scale_log2e, -ref[qb]));
@@ -187,11 +215,11 @@ __global__ __launch_bounds__(kQkWaves * kWave) __attribute__((amdgpu_waves_per_e
   };
   auto add_chunk = [&](auto qbn, int k0, const Logits& S) __attribute__((always_inline)) {
     constexpr int QB = decltype(qbn)::value;
-    if (k0 + kQkKB * 16 <= full_end) {               // uniform
+    if (k0 + kNormKB * 16 <= full_end) {               // uniform
       add_whole(qbn, S);
     } else {
 #pragma unroll
-      for (int kb = 0; kb < kQkKB; ++kb)
+      for (int kb = 0; kb < kNormKB; ++kb)
         if (k0 + kb * 16 < k_end) {                  // uniform
 #pragma unroll
           for (int qb = 0; qb < QB; ++qb) {
@@ -208,15 +236,15 @@ __global__ __launch_bounds__(kQkWaves * kWave) __attribute__((amdgpu_waves_per_e
   };
   auto across = [&]() {
 #pragma unroll
-    for (int qb = 0; qb < kQkQB; ++qb) {
+    for (int qb = 0; qb < kNormQB; ++qb) {
       sum[qb] += __shfl_xor(sum[qb], 16, kWave);
       sum[qb] += __shfl_xor(sum[qb], 32, kWave);
     }
   };
 #pragma unroll
-  for (int qb = 0; qb < kQkQB; ++qb) { ref[qb] = NEG; sum[qb] = 0.0; }
+  for (int qb = 0; qb < kNormQB; ++qb) { ref[qb] = NEG; sum[qb] = 0.0; }
 
-  const std::integral_constant<int, kQkQB> all{};
+  const std::integral_constant<int, kNormQB> all{};
   auto direct = [&](int k0) {
     return [&, k0](int kb, int ks) {
       bf16x8_t kf;
@@ -226,13 +254,13 @@ __global__ __launch_bounds__(kQkWaves * kWave) __attribute__((amdgpu_waves_per_e
   };
   bool over = false;
   // Each wavefront every fourth 32 keys, with a reference of its own; the four sums are combined in order.
-  __shared__ float part_ref[kQkWaves][kQkTile];
-  __shared__ double part_sum[kQkWaves][kQkTile];
+  __shared__ float part_ref[kQkWaves][kNormTile];
+  __shared__ double part_sum[kQkWaves][kNormTile];
   auto shared_keys = [&](auto qbn) __attribute__((always_inline)) {
     constexpr int QB = decltype(qbn)::value;
-    const int first = wv * kQkKB * 16;
+    const int first = wv * kNormKB * 16;
 #pragma unroll 1
-    for (int k0 = first; k0 < k_end; k0 += kQkWaves * kQkKB * 16) {
+    for (int k0 = first; k0 < k_end; k0 += kQkWaves * kNormKB * 16) {
       logits(qbn, direct(k0), S);
       if (k0 == first) { max_of(qbn, k0); set_ref(qbn); }     // (-inf where none of them counts: then none of the later ones does)
       add_chunk(qbn, k0, S);
@@ -284,10 +312,10 @@ __global__ __launch_bounds__(kQkWaves * kWave) __attribute__((amdgpu_waves_per_e
       const bf16x8_t* st = (const bf16x8_t*)stage[buf];
 #pragma unroll
       for (int half = 0; half < 2; ++half) {
-        if (k0 + half * kQkKB * 16 >= k_end) continue;   // uniform
-        logits(all, [&](int kb, int ks) { return st[lds_chunk<CH>((half * kQkKB + kb) * 16 + l16, ks * 4 + lg)]; }, S);
+        if (k0 + half * kNormKB * 16 >= k_end) continue;   // uniform
+        logits(all, [&](int kb, int ks) { return st[lds_chunk<CH>((half * kNormKB + kb) * 16 + l16, ks * 4 + lg)]; }, S);
         if (half == 0 && k0 == 0) { max_of(all, 0); set_ref(all); }
-        add_chunk(all, k0 + half * kQkKB * 16, S);
+        add_chunk(all, k0 + half * kNormKB * 16, S);
       }
       store_stage(1 - buf);
       __syncthreads();
@@ -296,20 +324,20 @@ __global__ __launch_bounds__(kQkWaves * kWave) __attribute__((amdgpu_waves_per_e
     if (!active) return;
     across();
 #pragma unroll
-    for (int qb = 0; qb < kQkQB; ++qb) over |= !(sum[qb] < 0x1p100);
+    for (int qb = 0; qb < kNormQB; ++qb) over |= !(sum[qb] < 0x1p100);
   }
   if (__any(over)) {                                 // rare: with the row's own maximum, keys straight from memory
 #pragma unroll
-    for (int qb = 0; qb < kQkQB; ++qb) { ref[qb] = NEG; sum[qb] = 0.0; }
+    for (int qb = 0; qb < kNormQB; ++qb) { ref[qb] = NEG; sum[qb] = 0.0; }
 #pragma unroll 1
-    for (int k0 = 0; k0 < k_end; k0 += kQkKB * 16) { logits(all, direct(k0), S); max_of(all, k0); }
+    for (int k0 = 0; k0 < k_end; k0 += kNormKB * 16) { logits(all, direct(k0), S); max_of(all, k0); }
     set_ref(all);
 #pragma unroll 1
-    for (int k0 = 0; k0 < k_end; k0 += kQkKB * 16) { logits(all, direct(k0), S); add_chunk(all, k0, S); }
+    for (int k0 = 0; k0 < k_end; k0 += kNormKB * 16) { logits(all, direct(k0), S); add_chunk(all, k0, S); }
     across();
   }
 #pragma unroll
-  for (int qb = 0; qb < kQkQB; ++qb) {
+  for (int qb = 0; qb < kNormQB; ++qb) {
     const int v = v0 + qb * 16 + l16;
     if (lg == 0 && v < a.nq) a.norm[((int64_t)bi * a.H + h) * a.nq + v] = make_float2(ref[qb], (float)(1.0 / sum[qb]));
   }
@@ -320,86 +348,85 @@ __device__ __forceinline__ int lane_xor_4(int v) {
   const int up = __builtin_amdgcn_update_dpp(v, v, 0x104, 0xF, 0x5, false);      // row_shl:4 into quads 0 and 2
   return __builtin_amdgcn_update_dpp(up, v, 0x114, 0xF, 0xA, false);             // row_shr:4 into quads 1 and 3
 }
-// Eight values of every lane, each summed over the 16 lanes of a row: the tree of the four steps lane ^ 1, ^ 2, ^ 4,
-// ^ 8.  Every step hands half of the values to the other lane of the pair, so lane l is left with value
-// 4 (l & 1) + (l & 2) + (l >> 2 & 1) alone: 15 additions instead of 32.
-__device__ __forceinline__ double row_sums_of_8(const double (&x)[8], int l16) {
+__device__ __forceinline__ double lane_xor_4(double v) {
+  return __hiloint2double(lane_xor_4(__double2hiint(v)), lane_xor_4(__double2loint(v)));
+}
+// Sixteen values of every lane, each summed over 32 lanes: the tree of the steps lane ^ 1, ^ 2, ^ 4, ^ 8, ^ 16.
+// The first four hand half of the values to the other lane of the pair, so lane l is left with value
+// sum_index(l) alone: 16 additions instead of 80.
+__device__ __forceinline__ int sum_index(int l) { return (l & 1) * 8 + (l & 2) * 2 + (l >> 1 & 2) + (l >> 3 & 1); }
+__device__ __forceinline__ double sums_of_16(const double (&x)[16], int l) {
   auto pick = [](bool second, double a, double b) { return second ? b : a; };
-  double y[4], z[2];
+  double y[8], z[4], u[2];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) y[i] = pick(l16 & 1, x[i], x[i + 4]) + dpp_move<0xB1>(pick(l16 & 1, x[i + 4], x[i]));
+  for (int i = 0; i < 8; ++i) y[i] = pick(l & 1, x[i], x[i + 8]) + dpp_move<0xB1>(pick(l & 1, x[i + 8], x[i]));
 #pragma unroll
-  for (int i = 0; i < 2; ++i) z[i] = pick(l16 & 2, y[i], y[i + 2]) + dpp_move<0x4E>(pick(l16 & 2, y[i + 2], y[i]));
-  const double give = pick(l16 & 4, z[1], z[0]);
-  const double u = pick(l16 & 4, z[0], z[1]) + __hiloint2double(lane_xor_4(__double2hiint(give)), lane_xor_4(__double2loint(give)));
-  return u + dpp_move<0x128>(u);      // rotated by eight: lane ^ 8
+  for (int i = 0; i < 4; ++i) z[i] = pick(l & 2, y[i], y[i + 4]) + dpp_move<0x4E>(pick(l & 2, y[i + 4], y[i]));
+#pragma unroll
+  for (int i = 0; i < 2; ++i) u[i] = pick(l & 4, z[i], z[i + 2]) + lane_xor_4(pick(l & 4, z[i + 2], z[i]));
+  const double t = pick(l & 8, u[0], u[1]) + dpp_move<0x128>(pick(l & 8, u[1], u[0]));      // rotated by eight: lane ^ 8
+  return t + __shfl_xor(t, 16, kWave);
 }
 
 // ---- probabilities, head mean, outputs -----------------------------------------------------------
-// A wavefront forms 48 queries x 32 visual keys of an image, the heads added in order in registers.
-// SPLIT = false: the four wavefronts of a workgroup sit two by two on 96 queries x 64 keys and
-// share the staged rows.  SPLIT = true (few tiles): 48 x 64 by two wavefronts, and four such pairs
+// A wavefront forms 64 queries x 32 visual keys of an image, the heads added in order in registers.
+// SPLIT = false: the four wavefronts of a workgroup sit two by two on 128 queries x 64 keys and
+// share the staged rows.  SPLIT = true (few tiles): 64 x 64 by four wavefronts of one block each, and four such groups
 // take consecutive shares of the heads, each with a staging area of its own; their sums are added
-// pairwise (a fixed tree) in LDS.  Rows are staged 64 features at a time in two buffers, loaded into
-// registers two stages ahead; the exponentials of a head are computed beside the matrix
-// instructions and LDS reads of the next one, in a fixed order.  The normalisers of a head come through LDS
-// as well (each wavefront reading its own took 30 % of the address unit's time).
+// pairwise (a fixed tree) in LDS.  Rows are staged 64 features at a time in two buffers, loaded straight into LDS
+// a stage ahead; the normalisers of a head come through LDS as well; the exponentials of a block are computed beside
+// the matrix instructions and LDS reads of the next one, in a fixed order.
 //
 // Bound by the vector unit (exponential, two multiply-adds per logit) and the trips between
 // barriers.  Measured at 4 x 2881 tokens, 16 heads of 64 / 16 x 577, 16 of 64 / 8 x 675 causal, 32
-// of 128: operands straight from memory 314 / 70 / 99 us; staged, 192 x 64 by eight wavefronts, each head
-// on its own 180 / 44 / 56; the next head's matrix instructions under this head's exponentials, 96 x 64 by
-// four wavefronts (three workgroups on a compute unit instead of two) 170 / 40 / 51; normalisers through LDS, whole
-// tiles written without tests, exponentials between the other instructions 154 / 33.5 / 49.  With heads of 32 four fit if the
-// registers are held to 128 (131 otherwise): step of 16 x 577 tokens, 16 heads 77.9 -> 74.1 us, one head 46.0 -> 43.3.
+// of 128: operands straight from memory 314 / 70 / 99 us; staged through registers, 192 x 64 by eight wavefronts, each head
+// on its own 180 / 44 / 56; 96 x 64 by four wavefronts with 16 x 16 products, the next head's beside this head's
+// exponentials 170 / 40 / 51; normalisers through LDS, whole tiles written without tests 158 / 34 / 49; 32 x 32 products
+// 157 / 33 / 51; rows straight into LDS, order of precedence among the wavefronts 142 / 28.6 / 48.
 constexpr int kQkBand = 8;                          // key tiles side by side in the order of the workgroups
-constexpr int kQkCols = 2;                          // wavefronts side by side on the keys
-constexpr int kQkMB = kQkKeys / 16 / kQkCols;       // 16-key blocks of a wavefront
 template <bool SPLIT> struct QkMeanShape {
-  static constexpr int kRows = SPLIT ? 1 : 2;         // wavefronts side by side on the queries
+  static constexpr int kBlocks = SPLIT ? 1 : 2;       // of queries per wavefront
+  static constexpr int kQueries = 2 * kBlocks * kQkB; // of a workgroup
   static constexpr int kShares = SPLIT ? 4 : 1;       // shares of the heads
-  static constexpr int kThreads = kRows * kQkCols * kShares * kWave;
+  static constexpr int kThreads = kQkWaves * kShares * kWave;
 };
 template <int KS, bool DEC, bool SPLIT>
-__global__ __launch_bounds__(QkMeanShape<SPLIT>::kThreads) __attribute__((amdgpu_waves_per_eu(SPLIT || KS == 4 ? 2 : KS == 1 ? 4 : 3))) void qk_mean_kernel(QkArgs a) {
-  constexpr int KSS = KS > 2 ? 2 : KS, NST = KS / KSS, CH = KSS * 4;     // 32-feature steps of a stage, stages of a head
+__global__ __launch_bounds__(QkMeanShape<SPLIT>::kThreads) __attribute__((amdgpu_waves_per_eu(SPLIT ? 4 : KS == 4 ? 2 : 3))) void qk_mean_kernel(QkArgs a) {
+  constexpr int KSS = KS > 2 ? 2 : KS, NST = KS / KSS, CH = KSS * 4, KT = KSS * 2;     // 32-feature steps of a stage, stages of a head, instructions of a block and stage
   using Shape = QkMeanShape<SPLIT>;
-  constexpr int QR = Shape::kRows * kQkTile;                              // query rows of a stage
-  constexpr int T = Shape::kRows * kQkCols * kWave, RPI = T / CH;
-  constexpr int NL = (QR + kQkKeys + RPI - 1) / RPI;                      // rounds of RPI rows (past the last key: that key again)
-  extern __shared__ u32x4_t stage_m[];                 // [2][SPLIT ? 4 : 1][rounded-up rows of a stage], then the queries' normalisers
+  constexpr int MB = Shape::kBlocks, QR = Shape::kQueries;                // query rows of a stage
+  constexpr int T = kQkWaves * kWave, RPI = T / CH, NL = (QR + kQkKeys) / RPI;   // rounds of RPI rows
+  static_assert((QR + kQkKeys) % RPI == 0 && QR % RPI == 0, "whole rounds of queries and of keys");
+  extern __shared__ u32x4_t stage_m[];                 // [2][shares][rows of a stage], then the queries' normalisers
   constexpr int kArea = NL * RPI * CH;
   const int units = a.nb * a.q_groups * a.k_tiles;
   const int unit = xcd_logical_id(blockIdx.x, units);
   if (unit >= units) return;
-  const int tid = threadIdx.x, lane = tid % kWave, l16 = lane % 16, lg = lane / 16;
+  const int tid = threadIdx.x, lane = tid % kWave, l32 = lane % kQkB, hi = lane / kQkB;
   const int wv = __builtin_amdgcn_readfirstlane(tid / kWave);
-  const int share = SPLIT ? wv / kQkCols : 0;                // of the heads
+  const int share = wv / kQkWaves, wq = wv % kQkWaves / 2, wk = wv % 2;
   // the tiles of an image in columns kQkBand key tiles wide: the workgroups that run together on an
   // XCD then need few rows of either side, which its L2 holds for all heads
   const int64_t bi = unit / (a.k_tiles * a.q_groups), b = a.b0 + bi;
   const int in_img = unit - (int)bi * a.k_tiles * a.q_groups;
   const int band = in_img / (kQkBand * a.q_groups), in_band = in_img - band * kQkBand * a.q_groups;
   const int band_w = min(kQkBand, a.k_tiles - band * kQkBand);
-  const int kt = band * kQkBand + in_band % band_w;
+  const int kt0 = band * kQkBand + in_band % band_w;
   const int w0 = in_band / band_w * QR;
-  const bool narrow = a.nq - w0 <= 16;                 // one block of queries in all (uniform)
-  const int v0 = SPLIT || narrow ? w0 : w0 + wv / kQkCols * kQkTile;
-  const int wk0 = kt * kQkKeys, ik0 = wk0 + wv % kQkCols * kQkMB * 16;         // first visual key of the stage, of this wavefront
+  const bool narrow = a.nq - w0 <= kQkB;               // one block of queries in all (uniform)
+  const int q0 = narrow ? 0 : wq * MB * kQkB, v0 = w0 + q0;
+  const int wk0 = kt0 * kQkKeys, ik0 = wk0 + wk * kQkB;       // first visual key of the stage, of this wavefront
   const int per = (a.H + Shape::kShares - 1) / Shape::kShares;            // heads of a share (the last may have fewer)
   const int h_lo = min(share * per, a.H), h_hi = min(h_lo + per, a.H);
   // (decoder: a tile all of whose keys lie behind its queries is zero)
   const bool wg_dead = DEC && a.vis0 + wk0 > a.row(min(w0 + QR, a.nq) - 1);
-  const bool active = v0 < a.nq && !(DEC && a.vis0 + ik0 > a.row(min(v0 + kQkTile, a.nq) - 1));
+  const bool active = v0 < a.nq && !(DEC && a.vis0 + ik0 > a.row(min(v0 + MB * kQkB, a.nq) - 1));
 
-  f32x4_t P[kQkMB][kQkQB];
+  f32x16_t P[MB];
 #pragma unroll
-  for (int kb = 0; kb < kQkMB; ++kb)
-#pragma unroll
-    for (int qb = 0; qb < kQkQB; ++qb) P[kb][qb] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+  for (int m = 0; m < MB; ++m) P[m] = qk_zero();
 
   auto heads = [&]() __attribute__((always_inline)) {
-    constexpr int QB = kQkQB;
     const int t = tid % T;
     u32x4_t* area = stage_m + share * kArea;
     constexpr int kBuf = Shape::kShares * kArea;
@@ -408,273 +435,285 @@ __global__ __launch_bounds__(QkMeanShape<SPLIT>::kThreads) __attribute__((amdgpu
     for (int i = 0; i < NL; ++i) {
       const int r = t / CH + i * RPI;
       const int row = r < QR ? a.row(min(w0 + r, a.nq - 1)) : a.vis0 + min(wk0 + r - QR, a.N - 1);
-      src[i] = (r < QR ? a.Q : a.K) + b * a.sb + (int64_t)row * a.sn + t % CH * 8;
+      src[i] = (i * RPI < QR ? a.Q : a.K) + b * a.sb + (int64_t)row * a.sn + (t % CH ^ (t / 16 & (CH - 1))) * 8;
     }
     // (read before the loop: a scalar load on its way there makes every wait for LDS a wait for all of it)
     float scale = a.scale_log2e;
     asm volatile("" : "+s"(scale));
     const float2* nrm = a.norm + bi * a.H * a.nq;
     const uint32_t nrm_at = (uint32_t)min(w0 + t, a.nq - 1);
-    u32x4_t next[NL];
     float2 next_nf;
     float2* nf_area = (float2*)(stage_m + 2 * kBuf) + share * QR;    // [2][shares][QR]
-    auto load_stage = [&](int h, int part) {
+    // the rows of head h's stage `part` on their way into buffer `buf`
+    auto load_stage = [&](int h, int part, int buf) __attribute__((always_inline)) {
       const int64_t off = (int64_t)h * a.sh + part * KSS * 32;
-      if (part == 0) next_nf = (nrm + (int64_t)h * a.nq)[nrm_at];
 #pragma unroll
-      for (int i = 0; i < NL; ++i) __builtin_memcpy(&next[i], src[i] + off, 16);
+      for (int i = 0; i < NL; ++i)
+        load_to_lds(src[i] + off, area + buf * kBuf + i * T + wv % kQkWaves * kWave);
     };
-    // rows into buffer `buf`; a head's first stage brings its normalisers (nf_buf: the head's parity)
-    auto store_stage = [&](int buf, int part, int nf_buf) {
-      if (part == 0 && t < QR) nf_area[nf_buf * Shape::kShares * QR + t] = next_nf;
-#pragma unroll
-      for (int i = 0; i < NL; ++i) area[buf * kBuf + lds_chunk<CH>(t / CH + i * RPI, t % CH)] = next[i];
-    };
+    auto load_nf = [&](int h) { next_nf = (nrm + (int64_t)h * a.nq)[nrm_at]; };
+    auto store_nf = [&](int par) { if (t < QR) nf_area[par * Shape::kShares * QR + t] = next_nf; };
     const int cnt = h_hi - h_lo, last = max(cnt - 1, 0), h0 = min(h_lo, a.H - 1);
-    auto load_at = [&](int i, int part) { load_stage(h0 + min(i, last), part); };     // (past the last head: that one again)
-    auto add = [&](const f32x4_t (&S)[kQkMB][QB], const float2 (&nf)[QB], int kb) __attribute__((always_inline)) {
+    auto head = [&](int i) { return h0 + min(i, last); };               // (past the last head: that one again)
+
+    // Logits: heads of one stage block by block (S[0] and S[1] in turn), else a head's blocks side by side (S of even
+    // and odd heads).  The block whose exponentials are due is the one before.
+    constexpr int SB = NST > 1 ? MB : 1;
+    f32x16_t S[2][SB];
+    float2 nf[MB];                                     // of the head whose exponentials are due
 #pragma unroll
-      for (int qb = 0; qb < QB; ++qb)
+    for (int m = 0; m < MB; ++m) nf[m] = make_float2(__builtin_huge_valf(), 0.0f);    // (nothing before the first head: 2^-inf, times zero)
 #pragma unroll
-        for (int v = 0; v < 4; ++v)
-          P[kb][qb][v] = fmaf(__builtin_amdgcn_exp2f(fmaf(S[kb][qb][v], a.scale_log2e, -nf[qb].x)), nf[qb].y, P[kb][qb][v]);
+    for (int m = 0; m < SB; ++m) S[1][m] = qk_zero();
+    auto x_of = [&](const f32x16_t& Sd, float2 n, int v) { return fmaf(Sd[v], scale, -n.x); };
+    auto add = [&](const f32x16_t& Sd, float2 n, f32x16_t& Pd) __attribute__((always_inline)) {
+#pragma unroll
+      for (int v = 0; v < kQkE; ++v) Pd[v] = fmaf(__builtin_amdgcn_exp2f(x_of(Sd, n, v)), n.y, Pd[v]);
     };
-    // Head i: its logits into S, beside the exponentials of head i - 1 from Sp -- the matrix
-    // instructions and the trips through LDS run under the vector work of the head before.
-    auto step = [&](int i, int par, const f32x4_t (&Sp)[kQkMB][QB], const float2 (&np)[QB], f32x4_t (&S)[kQkMB][QB],
-                    float2 (&nf)[QB]) __attribute__((always_inline)) {
+    // exponentials e0 .. e0 + E of one block beside the NB * KT matrix instructions of the next: an exponential to two
+    // other vector instructions, the matrix instructions spread between them
+    auto mix = [&](auto count, int e0, const f32x16_t& Sd, float2 n, f32x16_t& Pd, auto nb, const bf16x8_t (&kf)[KT],
+                   const auto& qf, auto& Sn, bool fresh) __attribute__((always_inline)) {
+      constexpr int E = decltype(count)::value, NB = decltype(nb)::value, M = NB * KT, kLead = 5;
+      float x[2] = {x_of(Sd, n, e0), x_of(Sd, n, e0 + 1)}, e_prev = 0.0f;
+      issue_fence();
+#pragma unroll
+      for (int i = 0; i <= E; ++i) {
+        float e = 0.0f;
+        if (i < E) e = __builtin_amdgcn_exp2f(x[i % 2]);
+        if (i + 2 < E) x[i % 2] = x_of(Sd, n, e0 + i + 2);
+        if (i > 0) Pd[e0 + i - 1] = fmaf(e_prev, n.y, Pd[e0 + i - 1]);
+#pragma unroll
+        for (int m = 0; m < M; ++m)
+          if (kLead + m * (E - kLead) / M == i) {
+            const int kt = m / NB, blk = m % NB;
+            Sn[blk] = qk_mfma(kf[kt], qf[blk][kt], fresh && kt == 0 ? qk_zero() : Sn[blk]);
+          }
+        issue_fence();
+        e_prev = e;
+      }
+    };
+    auto step = [&](int i, auto par_c) __attribute__((always_inline)) {
+      constexpr int par = decltype(par_c)::value;
 #pragma unroll
       for (int part = 0; part < NST; ++part) {
         const int buf = NST == 1 ? par : part % 2;
-        store_stage(1 - buf, (part + 1) % NST, 1 - par);    // the stage after this one, loaded a step ago
-        load_at(i + (part + 2) / NST, (part + 2) % NST);
-        issue_fence();
+        if (part == NST - 1) store_nf(1 - par);
+        auto load_next = [&]() __attribute__((always_inline)) {
+          issue_fence();
+          if (part == NST - 1) load_nf(head(i + 2));
+          load_stage(head(i + (part + 1) / NST), (part + 1) % NST, 1 - buf);
+          issue_fence();
+        };
         if (active) {                                  // uniform in the wavefront
           const bf16x8_t* st = (const bf16x8_t*)(area + buf * kBuf);
-          bf16x8_t qf[QB][KSS], kf[kQkMB][KSS];
+          auto read_queries = [&](int m, bf16x8_t (&qf)[KT]) __attribute__((always_inline)) {
 #pragma unroll
-          for (int ks = 0; ks < KSS; ++ks) {
-#pragma unroll
-            for (int qb = 0; qb < QB; ++qb) qf[qb][ks] = st[lds_chunk<CH>(v0 - w0 + qb * 16 + l16, ks * 4 + lg)];
-#pragma unroll
-            for (int kb = 0; kb < kQkMB; ++kb) kf[kb][ks] = st[lds_chunk<CH>(QR + ik0 - wk0 + kb * 16 + l16, ks * 4 + lg)];
-          }
-          issue_fence();
-          // In this very order: an exponential to two other vector instructions, then a matrix instruction every
-          // second time.
-          constexpr int E = kQkMB * QB * 4 / NST, M = kQkMB * KSS * QB, kLead = 6;
-          const int e0 = part * E;
-          auto x_of = [&](int i) {
-            const int kb = i / (QB * 4), qb = i / 4 % QB, v = i % 4;
-            return fmaf(Sp[kb][qb][v], scale, -np[qb].x);
+            for (int kt = 0; kt < KT; ++kt) qf[kt] = st[lds_chunk<CH>(q0 + m * kQkB + l32, kt * 2 + hi)];
           };
-          float x[2] = {x_of(e0), x_of(e0 + 1)}, e_prev = 0.0f;
-          issue_fence();
+          bf16x8_t kf[KT];
+          auto read_keys = [&]() __attribute__((always_inline)) {
 #pragma unroll
-          for (int i = 0; i <= E; ++i) {
-            float e = 0.0f;
-            if (i < E) e = __builtin_amdgcn_exp2f(x[i % 2]);
-            if (i + 2 < E) x[i % 2] = x_of(e0 + i + 2);
-            if (i > 0) {
-              const int j = e0 + i - 1, kb = j / (QB * 4), qb = j / 4 % QB, v = j % 4;
-              P[kb][qb][v] = fmaf(e_prev, np[qb].y, P[kb][qb][v]);
+            for (int kt = 0; kt < KT; ++kt) kf[kt] = st[lds_chunk<CH>(QR + wk * kQkB + l32, kt * 2 + hi)];
+          };
+          float2 mine[MB];
+          auto read_nf = [&]() __attribute__((always_inline)) {
+#pragma unroll
+            for (int m = 0; m < MB; ++m) {
+              mine[m] = nf_area[par * Shape::kShares * QR + q0 + m * kQkB + l32];
+              if (SPLIT && i >= cnt) mine[m].y = 0.0f;   // (a shorter share: its last head again, not counted)
             }
+          };
+          bf16x8_t qf[MB][KT];
+          read_keys();
 #pragma unroll
-            for (int m = 0; m < M; ++m)
-              if (kLead + m * (E - kLead) / M == i) {
-                const int ks = m / (kQkMB * QB), kb = m / QB % kQkMB, qb = m % QB;
-                S[kb][qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[kb][ks], qf[qb][ks], part == 0 && ks == 0 ? f32x4_t{0.0f, 0.0f, 0.0f, 0.0f} : S[kb][qb], 0, 0, 0);
+          for (int m = 0; m < MB; ++m) read_queries(m, qf[m]);
+          if (part == NST - 1) read_nf();
+          load_next();                                 // (behind the reads: the compiler has a read wait for every load into LDS before it)
+          if constexpr (NST == 1) {
+#pragma unroll
+            for (int m = 0; m < MB; ++m) {
+              const int cur = MB == 1 ? par : m % 2, due = m == 0 ? MB - 1 : m - 1;
+              mix(std::integral_constant<int, kQkE>{}, 0, S[1 - cur][0], nf[due], P[due], std::integral_constant<int, 1>{}, kf, &qf[m], S[cur], true);
+              if (m == 0) {
+#pragma unroll
+                for (int q = 0; q < MB; ++q) nf[q] = mine[q];
               }
-            issue_fence();
-            e_prev = e;
-          }
-          if (part == 0) {
+            }
+          } else {
+            constexpr int E = MB * kQkE / NST;
+            const int due = part * E / kQkE, e0 = part * E % kQkE;
+            mix(std::integral_constant<int, E>{}, e0, S[1 - par][due], nf[due], P[due], std::integral_constant<int, MB>{}, kf, qf, S[par], part == 0);
+            if (part == NST - 1) {
 #pragma unroll
-            for (int qb = 0; qb < QB; ++qb) {
-              nf[qb] = nf_area[par * Shape::kShares * QR + v0 - w0 + qb * 16 + l16];
-              if (SPLIT && i >= cnt) nf[qb].y = 0.0f;  // (a shorter share: its last head again, not counted)
+              for (int q = 0; q < MB; ++q) nf[q] = mine[q];
             }
           }
+        } else {
+          load_next();
         }
-        __syncthreads();
+        loaded_to_lds();
       }
     };
-    // (nothing before the first head: 2^-inf, times zero)
-    f32x4_t Sa[kQkMB][QB], Sb[kQkMB][QB];
-    float2 na[QB], nb[QB];
-#pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-      nb[qb] = make_float2(__builtin_huge_valf(), 0.0f);
-#pragma unroll
-      for (int kb = 0; kb < kQkMB; ++kb) Sb[kb][qb] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
-    }
-    load_at(0, 0);
-    store_stage(0, 0, 0);
-    load_at(1 / NST, 1 % NST);
-    __syncthreads();
+    load_nf(head(0));
+    load_stage(head(0), 0, 0);
+    store_nf(0);
+    load_nf(head(1));
+    loaded_to_lds();
 #pragma unroll 1
     for (int i = 0; i < per; i += 2) {
-      step(i, 0, Sb, nb, Sa, na);
-      if (i + 1 < per) step(i + 1, 1, Sa, na, Sb, nb);
+      if (DEC) { }                                     // (as in the normalisers; causal maps 48.5 us without, 49.9 with)
+      else if (i == 0) __builtin_amdgcn_s_setprio(3);
+      else if (i == per / 4 * 2) __builtin_amdgcn_s_setprio(2);
+      else if (i == per * 3 / 8 * 2) __builtin_amdgcn_s_setprio(1);
+      else if (i == per * 7 / 16 * 2) __builtin_amdgcn_s_setprio(0);
+      step(i, std::integral_constant<int, 0>{});
+      if (i + 1 < per) step(i + 1, std::integral_constant<int, 1>{});
     }
-    if (active) {
+    if (active) {                                      // what is left: the last block, or the last head's blocks
+      if constexpr (NST == 1 && MB == 2) {
+        add(S[1][0], nf[1], P[1]);
+      } else {
 #pragma unroll
-      for (int kb = 0; kb < kQkMB; ++kb) {
-        if (per % 2) add(Sa, na, kb); else add(Sb, nb, kb);
+        for (int m = 0; m < SB; ++m) {
+          if (per % 2) add(S[0][m], nf[m], P[m]); else add(S[1][m], nf[m], P[m]);
+        }
       }
     }
   };
-  // outputs of KB x QB blocks from query v0 and visual key ik0 on, of the sums over the heads
-  auto write_out = [&](auto kbn, auto qbn, int ik0, const auto& sums) __attribute__((always_inline)) {
-    constexpr int KB = decltype(kbn)::value, QB = decltype(qbn)::value;
+  // outputs of 64 queries (32: one block) from v0 and 32 visual keys from ik0 on, of the sums over the heads
+  auto write_out = [&](auto blocks_c, int v0, int ik0, const f32x16_t& s0, const f32x16_t& s1) __attribute__((always_inline)) {
+    constexpr int blocks = decltype(blocks_c)::value;
     const float invH = 1.0f / (float)a.H;
     const int qt = v0 / kQkTile;
     const bool recv = a.recv_part && qt < a.n_tiles;    // uniform
-    // Whole blocks of visual queries that all count (all but the edges): no test per value, the rows' addresses in
-    // scalar registers, and the column sums of eight keys halved between the lanes step by step.
-    if constexpr (KB == 2) {
-      if (a.abar && recv && ik0 + KB * 16 <= a.N && v0 + QB * 16 <= a.n_visq && !(DEC && ik0 + KB * 16 - 1 > v0)) {     // uniform
-        double cs[KB * 4];
-        const uint32_t at = (uint32_t)(lg * 4 * a.map_pitch + l16);
+    double cs[kQkE];                                    // received from this tile's visual queries
+    if (blocks == 2 && a.abar && ik0 + kQkB <= a.N && v0 + kQkTile <= a.n_visq && !(DEC && ik0 + kQkB - 1 > v0)) {     // uniform
+      // Whole blocks of visual queries that all count (all but the edges): no test per value, the rows' addresses in
+      // scalar registers.
+      const uint32_t at = (uint32_t)(hi * 4 * a.map_pitch + l32);
 #pragma unroll
-        for (int kb = 0; kb < KB; ++kb)
+      for (int v = 0; v < kQkE; ++v) {
+        float* row = a.abar + (b * a.N + ik0 + key_of(v)) * a.map_pitch + v0;
+        const float p0 = s0[v] * invH, p1 = s1[v] * invH;      // head-mean probabilities
+        row[at] = p0;
+        row[at + kQkB] = p1;
+        cs[v] = (double)p0 + (double)p1;
+      }
+    } else {
 #pragma unroll
-          for (int v = 0; v < 4; ++v) {
-            float* row = a.abar + (b * a.N + ik0 + kb * 16 + v) * a.map_pitch + v0;
-            cs[kb * 4 + v] = 0.0;
+      for (int v = 0; v < kQkE; ++v) cs[v] = 0.0;
 #pragma unroll
-            for (int qb = 0; qb < QB; ++qb) {
-              const float pm = sums[kb][qb][v] * invH;
-              row[at + qb * 16] = pm;
-              cs[kb * 4 + v] += (double)pm;
-            }
+      for (int m = 0; m < blocks; ++m) {
+        const int vq = v0 + m * kQkB + l32, k_first = ik0 + 4 * hi, n_k = a.N - k_first;
+        const bool q_vis = vq < a.n_visq, q_in = vq < a.nq;
+        const int behind = DEC ? a.row(vq) - a.vis0 - k_first : 0;     // keys from there on lie behind the query
+        const int64_t key = b * a.N + k_first;
+        float* map = a.abar + key * a.map_pitch + vq;
+        double* other = DEC ? a.ttext + key * a.M + (vq - a.n_visq) : a.cls + key;
+        const int64_t other_pitch = DEC ? a.M : 1;
+#pragma unroll
+        for (int v = 0; v < kQkE; ++v) {
+          const int k = key_of(v);
+          float pm = (m == 0 ? s0[v] : s1[v]) * invH;
+          if (DEC && k > behind) pm = 0.0f;
+          if (k < n_k) {
+            if (q_vis) { if (a.abar) map[k * (int64_t)a.map_pitch] = pm; }
+            else if (q_in) other[k * other_pitch] = (double)pm;
           }
-        const double mine = row_sums_of_8(cs, l16);
-        const int i = (l16 & 1) * 4 + (l16 & 2) + (l16 >> 2 & 1);       // the key whose sum this lane holds
-        if (l16 < 8) a.recv_part[(b * a.n_tiles + qt) * a.N + ik0 + i / 4 * 16 + lg * 4 + i % 4] = mine;
-        return;
+          cs[v] += q_vis ? (double)pm : 0.0;
+        }
       }
     }
-#pragma unroll
-    for (int kb = 0; kb < KB; ++kb) {
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int ik = ik0 + kb * 16 + lg * 4 + v;      // visual key
-        const bool k_vis = ik < a.N;
-        double cs = 0.0;                                // received from this tile's visual queries
-#pragma unroll
-        for (int qb = 0; qb < QB; ++qb) {
-          const int vq = v0 + qb * 16 + l16;
-          float pm = sums[kb][qb][v] * invH;            // head-mean probability
-          if (DEC && a.vis0 + ik > a.row(vq)) pm = 0.0f;     // a key behind its query
-          const bool q_vis = vq < a.n_visq;
-          if (k_vis && q_vis && a.abar) a.abar[(b * a.N + ik) * a.map_pitch + vq] = pm;
-          if (k_vis && !q_vis && vq < a.nq) {
-            if (DEC) a.ttext[(b * a.N + ik) * a.M + (vq - a.n_visq)] = (double)pm;
-            else a.cls[b * a.N + ik] = (double)pm;
-          }
-          cs += q_vis ? (double)pm : 0.0;
-        }
-        if (recv) {
-          // sum over the 16 lanes that hold the tile's other queries of this key (a fixed tree)
-          cs += dpp_move<0xB1>(cs);
-          cs += dpp_move<0x4E>(cs);
-          cs += dpp_move<0x141>(cs);
-          cs += dpp_move<0x140>(cs);
-          if (l16 == 0 && k_vis) a.recv_part[(b * a.n_tiles + qt) * a.N + ik] = cs;
-        }
-      }
+    if (recv) {
+      const double mine = sums_of_16(cs, l32);
+      const int i = sum_index(l32), ik = ik0 + i / 4 * 8 + i % 4 + 4 * hi;
+      if (l32 < 16 && ik < a.N) a.recv_part[(b * a.n_tiles + qt) * a.N + ik] = mine;
     }
   };
 
   if (narrow) {
     // The wavefronts take consecutive shares of the heads,
-    // operands straight from memory, and their sums are added in order.
-    constexpr int KB = kQkKeys / 16, W = Shape::kThreads / kWave;
-    f32x4_t P1[KB][1];
+    // operands straight from memory, and their sums are added pairwise (a fixed tree).
+    constexpr int W = Shape::kThreads / kWave;
+    f32x16_t P1[2];
 #pragma unroll
-    for (int kb = 0; kb < KB; ++kb) P1[kb][0] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
-    const int hs = (a.H + W - 1) / W, lo = min(wv * hs, a.H), hi = min(lo + hs, a.H);
-    if (lo < hi && !wg_dead) {
-      const int v = min(v0 + l16, a.nq - 1);
-      const bf16_t* q_at = a.Q + b * a.sb + (int64_t)a.row(v) * a.sn + lg * 8;
-      const bf16_t* k_at[KB];
+    for (int kb = 0; kb < 2; ++kb) P1[kb] = qk_zero();
+    const int hs = (a.H + W - 1) / W, lo = min(wv * hs, a.H), h_end = min(lo + hs, a.H);
+    if (!wg_dead) {
+      const int v = min(w0 + l32, a.nq - 1);
+      const bf16_t* q_at = a.Q + b * a.sb + (int64_t)a.row(v) * a.sn + hi * 8;
+      const bf16_t* k_at[2];
 #pragma unroll
-      for (int kb = 0; kb < KB; ++kb) k_at[kb] = a.K + b * a.sb + (int64_t)(a.vis0 + min(wk0 + kb * 16 + l16, a.N - 1)) * a.sn + lg * 8;
-      bf16x8_t qf[KS], kf[KB][KS];
-      float2 nf;
-      auto load_head = [&](int h) {
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-          __builtin_memcpy(&qf[ks], q_at + (int64_t)h * a.sh + ks * 32, 16);
-#pragma unroll
-          for (int kb = 0; kb < KB; ++kb) __builtin_memcpy(&kf[kb][ks], k_at[kb] + (int64_t)h * a.sh + ks * 32, 16);
-        }
-        nf = a.norm[(bi * a.H + h) * a.nq + v];
-      };
-      load_head(lo);
+      for (int kb = 0; kb < 2; ++kb) k_at[kb] = a.K + b * a.sb + (int64_t)(a.vis0 + min(wk0 + kb * kQkB + l32, a.N - 1)) * a.sn + hi * 8;
 #pragma unroll 1
-      for (int h = lo; h < hi; ++h) {
-        f32x4_t S[KB];
+      for (int h = lo; h < h_end; ++h) {
+        const float2 n = a.norm[(bi * a.H + h) * a.nq + v];
+        f32x16_t S[2];
 #pragma unroll
-        for (int kb = 0; kb < KB; ++kb) {
-          S[kb] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+        for (int c = 0; c < KS * 2; c += KT) {         // a stage's features at a time
+          bf16x8_t qf[KT], kf[2][KT];
 #pragma unroll
-          for (int ks = 0; ks < KS; ++ks) S[kb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[kb][ks], qf[ks], S[kb], 0, 0, 0);
+          for (int kt = 0; kt < KT; ++kt) {
+            __builtin_memcpy(&qf[kt], q_at + (int64_t)h * a.sh + (c + kt) * 16, 16);
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb) __builtin_memcpy(&kf[kb][kt], k_at[kb] + (int64_t)h * a.sh + (c + kt) * 16, 16);
+          }
+          issue_fence();
+#pragma unroll
+          for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+            for (int kt = 0; kt < KT; ++kt) S[kb] = qk_mfma(kf[kb][kt], qf[kt], c + kt == 0 ? qk_zero() : S[kb]);
         }
-        const float2 n = nf;
-        load_head(min(h + 1, hi - 1));
-        issue_fence();
 #pragma unroll
-        for (int kb = 0; kb < KB; ++kb)
+        for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-          for (int v4 = 0; v4 < 4; ++v4)
-            P1[kb][0][v4] = fmaf(__builtin_amdgcn_exp2f(fmaf(S[kb][v4], a.scale_log2e, -n.x)), n.y, P1[kb][0][v4]);
+          for (int e = 0; e < kQkE; ++e) P1[kb][e] = fmaf(__builtin_amdgcn_exp2f(fmaf(S[kb][e], a.scale_log2e, -n.x)), n.y, P1[kb][e]);
       }
     }
-    f32x4_t* sums = (f32x4_t*)stage_m;
+    f32x16_t* sums = (f32x16_t*)stage_m;
 #pragma unroll
-    for (int kb = 0; kb < KB; ++kb)
-      if (wv > 0) sums[((wv - 1) * KB + kb) * kWave + lane] = P1[kb][0];
+    for (int step = W / 2; step >= 2; step /= 2) {
+      f32x16_t* slot = sums + wv % step * 2 * kWave + lane;
+      if (wv >= step && wv < 2 * step) { slot[0] = P1[0]; slot[kWave] = P1[1]; }
+      __syncthreads();
+      if (wv < step) { P1[0] += slot[0]; P1[1] += slot[kWave]; }
+      __syncthreads();
+    }
+    // the last two wavefronts write a block of keys each
+    if (wv < 2) sums[wv * kWave + lane] = wv == 0 ? P1[1] : P1[0];
     __syncthreads();
-    if (wv != 0) return;
-    for (int w = 0; w < W - 1; ++w)
-#pragma unroll
-      for (int kb = 0; kb < KB; ++kb) P1[kb][0] += sums[(w * KB + kb) * kWave + lane];
-    write_out(std::integral_constant<int, KB>{}, std::integral_constant<int, 1>{}, wk0, P1);
+    if (wv >= 2) return;
+    const f32x16_t mine = wv == 0 ? P1[0] + sums[kWave + lane] : sums[lane] + P1[1];
+    write_out(std::integral_constant<int, 1>{}, w0, wk0 + wv * kQkB, mine, mine);
     return;
   }
 
   if (!wg_dead) heads();                                // uniform in the workgroup
   if constexpr (SPLIT) {
-    f32x4_t* sums = (f32x4_t*)stage_m;                // (the staging areas are free)
+    f32x16_t* sums = (f32x16_t*)stage_m;              // (the staging areas are free)
 #pragma unroll
     for (int step = Shape::kShares / 2; step >= 1; step /= 2) {
-      f32x4_t* slot = sums + (wv % (kQkCols * step)) * kQkMB * kQkQB * kWave + lane;
-      if (share >= step && share < 2 * step) {
-#pragma unroll
-        for (int kb = 0; kb < kQkMB; ++kb)
-#pragma unroll
-          for (int qb = 0; qb < kQkQB; ++qb) slot[(kb * kQkQB + qb) * kWave] = P[kb][qb];
-      }
+      f32x16_t* slot = sums + (wv % (kQkWaves * step)) * kWave + lane;
+      if (share >= step && share < 2 * step) *slot = P[0];
       __syncthreads();
-      if (share < step) {
-#pragma unroll
-        for (int kb = 0; kb < kQkMB; ++kb)
-#pragma unroll
-          for (int qb = 0; qb < kQkQB; ++qb) P[kb][qb] += slot[(kb * kQkQB + qb) * kWave];
-      }
+      if (share < step) P[0] += *slot;
       __syncthreads();
     }
-    if (share != 0) return;
+    // the upper block of a tile's queries goes to the wavefront that has the lower one
+    if (share == 0 && wq == 1) sums[wk * kWave + lane] = P[0];
+    __syncthreads();
+    if (share != 0 || wq != 0) return;
+    write_out(std::integral_constant<int, 2>{}, w0, ik0, P[0], sums[wk * kWave + lane]);
+  } else {
+    if (v0 < a.nq) write_out(std::integral_constant<int, 2>{}, v0, ik0, P[0], P[MB - 1]);
   }
-  if (v0 < a.nq) write_out(std::integral_constant<int, kQkMB>{}, std::integral_constant<int, kQkQB>{}, ik0, P);
 }
 
 template <int KS, bool DEC>
 static void launch_qk(QkArgs a, hipStream_t s) {
   constexpr int CH = (KS > 2 ? 2 : KS) * 4;
-  const int tiles = (a.nq + kQkTile - 1) / kQkTile;
+  const int tiles = (a.nq + kNormTile - 1) / kNormTile;
   a.q_groups = (tiles + kQkWaves - 1) / kQkWaves;
   // Fewer than one workgroup per compute unit (for heads of 32, whose steps are short, four): one tile each, whose keys
   // the wavefronts share.  Step of 16 x 577 tokens, whole tiles per wavefront and shared: one head of 64
@@ -683,23 +722,25 @@ static void launch_qk(QkArgs a, hipStream_t s) {
   // 38.8 and 35.0.
   a.share_keys = (int64_t)a.nb * a.H * a.q_groups < (KS == 1 ? 1024 : 256);
   if (a.share_keys) a.q_groups = tiles;
-  const bool narrow = a.nq - (a.q_groups - 1) * (a.share_keys ? 1 : kQkWaves) * kQkTile <= 16;      // (as the kernel sees it)
+  const bool narrow = a.nq - (a.q_groups - 1) * (a.share_keys ? 1 : kQkWaves) * kNormTile <= 16;      // (as the kernel sees it)
   const int groups = a.q_groups - (narrow ? 1 : 0);
   hipLaunchKernelGGL((qk_norm_kernel<KS, DEC>), dim3(xcd_padded_total(a.nb * a.H * groups) + (narrow ? xcd_padded_total(a.nb * a.H) : 0)), dim3(kQkWaves * kWave), 0, s, a);
   auto mean = [&](auto kern, auto shape) {
     using Shape = decltype(shape);
-    // two stages of (queries + keys) rows, in whole rounds of the loader; one pair per share of the heads
-    constexpr int kLoaders = Shape::kRows * kQkCols * kWave / CH;
-    constexpr int kStageRows = (Shape::kRows * kQkTile + kQkKeys + kLoaders - 1) / kLoaders * kLoaders;
-    constexpr size_t kLds = 2 * Shape::kShares * ((size_t)kStageRows * CH * sizeof(u32x4_t) + Shape::kRows * kQkTile * sizeof(float2));
+    // two stages of (queries + keys) rows per share of the heads, and the queries' normalisers of two heads
+    constexpr size_t kStages = 2 * Shape::kShares * ((size_t)(Shape::kQueries + kQkKeys) * CH * sizeof(u32x4_t) + Shape::kQueries * sizeof(float2));
+    constexpr size_t kSums = (size_t)Shape::kThreads * sizeof(f32x16_t);      // (of a narrow tile, at most)
+    constexpr size_t kLds = kStages > kSums ? kStages : kSums;
     if (kLds > 32768)
       (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLds);
-    a.q_groups = (tiles + Shape::kRows - 1) / Shape::kRows;
+    a.q_groups = (a.nq + Shape::kQueries - 1) / Shape::kQueries;
     hipLaunchKernelGGL(kern, dim3(xcd_padded_total(a.nb * a.q_groups * a.k_tiles)), dim3(Shape::kThreads), kLds, s, a);
   };
-  // Fewer than one workgroup of the wide form per compute unit: the heads of a tile are split instead
-  // (one image of 577 tokens: step 96 us before, 46 us so).
-  const bool split = (int64_t)a.nb * ((tiles + QkMeanShape<false>::kRows - 1) / QkMeanShape<false>::kRows) * a.k_tiles < 256;
+  // Fewer than a workgroup of the wide form for every other compute unit: the heads of a tile are split instead
+  // (steps of 577 tokens, 16 heads, split and wide: two images, 90 workgroups, 40.0 and 43.8 us; three, 135 workgroups,
+  // 52.6 and 46.7; five, 225 workgroups, 54.9 and 49.1).
+  const int wide = QkMeanShape<false>::kQueries;
+  const bool split = (int64_t)a.nb * ((a.nq + wide - 1) / wide) * a.k_tiles < 128;
   if (split) mean(qk_mean_kernel<KS, DEC, true>, QkMeanShape<true>{});
   else mean(qk_mean_kernel<KS, DEC, false>, QkMeanShape<false>{});
 }

@@ -87,7 +87,7 @@ int make_plan(const ficoco_problem& p, Plan& plan, const char** why, size_t scra
 // feature stage's launch)
 void launch_attn_reduce(const ficoco_problem& p, const Plan& pl, char* ws, hipStream_t s, bool text_elsewhere = false);
 void launch_attn_qk(const ficoco_problem& p, const Plan& pl, char* ws, hipStream_t s);
-constexpr int kQkTile = 48;        // query rows of a unit of the query/key form (its column partials are one per tile)
+constexpr int kQkTile = 64;        // query rows of a column partial of the query/key form
 // The row normalisers are kept for as many images at a time as fit in this many bytes (at least one).
 constexpr size_t kQkNormBytes = (size_t)8 << 20;
 // With more keys than kQkMaxKeys, and for FiCoCo-L, at most kQkLongMaxHeads heads are taken: one image of FiCoCo-V then

@@ -202,6 +202,22 @@ def test_query_tiles_and_head_shares(ctx, B, grid, H, d):
     assert full >= (B + 1) // 2
 
 
+@pytest.mark.parametrize("B,grid,H,d", [(1, 8, 5, 64), (1, 9, 6, 128), (63, 9, 3, 64), (64, 9, 2, 128), (50, 16, 2, 64), (6, 18, 17, 128),
+                                        (70, 10, 3, 32)])
+def test_tiles_of_64_and_128_queries_of_the_head_mean(ctx, B, grid, H, d):
+    """65 queries (a tile of 64 and one left), 82 (18 left, at 63 images the heads split, at 64 not), 257 (wide tiles and one
+    query left), 325 and 101 (a wide tile that is not full); fewer heads than shares, and a share that is shorter."""
+    full = _case(ctx, 360 + B + grid, B, grid, 72, H, d, "bf16", max(1, grid * grid // 3), 1.0)
+    assert full >= (B + 1) // 2
+
+
+@pytest.mark.parametrize("B,N,M,H,d", [(30, 230, 40, 2, 64), (1, 230, 40, 6, 128), (40, 100, 33, 3, 32)])
+def test_causal_tiles_of_64_and_128_queries(ctx, B, N, M, H, d):
+    """270 queries of which a block of 14 is left behind wide tiles, or behind tiles of 64 (split heads), and 133."""
+    full = _case_l(ctx, 380 + B, B, 3, N, M, 72, H, d, N // 3, fc.R_ATTN_RECV, fc.C_ATTN)
+    assert full >= (B + 1) // 2
+
+
 @pytest.mark.parametrize("B,grid,H,d", [(16, 24, 3, 64), (16, 24, 4, 64), (16, 14, 15, 32), (32, 14, 16, 32)])
 def test_keys_shared_by_the_wavefronts_or_not(ctx, B, grid, H, d):
     """192 and 256 workgroups of the row normalisers with heads of 64, 480 and 1024 with heads of 32: below 256
