@@ -114,18 +114,21 @@ __device__ __forceinline__ void col_sum_block(const FeatArgs& a, int chunk, int 
 template <typename T>
 __global__ __launch_bounds__(256) void col_sum_kernel(FeatArgs a) { col_sum_block<T>(a, blockIdx.x, blockIdx.y, blockIdx.z); }
 
-// The column sums with the statistics of the text profiles (FiCoCo-L) in the same launch: the first
-// `stat_blocks * B` workgroups take the statistics, the others the column sums (chunk fastest,
-// then feature span, then image).
+// The column sums with the statistics of the text profiles (FiCoCo-L) in the same launch: first the workgroups of the
+// profiles' maxima (the longest chains), then the column sums (chunk fastest, then feature span, then image), which are
+// most of the launch, then the short means.
 template <typename T>
-__global__ __launch_bounds__(256) void colsum_stats_kernel(FeatArgs a, TextStatsArgs t, int stat_blocks, int spans) {
-  const int n_stat = stat_blocks * a.B;
-  if ((int)blockIdx.x < n_stat) {
-    text_stats_block(t, (int)blockIdx.x % stat_blocks, (int)blockIdx.x / stat_blocks);
-    return;
+__global__ __launch_bounds__(256) void colsum_stats_kernel(FeatArgs a, TextStatsArgs t, int spans) {
+  const int n_cmax = t.cmax_blocks * a.B, n_sum = a.f_chunks * spans * a.B;
+  int q = blockIdx.x;
+  if (q < n_cmax) {
+    text_cmax_block(t, q % t.cmax_blocks, q / t.cmax_blocks);
+  } else if ((q -= n_cmax) < n_sum) {
+    col_sum_block<T>(a, q % a.f_chunks, (q / a.f_chunks) % spans, q / (a.f_chunks * spans));
+  } else {
+    q -= n_sum;
+    text_mean_block(t, q % t.mean_blocks, q / t.mean_blocks);
   }
-  const int q = (int)blockIdx.x - n_stat;
-  col_sum_block<T>(a, q % a.f_chunks, (q / a.f_chunks) % spans, q / (a.f_chunks * spans));
 }
 
 // Column means from the chunk partials (added in chunk order, 8 loads in flight).  Every
@@ -309,11 +312,10 @@ void launch_features(const ficoco_problem& p, const Plan& pl, char* ws, hipStrea
   const int spans = (pl.Df + kColSpan - 1) / kColSpan;
   if (with_text) {
     TextStatsArgs t{};
-    fill_text_stats(p, pl, ws, t);
-    const int stat_blocks = text_stats_blocks(t, with_cmax);
-    const dim3 grid(stat_blocks * p.B + pl.f_chunks * spans * p.B);
-    if (bf16) hipLaunchKernelGGL(colsum_stats_kernel<bf16_t>, grid, block, 0, s, a, t, stat_blocks, spans);
-    else hipLaunchKernelGGL(colsum_stats_kernel<float>, grid, block, 0, s, a, t, stat_blocks, spans);
+    fill_text_stats(p, pl, ws, with_cmax, t);
+    const dim3 grid((t.cmax_blocks + t.mean_blocks + pl.f_chunks * spans) * p.B);
+    if (bf16) hipLaunchKernelGGL(colsum_stats_kernel<bf16_t>, grid, block, 0, s, a, t, spans);
+    else hipLaunchKernelGGL(colsum_stats_kernel<float>, grid, block, 0, s, a, t, spans);
   } else {
     dim3 cgrid(pl.f_chunks, spans, p.B);
     if (bf16) hipLaunchKernelGGL(col_sum_kernel<bf16_t>, cgrid, block, 0, s, a);

@@ -934,7 +934,10 @@ __global__ __launch_bounds__(256) void vector_scores_cells_kernel(const void* re
   if (t >= 0) scores[b * N + t] = penalize && best_of[lw] == t ? coef * st : st;
 }
 
-__global__ __launch_bounds__(256) void text_stats_kernel(TextStatsArgs a) { text_stats_block(a, blockIdx.x, blockIdx.y); }
+__global__ __launch_bounds__(256) void text_stats_kernel(TextStatsArgs a) {
+  if ((int)blockIdx.x < a.cmax_blocks) text_cmax_block(a, blockIdx.x, blockIdx.y);
+  else text_mean_block(a, blockIdx.x - a.cmax_blocks, blockIdx.y);
+}
 
 static size_t select_lds(const ficoco_problem& p, bool penalty) {
   const size_t cells = penalty ? (size_t)p.grid_g * p.grid_h * p.grid_w : 0;
@@ -942,11 +945,12 @@ static size_t select_lds(const ficoco_problem& p, bool penalty) {
   return (size_t)p.N * sizeof(double) + (2 * kSelectThreads + 256 + 8 + (p.N + 31) / 32 + (cells > wide ? cells : wide)) * sizeof(int);
 }
 
-void fill_text_stats(const ficoco_problem& p, const Plan& pl, char* ws, TextStatsArgs& t) {
+void fill_text_stats(const ficoco_problem& p, const Plan& pl, char* ws, bool with_cmax, TextStatsArgs& t) {
   t.ttext = (const double*)(ws + pl.ttext);
   t.N = p.N; t.M = p.M;
   t.out_g = (double*)(ws + pl.fterm2);
   t.cmax = (double*)(ws + pl.cmax);
+  t.cmax_blocks = with_cmax ? (p.M + kCmaxQueries - 1) / kCmaxQueries : 0;
   t.mean_blocks = (p.N + 3) / 4;
 }
 
@@ -1004,8 +1008,8 @@ void launch_select(const ficoco_problem& p, const Plan& pl, char* ws, double* sc
     if (!text_stats_done) {
       const bool with_cmax = do_filter && text_stats_in_score(p);
       TextStatsArgs t{};
-      fill_text_stats(p, pl, ws, t);
-      hipLaunchKernelGGL(text_stats_kernel, dim3(text_stats_blocks(t, with_cmax), p.B), dim3(256), 0, s, t);
+      fill_text_stats(p, pl, ws, with_cmax, t);
+      hipLaunchKernelGGL(text_stats_kernel, dim3(t.cmax_blocks + t.mean_blocks, p.B), dim3(256), 0, s, t);
     }
     a.sem_src = FICOCO_G_EQ_TOKEN;             // "read the precomputed term"
   }

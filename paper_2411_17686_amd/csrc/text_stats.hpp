@@ -12,58 +12,55 @@ namespace ficoco {
 // workgroup walking its token's profile touches a cache line per lane and load, all on one
 // compute unit (64 queries: 17 us for the select kernel against 9 + 4 us this way).
 // In the fused step the same launch also forms cmax[b][k], the maximum over the visual tokens of
-// profile entry k (the bound of Eq. 4's indirect term that the correlate stage needs): the
-// workgroups behind the first `mean_blocks` take 64 text queries of one image each, thread
-// (k, g) walking the tokens g, g + 4, ... with 16 independent loads per round, the four token
-// groups meeting in LDS.  Both are short chains of dependent loads on few workgroups; in one
-// launch they overlap instead of following each other.
+// profile entry k (the bound of Eq. 4's indirect term that the correlate stage needs).  The first workgroups take
+// kCmaxQueries text queries of one image each, thread (k, g) walking the tokens g, g + 16, ... with 16 independent
+// loads per round, the sixteen token groups meeting in LDS: three rounds at 576 tokens, and the cache lines of a row are read whole.
+// (64 queries and four token groups a workgroup were nine rounds, one after the other: 7.2 us for the launch at 8 x 576 tokens
+// and 64 queries, 4.8 so.)
 struct TextStatsArgs {
   const double* ttext;   // [B][N][M]
   int N, M;
   double* out_g;         // [B][N]
-  double* cmax;          // [B][M], written by the workgroups behind the first mean_blocks (if any are launched)
-  int mean_blocks;
+  double* cmax;          // [B][M]
+  int cmax_blocks, mean_blocks;      // workgroups per image (cmax_blocks = 0: no maxima)
 };
-void fill_text_stats(const ficoco_problem& p, const Plan& pl, char* ws, TextStatsArgs& t);
-inline int text_stats_blocks(const TextStatsArgs& a, bool with_cmax) { return a.mean_blocks + (with_cmax ? (a.M + 63) / 64 : 0); }
+constexpr int kCmaxQueries = 16;
+void fill_text_stats(const ficoco_problem& p, const Plan& pl, char* ws, bool with_cmax, TextStatsArgs& t);
 
-__device__ __forceinline__ void text_stats_block(const TextStatsArgs& a, int bx, int64_t b) {
-  __shared__ double part[256];
-  const double* __restrict__ ttext = a.ttext;
-  double* __restrict__ out_g = a.out_g;
-  double* __restrict__ cmax = a.cmax;
-  const int N = a.N, M = a.M, mean_blocks = a.mean_blocks;
-  if (bx < mean_blocks) {
-    const int lane = threadIdx.x % kWave;
-    const int i = bx * (blockDim.x / kWave) + threadIdx.x / kWave;
-    if (i >= N) return;      // whole wavefront leaves together
-    const double* p = ttext + (b * N + i) * M;
-    double acc = 0.0;
-    for (int k = lane; k < M; k += kWave) acc += p[k];
+// mean of the profiles of tokens 4 bx .. 4 bx + 4, a wavefront each
+__device__ __forceinline__ void text_mean_block(const TextStatsArgs& a, int bx, int64_t b) {
+  const int lane = threadIdx.x % kWave;
+  const int i = bx * (blockDim.x / kWave) + threadIdx.x / kWave;
+  if (i >= a.N) return;      // whole wavefront leaves together
+  const double* __restrict__ p = a.ttext + (b * a.N + i) * a.M;
+  double acc = 0.0;
+  for (int k = lane; k < a.M; k += kWave) acc += p[k];
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, kWave);
-    if (lane == 0) out_g[b * N + i] = acc / (double)M;
-    return;
-  }
-  const int tid = threadIdx.x;
-  const int k = (bx - mean_blocks) * 64 + tid % 64, g = tid / 64;
+  for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, kWave);
+  if (lane == 0) a.out_g[b * a.N + i] = acc / (double)a.M;
+}
+
+// maxima of the profile entries kCmaxQueries bx and on (256 threads)
+__device__ __forceinline__ void text_cmax_block(const TextStatsArgs& a, int bx, int64_t b) {
+  constexpr int kGroups = 256 / kCmaxQueries;
+  __shared__ double part[kGroups][kCmaxQueries];
+  const int kl = threadIdx.x % kCmaxQueries, g = threadIdx.x / kCmaxQueries, k = bx * kCmaxQueries + kl;
+  const double* __restrict__ p = a.ttext + b * a.N * a.M + min(k, a.M - 1);
   double mx = 0.0;
-  if (k < M) {
-    int i = g;
-    for (; i + 4 * 15 < N; i += 4 * 16) {              // 16 independent loads per round
-      double v[16];
+  for (int i0 = g; i0 < a.N; i0 += 16 * kGroups) {     // past the last token that one again
+    double v[16];
 #pragma unroll
-      for (int u = 0; u < 16; ++u) v[u] = ttext[(b * N + i + 4 * u) * M + k];
+    for (int u = 0; u < 16; ++u) v[u] = p[(int64_t)min(i0 + u * kGroups, a.N - 1) * a.M];
+    issue_fence();
 #pragma unroll
-      for (int u = 0; u < 16; ++u) mx = v[u] > mx ? v[u] : mx;
-    }
-    for (; i < N; i += 4) { const double v = ttext[(b * N + i) * M + k]; mx = v > mx ? v : mx; }
+    for (int u = 0; u < 16; ++u) mx = v[u] > mx ? v[u] : mx;
   }
-  part[tid] = mx;
+  part[g][kl] = mx;
   __syncthreads();
-  if (g == 0 && k < M) {
-    for (int q = 1; q < 4; ++q) mx = part[q * 64 + tid] > mx ? part[q * 64 + tid] : mx;
-    cmax[b * M + k] = mx;
+  if (g == 0 && k < a.M) {
+#pragma unroll
+    for (int q = 1; q < kGroups; ++q) { const double t = part[q][kl]; mx = t > mx ? t : mx; }
+    a.cmax[b * a.M + k] = mx;
   }
 }
 
