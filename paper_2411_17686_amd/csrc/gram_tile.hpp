@@ -161,152 +161,199 @@ __global__ __launch_bounds__(256) void gram_tile_kernel(GramArgs a) {
 }
 
 // ---- the same product for large blocks ---------------------------------------------------------
-// 256 x 192 output tile per workgroup of 8 wavefronts (4 x 2), 64 x 96 per wavefront = 2 x 3 blocks
-// of v_mfma_f32_32x32x16_bf16: five fragment reads feed six matrix instructions (the 64 x 64 form
-// above reads four for four), and every operand row is fetched by 6 (A) or 32 (B) workgroups
-// instead of 9 and 63 at the 8064 x 1152 shape.  K is staged 64 features at a time (half the
-// barriers of the 32-feature stages above).  LDS rows are the 128 bytes of a stage with no padding;
-// the eight 16-byte chunks of row r sit at chunk ^ ((r >> 1) & 7), which makes both the loader's
-// stores (consecutive lanes = consecutive chunks of consecutive rows) and the fragment reads
-// (sixteen consecutive rows, one chunk) free of bank conflicts.
-constexpr int kG2M = 256, kG2N = 192, kG2K = 64;
-constexpr int kG2Threads = 512;
+// 192 x 192 or 256 x 192 output tile per workgroup of four wavefronts (2 x 2), 96 x 96 or 128 x 96 per wavefront = 3 x 3 or
+// 4 x 3 blocks of v_mfma_f32_32x32x16_bf16, one wavefront per SIMD: six fragment reads feed nine matrix instructions, seven
+// twelve.  Whole rows go from memory straight into LDS, 64 features at a time, three stages ahead (144 KB) or two (112 KB);
+// the fragments of the next sixteen features are read while the matrix cores work on the ones before, across the one barrier of
+// a stage too.  LDS rows are the 128 bytes of a stage with no padding; the eight 16-byte chunks of row r sit at
+// chunk ^ ((r >> 1) & 7), which keeps the fragment reads (sixteen consecutive rows, one chunk) free of bank conflicts; a
+// load fills LDS in the order of the lanes, so it is its source that is permuted.
+//
+// What bounds it: the matrix cores and, since all workgroups end together, the output.  8064 x 1152 x 1024 (252 tiles, one
+// round): 28.3 us; without the stores 21.8, without the loads inside the loop 24, without both 16.5; the 37 MB of output alone
+// are 7 us at the rate of a large copy, the product 15.5 us at the rate of a large library product.  Before (256 x 192 tiles of eight
+// wavefronts through registers into LDS, one stage ahead): 34.2 us; 8064 x 1152 x 3584: 90 us before, 69 now; two images of
+// it: 59.5 before, 50 now.  Two buffers in place of three for the 192-row form: 27.8 us here, but 64 images of 768 x 384 x 1024
+// (rows out of HBM) 74 us instead of 64.
+constexpr int kG2N = 192, kG2K = 64;
+constexpr int kG2Threads = 256;
 constexpr int kG2Chunks = kG2K / 8;        // 16-byte chunks per operand row and stage
+static __device__ const uint4 g_zero_chunk = {0, 0, 0, 0};
 __device__ __forceinline__ int g2_slot(int row, int chunk) { return row * kG2Chunks + (chunk ^ ((row >> 1) & 7)); }
 
-__global__ __launch_bounds__(kG2Threads) void gram_tile2_kernel(GramArgs a) {
-  static_assert(kG2Chunks == 8, "the swizzle spreads eight chunks");
-  extern __shared__ uint4 g2_lds[];
-  uint4* Abuf = g2_lds;                                   // [2][256 rows][8 chunks]
-  uint4* Bbuf = g2_lds + 2 * kG2M * kG2Chunks;            // [2][192 rows][8 chunks]
-  __shared__ int rowA[kG2M];
-  __shared__ int rowB[kG2N];
-  const int tid = threadIdx.x, lane = tid % kWave, wv = tid / kWave;
-  const int tiles_m = (a.n_disc + kG2M - 1) / kG2M, tiles_n = (a.n_keep + kG2N - 1) / kG2N;
-  const int total = a.B * tiles_m * tiles_n;
-  const int logical = xcd_logical_id(blockIdx.x, total);     // the column tiles of the same rows share an XCD
+template <int MB>
+__global__ __launch_bounds__(kG2Threads) __attribute__((amdgpu_waves_per_eu(1, 1))) void gram_tile2_kernel(GramArgs a) {
+  static_assert(kG2Chunks == 8 && kG2K == 64, "the swizzle spreads eight chunks; four products of sixteen features a stage");
+  constexpr int kM = 64 * MB, kRows = kM + kG2N;
+  constexpr int kLoads = kRows * kG2Chunks / kG2Threads;  // per thread and stage: rows of A, then of B
+  constexpr int kBufs = MB == 3 ? 3 : 2;                  // 144 KB and 112 KB
+  __shared__ uint4 buf0[kRows * kG2Chunks], buf1[kRows * kG2Chunks], buf2[kBufs == 3 ? kRows * kG2Chunks : 1];
+  __shared__ __attribute__((aligned(16))) int tok[kRows]; // of the rows of A, then of B
+  const int tid = threadIdx.x, lane = tid % kWave, l32 = lane % 32, hi = lane / 32;
+  const int wv = __builtin_amdgcn_readfirstlane(tid / kWave), wm = wv / 2, wn = wv % 2;
+  const int tiles_m = (a.n_disc + kM - 1) / kM, tiles_n = (a.n_keep + kG2N - 1) / kG2N;
+  const int per_split = a.B * tiles_m * tiles_n, total = per_split * a.splits;
+  int logical = xcd_logical_id(blockIdx.x, total);           // the column tiles of the same rows share an XCD
   if (logical >= total) return;   // padding workgroup
+  const int split = logical / per_split;
+  logical %= per_split;
   const int64_t b = logical / (tiles_m * tiles_n);
   const int tm = (logical % (tiles_m * tiles_n)) / tiles_n, tn = logical % tiles_n;
-
-  if (tid < kG2M) {
-    const int r = tm * kG2M + tid;
-    const int i = r < a.n_disc ? a.S[b * a.n_disc + r] : -1;
-    rowA[tid] = (unsigned)i < (unsigned)a.N ? i : -1;      // index sets are device data
-  } else if (tid < kG2M + kG2N) {
-    const int c = tn * kG2N + tid - kG2M;
-    const int j = c < a.n_keep ? a.T[b * a.n_keep + c] : -1;
-    rowB[tid - kG2M] = (unsigned)j < (unsigned)a.N ? j : -1;
+  bool mine = true;
+  for (int q = tid; q < kRows; q += kG2Threads) {
+    const int r = q < kM ? tm * kM + q : tn * kG2N + q - kM;
+    const int t = q < kM ? (r < a.n_disc ? a.S[b * a.n_disc + r] : -1) : (r < a.n_keep ? a.T[b * a.n_keep + r] : -1);
+    tok[q] = (unsigned)t < (unsigned)a.N ? t : -1;         // index sets are device data
+    mine &= tok[q] >= 0;
   }
-  __syncthreads();
+  const bool whole = __syncthreads_and(mine);              // every row and column of the tile is a token's
 
-  // loader: per stage 2048 chunks of A (four per thread) and 1536 of B (three per thread);
-  // chunk q = (row q / 8, 16 bytes q % 8)
-  const bf16_t* Xb = a.xhat + b * a.N * (int64_t)a.Df;
-  constexpr int kSlotsA = kG2M * kG2Chunks / kG2Threads, kSlotsB = kG2N * kG2Chunks / kG2Threads;
-  constexpr int kSlots = kSlotsA + kSlotsB;
-  static_assert(kSlotsA * kG2Threads == kG2M * kG2Chunks && kSlotsB * kG2Threads == kG2N * kG2Chunks, "whole slots");
-  // Every load of the loader is unconditional: a row past the block reads token 0 and a chunk past
-  // the K range reads the row's first chunk (both valid addresses: N >= 1, Df >= 8), and what was
-  // read is cleared when it is put into LDS.  Under a per-lane condition the loads sit in
-  // branches, and the compiler then waits for ALL outstanding loads before it issues the next
-  // stage's -- one stage in flight instead of two, and the wait at the head of every stage
-  // (measured here: 33-35 -> 30-33 us; the 128 x 128 kernel above, with four loads per stage, is
-  // no faster for it and keeps its conditional loads).
-  const bf16_t* src[kSlots];
-  bool row_ok[kSlots];
-  int lds_at[kSlots], kc[kSlots];
+  const int k_begin = split * a.st_per_split * kGramStage;
+  const int k_len = max(min(a.Df - k_begin, a.st_per_split * kGramStage), 0);
+  const int n_st = k_len / kG2K;                            // whole stages; what is left is a stage of its own
+  // A row past the block, or of no token, reads token 0 (its values are not used).
+  const bf16_t* xb = a.xhat + b * a.N * (int64_t)a.Df + k_begin;
+  uint32_t src[kLoads];                                   // in bytes: the rows of an image take less than 4 GiB on this path
+  const int chunk = (tid % kG2Chunks ^ (tid / 16 % kG2Chunks)) * 8;
 #pragma unroll
-  for (int u = 0; u < kSlots; ++u) {
-    const bool aop = u < kSlotsA;
-    const int q = tid + kG2Threads * (aop ? u : u - kSlotsA);
-    const int row = q / kG2Chunks, chunk = q % kG2Chunks;
-    const int tok = aop ? rowA[row] : rowB[row];
-    kc[u] = chunk * 8;
-    lds_at[u] = g2_slot(row, chunk);
-    row_ok[u] = tok >= 0;
-    src[u] = Xb + (int64_t)max(tok, 0) * a.Df;
-  }
-  uint4 rg[kGStages][kSlots];
-  const int n_st = (a.Df + kG2K - 1) / kG2K;
-  auto in_range = [&](int st, int u) { return st < n_st && st * kG2K + kc[u] + 8 <= a.Df; };   // Df is a multiple of 8 on this path
-  auto fetch = [&](int slot, int st) {
-#pragma unroll
-    for (int u = 0; u < kSlots; ++u) __builtin_memcpy(&rg[slot][u], src[u] + (in_range(st, u) ? st * kG2K + kc[u] : 0), 16);
+  for (int i = 0; i < kLoads; ++i)
+    src[i] = ((uint32_t)max(tok[tid / kG2Chunks + i * (kG2Threads / kG2Chunks)], 0) * (uint32_t)a.Df + chunk) * 2u;
+  auto load = [&](int i, const void* from, uint4* buf) __attribute__((always_inline)) {
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)from,
+                                     (__attribute__((address_space(3))) void*)(buf + i * kG2Threads + wv * kWave), 16, 0, 0);
   };
-  auto stash = [&](int slot, int buf, int st) {      // st: the stage that slot holds
+  auto fetch = [&](int st, uint4* buf) __attribute__((always_inline)) {
+    const char* at = (const char*)(xb + min(st, n_st - 1) * kG2K);   // past the last stage: that one again, so that the counts below hold
 #pragma unroll
-    for (int u = 0; u < kSlots; ++u) {
-      const uint4 v = row_ok[u] && in_range(st, u) ? rg[slot][u] : make_uint4(0, 0, 0, 0);
-      if (u < kSlotsA) Abuf[buf * kG2M * kG2Chunks + lds_at[u]] = v;
-      else Bbuf[buf * kG2N * kG2Chunks + lds_at[u]] = v;
-    }
+    for (int i = 0; i < kLoads; ++i) load(i, at + src[i], buf);
+    issue_fence();                                          // the loads of the stages stay in their order
   };
 
-  f32x16_t acc[2][3];
+  f32x16_t acc[MB][3];
 #pragma unroll
-  for (int mi = 0; mi < 2; ++mi)
+  for (int mi = 0; mi < MB; ++mi)
 #pragma unroll
     for (int ni = 0; ni < 3; ++ni)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[mi][ni][v] = 0.0f;
 
-  const int wm = wv / 2, wn = wv % 2;
-  const int frow = lane % 32, fch = lane / 32;     // fragment: row within the block, 16-byte chunk within a 16-feature step
+  bf16x8_t fr[2][MB + 3];                                   // fragments of sixteen features, of A and then of B; the next ones ahead
+  auto read = [&](const uint4* buf, int kk, bf16x8_t (&f)[MB + 3]) __attribute__((always_inline)) {
 #pragma unroll
-  for (int sl = 0; sl < kGStages; ++sl) fetch(sl, sl);
-  stash(0, 0, 0);
-  __syncthreads();
-  int cur = 0;
-  for (int base = 0; base < n_st; base += kGStages) {
+    for (int q = 0; q < MB + 3; ++q)
+      f[q] = ((const bf16x8_t*)buf)[g2_slot((q < MB ? wm * kM / 2 + q * 32 : kM + wn * 96 + (q - MB) * 32) + l32, kk * 2 + hi)];
+  };
+  auto multiply = [&](const bf16x8_t (&f)[MB + 3]) __attribute__((always_inline)) {
 #pragma unroll
-    for (int sl = 0; sl < kGStages; ++sl) {
-      const int it = base + sl;
-      if (it < n_st) {                          // uniform over the workgroup
-        fetch(sl, it + kGStages);               // slot sl was stashed one iteration ago
+    for (int mi = 0; mi < MB; ++mi)
 #pragma unroll
-        for (int kk = 0; kk < kG2K / 16; ++kk) {
-          bf16x8_t fa[2], fb[3];
+      for (int ni = 0; ni < 3; ++ni)
+        acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[mi], f[MB + ni], acc[mi][ni], 0, 0, 0);
+    issue_fence();
+  };
+  // One stage, its first fragments already read: before its last nine products the wavefronts meet, all done with `buf`
+  // and the next stage arrived (the twelve loads of the one after may be on their way); `buf` is filled three stages ahead.
+  auto stage = [&](int st, uint4* buf, const uint4* next) __attribute__((always_inline)) {
+    // the fragments asked for a group of products ago are waited for before the next ones are asked for
 #pragma unroll
-          for (int mi = 0; mi < 2; ++mi) {
-            const uint4 t = Abuf[cur * kG2M * kG2Chunks + g2_slot(wm * 64 + mi * 32 + frow, kk * 2 + fch)];
-            __builtin_memcpy(&fa[mi], &t, 16);
-          }
-#pragma unroll
-          for (int ni = 0; ni < 3; ++ni) {
-            const uint4 t = Bbuf[cur * kG2N * kG2Chunks + g2_slot(wn * 96 + ni * 32 + frow, kk * 2 + fch)];
-            __builtin_memcpy(&fb[ni], &t, 16);
-          }
-#pragma unroll
-          for (int mi = 0; mi < 2; ++mi)
-#pragma unroll
-            for (int ni = 0; ni < 3; ++ni)
-              acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[mi], fb[ni], acc[mi][ni], 0, 0, 0);
-        }
-        if (it + 1 < n_st) {
-          stash((sl + 1) % kGStages, cur ^ 1, it + 1);  // the other buffer was last read before the previous barrier
-          __syncthreads();
-          cur ^= 1;
-        }
+    for (int kk = 0; kk < 3; ++kk) {
+      __builtin_amdgcn_s_waitcnt(0xc07f);                    // lgkmcnt(0)
+      read(buf, kk + 1, fr[(kk + 1) & 1]);
+      issue_fence();
+      multiply(fr[kk & 1]);
+    }
+    __builtin_amdgcn_s_waitcnt(0x0070 | (kBufs - 2) * kLoads);   // lgkmcnt(0), vmcnt: all but the loads of the stage after the next
+    asm volatile("s_barrier" ::: "memory");
+    read(next, 0, fr[0]);
+    issue_fence();
+    fetch(st + kBufs, buf);
+    multiply(fr[1]);
+  };
+  if (n_st > 0) {                                           // uniform over the workgroup
+    issue_fence();
+    fetch(0, buf0);
+    fetch(1, buf1);
+    if (kBufs == 3) fetch(2, buf2);
+    __builtin_amdgcn_s_waitcnt(kBufs == 3 ? 0x4070 | (2 * kLoads & 15) : 0x0070 | kLoads);   // vmcnt: all but the later stages' loads
+    asm volatile("s_barrier" ::: "memory");
+    read(buf0, 0, fr[0]);
+    int st = 0;
+    // Whole turns of the buffers with no way out in between: the compiler would wait for every load at the loop's head.
+    if (kBufs == 3) {
+      for (; st + 2 < n_st; st += 3) {
+        stage(st, buf0, buf1);
+        stage(st + 1, buf1, buf2);
+        stage(st + 2, buf2, buf0);
       }
+      if (st < n_st) stage(st, buf0, buf1);
+      if (st + 1 < n_st) stage(st + 1, buf1, buf2);
+    } else {
+      for (; st + 1 < n_st; st += 2) {
+        stage(st, buf0, buf1);
+        stage(st + 1, buf1, buf0);
+      }
+      if (st < n_st) stage(st, buf0, buf1);
+    }
+    __builtin_amdgcn_s_waitcnt(0x0f70);                     // vmcnt(0): nothing may arrive in LDS after the workgroup's end
+  }
+  if (n_st * kG2K < k_len) {                                // less than a stage left: chunks past the range are zeros
+    __syncthreads();
+    const bool in = n_st * kG2K + chunk + 8 <= k_len;       // Df is a multiple of 8 on this path
+    const char* at = (const char*)(xb + n_st * kG2K);
+#pragma unroll
+    for (int i = 0; i < kLoads; ++i) load(i, in ? at + src[i] : (const char*)&g_zero_chunk, buf0);
+    __builtin_amdgcn_s_waitcnt(0x0f70);                     // vmcnt(0)
+    __syncthreads();
+#pragma unroll 1
+    for (int kk = 0; kk < kG2K / 16; ++kk) {
+      read(buf0, kk, fr[0]);
+      multiply(fr[0]);
     }
   }
 
   // C block layout of the 32x32 MFMA: lane holds column lane%32; register v holds row
   // 8*(v/4) + 4*(lane/32) + v%4.
-  float* ctb = a.ct + b * a.n_disc * (int64_t)a.n_keep;
+  float* ctb = a.ct + ((int64_t)split * a.B + b) * a.n_disc * (int64_t)a.n_keep;
+  if (whole) {                                              // uniform over the workgroup
+    const int row0 = tm * kM + wm * (kM / 2), col0 = tn * kG2N + wn * 96;
+    const uint32_t at = (uint32_t)(4 * hi * a.n_keep + l32);
 #pragma unroll
-  for (int mi = 0; mi < 2; ++mi)
-#pragma unroll
-    for (int ni = 0; ni < 3; ++ni) {
-      const int col = tn * kG2N + wn * 96 + ni * 32 + lane % 32;
-      const int row0 = tm * kG2M + wm * 64 + mi * 32 + 4 * (lane / 32);
+    for (int mi = 0; mi < MB; ++mi)
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
-        const int row = row0 + 8 * (v / 4) + v % 4;
-        if (row < a.n_disc && col < a.n_keep) ctb[(int64_t)row * a.n_keep + col] = acc[mi][ni][v];
+        float* dst = ctb + (int64_t)(row0 + mi * 32 + 8 * (v / 4) + v % 4) * a.n_keep + col0;
+#pragma unroll
+        for (int ni = 0; ni < 3; ++ni) dst[at + ni * 32] = acc[mi][ni][v];
       }
-    }
+    return;
+  }
+  // an edge: zeros where a row or column is of no token, whole groups of eight rows without a check of each
+#pragma unroll
+  for (int ni = 0; ni < 3; ++ni) {
+    const int lc = wn * 96 + ni * 32 + l32, col = tn * kG2N + lc;
+    if (col >= a.n_keep) continue;
+    const bool col_ok = tok[kM + lc] >= 0;
+#pragma unroll
+    for (int mi = 0; mi < MB; ++mi)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const int lr = wm * (kM / 2) + mi * 32 + 8 * g, row = tm * kM + lr;
+        if (row >= a.n_disc) break;                         // uniform, as is the next one
+        const int4 t = *(const int4*)&tok[lr + 4 * hi];
+        float* dst = ctb + (int64_t)row * a.n_keep + (uint32_t)(4 * hi * a.n_keep + col);
+        const float c0 = col_ok && t.x >= 0 ? acc[mi][ni][4 * g] : 0.0f, c1 = col_ok && t.y >= 0 ? acc[mi][ni][4 * g + 1] : 0.0f;
+        const float c2 = col_ok && t.z >= 0 ? acc[mi][ni][4 * g + 2] : 0.0f, c3 = col_ok && t.w >= 0 ? acc[mi][ni][4 * g + 3] : 0.0f;
+        if (row + 8 <= a.n_disc) {
+          dst[0] = c0, dst[a.n_keep] = c1, dst[2 * (int64_t)a.n_keep] = c2, dst[3 * (int64_t)a.n_keep] = c3;
+        } else {
+          const int left = a.n_disc - row - 4 * hi;
+          if (left > 0) dst[0] = c0;
+          if (left > 1) dst[a.n_keep] = c1;
+          if (left > 2) dst[2 * (int64_t)a.n_keep] = c2;
+          if (left > 3) dst[3 * (int64_t)a.n_keep] = c3;
+        }
+      }
+  }
 }
 
 }  // namespace ficoco

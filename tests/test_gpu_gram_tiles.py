@@ -1,0 +1,32 @@
+"""Cosine correlation of batches whose products take the wide tiles (at least 128 tiles of 192 x 192, or of 256 x 192
+where those are one round of workgroups instead of two): rows and columns that fill a tile, miss it by one and pass it
+by one, and feature counts of less than a stage of 64, whole stages (one to five, three or two of them in flight) and
+stages with a remainder."""
+import pytest
+
+from paper_2411_17686_amd import ficoco as fc
+from paper_2411_17686_amd import synth
+from tests import parity as P
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    c = fc.Context(0)
+    yield c
+    c.close()
+
+
+# images, side of the grid, kept tokens (the others are the rows of the product), features
+CASES = [(128, 15, 33, 8), (128, 15, 34, 72), (64, 15, 32, 136), (33, 20, 193, 200), (32, 20, 192, 256), (128, 15, 33, 320),
+         (129, 17, 33, 64), (129, 17, 34, 192), (130, 17, 35, 328), (150, 16, 40, 24), (65, 21, 193, 128)]
+
+
+@pytest.mark.parametrize("B,grid,n_keep,D", CASES)
+def test_wide_tiles(ctx, B, grid, n_keep, D):
+    cfg = synth.ficoco_v_single(seed=900 + D + n_keep, B=B, grid=grid, D=D, H=1, centres=7, dtype="bf16", n_keep=n_keep)
+    kw = dict(red_src=fc.R_ATTN_RECV, sem_src=fc.G_CLS_ATTN, corr_src=fc.C_COSINE)
+    out, _ = P.run_v(cfg, cfg["A"], ctx=ctx, k_max=16, **kw)
+    for b in (0, B // 2, B - 1):
+        P.compare_image(out, b, P.oracle_v(cfg, cfg["A"], b, **kw), "bf16", cfg["vis_begin"], False)
