@@ -353,11 +353,11 @@ constexpr int kCorrSteps = 2;   // 512-feature steps of the exact dot products l
 // (all lanes return the values).  The loads of all CB rows are issued before the first use, so
 // a batch costs one memory round trip per 512 features instead of one per target.  Per target
 // the arithmetic and its order are those of corr_value_wave.
-template <int CB>
+template <int CB, int MODE>
 __device__ __forceinline__ void corr_values_wave(const CorrArgs& a, int64_t b, int i, const int (&j)[CB], int lane,
                                                  double (&out)[CB]) {
   double direct[CB];
-  if (a.mode == kAttnL) {
+  if (MODE == kAttnL) {
 #pragma unroll
     for (int q = 0; q < CB; ++q) direct[q] = (double)a.abar[(b * a.N + i) * a.map_pitch + j[q]];
   } else {
@@ -404,7 +404,7 @@ __device__ __forceinline__ void corr_values_wave(const CorrArgs& a, int64_t b, i
       direct[q] = t > 0.0 ? t : 0.0;
     }
   }
-  if (a.mode == kCosV) {
+  if (MODE == kCosV) {
 #pragma unroll
     for (int q = 0; q < CB; ++q) out[q] = direct[q];
     return;
@@ -434,9 +434,14 @@ constexpr int kCandBatch = 4;                    // targets evaluated exactly at
 // Rows whose targets are clear from the approximate values skip the exact dot products (K = 1) or take
 // them of the K targets only, and the largest values are kept by medians: 31.6 -> 18.1 us at 8 x 432 rows
 // of 144 targets and 4096 features (K = 1), 32.5 -> 27.4 us at 8064 rows of 1152 (K = 3, 1024 features).
-// Compiled for four wavefronts per SIMD (128 registers; it would take 132): the decoder shape has
+// One instance per correlation: with the mode a run-time value it held 127 registers, spilled two and turned
+// the scalars over vector registers.  That, no threshold where the targets are known, masks in the row's last step
+// only and the text rows of the bound asked for ahead of the row (1353 -> 1098 vector instructions per row of 1152):
+// 28.2 -> 25.2 us at 8064 rows of 1152, 18.5 -> 17.6 at 8 x 432 rows of 144, 12.1 -> 10.5 on the map's rows.  Exact
+// products of three targets where three are left, not four with one of them twice: 25.0, left out.
+// Compiled for four wavefronts per SIMD (128 registers): the decoder shape has
 // 3456 discarded rows, one wavefront each, and the chip holds 3072 of them at three per SIMD.
-template <int MC>   // lower bounds kept per lane (>= sel_m: one lane may hold the m largest of the row)
+template <int MC, int MODE>   // MC: lower bounds kept per lane (>= sel_m: one lane may hold the m largest of the row)
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void corr_cand_rows_kernel(CorrArgs a) {
   __shared__ int cand_j[4][kCandCap];
   const int lane = threadIdx.x % kWave, wv = threadIdx.x / kWave;
@@ -452,16 +457,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void c
   }
   // approximate direct term of the row: the matrix-core cosines, or (FiCoCo-L with the
   // attention correlation) the token's row of the exact head-mean map, delta = 0
-  const bool from_map = a.mode == kAttnL;
+  constexpr bool from_map = MODE == kAttnL;
   const float* ct = from_map ? a.abar + (b * a.N + i) * a.map_pitch : a.ct + (b * a.n_disc + row) * n;
-  const bool L = a.mode == kCosL || a.mode == kAttnL;
+  constexpr bool L = MODE == kCosL || MODE == kAttnL;
   const float gam = L ? (float)a.gamma : 1.0f;
-  float extra = 0.0f;                      // upper bound of (1 - gamma) * indirect term of this row
-  if (L) {
-    double bd = 0.0;
-    for (int k = lane; k < a.M; k += kWave) bd += a.ttext[(b * a.N + i) * a.M + k] * a.cmax[b * a.M + k];
-    bd = wave_sum_f64(bd) * a.invM * (1.0 - a.gamma);
-    extra = (float)bd * 1.000001f + 1e-30f;   // rounded up
+  double bd = 0.0, bd_max = 0.0;           // first text rows of the indirect term's bound: asked for ahead of the row itself
+  if (L && lane < a.M) {
+    bd = a.ttext[(b * a.N + i) * a.M + lane];
+    bd_max = a.cmax[b * a.M + lane];
   }
   const float delta = from_map ? 0.0f : a.delta;
   const float NEGF = -__builtin_huge_valf();
@@ -527,7 +530,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void c
 #pragma unroll
       for (int u = 0; u < kCandKeep; ++u) {
         if (c0 + u * kWave >= n) break;         // uniform: no reader looks at slots past the row
-        if (c0 + u * kWave + lane >= n) val[u] = NEGF;
+        if (c0 + (u + 1) * kWave > n) val[u] = c0 + u * kWave + lane < n ? val[u] : NEGF;   // (uniform: the row's last step)
       }
     }
   };
@@ -544,8 +547,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void c
       if (c0 + u * kWave >= n) break;           // uniform: slots past the row hold nothing
 #pragma unroll
       for (int k = MC - 1; k > 0; --k) top[k] = __builtin_amdgcn_fmed3f(top[k - 1], top[k], val[u]);
-      top[0] = fmaxf(top[0], val[u]);
+      top[0] = __builtin_amdgcn_fmed3f(top[0], val[u], __builtin_huge_valf());   // the larger one
     }
+  }
+  float extra = 0.0f;                      // upper bound of (1 - gamma) * indirect term of this row
+  if (L) {
+    bd *= bd_max;
+    for (int k = lane + kWave; k < a.M; k += kWave) bd += a.ttext[(b * a.N + i) * a.M + k] * a.cmax[b * a.M + k];
+    bd = wave_sum_f64(bd) * a.invM * (1.0 - a.gamma);
+    extra = (float)bd * 1.000001f + 1e-30f;   // rounded up
   }
   auto lower = [&](float v) { return v == NEGF ? NEGF : gam * fmaxf(v - delta, 0.0f); };     // (grows with v)
   float lambda = NEGF, lambda_k = NEGF;
@@ -617,7 +627,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void c
       j[q] = ok[q] ? jq : i;                   // a valid row to read; the value is dropped
     }
     double v[kCandBatch];
-    corr_values_wave<kCandBatch>(a, b, i, j, lane, v);
+    corr_values_wave<kCandBatch, MODE>(a, b, i, j, lane, v);
 #pragma unroll
     for (int q = 0; q < kCandBatch; ++q)
       if (lane == c + q && c + q < n_cand) myv = ok[q] ? v[q] : NEG;
@@ -625,7 +635,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void c
   // v[f], v[f+1] = m-th and (m-1)-th largest of the exact candidate values
   double v_f = NEG, v_f1 = NEG;
   int n_gt = 0;
-  {
+  if (!known) {                    // uniform; (known targets need no threshold)
     double act = myv;
     for (int r = 0; r < a.sel_m; ++r) {
       const double mx = wave_max(act);
@@ -884,10 +894,11 @@ __global__ void zero_i32_kernel(int32_t* p, int n) {
   if (i < n) p[i] = 0;
 }
 
+template <int MODE>
 static void launch_cand_rows(int sel_m, dim3 grid, dim3 block, hipStream_t s, const CorrArgs& a) {
-  if (sel_m <= 2) hipLaunchKernelGGL(corr_cand_rows_kernel<2>, grid, block, 0, s, a);
-  else if (sel_m <= 4) hipLaunchKernelGGL(corr_cand_rows_kernel<4>, grid, block, 0, s, a);
-  else hipLaunchKernelGGL(corr_cand_rows_kernel<8>, grid, block, 0, s, a);
+  if (sel_m <= 2) hipLaunchKernelGGL((corr_cand_rows_kernel<2, MODE>), grid, block, 0, s, a);
+  else if (sel_m <= 4) hipLaunchKernelGGL((corr_cand_rows_kernel<4, MODE>), grid, block, 0, s, a);
+  else hipLaunchKernelGGL((corr_cand_rows_kernel<8, MODE>), grid, block, 0, s, a);
 }
 
 void launch_correlate(const ficoco_problem& p, const Plan& pl, char* ws, const int32_t* discard_idx,
@@ -958,7 +969,7 @@ void launch_correlate(const ficoco_problem& p, const Plan& pl, char* ws, const i
   }
   if (a.mode == kAttnL && !pl.dense_rows && p.k_max <= 64) {
     if (need_colmax) hipLaunchKernelGGL(text_colmax_kernel, dim3((p.M + 63) / 64, p.B), dim3(256), 0, s, a);
-    launch_cand_rows(pl.sel_m, grid, block, s, a);
+    launch_cand_rows<kAttnL>(pl.sel_m, grid, block, s, a);
     return;
   }
   if (pl.use_gram) {
@@ -982,7 +993,8 @@ void launch_correlate(const ficoco_problem& p, const Plan& pl, char* ws, const i
     }
     if (gram_stop) (void)hipEventRecord(gram_stop, s);
     if (L && need_colmax) hipLaunchKernelGGL(text_colmax_kernel, dim3((p.M + 63) / 64, p.B), dim3(256), 0, s, a);
-    launch_cand_rows(pl.sel_m, grid, block, s, a);
+    if (L) launch_cand_rows<kCosL>(pl.sel_m, grid, block, s, a);
+    else launch_cand_rows<kCosV>(pl.sel_m, grid, block, s, a);
     return;
   }
   if (pl.dense_rows) hipLaunchKernelGGL(corr_fill_rows_kernel, grid, block, 0, s, a);
