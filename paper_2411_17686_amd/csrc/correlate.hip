@@ -975,20 +975,27 @@ void launch_correlate(const ficoco_problem& p, const Plan& pl, char* ws, const i
   if (pl.use_gram) {
     GramArgs g{a.xhat, p.B, p.N, pl.Df, pl.n_disc, p.n_keep, discard_idx, keep_idx, a.ct, pl.gram_splits, pl.gram_st_per_split};
     const int tiles = pl.gram_splits * p.B * ((pl.n_disc + kGT - 1) / kGT) * ((p.n_keep + kGT - 1) / kGT);
-    // Large blocks (one K range, enough 192 x 192 tiles for most of the chip): the wide-tile forms.  One workgroup takes a
+    // Large blocks (one K range, enough 192 x 192 tiles for half the chip): the wide-tile forms.  One workgroup takes a
     // compute unit to itself, so it is rounds of 256 tiles that count: the taller tile where that saves more than its height
     // costs.  us with 192 / 256 rows: 8064 x 1152 28 / 36 (252 tiles, one round either way), 10368 x 1152 45 / 35.5
     // (324 and 246 tiles), 36 images of 768 x 384 44 / 32.5 (288 and 216), 44 of them 49 / 55 (352 and 264: two rounds each).
     // Against the 128 x 128 tiles: 8064 x 1152 40, 16 images of 768 x 384 with 384 features 14.9 (here 14.4), 12 of them the same.
+    // With several K ranges: where their wide tiles are one round that fills half the chip or more and at most an eighth of them
+    // is padding.  us with 128 x 128 / 192 x 192 tiles: 16 images of 768 x 384 with 1024 features 24.5 / 20.2, with 4096 82 / 58;
+    // 8 of them 17.2 / 16.0, 4 of them 13.3 / 13.3; 64 of 384 x 192 24.5 / 22.0; 8 with 4096 features 18.4 / 16.6.  Two rounds: 6048 x 864
+    // 25 / 33; padding: 8 images of 432 x 144 with 4096 features 19.0 / 21.4, one of 2240 x 640 (a fifth) 14.1 / 16.3.
     auto tiles2 = [&](int rows) { return p.B * ((pl.n_disc + rows - 1) / rows) * ((p.n_keep + kG2N - 1) / kG2N); };
     auto rounds = [](int t) { return (t + 255) / 256; };
-    const bool wide = pl.gram_splits == 1 && tiles2(192) >= 128 && (int64_t)p.N * pl.Df * sizeof(bf16_t) < (int64_t(1) << 32);
-    const bool tall = 4 * rounds(tiles2(256)) < 3 * rounds(tiles2(192));
+    const int wide_wgs = pl.gram_splits * tiles2(192);
+    const bool fits = wide_wgs <= 256 && (int64_t)tiles2(192) * (192 * kG2N * 7 / 8) <= (int64_t)p.B * pl.n_disc * p.n_keep;
+    const bool wide = wide_wgs >= 128 && (pl.gram_splits == 1 || fits) &&
+                      (int64_t)p.N * pl.Df * sizeof(bf16_t) < (int64_t(1) << 32);
+    const bool tall = pl.gram_splits == 1 && 4 * rounds(tiles2(256)) < 3 * rounds(tiles2(192));
     if (gram_start) (void)hipEventRecord(gram_start, s);
     // gram_repeat > 1 (measurement only): the same launch again and again between the two events
     for (int rep = 0; rep < gram_repeat; ++rep) {
       if (wide && tall) hipLaunchKernelGGL(gram_tile2_kernel<4>, dim3(xcd_padded_total(tiles2(256))), dim3(kG2Threads), 0, s, g);
-      else if (wide) hipLaunchKernelGGL(gram_tile2_kernel<3>, dim3(xcd_padded_total(tiles2(192))), dim3(kG2Threads), 0, s, g);
+      else if (wide) hipLaunchKernelGGL(gram_tile2_kernel<3>, dim3(xcd_padded_total(wide_wgs)), dim3(kG2Threads), 0, s, g);
       else hipLaunchKernelGGL(gram_tile_kernel, dim3(xcd_padded_total(tiles)), dim3(256), 0, s, g);
     }
     if (gram_stop) (void)hipEventRecord(gram_stop, s);

@@ -19,8 +19,10 @@ def ctx():
 
 
 # images, side of the grid, kept tokens (the others are the rows of the product), features
-CASES = [(128, 15, 33, 8), (128, 15, 34, 72), (64, 15, 32, 136), (33, 20, 193, 200), (32, 20, 192, 256), (128, 15, 33, 320),
-         (129, 17, 33, 64), (129, 17, 34, 192), (130, 17, 35, 328), (150, 16, 40, 24), (65, 21, 193, 128)]
+CASES = [(128, 15, 33, 8), (128, 15, 34, 72), (64, 15, 32, 136), (33, 20, 193, 200), (64, 20, 190, 256), (128, 15, 33, 320),
+         (129, 17, 33, 64), (129, 17, 34, 192), (130, 17, 35, 328), (150, 16, 40, 24), (65, 21, 193, 128),
+         # several K ranges: 288 and 232 features, 416 and 360, eight of which the last has 40
+         (64, 19, 169, 520), (64, 19, 170, 776), (16, 19, 169, 2056), (24, 24, 192, 1032)]
 
 
 @pytest.mark.parametrize("B,grid,n_keep,D", CASES)
