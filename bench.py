@@ -481,7 +481,7 @@ def main():
         # 2 * d_head matrix-core flops; the vector operations are what the kernel waits for.
         algo = 7.0 * W["qk_elements"]
         achieved = algo / (alone_ms * 1e-3) / 1e12
-        roof = {"kernel": "qk_norm_kernel + qk_mean_kernel (softmax(QK^T) on bf16 MFMA 16x16x32, reduced on the fly)", "bound": "alu",
+        roof = {"kernel": "qk_norm_kernel + qk_mean_kernel (softmax(QK^T) on bf16 MFMA, reduced on the fly)", "bound": "alu",
                 "achieved": achieved, "peak": 157.3, "unit": "TFLOP/s", "frac": achieved / 157.3, "traffic": None,
                 "algorithmic_flops": algo, "mfma_flops": 2.0 * W["d_head"] * W["qk_elements"],
                 "hbm_bytes_algorithmic": W["qk_bytes"],
@@ -500,7 +500,7 @@ def main():
     else:
         algo = W["gram_flops"]
         achieved = algo / (alone_ms * 1e-3) / 1e12
-        gram_name = "gram_tile2_kernel" if args.config == "4" else "gram_tile_kernel"    # wide tiles from 128 blocks up
+        gram_name = "gram_tile2_kernel" if args.config in ("4", "1c") else "gram_tile_kernel"    # wide tiles: 128 workgroups or more
         roof = {"kernel": gram_name + " (bf16 MFMA 32x32x16)", "bound": "mfma", "achieved": achieved,
                 "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": achieved / MFMA_BF16_PEAK_TFLOPS,
                 "traffic": None, "algorithmic_flops": algo}
