@@ -63,6 +63,22 @@ def build_c_caller(verbose=True):
     return out
 
 
+def build_plan_hook(verbose=True):
+    """The tests' view of a problem's plan (tests/c_abi/plan_hook.cpp) as a shared object, with hipcc."""
+    root = os.path.dirname(HERE)
+    src = os.path.join(root, "tests", "c_abi", "plan_hook.cpp")
+    out = os.path.join(root, "tests", "c_abi", "libplan_hook.so")
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    log = subprocess.run([hipcc] + FLAGS + ["-x", "hip", src, "-x", "none", LIB, "-Wl,-rpath," + HERE, "-o", out],
+                         stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if log.returncode != 0:
+        raise RuntimeError("hipcc failed on plan_hook.cpp:\n" + log.stdout)
+    if verbose:
+        print("built", out)
+    return out
+
+
 if __name__ == "__main__":
     build()
     build_c_caller()
+    build_plan_hook()

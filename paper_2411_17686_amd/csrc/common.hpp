@@ -131,6 +131,15 @@ void launch_correlate(const ficoco_problem& p, const Plan& pl, char* ws, const i
                       const int32_t* keep_idx, int32_t* edge_cnt, int32_t* edge_tgt,
                       double* edge_alpha, int32_t* overflow, bool fused,
                       hipEvent_t gram_start, hipEvent_t gram_stop, hipStream_t s, int gram_repeat = 1);
+// The tiles that the block of approximate cosines is cut into (Plan::use_gram): 128 x 128, 192 x 192 or 256 x 192.
+enum GramForm { kGramSquare, kGramWide, kGramTall };
+GramForm gram_form(const ficoco_problem& p, const Plan& pl);
+// Bound of their error.  Every step of an accumulation adds at most 2^-22 of the sum of its terms' magnitudes; the
+// magnitudes of all K ranges together add up to at most |x||y|, so the length that counts is that of one range.
+inline float gram_delta(const Plan& pl) {
+  const int len = pl.gram_st_per_split * kGramStage;
+  return (float)((len < pl.Df ? len : pl.Df) + 4 * pl.gram_splits) * 2.384185791015625e-07f;
+}
 void launch_gather(const ficoco_problem& p, const Plan& pl, const int32_t* keep_idx, const void* in,
                    int64_t sb, int64_t sn, int row_bytes, void* out, hipStream_t s);
 void launch_corr_gap(const ficoco_problem& p, const Plan& pl, char* ws, const int32_t* discard_idx,

@@ -901,6 +901,25 @@ static void launch_cand_rows(int sel_m, dim3 grid, dim3 block, hipStream_t s, co
   else hipLaunchKernelGGL((corr_cand_rows_kernel<8, MODE>), grid, block, 0, s, a);
 }
 
+GramForm gram_form(const ficoco_problem& p, const Plan& pl) {
+  // Large blocks (one K range, enough 192 x 192 tiles for half the chip): the wide-tile forms.  One workgroup takes a
+  // compute unit to itself, so it is rounds of 256 tiles that count: the taller tile where that saves more than its height
+  // costs.  us with 192 / 256 rows: 8064 x 1152 28 / 36 (252 tiles, one round either way), 10368 x 1152 45 / 35.5
+  // (324 and 246 tiles), 36 images of 768 x 384 44 / 32.5 (288 and 216), 44 of them 49 / 55 (352 and 264: two rounds each).
+  // Against the 128 x 128 tiles: 8064 x 1152 40, 16 images of 768 x 384 with 384 features 14.9 (here 14.4), 12 of them the same.
+  // With several K ranges: where their wide tiles are one round that fills half the chip or more and at most an eighth of them
+  // is padding.  us with 128 x 128 / 192 x 192 tiles: 16 images of 768 x 384 with 1024 features 24.5 / 20.2, with 4096 82 / 58;
+  // 8 of them 17.2 / 16.0, 4 of them 13.3 / 13.3; 64 of 384 x 192 24.5 / 22.0; 8 with 4096 features 18.4 / 16.6.  Two rounds: 6048 x 864
+  // 25 / 33; padding: 8 images of 432 x 144 with 4096 features 19.0 / 21.4, one of 2240 x 640 (a fifth) 14.1 / 16.3.
+  auto tiles2 = [&](int rows) { return p.B * ((pl.n_disc + rows - 1) / rows) * ((p.n_keep + kG2N - 1) / kG2N); };
+  auto rounds = [](int t) { return (t + 255) / 256; };
+  const int wide_wgs = pl.gram_splits * tiles2(192);
+  const bool fits = wide_wgs <= 256 && (int64_t)tiles2(192) * (192 * kG2N * 7 / 8) <= (int64_t)p.B * pl.n_disc * p.n_keep;
+  if (wide_wgs < 128 || (pl.gram_splits > 1 && !fits) || (int64_t)p.N * pl.Df * sizeof(bf16_t) >= (int64_t(1) << 32))
+    return kGramSquare;
+  return pl.gram_splits == 1 && 4 * rounds(tiles2(256)) < 3 * rounds(tiles2(192)) ? kGramTall : kGramWide;
+}
+
 void launch_correlate(const ficoco_problem& p, const Plan& pl, char* ws, const int32_t* discard_idx,
                       const int32_t* keep_idx, int32_t* edge_cnt, int32_t* edge_tgt,
                       double* edge_alpha, int32_t* overflow, bool fused,
@@ -936,9 +955,7 @@ void launch_correlate(const ficoco_problem& p, const Plan& pl, char* ws, const i
   a.cmax = (double*)(ws + pl.cmax);
   a.fixed_k = pl.fixed_k;
   a.ct_splits = pl.gram_splits;
-  // Every step of an accumulation adds at most 2^-22 of the sum of its terms' magnitudes; the magnitudes of
-  // all K ranges together add up to at most |x||y|, so the length that counts is that of one range.
-  a.delta = (float)(std::min(pl.Df, pl.gram_st_per_split * kGramStage) + 4 * pl.gram_splits) * 2.384185791015625e-07f;
+  a.delta = gram_delta(pl);
   // J_i is the top_k largest values where the next one is clear of them: the threshold lies strictly
   // between v[f] and v[f+1] (g well inside (0, 1)), or at v[f] itself (g = 0, fixed K)
   a.top_k = pl.sel_g == 0.0 ? pl.sel_m : (pl.sel_g > 1e-6 && pl.sel_g < 1.0 - 1e-6) ? pl.sel_m - 1 : 0;
@@ -974,29 +991,14 @@ void launch_correlate(const ficoco_problem& p, const Plan& pl, char* ws, const i
   }
   if (pl.use_gram) {
     GramArgs g{a.xhat, p.B, p.N, pl.Df, pl.n_disc, p.n_keep, discard_idx, keep_idx, a.ct, pl.gram_splits, pl.gram_st_per_split};
-    const int tiles = pl.gram_splits * p.B * ((pl.n_disc + kGT - 1) / kGT) * ((p.n_keep + kGT - 1) / kGT);
-    // Large blocks (one K range, enough 192 x 192 tiles for half the chip): the wide-tile forms.  One workgroup takes a
-    // compute unit to itself, so it is rounds of 256 tiles that count: the taller tile where that saves more than its height
-    // costs.  us with 192 / 256 rows: 8064 x 1152 28 / 36 (252 tiles, one round either way), 10368 x 1152 45 / 35.5
-    // (324 and 246 tiles), 36 images of 768 x 384 44 / 32.5 (288 and 216), 44 of them 49 / 55 (352 and 264: two rounds each).
-    // Against the 128 x 128 tiles: 8064 x 1152 40, 16 images of 768 x 384 with 384 features 14.9 (here 14.4), 12 of them the same.
-    // With several K ranges: where their wide tiles are one round that fills half the chip or more and at most an eighth of them
-    // is padding.  us with 128 x 128 / 192 x 192 tiles: 16 images of 768 x 384 with 1024 features 24.5 / 20.2, with 4096 82 / 58;
-    // 8 of them 17.2 / 16.0, 4 of them 13.3 / 13.3; 64 of 384 x 192 24.5 / 22.0; 8 with 4096 features 18.4 / 16.6.  Two rounds: 6048 x 864
-    // 25 / 33; padding: 8 images of 432 x 144 with 4096 features 19.0 / 21.4, one of 2240 x 640 (a fifth) 14.1 / 16.3.
-    auto tiles2 = [&](int rows) { return p.B * ((pl.n_disc + rows - 1) / rows) * ((p.n_keep + kG2N - 1) / kG2N); };
-    auto rounds = [](int t) { return (t + 255) / 256; };
-    const int wide_wgs = pl.gram_splits * tiles2(192);
-    const bool fits = wide_wgs <= 256 && (int64_t)tiles2(192) * (192 * kG2N * 7 / 8) <= (int64_t)p.B * pl.n_disc * p.n_keep;
-    const bool wide = wide_wgs >= 128 && (pl.gram_splits == 1 || fits) &&
-                      (int64_t)p.N * pl.Df * sizeof(bf16_t) < (int64_t(1) << 32);
-    const bool tall = pl.gram_splits == 1 && 4 * rounds(tiles2(256)) < 3 * rounds(tiles2(192));
+    auto tiles = [&](int rows, int cols) { return pl.gram_splits * p.B * ((pl.n_disc + rows - 1) / rows) * ((p.n_keep + cols - 1) / cols); };
+    const GramForm form = gram_form(p, pl);
     if (gram_start) (void)hipEventRecord(gram_start, s);
     // gram_repeat > 1 (measurement only): the same launch again and again between the two events
     for (int rep = 0; rep < gram_repeat; ++rep) {
-      if (wide && tall) hipLaunchKernelGGL(gram_tile2_kernel<4>, dim3(xcd_padded_total(tiles2(256))), dim3(kG2Threads), 0, s, g);
-      else if (wide) hipLaunchKernelGGL(gram_tile2_kernel<3>, dim3(xcd_padded_total(wide_wgs)), dim3(kG2Threads), 0, s, g);
-      else hipLaunchKernelGGL(gram_tile_kernel, dim3(xcd_padded_total(tiles)), dim3(256), 0, s, g);
+      if (form == kGramTall) hipLaunchKernelGGL(gram_tile2_kernel<4>, dim3(xcd_padded_total(tiles(256, kG2N))), dim3(kG2Threads), 0, s, g);
+      else if (form == kGramWide) hipLaunchKernelGGL(gram_tile2_kernel<3>, dim3(xcd_padded_total(tiles(192, kG2N))), dim3(kG2Threads), 0, s, g);
+      else hipLaunchKernelGGL(gram_tile_kernel, dim3(xcd_padded_total(tiles(kGT, kGT))), dim3(256), 0, s, g);
     }
     if (gram_stop) (void)hipEventRecord(gram_stop, s);
     if (L && need_colmax) hipLaunchKernelGGL(text_colmax_kernel, dim3((p.M + 63) / 64, p.B), dim3(256), 0, s, a);

@@ -1,0 +1,19 @@
+"""ctypes view of tests/c_abi/plan_hook.cpp: how the library lays out and cuts the block of approximate cosines."""
+import ctypes as C
+import os
+
+_SO = os.path.join(os.path.dirname(os.path.abspath(__file__)), "c_abi", "libplan_hook.so")
+SQUARE, WIDE, TALL = 0, 1, 2            # tiles of 128 x 128, 192 x 192, 256 x 192
+
+
+class GramPlan(C.Structure):
+    _fields_ = [("ct", C.c_int64), ("xhat", C.c_int64), ("use_gram", C.c_int32), ("splits", C.c_int32),
+                ("st_per_split", C.c_int32), ("form", C.c_int32), ("Df", C.c_int32), ("delta", C.c_float)]
+
+
+def gram_plan(p):
+    assert os.path.exists(_SO), "tests/c_abi/libplan_hook.so is not built: run `python -m paper_2411_17686_amd.build`"
+    g = GramPlan()
+    rc = C.CDLL(_SO).plan_hook_gram(C.byref(p), C.byref(g))
+    assert rc == 0, rc
+    return g

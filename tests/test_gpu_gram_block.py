@@ -1,0 +1,112 @@
+"""The block of approximate cosines itself, read out of the workspace, for every form of its tiles.
+
+The block only proposes candidates: whatever it holds, a step decides by exact values, and with small enough values
+in it (zeros, say) every target is a candidate and the outputs are right all the same.  So the outputs do not
+show a wrong block; here all its values are compared with products of the same unit rows in double precision, within the
+error that the readers of the block allow for."""
+import pytest
+import torch
+
+from paper_2411_17686_amd import ficoco as fc
+from tests import plan_hook as H
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    c = fc.Context(0)
+    yield c
+    c.close()
+
+
+def _problem(B, n_disc, n_keep, D, M=0):
+    """Unit rows of mixed directions; FiCoCo-L with M text queries, else FiCoCo-V from score vectors."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(B + n_disc + n_keep + D + M)
+    N = n_disc + n_keep
+    X = torch.randn(B, N + M, D, device="cuda", generator=g)
+    X += 2.0 * X[:, :1] * torch.rand(B, N + M, 1, device="cuda", generator=g)
+    X = X.to(torch.bfloat16)
+    if M:
+        At = torch.softmax(torch.randn(B, 1, M, N, device="cuda", generator=g), -1).to(torch.bfloat16)
+        p = fc.make_problem(X, variant=fc.VARIANT_L, vis_begin=0, N=N, n_keep=n_keep, A_text=At, at_k_begin=0, window=0,
+                            sem_src=fc.G_TEXT_ATTN, red_src=fc.R_SIM_MEAN, corr_src=fc.C_COSINE)
+        alive = (X, At)
+    else:
+        v = [torch.softmax(torch.randn(B, 1, N, device="cuda", generator=g), -1).to(torch.bfloat16) for _ in range(2)]
+        p = fc.make_problem(X, variant=fc.VARIANT_V, vis_begin=0, N=N, n_keep=n_keep, recv_vec=v[0], sem_vec=v[1], window=0,
+                            red_src=fc.R_VECTOR, sem_src=fc.G_VECTOR, corr_src=fc.C_COSINE)
+        alive = (X, v)
+    buf = fc.Buffers(p, "cuda", X.dtype)
+    buf.ws.fill_(0xFF)                      # not-a-numbers wherever the step writes nothing
+    return p, buf, alive
+
+
+def _check(p, buf, plan, S, T):
+    """ct[b][a][j] against x[S[b][a]] . x[T[b][j]]; zero where an index is of no token."""
+    B, N, nd, nk, D = p.B, p.N, S.shape[1], T.shape[1], plan.Df
+    at = buf.ws_ptr - buf.ws.data_ptr()
+    ct = buf.ws[at + plan.ct:at + plan.ct + 4 * plan.splits * B * nd * nk].view(torch.float32).view(plan.splits, B, nd, nk)
+    xh = buf.ws[at + plan.xhat:at + plan.xhat + 2 * B * N * D].view(torch.bfloat16).view(B, N, D)
+    largest = 0.0
+    for b0 in range(0, B, 16):
+        s, t = S[b0:b0 + 16].long(), T[b0:b0 + 16].long()
+        x = xh[b0:b0 + 16].double()
+
+        def rows(i):
+            ok = (i >= 0) & (i < N)
+            r = torch.gather(x, 1, torch.where(ok, i, 0)[..., None].expand(-1, -1, D))
+            return r * ok[..., None]
+
+        want = torch.bmm(rows(s), rows(t).transpose(1, 2).contiguous())
+        err = (ct[:, b0:b0 + 16].double().sum(0) - want).abs()
+        assert not torch.isnan(err).any(), "values that were not written"
+        assert float(err.max()) <= plan.delta, (b0, float(err.max()), plan.delta)
+        bad = ((s < 0) | (s >= N))[..., None] | ((t < 0) | (t >= N))[:, None]
+        assert (ct[:, b0:b0 + 16].abs().sum(0)[bad] == 0).all()
+        largest = max(largest, float(want.abs().max()))
+    assert largest > 100 * plan.delta       # a block of zeros would not pass
+
+
+# images, discarded, kept tokens, features, text queries, form
+CASES = [
+    # 128 x 128: less than a stage of 32, whole stages, a remainder; several K ranges, the last one shorter
+    (3, 127, 129, 8, 0, H.SQUARE), (2, 128, 256, 64, 0, H.SQUARE), (2, 257, 40, 136, 5, H.SQUARE), (1, 300, 200, 1064, 0, H.SQUARE),
+    # 192 x 192: features in the remainder alone (8, 24), one stage of 64, two, three, whole turns of the buffers and what is left
+    (128, 192, 192, 8, 0, H.WIDE), (128, 193, 191, 24, 0, H.WIDE), (128, 191, 192, 64, 0, H.WIDE), (64, 384, 193, 128, 3, H.WIDE),
+    (128, 100, 180, 192, 0, H.WIDE), (128, 192, 185, 328, 0, H.WIDE), (32, 380, 384, 392, 9, H.WIDE), (1, 3000, 1600, 504, 0, H.WIDE),
+    # several K ranges: 288 and 232 features; eight of which the last has 40
+    (64, 191, 192, 520, 0, H.WIDE), (16, 190, 192, 2056, 4, H.WIDE),
+    # 256 x 192: whole and edge tiles in one launch, the same feature counts
+    (150, 256, 192, 24, 0, H.TALL), (86, 500, 193, 200, 6, H.TALL), (86, 512, 384, 64, 0, H.TALL), (260, 255, 40, 136, 0, H.TALL),
+    (1, 6216, 3000, 320, 0, H.TALL), (86, 512, 300, 520, 0, H.TALL),
+]
+
+
+@pytest.mark.parametrize("B,n_disc,n_keep,D,M,form", CASES)
+def test_block_of_every_form(ctx, B, n_disc, n_keep, D, M, form):
+    p, buf, alive = _problem(B, n_disc, n_keep, D, M)
+    plan = H.gram_plan(p)
+    assert plan.use_gram and plan.form == form
+    (fc.ficoco_l_step if M else fc.ficoco_v_step)(ctx, p, buf)
+    torch.cuda.synchronize()
+    _check(p, buf, plan, buf.discard_idx, buf.keep_idx)
+
+
+@pytest.mark.parametrize("B,n_disc,n_keep,D,M,form", [(2, 200, 150, 72, 0, H.SQUARE), (128, 192, 192, 72, 0, H.WIDE),
+                                                      (128, 100, 191, 200, 4, H.WIDE), (150, 256, 192, 72, 0, H.TALL), (86, 500, 193, 64, 0, H.TALL)])
+def test_rows_and_columns_of_no_token_are_zero(ctx, B, n_disc, n_keep, D, M, form):
+    """Index sets of the caller (staged calls), some entries outside the image."""
+    p, buf, alive = _problem(B, n_disc, n_keep, D, M)
+    plan = H.gram_plan(p)
+    assert plan.use_gram and plan.form == form
+    fc.ficoco_score(ctx, p, buf)
+    fc.ficoco_filter(ctx, p, buf)
+    for idx in (buf.discard_idx, buf.keep_idx):
+        idx[0, 0], idx[0, -1], idx[B - 1, idx.shape[1] // 2], idx[B // 2, 1] = -1, p.N, 2 ** 31 - 1, -2 ** 31
+    fc.ficoco_correlate(ctx, p, buf)
+    torch.cuda.synchronize()
+    _check(p, buf, plan, buf.discard_idx, buf.keep_idx)
+    for b, a in ((0, 0), (0, n_disc - 1), (B - 1, n_disc // 2), (B // 2, 1)):
+        assert int(buf.edge_cnt[b, a]) == 0
