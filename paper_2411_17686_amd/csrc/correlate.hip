@@ -904,8 +904,8 @@ static void launch_cand_rows(int sel_m, dim3 grid, dim3 block, hipStream_t s, co
 GramForm gram_form(const ficoco_problem& p, const Plan& pl) {
   // Large blocks (one K range, enough 192 x 192 tiles for half the chip): the wide-tile forms.  One workgroup takes a
   // compute unit to itself, so it is rounds of 256 tiles that count: the taller tile where that saves more than its height
-  // costs.  us with 192 / 256 rows: 8064 x 1152 28 / 36 (252 tiles, one round either way), 10368 x 1152 45 / 35.5
-  // (324 and 246 tiles), 36 images of 768 x 384 44 / 32.5 (288 and 216), 44 of them 49 / 55 (352 and 264: two rounds each).
+  // costs.  us with 192 / 256 rows: 8064 x 1152 28 / 36 (252 tiles, one round either way), 10368 x 1152 45 / 36.7
+  // (324 and 246 tiles), 36 images of 768 x 384 44 / 33.8 (288 and 216).
   // Against the 128 x 128 tiles: 8064 x 1152 40, 16 images of 768 x 384 with 384 features 14.9 (here 14.4), 12 of them the same.
   // With several K ranges: where their wide tiles are one round that fills half the chip or more and at most an eighth of them
   // is padding.  us with 128 x 128 / 192 x 192 tiles: 16 images of 768 x 384 with 1024 features 24.5 / 20.2, with 4096 82 / 58;
@@ -915,8 +915,9 @@ GramForm gram_form(const ficoco_problem& p, const Plan& pl) {
   auto rounds = [](int t) { return (t + 255) / 256; };
   const int wide_wgs = pl.gram_splits * tiles2(192);
   const bool fits = wide_wgs <= 256 && (int64_t)tiles2(192) * (192 * kG2N * 7 / 8) <= (int64_t)p.B * pl.n_disc * p.n_keep;
-  if (wide_wgs < 128 || (pl.gram_splits > 1 && !fits) || (int64_t)p.N * pl.Df * sizeof(bf16_t) >= (int64_t(1) << 32))
-    return kGramSquare;
+  if (wide_wgs < 128 || (pl.gram_splits > 1 && !fits)) return kGramSquare;
+  // (the 192-row tiles address the rows of an image with 32 bits, the others with 64)
+  if ((int64_t)p.N * pl.Df * sizeof(bf16_t) >= (int64_t(1) << 32)) return pl.gram_splits == 1 && tiles2(256) >= 128 ? kGramTall : kGramSquare;
   return pl.gram_splits == 1 && 4 * rounds(tiles2(256)) < 3 * rounds(tiles2(192)) ? kGramTall : kGramWide;
 }
 
@@ -996,8 +997,8 @@ void launch_correlate(const ficoco_problem& p, const Plan& pl, char* ws, const i
     if (gram_start) (void)hipEventRecord(gram_start, s);
     // gram_repeat > 1 (measurement only): the same launch again and again between the two events
     for (int rep = 0; rep < gram_repeat; ++rep) {
-      if (form == kGramTall) hipLaunchKernelGGL(gram_tile2_kernel<4>, dim3(xcd_padded_total(tiles(256, kG2N))), dim3(kG2Threads), 0, s, g);
-      else if (form == kGramWide) hipLaunchKernelGGL(gram_tile2_kernel<3>, dim3(xcd_padded_total(tiles(192, kG2N))), dim3(kG2Threads), 0, s, g);
+      if (form == kGramTall) hipLaunchKernelGGL(gram_tall_kernel, dim3(xcd_padded_total(tiles(kTallM, kG2N))), dim3(kTallThreads), 0, s, g);
+      else if (form == kGramWide) hipLaunchKernelGGL(gram_tile2_kernel, dim3(xcd_padded_total(tiles(kG2M, kG2N))), dim3(kG2Threads), 0, s, g);
       else hipLaunchKernelGGL(gram_tile_kernel, dim3(xcd_padded_total(tiles(kGT, kGT))), dim3(256), 0, s, g);
     }
     if (gram_stop) (void)hipEventRecord(gram_stop, s);

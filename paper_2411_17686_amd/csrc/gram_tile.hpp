@@ -161,9 +161,9 @@ __global__ __launch_bounds__(256) void gram_tile_kernel(GramArgs a) {
 }
 
 // ---- the same product for large blocks ---------------------------------------------------------
-// 192 x 192 or 256 x 192 output tile per workgroup of four wavefronts (2 x 2), 96 x 96 or 128 x 96 per wavefront = 3 x 3 or
-// 4 x 3 blocks of v_mfma_f32_32x32x16_bf16, one wavefront per SIMD: six fragment reads feed nine matrix instructions, seven
-// twelve.  Whole rows go from memory straight into LDS, 64 features at a time, three stages ahead (144 KB) or two (112 KB);
+// 192 x 192 output tile per workgroup of four wavefronts (2 x 2), 96 x 96 per wavefront = 3 x 3 blocks of
+// v_mfma_f32_32x32x16_bf16, one wavefront per SIMD: six fragment reads feed nine matrix instructions.
+// Whole rows go from memory straight into LDS, 64 features at a time, three stages ahead (144 KB);
 // the fragments of the next sixteen features are read while the matrix cores work on the ones before, across the one barrier of
 // a stage too.  LDS rows are the 128 bytes of a stage with no padding; the eight 16-byte chunks of row r sit at
 // chunk ^ ((r >> 1) & 7), which keeps the fragment reads (sixteen consecutive rows, one chunk) free of bank conflicts; a
@@ -173,25 +173,23 @@ __global__ __launch_bounds__(256) void gram_tile_kernel(GramArgs a) {
 // round): 28.3 us; without the stores 21.8, without the loads inside the loop 24, without both 16.5; the 37 MB of output alone
 // are 7 us at the rate of a large copy, the product 15.5 us at the rate of a large library product.  Before (256 x 192 tiles of eight
 // wavefronts through registers into LDS, one stage ahead): 34.2 us; 8064 x 1152 x 3584: 90 us before, 69 now; two images of
-// it: 59.5 before, 50 now.  Two buffers in place of three for the 192-row form: 27.8 us here, but 64 images of 768 x 384 x 1024
+// it: 59.5 before, 50 now.  Two buffers in place of three: 27.8 us here, but 64 images of 768 x 384 x 1024
 // (rows out of HBM) 74 us instead of 64.
-constexpr int kG2N = 192, kG2K = 64;
+constexpr int kG2M = 192, kG2N = 192, kG2K = 64;
 constexpr int kG2Threads = 256;
 constexpr int kG2Chunks = kG2K / 8;        // 16-byte chunks per operand row and stage
 static __device__ const uint4 g_zero_chunk = {0, 0, 0, 0};
 __device__ __forceinline__ int g2_slot(int row, int chunk) { return row * kG2Chunks + (chunk ^ ((row >> 1) & 7)); }
 
-template <int MB>
 __global__ __launch_bounds__(kG2Threads) __attribute__((amdgpu_waves_per_eu(1, 1))) void gram_tile2_kernel(GramArgs a) {
   static_assert(kG2Chunks == 8 && kG2K == 64, "the swizzle spreads eight chunks; four products of sixteen features a stage");
-  constexpr int kM = 64 * MB, kRows = kM + kG2N;
+  constexpr int MB = kG2M / 64, kRows = kG2M + kG2N;
   constexpr int kLoads = kRows * kG2Chunks / kG2Threads;  // per thread and stage: rows of A, then of B
-  constexpr int kBufs = MB == 3 ? 3 : 2;                  // 144 KB and 112 KB
-  __shared__ uint4 buf0[kRows * kG2Chunks], buf1[kRows * kG2Chunks], buf2[kBufs == 3 ? kRows * kG2Chunks : 1];
+  __shared__ uint4 buf0[kRows * kG2Chunks], buf1[kRows * kG2Chunks], buf2[kRows * kG2Chunks];
   __shared__ __attribute__((aligned(16))) int tok[kRows]; // of the rows of A, then of B
   const int tid = threadIdx.x, lane = tid % kWave, l32 = lane % 32, hi = lane / 32;
   const int wv = __builtin_amdgcn_readfirstlane(tid / kWave), wm = wv / 2, wn = wv % 2;
-  const int tiles_m = (a.n_disc + kM - 1) / kM, tiles_n = (a.n_keep + kG2N - 1) / kG2N;
+  const int tiles_m = (a.n_disc + kG2M - 1) / kG2M, tiles_n = (a.n_keep + kG2N - 1) / kG2N;
   const int per_split = a.B * tiles_m * tiles_n, total = per_split * a.splits;
   int logical = xcd_logical_id(blockIdx.x, total);           // the column tiles of the same rows share an XCD
   if (logical >= total) return;   // padding workgroup
@@ -201,8 +199,8 @@ __global__ __launch_bounds__(kG2Threads) __attribute__((amdgpu_waves_per_eu(1, 1
   const int tm = (logical % (tiles_m * tiles_n)) / tiles_n, tn = logical % tiles_n;
   bool mine = true;
   for (int q = tid; q < kRows; q += kG2Threads) {
-    const int r = q < kM ? tm * kM + q : tn * kG2N + q - kM;
-    const int t = q < kM ? (r < a.n_disc ? a.S[b * a.n_disc + r] : -1) : (r < a.n_keep ? a.T[b * a.n_keep + r] : -1);
+    const int r = q < kG2M ? tm * kG2M + q : tn * kG2N + q - kG2M;
+    const int t = q < kG2M ? (r < a.n_disc ? a.S[b * a.n_disc + r] : -1) : (r < a.n_keep ? a.T[b * a.n_keep + r] : -1);
     tok[q] = (unsigned)t < (unsigned)a.N ? t : -1;         // index sets are device data
     mine &= tok[q] >= 0;
   }
@@ -241,7 +239,7 @@ __global__ __launch_bounds__(kG2Threads) __attribute__((amdgpu_waves_per_eu(1, 1
   auto read = [&](const uint4* buf, int kk, bf16x8_t (&f)[MB + 3]) __attribute__((always_inline)) {
 #pragma unroll
     for (int q = 0; q < MB + 3; ++q)
-      f[q] = ((const bf16x8_t*)buf)[g2_slot((q < MB ? wm * kM / 2 + q * 32 : kM + wn * 96 + (q - MB) * 32) + l32, kk * 2 + hi)];
+      f[q] = ((const bf16x8_t*)buf)[g2_slot((q < MB ? wm * kG2M / 2 + q * 32 : kG2M + wn * 96 + (q - MB) * 32) + l32, kk * 2 + hi)];
   };
   auto multiply = [&](const bf16x8_t (&f)[MB + 3]) __attribute__((always_inline)) {
 #pragma unroll
@@ -262,38 +260,30 @@ __global__ __launch_bounds__(kG2Threads) __attribute__((amdgpu_waves_per_eu(1, 1
       issue_fence();
       multiply(fr[kk & 1]);
     }
-    __builtin_amdgcn_s_waitcnt(0x0070 | (kBufs - 2) * kLoads);   // lgkmcnt(0), vmcnt: all but the loads of the stage after the next
+    __builtin_amdgcn_s_waitcnt(0x0070 | kLoads);          // lgkmcnt(0), vmcnt: all but the loads of the stage after the next
     asm volatile("s_barrier" ::: "memory");
     read(next, 0, fr[0]);
     issue_fence();
-    fetch(st + kBufs, buf);
+    fetch(st + 3, buf);
     multiply(fr[1]);
   };
   if (n_st > 0) {                                           // uniform over the workgroup
     issue_fence();
     fetch(0, buf0);
     fetch(1, buf1);
-    if (kBufs == 3) fetch(2, buf2);
-    __builtin_amdgcn_s_waitcnt(kBufs == 3 ? 0x4070 | (2 * kLoads & 15) : 0x0070 | kLoads);   // vmcnt: all but the later stages' loads
+    fetch(2, buf2);
+    __builtin_amdgcn_s_waitcnt(0x4070 | (2 * kLoads & 15)); // lgkmcnt(0), vmcnt: all but the later two stages' loads
     asm volatile("s_barrier" ::: "memory");
     read(buf0, 0, fr[0]);
     int st = 0;
     // Whole turns of the buffers with no way out in between: the compiler would wait for every load at the loop's head.
-    if (kBufs == 3) {
-      for (; st + 2 < n_st; st += 3) {
-        stage(st, buf0, buf1);
-        stage(st + 1, buf1, buf2);
-        stage(st + 2, buf2, buf0);
-      }
-      if (st < n_st) stage(st, buf0, buf1);
-      if (st + 1 < n_st) stage(st + 1, buf1, buf2);
-    } else {
-      for (; st + 1 < n_st; st += 2) {
-        stage(st, buf0, buf1);
-        stage(st + 1, buf1, buf0);
-      }
-      if (st < n_st) stage(st, buf0, buf1);
+    for (; st + 2 < n_st; st += 3) {
+      stage(st, buf0, buf1);
+      stage(st + 1, buf1, buf2);
+      stage(st + 2, buf2, buf0);
     }
+    if (st < n_st) stage(st, buf0, buf1);
+    if (st + 1 < n_st) stage(st + 1, buf1, buf2);
     __builtin_amdgcn_s_waitcnt(0x0f70);                     // vmcnt(0): nothing may arrive in LDS after the workgroup's end
   }
   if (n_st * kG2K < k_len) {                                // less than a stage left: chunks past the range are zeros
@@ -315,7 +305,7 @@ __global__ __launch_bounds__(kG2Threads) __attribute__((amdgpu_waves_per_eu(1, 1
   // 8*(v/4) + 4*(lane/32) + v%4.
   float* ctb = a.ct + ((int64_t)split * a.B + b) * a.n_disc * (int64_t)a.n_keep;
   if (whole) {                                              // uniform over the workgroup
-    const int row0 = tm * kM + wm * (kM / 2), col0 = tn * kG2N + wn * 96;
+    const int row0 = tm * kG2M + wm * (kG2M / 2), col0 = tn * kG2N + wn * 96;
     const uint32_t at = (uint32_t)(4 * hi * a.n_keep + l32);
 #pragma unroll
     for (int mi = 0; mi < MB; ++mi)
@@ -332,12 +322,12 @@ __global__ __launch_bounds__(kG2Threads) __attribute__((amdgpu_waves_per_eu(1, 1
   for (int ni = 0; ni < 3; ++ni) {
     const int lc = wn * 96 + ni * 32 + l32, col = tn * kG2N + lc;
     if (col >= a.n_keep) continue;
-    const bool col_ok = tok[kM + lc] >= 0;
+    const bool col_ok = tok[kG2M + lc] >= 0;
 #pragma unroll
     for (int mi = 0; mi < MB; ++mi)
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
-        const int lr = wm * (kM / 2) + mi * 32 + 8 * g, row = tm * kM + lr;
+        const int lr = wm * (kG2M / 2) + mi * 32 + 8 * g, row = tm * kG2M + lr;
         if (row >= a.n_disc) break;                         // uniform, as is the next one
         const int4 t = *(const int4*)&tok[lr + 4 * hi];
         float* dst = ctb + (int64_t)row * a.n_keep + (uint32_t)(4 * hi * a.n_keep + col);
@@ -354,6 +344,149 @@ __global__ __launch_bounds__(kG2Threads) __attribute__((amdgpu_waves_per_eu(1, 1
         }
       }
   }
+}
+
+// ---- a taller tile ---------------------------------------------------------------------------------
+// 256 x 192 output tile per workgroup of 8 wavefronts (4 x 2), 64 x 96 per wavefront = 2 x 3 blocks
+// of v_mfma_f32_32x32x16_bf16: five fragment reads feed six matrix instructions.  Rows come through registers, a stage of
+// 64 features ahead, into LDS laid out as above; the loader's stores (consecutive lanes = consecutive chunks of consecutive
+// rows) are free of bank conflicts too.  Two wavefronts per SIMD hide each other's waits at the head of a tile and its stores at the
+// end, so it is the better one where tiles are short or come in several rounds.  us with 256 rows by four wavefronts as above
+// and by these eight: 36 images of 768 x 384, 4096 features 126 and 117; 64 of 1000 x 150, 4096 170 and 154; 128 of
+// 432 x 144, 256 features 20.8 and 15.7.
+constexpr int kTallM = 256, kTallThreads = 512;
+__global__ __launch_bounds__(kTallThreads) void gram_tall_kernel(GramArgs a) {
+  static_assert(kG2Chunks == 8, "the swizzle spreads eight chunks");
+  __shared__ uint4 Abuf[2 * kTallM * kG2Chunks];          // [2][256 rows][8 chunks]
+  __shared__ uint4 Bbuf[2 * kG2N * kG2Chunks];            // [2][192 rows][8 chunks]
+  __shared__ int rowA[kTallM];
+  __shared__ int rowB[kG2N];
+  const int tid = threadIdx.x, lane = tid % kWave, wv = tid / kWave;
+  const int tiles_m = (a.n_disc + kTallM - 1) / kTallM, tiles_n = (a.n_keep + kG2N - 1) / kG2N;
+  const int total = a.B * tiles_m * tiles_n;
+  const int logical = xcd_logical_id(blockIdx.x, total);     // the column tiles of the same rows share an XCD
+  if (logical >= total) return;   // padding workgroup
+  const int64_t b = logical / (tiles_m * tiles_n);
+  const int tm = (logical % (tiles_m * tiles_n)) / tiles_n, tn = logical % tiles_n;
+
+  if (tid < kTallM) {
+    const int r = tm * kTallM + tid;
+    const int i = r < a.n_disc ? a.S[b * a.n_disc + r] : -1;
+    rowA[tid] = (unsigned)i < (unsigned)a.N ? i : -1;      // index sets are device data
+  } else if (tid < kTallM + kG2N) {
+    const int c = tn * kG2N + tid - kTallM;
+    const int j = c < a.n_keep ? a.T[b * a.n_keep + c] : -1;
+    rowB[tid - kTallM] = (unsigned)j < (unsigned)a.N ? j : -1;
+  }
+  __syncthreads();
+
+  // loader: per stage 2048 chunks of A (four per thread) and 1536 of B (three per thread);
+  // chunk q = (row q / 8, 16 bytes q % 8)
+  const bf16_t* Xb = a.xhat + b * a.N * (int64_t)a.Df;
+  constexpr int kSlotsA = kTallM * kG2Chunks / kTallThreads, kSlotsB = kG2N * kG2Chunks / kTallThreads;
+  constexpr int kSlots = kSlotsA + kSlotsB;
+  static_assert(kSlotsA * kTallThreads == kTallM * kG2Chunks && kSlotsB * kTallThreads == kG2N * kG2Chunks, "whole slots");
+  // Every load of the loader is unconditional: a row past the block reads token 0 and a chunk past
+  // the K range reads the row's first chunk (both valid addresses: N >= 1, Df >= 8), and what was
+  // read is cleared when it is put into LDS.  Under a per-lane condition the loads sit in
+  // branches, and the compiler then waits for ALL outstanding loads before it issues the next
+  // stage's -- one stage in flight instead of two, and the wait at the head of every stage
+  // (measured here: 33-35 -> 30-33 us; the 128 x 128 kernel above, with four loads per stage, is
+  // no faster for it and keeps its conditional loads).
+  const bf16_t* src[kSlots];
+  bool row_ok[kSlots];
+  int lds_at[kSlots], kc[kSlots];
+#pragma unroll
+  for (int u = 0; u < kSlots; ++u) {
+    const bool aop = u < kSlotsA;
+    const int q = tid + kTallThreads * (aop ? u : u - kSlotsA);
+    const int row = q / kG2Chunks, chunk = q % kG2Chunks;
+    const int tok = aop ? rowA[row] : rowB[row];
+    kc[u] = chunk * 8;
+    lds_at[u] = g2_slot(row, chunk);
+    row_ok[u] = tok >= 0;
+    src[u] = Xb + (int64_t)max(tok, 0) * a.Df;
+  }
+  uint4 rg[kGStages][kSlots];
+  const int n_st = (a.Df + kG2K - 1) / kG2K;
+  auto in_range = [&](int st, int u) { return st < n_st && st * kG2K + kc[u] + 8 <= a.Df; };   // Df is a multiple of 8 on this path
+  auto fetch = [&](int slot, int st) {
+#pragma unroll
+    for (int u = 0; u < kSlots; ++u) __builtin_memcpy(&rg[slot][u], src[u] + (in_range(st, u) ? st * kG2K + kc[u] : 0), 16);
+  };
+  auto stash = [&](int slot, int buf, int st) {      // st: the stage that slot holds
+#pragma unroll
+    for (int u = 0; u < kSlots; ++u) {
+      const uint4 v = row_ok[u] && in_range(st, u) ? rg[slot][u] : make_uint4(0, 0, 0, 0);
+      if (u < kSlotsA) Abuf[buf * kTallM * kG2Chunks + lds_at[u]] = v;
+      else Bbuf[buf * kG2N * kG2Chunks + lds_at[u]] = v;
+    }
+  };
+
+  f32x16_t acc[2][3];
+#pragma unroll
+  for (int mi = 0; mi < 2; ++mi)
+#pragma unroll
+    for (int ni = 0; ni < 3; ++ni)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[mi][ni][v] = 0.0f;
+
+  const int wm = wv / 2, wn = wv % 2;
+  const int frow = lane % 32, fch = lane / 32;     // fragment: row within the block, 16-byte chunk within a 16-feature step
+#pragma unroll
+  for (int sl = 0; sl < kGStages; ++sl) fetch(sl, sl);
+  stash(0, 0, 0);
+  __syncthreads();
+  int cur = 0;
+  for (int base = 0; base < n_st; base += kGStages) {
+#pragma unroll
+    for (int sl = 0; sl < kGStages; ++sl) {
+      const int it = base + sl;
+      if (it < n_st) {                          // uniform over the workgroup
+        fetch(sl, it + kGStages);               // slot sl was stashed one iteration ago
+#pragma unroll
+        for (int kk = 0; kk < kG2K / 16; ++kk) {
+          bf16x8_t fa[2], fb[3];
+#pragma unroll
+          for (int mi = 0; mi < 2; ++mi) {
+            const uint4 t = Abuf[cur * kTallM * kG2Chunks + g2_slot(wm * 64 + mi * 32 + frow, kk * 2 + fch)];
+            __builtin_memcpy(&fa[mi], &t, 16);
+          }
+#pragma unroll
+          for (int ni = 0; ni < 3; ++ni) {
+            const uint4 t = Bbuf[cur * kG2N * kG2Chunks + g2_slot(wn * 96 + ni * 32 + frow, kk * 2 + fch)];
+            __builtin_memcpy(&fb[ni], &t, 16);
+          }
+#pragma unroll
+          for (int mi = 0; mi < 2; ++mi)
+#pragma unroll
+            for (int ni = 0; ni < 3; ++ni)
+              acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[mi], fb[ni], acc[mi][ni], 0, 0, 0);
+        }
+        if (it + 1 < n_st) {
+          stash((sl + 1) % kGStages, cur ^ 1, it + 1);  // the other buffer was last read before the previous barrier
+          __syncthreads();
+          cur ^= 1;
+        }
+      }
+    }
+  }
+
+  // C block layout of the 32x32 MFMA: lane holds column lane%32; register v holds row
+  // 8*(v/4) + 4*(lane/32) + v%4.
+  float* ctb = a.ct + b * a.n_disc * (int64_t)a.n_keep;
+#pragma unroll
+  for (int mi = 0; mi < 2; ++mi)
+#pragma unroll
+    for (int ni = 0; ni < 3; ++ni) {
+      const int col = tn * kG2N + wn * 96 + ni * 32 + lane % 32;
+      const int row0 = tm * kTallM + wm * 64 + mi * 32 + 4 * (lane / 32);
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int row = row0 + 8 * (v / 4) + v % 4;
+        if (row < a.n_disc && col < a.n_keep) ctb[(int64_t)row * a.n_keep + col] = acc[mi][ni][v];
+      }
+    }
 }
 
 }  // namespace ficoco
