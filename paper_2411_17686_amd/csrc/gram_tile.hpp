@@ -186,7 +186,7 @@ __global__ __launch_bounds__(kG2Threads) __attribute__((amdgpu_waves_per_eu(1, 1
   constexpr int MB = kG2M / 64, kRows = kG2M + kG2N;
   constexpr int kLoads = kRows * kG2Chunks / kG2Threads;  // per thread and stage: rows of A, then of B
   __shared__ uint4 buf0[kRows * kG2Chunks], buf1[kRows * kG2Chunks], buf2[kRows * kG2Chunks];
-  __shared__ __attribute__((aligned(16))) int tok[kRows]; // of the rows of A, then of B
+  __shared__ int tok[kRows];                              // of the rows of A, then of B
   const int tid = threadIdx.x, lane = tid % kWave, l32 = lane % 32, hi = lane / 32;
   const int wv = __builtin_amdgcn_readfirstlane(tid / kWave), wm = wv / 2, wn = wv % 2;
   const int tiles_m = (a.n_disc + kG2M - 1) / kG2M, tiles_n = (a.n_keep + kG2N - 1) / kG2N;
@@ -317,22 +317,21 @@ __global__ __launch_bounds__(kG2Threads) __attribute__((amdgpu_waves_per_eu(1, 1
       }
     return;
   }
-  // an edge: zeros where a row or column is of no token, whole groups of eight rows without a check of each
+  // An edge: whole groups of eight rows without a check of each.  (With a look at the rows' tokens before every group of
+  // stores, 260 images of 98 x 98, all edges, took 22.8 us instead of 18.8.)
 #pragma unroll
   for (int ni = 0; ni < 3; ++ni) {
     const int lc = wn * 96 + ni * 32 + l32, col = tn * kG2N + lc;
     if (col >= a.n_keep) continue;
-    const bool col_ok = tok[kG2M + lc] >= 0;
 #pragma unroll
     for (int mi = 0; mi < MB; ++mi)
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
         const int lr = wm * (kG2M / 2) + mi * 32 + 8 * g, row = tm * kG2M + lr;
         if (row >= a.n_disc) break;                         // uniform, as is the next one
-        const int4 t = *(const int4*)&tok[lr + 4 * hi];
         float* dst = ctb + (int64_t)row * a.n_keep + (uint32_t)(4 * hi * a.n_keep + col);
-        const float c0 = col_ok && t.x >= 0 ? acc[mi][ni][4 * g] : 0.0f, c1 = col_ok && t.y >= 0 ? acc[mi][ni][4 * g + 1] : 0.0f;
-        const float c2 = col_ok && t.z >= 0 ? acc[mi][ni][4 * g + 2] : 0.0f, c3 = col_ok && t.w >= 0 ? acc[mi][ni][4 * g + 3] : 0.0f;
+        const float c0 = acc[mi][ni][4 * g], c1 = acc[mi][ni][4 * g + 1];
+        const float c2 = acc[mi][ni][4 * g + 2], c3 = acc[mi][ni][4 * g + 3];
         if (row + 8 <= a.n_disc) {
           dst[0] = c0, dst[a.n_keep] = c1, dst[2 * (int64_t)a.n_keep] = c2, dst[3 * (int64_t)a.n_keep] = c3;
         } else {
@@ -343,6 +342,16 @@ __global__ __launch_bounds__(kG2Threads) __attribute__((amdgpu_waves_per_eu(1, 1
           if (left > 3) dst[3 * (int64_t)a.n_keep] = c3;
         }
       }
+  }
+  // Zeros where a row or column of the block is of no token (rare), behind the stores above, of all wavefronts.
+  const int rows = min(kG2M, a.n_disc - tm * kG2M), cols = min(kG2N, a.n_keep - tn * kG2N);
+  bool none = false;
+  for (int q = tid; q < kRows; q += kG2Threads) none |= tok[q] < 0 && (q < kG2M ? q < rows : q - kG2M < cols);
+  __builtin_amdgcn_s_waitcnt(0x0f70);                       // vmcnt(0)
+  if (!__syncthreads_or(none)) return;
+  for (int q = tid; q < rows * cols; q += kG2Threads) {
+    const int r = q / cols, c = q % cols;
+    if (tok[r] < 0 || tok[kG2M + c] < 0) ctb[(int64_t)(tm * kG2M + r) * a.n_keep + tn * kG2N + c] = 0.0f;
   }
 }
 
