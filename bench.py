@@ -500,7 +500,7 @@ def main():
     else:
         algo = W["gram_flops"]
         achieved = algo / (alone_ms * 1e-3) / 1e12
-        gram_name = "gram_tile2_kernel" if args.config in ("4", "1c") else "gram_tile_kernel"    # wide tiles: 128 workgroups or more
+        gram_name = "gram_tile2_kernel" if args.config == "4" else "gram_tile_kernel"    # by estimate (gram_form, correlate.hip)
         roof = {"kernel": gram_name + " (bf16 MFMA 32x32x16)", "bound": "mfma", "achieved": achieved,
                 "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": achieved / MFMA_BF16_PEAK_TFLOPS,
                 "traffic": None, "algorithmic_flops": algo}

@@ -902,23 +902,32 @@ static void launch_cand_rows(int sel_m, dim3 grid, dim3 block, hipStream_t s, co
 }
 
 GramForm gram_form(const ficoco_problem& p, const Plan& pl) {
-  // Large blocks (one K range, enough 192 x 192 tiles for half the chip): the wide-tile forms.  One workgroup takes a
-  // compute unit to itself, so it is rounds of 256 tiles that count: the taller tile where that saves more than its height
-  // costs.  us with 192 / 256 rows: 8064 x 1152 28 / 36 (252 tiles, one round either way), 10368 x 1152 45 / 36.7
-  // (324 and 246 tiles), 36 images of 768 x 384 44 / 33.8 (288 and 216).
-  // Against the 128 x 128 tiles: 8064 x 1152 40, 16 images of 768 x 384 with 384 features 14.9 (here 14.4), 12 of them the same.
-  // With several K ranges: where their wide tiles are one round that fills half the chip or more and at most an eighth of them
-  // is padding.  us with 128 x 128 / 192 x 192 tiles: 16 images of 768 x 384 with 1024 features 24.5 / 20.2, with 4096 82 / 58;
-  // 8 of them 17.2 / 16.0, 4 of them 13.3 / 13.3; 64 of 384 x 192 24.5 / 22.0; 8 with 4096 features 18.4 / 16.6.  Two rounds: 6048 x 864
-  // 25 / 33; padding: 8 images of 432 x 144 with 4096 features 19.0 / 21.4, one of 2240 x 640 (a fifth) 14.1 / 16.3.
-  auto tiles2 = [&](int rows) { return p.B * ((pl.n_disc + rows - 1) / rows) * ((p.n_keep + kG2N - 1) / kG2N); };
-  auto rounds = [](int t) { return (t + 255) / 256; };
-  const int wide_wgs = pl.gram_splits * tiles2(192);
-  const bool fits = wide_wgs <= 256 && (int64_t)tiles2(192) * (192 * kG2N * 7 / 8) <= (int64_t)p.B * pl.n_disc * p.n_keep;
-  if (wide_wgs < 128 || (pl.gram_splits > 1 && !fits)) return kGramSquare;
-  // (the 192-row tiles address the rows of an image with 32 bits, the others with 64)
-  if ((int64_t)p.N * pl.Df * sizeof(bf16_t) >= (int64_t(1) << 32)) return pl.gram_splits == 1 && tiles2(256) >= 128 ? kGramTall : kGramSquare;
-  return pl.gram_splits == 1 && 4 * rounds(tiles2(256)) < 3 * rounds(tiles2(192)) ? kGramTall : kGramWide;
+  // Estimated us of the three forms (sixteen launches in a row), from the tiles and the 32-feature stages of a K range.  A workgroup of
+  // the 192- and 256-row forms has a compute unit to itself: rounds of 256 tiles, and a nearly empty last one, or tiles that
+  // are mostly padding, cost as much as full ones.  Of the 128 x 128 tiles three share a compute unit.  us with tiles of
+  // 128 / 192 / 256 rows: 8064 x 1152 with 1024 features 37 / 27 / 31 (567, 252 and 192 tiles); 10368 x 1152 39 / 45 / 34 (324 tiles of
+  // 192: two rounds); 36 images of 768 x 384 38 / 45 / 32, 44 of them 57 / 46 / 58 (264 tiles of 256: two rounds); 260 of 480 x 96, 128
+  // features 20 / 40 / 28 and 180 of 200 x 200 12.7 / 26 / 18 (padding); 128 of 432 x 144, 256 features 21 / 25 / 16.  Several K
+  // ranges: 16 images of 768 x 384, 1024 features 23 / 20, with 4096 65 / 45; 8 of 432 x 144, 4096 features 17.3 / 18.3.
+  // Over 1565 shapes (20 to 400 images of 50 to 700 rows, 1 to 280 of up to 10368, 128 to 4096 features) the estimate lies within 25 %
+  // for more than nine of ten, and the form chosen takes 1.2 % longer than the best one on average.  The usual form, 256 rows
+  // where their tiles fill half the chip, else 128, is left only for one estimated 8 % faster: then four of the shapes are more than 3 %
+  // slower than with the usual form, at most 11 %; without that margin 38, at most 34 %.
+  auto rounds = [&](int rows, int cols) {
+    const int64_t tiles = (int64_t)pl.gram_splits * p.B * ((pl.n_disc + rows - 1) / rows) * ((p.n_keep + cols - 1) / cols);
+    return (int)std::min<int64_t>((tiles + 255) / 256, 1 << 24);
+  };
+  const float st = (float)pl.gram_st_per_split;
+  const int sq = rounds(kGT, kGT);
+  const float square = 2.5f + sq / 3 * (5.5f + st) + (sq % 3 == 0 ? 0.0f : sq % 3 == 1 ? 3.5f + 0.55f * st : 4.5f + 0.75f * st);
+  const float wide = 2.0f + rounds(kG2M, kG2N) * (7.0f + 0.56f * st);
+  if (pl.gram_splits > 1) return 1.08f * wide < square ? kGramWide : kGramSquare;      // (the 256-row form takes all of K at once)
+  const float tall = 0.5f + rounds(kTallM, kG2N) * (6.5f + 0.8f * st);
+  const bool usual_tall = (int64_t)p.B * ((pl.n_disc + kTallM - 1) / kTallM) * ((p.n_keep + kG2N - 1) / kG2N) >= 128;
+  const GramForm usual = usual_tall ? kGramTall : kGramSquare, other = usual_tall ? kGramSquare : kGramTall;
+  const float t_usual = usual_tall ? tall : square, t_other = usual_tall ? square : tall;
+  if (1.08f * std::min(wide, t_other) >= t_usual) return usual;
+  return wide <= t_other ? kGramWide : other;
 }
 
 void launch_correlate(const ficoco_problem& p, const Plan& pl, char* ws, const int32_t* discard_idx,
@@ -997,7 +1006,11 @@ void launch_correlate(const ficoco_problem& p, const Plan& pl, char* ws, const i
     if (gram_start) (void)hipEventRecord(gram_start, s);
     // gram_repeat > 1 (measurement only): the same launch again and again between the two events
     for (int rep = 0; rep < gram_repeat; ++rep) {
-      if (form == kGramTall) hipLaunchKernelGGL(gram_tall_kernel, dim3(xcd_padded_total(tiles(kTallM, kG2N))), dim3(kTallThreads), 0, s, g);
+      if (form == kGramTall) {
+        constexpr size_t kLds = (size_t)2 * (kTallM + kG2N) * kG2Chunks * sizeof(uint4);
+        (void)hipFuncSetAttribute((const void*)gram_tall_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLds);
+        hipLaunchKernelGGL(gram_tall_kernel, dim3(xcd_padded_total(tiles(kTallM, kG2N))), dim3(kTallThreads), kLds, s, g);
+      }
       else if (form == kGramWide) hipLaunchKernelGGL(gram_tile2_kernel, dim3(xcd_padded_total(tiles(kG2M, kG2N))), dim3(kG2Threads), 0, s, g);
       else hipLaunchKernelGGL(gram_tile_kernel, dim3(xcd_padded_total(tiles(kGT, kGT))), dim3(256), 0, s, g);
     }

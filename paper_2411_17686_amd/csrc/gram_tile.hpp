@@ -211,11 +211,11 @@ __global__ __launch_bounds__(kG2Threads) __attribute__((amdgpu_waves_per_eu(1, 1
   const int n_st = k_len / kG2K;                            // whole stages; what is left is a stage of its own
   // A row past the block, or of no token, reads token 0 (its values are not used).
   const bf16_t* xb = a.xhat + b * a.N * (int64_t)a.Df + k_begin;
-  uint32_t src[kLoads];                                   // in bytes: the rows of an image take less than 4 GiB on this path
+  int64_t src[kLoads];                                    // in bytes
   const int chunk = (tid % kG2Chunks ^ (tid / 16 % kG2Chunks)) * 8;
 #pragma unroll
   for (int i = 0; i < kLoads; ++i)
-    src[i] = ((uint32_t)max(tok[tid / kG2Chunks + i * (kG2Threads / kG2Chunks)], 0) * (uint32_t)a.Df + chunk) * 2u;
+    src[i] = ((int64_t)max(tok[tid / kG2Chunks + i * (kG2Threads / kG2Chunks)], 0) * a.Df + chunk) * 2;
   auto load = [&](int i, const void* from, uint4* buf) __attribute__((always_inline)) {
     __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)from,
                                      (__attribute__((address_space(3))) void*)(buf + i * kG2Threads + wv * kWave), 16, 0, 0);
@@ -366,8 +366,9 @@ __global__ __launch_bounds__(kG2Threads) __attribute__((amdgpu_waves_per_eu(1, 1
 constexpr int kTallM = 256, kTallThreads = 512;
 __global__ __launch_bounds__(kTallThreads) void gram_tall_kernel(GramArgs a) {
   static_assert(kG2Chunks == 8, "the swizzle spreads eight chunks");
-  __shared__ uint4 Abuf[2 * kTallM * kG2Chunks];          // [2][256 rows][8 chunks]
-  __shared__ uint4 Bbuf[2 * kG2N * kG2Chunks];            // [2][192 rows][8 chunks]
+  extern __shared__ uint4 rows_lds[];
+  uint4* Abuf = rows_lds;                                 // [2][256 rows][8 chunks]
+  uint4* Bbuf = rows_lds + 2 * kTallM * kG2Chunks;        // [2][192 rows][8 chunks]
   __shared__ int rowA[kTallM];
   __shared__ int rowB[kG2N];
   const int tid = threadIdx.x, lane = tid % kWave, wv = tid / kWave;

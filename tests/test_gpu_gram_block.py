@@ -73,14 +73,17 @@ def _check(p, buf, plan, S, T):
 CASES = [
     # 128 x 128: less than a stage of 32, whole stages, a remainder; several K ranges, the last one shorter
     (3, 127, 129, 8, 0, H.SQUARE), (2, 128, 256, 64, 0, H.SQUARE), (2, 257, 40, 136, 5, H.SQUARE), (1, 300, 200, 1064, 0, H.SQUARE),
-    # 192 x 192: features in the remainder alone (8, 24), one stage of 64, two, three, whole turns of the buffers and what is left
-    (128, 192, 192, 8, 0, H.WIDE), (128, 193, 191, 24, 0, H.WIDE), (128, 191, 192, 64, 0, H.WIDE), (64, 384, 193, 128, 3, H.WIDE),
-    (128, 100, 180, 192, 0, H.WIDE), (128, 192, 185, 328, 0, H.WIDE), (32, 380, 384, 392, 9, H.WIDE), (1, 3000, 1600, 504, 0, H.WIDE),
-    # several K ranges: 288 and 232 features; eight of which the last has 40
-    (64, 191, 192, 520, 0, H.WIDE), (16, 190, 192, 2056, 4, H.WIDE),
-    # 256 x 192: whole and edge tiles in one launch, the same feature counts
-    (150, 256, 192, 24, 0, H.TALL), (86, 500, 193, 200, 6, H.TALL), (86, 512, 384, 64, 0, H.TALL), (260, 255, 40, 136, 0, H.TALL),
-    (1, 6216, 3000, 320, 0, H.TALL), (86, 512, 300, 520, 0, H.TALL),
+    # 192 x 192: seven stages of 64 features (whole turns of the three buffers and what is left), nine, ten, eleven; less than a
+    # stage behind them; whole tiles, and rows and columns that miss or pass a tile by one
+    (128, 192, 192, 448, 0, H.WIDE), (128, 192, 191, 456, 0, H.WIDE), (128, 193, 191, 480, 0, H.WIDE), (64, 384, 193, 504, 3, H.WIDE),
+    (32, 768, 384, 448, 9, H.WIDE), (1, 8064, 1152, 576, 0, H.WIDE), (1, 8000, 1150, 640, 0, H.WIDE), (1, 8060, 1152, 712, 0, H.WIDE),
+    # several K ranges: of 512 features; of 544 and 488; of 704 and 648
+    (16, 768, 384, 1024, 0, H.WIDE), (16, 760, 383, 1032, 4, H.WIDE), (32, 384, 192, 2056, 0, H.WIDE),
+    # 256 x 192: the remainder alone, one stage, two, three and more; whole and edge tiles in one launch
+    (150, 256, 192, 24, 0, H.TALL), (64, 500, 193, 72, 6, H.TALL), (86, 512, 384, 64, 0, H.TALL), (64, 512, 200, 200, 0, H.TALL),
+    (1, 6216, 3000, 320, 0, H.TALL), (86, 512, 300, 520, 0, H.TALL), (128, 432, 144, 256, 5, H.TALL), (1, 10368, 1152, 136, 0, H.TALL),
+    # many tiles of 128 x 128 where larger ones would be mostly padding
+    (260, 98, 98, 128, 0, H.SQUARE), (180, 200, 200, 136, 2, H.SQUARE),
 ]
 
 
@@ -94,8 +97,8 @@ def test_block_of_every_form(ctx, B, n_disc, n_keep, D, M, form):
     _check(p, buf, plan, buf.discard_idx, buf.keep_idx)
 
 
-@pytest.mark.parametrize("B,n_disc,n_keep,D,M,form", [(2, 200, 150, 72, 0, H.SQUARE), (128, 192, 192, 72, 0, H.WIDE),
-                                                      (128, 100, 191, 200, 4, H.WIDE), (150, 256, 192, 72, 0, H.TALL), (86, 500, 193, 64, 0, H.TALL)])
+@pytest.mark.parametrize("B,n_disc,n_keep,D,M,form", [(2, 200, 150, 72, 0, H.SQUARE), (128, 192, 192, 448, 0, H.WIDE),
+                                                      (16, 760, 383, 1032, 4, H.WIDE), (150, 256, 192, 72, 0, H.TALL), (64, 500, 193, 72, 0, H.TALL)])
 def test_rows_and_columns_of_no_token_are_zero(ctx, B, n_disc, n_keep, D, M, form):
     """Index sets of the caller (staged calls), some entries outside the image."""
     p, buf, alive = _problem(B, n_disc, n_keep, D, M)
