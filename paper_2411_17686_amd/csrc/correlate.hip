@@ -434,11 +434,12 @@ constexpr int kCandBatch = 4;                    // targets evaluated exactly at
 // Rows whose targets are clear from the approximate values skip the exact dot products (K = 1) or take
 // them of the K targets only, and the largest values are kept by medians: 31.6 -> 18.1 us at 8 x 432 rows
 // of 144 targets and 4096 features (K = 1), 32.5 -> 27.4 us at 8064 rows of 1152 (K = 3, 1024 features).
-// One instance per correlation: with the mode a run-time value it held 127 registers, spilled two and turned
-// the scalars over vector registers.  That, no threshold where the targets are known, masks in the row's last step
-// only and the text rows of the bound asked for ahead of the row (1353 -> 1098 vector instructions per row of 1152):
-// 28.2 -> 25.2 us at 8064 rows of 1152, 18.5 -> 17.6 at 8 x 432 rows of 144, 12.1 -> 10.5 on the map's rows.  Exact
-// products of three targets where three are left, not four with one of them twice: 25.0, left out.
+// One instance per correlation (with the mode a run-time value it held 127 registers and spilled four), no threshold where the
+// targets are known, and the text rows of the bound asked for ahead of the row (1353 -> 1098 vector instructions per row of 1152):
+// 28.2 -> 25.2 us at 8064 rows of 1152, 18.5 -> 17.6 at 8 x 432 rows of 144, 12.1 -> 10.5 on the map's rows.  What is
+// asked of every slot of a row (past its end? of a token?) is worked out where it is used, in branches: kept for all of them, the
+// answers went over 51 to 113 lanes of vector registers and back.  Map's rows 9.7 -> 8.7 us, the others 28.9 / 28.9 and
+// 17.0 / 16.7.  Exact products of three targets where three are left, not four with one of them twice: no faster, left out.
 // Compiled for four wavefronts per SIMD (128 registers): the decoder shape has
 // 3456 discarded rows, one wavefront each, and the chip holds 3072 of them at three per SIMD.
 template <int MC, int MODE>   // MC: lower bounds kept per lane (>= sel_m: one lane may hold the m largest of the row)
@@ -478,16 +479,29 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void c
     if (from_map) {
       int jt[kCandKeep];
 #pragma unroll
-      for (int u = 0; u < kCandKeep; ++u) {
-        const int jj = c0 + u * kWave + lane;
-        jt[u] = (u < n_u && jj < n) ? T[jj] : -1;
+      for (int ub = 0; ub < kCandKeep; ub += 8) {
+        if (ub < n_u) {                                              // uniform: groups of 8 slots that hold targets
+#pragma unroll
+          for (int u = ub; u < ub + 8; ++u) jt[u] = T[min(c0 + u * kWave + lane, n - 1)];    // (past the row: its last target, masked below)
+        } else {
+#pragma unroll
+          for (int u = ub; u < ub + 8; ++u) jt[u] = -1;
+        }
+      }
+#pragma unroll
+      for (int ub = 0; ub < kCandKeep; ub += 8) {
+        if (ub < n_u) {                                              // uniform
+#pragma unroll
+          for (int u = ub; u < ub + 8; ++u) val[u] = ct[(unsigned)jt[u] < (unsigned)a.N ? jt[u] : 0];
+        } else {
+#pragma unroll
+          for (int u = ub; u < ub + 8; ++u) val[u] = 0.0f;
+        }
       }
 #pragma unroll
       for (int u = 0; u < kCandKeep; ++u) {
-        const bool ok = (unsigned)jt[u] < (unsigned)a.N;
-        float v = 0.0f;
-        if (u < n_u) v = ct[ok ? jt[u] : 0];
-        val[u] = c0 + u * kWave + lane < n ? (ok ? v : 0.0f) : NEGF;
+        asm volatile("" : "+v"(jt[u]));         // (compared again: the answers of all slots take more scalar registers than there are)
+        val[u] = (unsigned)jt[u] < (unsigned)a.N ? val[u] : 0.0f;
       }
     } else {
       // The block is followed by kCandChunk floats of padding, so a pass may read past the end
@@ -527,10 +541,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void c
           }
         }
       }
+    }
 #pragma unroll
-      for (int u = 0; u < kCandKeep; ++u) {
-        if (c0 + u * kWave >= n) break;         // uniform: no reader looks at slots past the row
-        if (c0 + (u + 1) * kWave > n) val[u] = c0 + u * kWave + lane < n ? val[u] : NEGF;   // (uniform: the row's last step)
+    for (int u = 0; u < kCandKeep; ++u) {
+      if (c0 + u * kWave >= n) break;         // uniform: no reader looks at slots past the row
+      if (c0 + (u + 1) * kWave > n) {         // uniform: the row's last step
+        val[u] = c0 + u * kWave + lane < n ? val[u] : NEGF;
+        asm volatile("" : "+v"(val[u]));      // (a branch: as selects for every step, the conditions of all of them are kept)
       }
     }
   };
