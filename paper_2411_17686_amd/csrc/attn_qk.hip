@@ -584,6 +584,10 @@ __global__ __launch_bounds__(QkMeanShape<SPLIT>::kThreads) __attribute__((amdgpu
   // outputs of 64 queries (32: one block) from v0 and 32 visual keys from ik0 on, of the sums over the heads
   auto write_out = [&](auto blocks_c, int v0, int ik0, const f32x16_t& s0, const f32x16_t& s1) __attribute__((always_inline)) {
     constexpr int blocks = decltype(blocks_c)::value;
+    // (again from the thread's number: kept over the heads, these took registers that heads of 128, split, do not have)
+    int here = threadIdx.x;
+    asm volatile("" : "+v"(here));
+    const int l32 = here % kQkB, hi = here % kWave / kQkB;
     const float invH = 1.0f / (float)a.H;
     const int qt = v0 / kQkTile;
     const bool recv = a.recv_part && qt < a.n_tiles;    // uniform

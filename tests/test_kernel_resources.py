@@ -40,3 +40,8 @@ def _all(kernels, part):
 def test_candidate_rows_keep_their_scalars(kernels):
     for n, r in _all(kernels, "corr_cand_rows_kernel").items():
         assert r["sgpr_spill_count"] == r["vgpr_spill_count"] == r["private_segment_fixed_size"] == 0, (n, r)
+
+
+def test_head_mean_of_queries_and_keys_uses_no_scratch(kernels):
+    for n, r in _all(kernels, "qk_mean_kernel").items():
+        assert r["vgpr_spill_count"] == r["private_segment_fixed_size"] == 0, (n, r)
