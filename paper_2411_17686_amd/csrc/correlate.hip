@@ -12,6 +12,7 @@
 // the workspace and the two order statistics are found bit by bit.
 #include "common.hpp"
 #include "gram_tile.hpp"
+#include "text_stats.hpp"
 
 #include <algorithm>
 
@@ -319,33 +320,10 @@ __device__ __forceinline__ double corr_value_wave(const CorrArgs& a, int64_t b, 
   return a.gamma * direct + (1.0 - a.gamma) * (br * a.invM);
 }
 
-// cmax[b][k] = max over the visual tokens of the text profile entry k (bound of Eq. 4's indirect
-// term).  A workgroup takes 64 consecutive text queries k of one image: thread (k, g) walks the
-// tokens g, g+4, ... (16 independent loads per round), the four token groups meet in LDS.
-__global__ __launch_bounds__(256) void text_colmax_kernel(CorrArgs a) {
-  __shared__ double part[256];
-  const int64_t b = blockIdx.y;
-  const int tid = threadIdx.x;
-  const int k = blockIdx.x * 64 + tid % 64, g = tid / 64;
-  double mx = 0.0;
-  if (k < a.M) {
-    int i = g;
-    for (; i + 4 * 15 < a.N; i += 4 * 16) {            // 16 independent loads per round
-      double v[16];
-#pragma unroll
-      for (int u = 0; u < 16; ++u) v[u] = a.ttext[(b * a.N + i + 4 * u) * a.M + k];
-#pragma unroll
-      for (int u = 0; u < 16; ++u) mx = v[u] > mx ? v[u] : mx;
-    }
-    for (; i < a.N; i += 4) { const double v = a.ttext[(b * a.N + i) * a.M + k]; mx = v > mx ? v : mx; }
-  }
-  part[tid] = mx;
-  __syncthreads();
-  if (g == 0 && k < a.M) {
-    for (int q = 1; q < 4; ++q) mx = part[q * 64 + tid] > mx ? part[q * 64 + tid] : mx;
-    a.cmax[b * a.M + k] = mx;
-  }
-}
+// Maxima of the text profiles (bound of Eq. 4's indirect term) where the score stage did not form them: staged calls, and steps
+// with fewer text queries than the score stage's launch is worth.  (64 queries and four token groups a workgroup, nine rounds of loads:
+// 7.3 us at 8 x 576 tokens, 4.1 so; 69 and 23 at 9216 tokens.)
+__global__ __launch_bounds__(256) void text_colmax_kernel(TextStatsArgs t) { text_cmax_block(t, blockIdx.x, blockIdx.y); }
 
 constexpr int kCorrSteps = 2;   // 512-feature steps of the exact dot products loaded together
 
@@ -918,6 +896,12 @@ static void launch_cand_rows(int sel_m, dim3 grid, dim3 block, hipStream_t s, co
   else hipLaunchKernelGGL((corr_cand_rows_kernel<8, MODE>), grid, block, 0, s, a);
 }
 
+static void launch_text_colmax(const ficoco_problem& p, const Plan& pl, char* ws, hipStream_t s) {
+  TextStatsArgs t{};
+  fill_text_stats(p, pl, ws, true, t);
+  hipLaunchKernelGGL(text_colmax_kernel, dim3(t.cmax_blocks, p.B), dim3(256), 0, s, t);
+}
+
 GramForm gram_form(const ficoco_problem& p, const Plan& pl) {
   // Estimated us of the three forms (sixteen launches in a row), from the tiles and the 32-feature stages of a K range.  A workgroup of
   // the 192- and 256-row forms has a compute unit to itself: rounds of 256 tiles, and a nearly empty last one, or tiles that
@@ -1012,7 +996,7 @@ void launch_correlate(const ficoco_problem& p, const Plan& pl, char* ws, const i
     return;
   }
   if (a.mode == kAttnL && !pl.dense_rows && p.k_max <= 64) {
-    if (need_colmax) hipLaunchKernelGGL(text_colmax_kernel, dim3((p.M + 63) / 64, p.B), dim3(256), 0, s, a);
+    if (need_colmax) launch_text_colmax(p, pl, ws, s);
     launch_cand_rows<kAttnL>(pl.sel_m, grid, block, s, a);
     return;
   }
@@ -1032,7 +1016,7 @@ void launch_correlate(const ficoco_problem& p, const Plan& pl, char* ws, const i
       else hipLaunchKernelGGL(gram_tile_kernel, dim3(xcd_padded_total(tiles(kGT, kGT))), dim3(256), 0, s, g);
     }
     if (gram_stop) (void)hipEventRecord(gram_stop, s);
-    if (L && need_colmax) hipLaunchKernelGGL(text_colmax_kernel, dim3((p.M + 63) / 64, p.B), dim3(256), 0, s, a);
+    if (L && need_colmax) launch_text_colmax(p, pl, ws, s);
     if (L) launch_cand_rows<kCosL>(pl.sel_m, grid, block, s, a);
     else launch_cand_rows<kCosV>(pl.sel_m, grid, block, s, a);
     return;

@@ -1,11 +1,11 @@
-// What a test may ask about the plan of a problem: where the block of approximate cosines and the unit rows lie in the
-// workspace, how the block is cut, and the error its readers allow for.  (Host code only.)
+// What a test may ask about the plan of a problem: where the block of approximate cosines, the unit rows, the text
+// profiles and their maxima lie in the workspace, how the block is cut, and the error its readers allow for.  (Host code only.)
 #include "../../paper_2411_17686_amd/csrc/common.hpp"
 
 extern "C" {
 
 struct gram_plan {
-  int64_t ct, xhat;          // byte offsets in the workspace
+  int64_t ct, xhat, ttext, cmax;   // byte offsets in the workspace
   int32_t use_gram, splits;  // K ranges: [splits][B][n_disc][n_keep]
   int32_t st_per_split, form, Df;
   float delta;
@@ -17,7 +17,7 @@ int plan_hook_gram(const ficoco_problem* p, gram_plan* out) {
   const char* why = nullptr;
   const int rc = ficoco::make_plan(*p, pl, &why);
   if (rc != FICOCO_OK) return rc;
-  *out = gram_plan{(int64_t)pl.ct, (int64_t)pl.xhat, pl.use_gram, pl.gram_splits, pl.gram_st_per_split,
+  *out = gram_plan{(int64_t)pl.ct, (int64_t)pl.xhat, (int64_t)pl.ttext, (int64_t)pl.cmax, pl.use_gram, pl.gram_splits, pl.gram_st_per_split,
                    pl.use_gram ? (int32_t)ficoco::gram_form(*p, pl) : 0, pl.Df, ficoco::gram_delta(pl)};
   return rc;
 }

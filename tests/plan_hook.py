@@ -1,4 +1,5 @@
-"""ctypes view of tests/c_abi/plan_hook.cpp: how the library lays out and cuts the block of approximate cosines."""
+"""ctypes view of tests/c_abi/plan_hook.cpp: how the library lays out and cuts the block of approximate cosines, and
+where the text profiles lie."""
 import ctypes as C
 import os
 
@@ -7,7 +8,7 @@ SQUARE, WIDE, TALL = 0, 1, 2            # tiles of 128 x 128, 192 x 192, 256 x 1
 
 
 class GramPlan(C.Structure):
-    _fields_ = [("ct", C.c_int64), ("xhat", C.c_int64), ("use_gram", C.c_int32), ("splits", C.c_int32),
+    _fields_ = [("ct", C.c_int64), ("xhat", C.c_int64), ("ttext", C.c_int64), ("cmax", C.c_int64), ("use_gram", C.c_int32), ("splits", C.c_int32),
                 ("st_per_split", C.c_int32), ("form", C.c_int32), ("Df", C.c_int32), ("delta", C.c_float)]
 
 
