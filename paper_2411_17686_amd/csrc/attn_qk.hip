@@ -719,12 +719,14 @@ static void launch_qk(QkArgs a, hipStream_t s) {
   constexpr int CH = (KS > 2 ? 2 : KS) * 4;
   const int tiles = (a.nq + kNormTile - 1) / kNormTile;
   a.q_groups = (tiles + kQkWaves - 1) / kQkWaves;
-  // Fewer than one workgroup per compute unit (for heads of 32, whose steps are short, four): one tile each, whose keys
-  // the wavefronts share.  Step of 16 x 577 tokens, whole tiles per wavefront and shared: one head of 64
-  // 52.7 and 47.6 us, three 55.5 and 54.8, four (256 workgroups) 57.4 and 59.5, twelve 76.6 and 88.4; heads of 32: one 49.5 and
-  // 45.9, eight 62.0 and 61.6, twelve 70.1 and 69.6.  One image of 577, one head 38.4 and 34.0; of 626, sixteen of 32
-  // 38.8 and 35.0.
-  a.share_keys = (int64_t)a.nb * a.H * a.q_groups < (KS == 1 ? 1024 : 256);
+  // Few workgroups: one tile each, whose keys the wavefronts share.  Fewer than one per compute unit for heads of 64, 192 for heads
+  // of 128, whose steps are longer, 640 for heads of 32.  us of the two kernels, whole tiles per wavefront and shared:
+  // heads of 64, 1 image of 577 tokens and 2 heads 20.0 / 14.6, 12 and 1 21.1 / 15.6, 16 of 197 and 6 (192 workgroups)
+  // 16.4 / 15.8, 12 of 577 and 12 (576) 35.4 / 43.8; of 128, 16 of 197 and 4 (128) 18.2 / 17.6, 12 of 577 and 4 (192) 34.3 / 38.0,
+  // 12 of 1025 and 3 (216) 54 / 69; of 32, 12 of 1025 and 4 (288) 39.4 / 34.3, 12 of 577 and 12 (576) 29.9 / 30.1, 20 (960) 39.4 / 43.0.
+  // Over 700 shapes, shared relative to whole by the number of workgroups: heads of 64 0.98 at 192 to 256 and 1.03 at 256 to 320; of
+  // 128 1.00 at 128 to 192 and 1.09 at 192 to 256; of 32 0.995 at 448 to 640 and 1.05 at 640 to 1024.
+  a.share_keys = (int64_t)a.nb * a.H * a.q_groups < (KS == 1 ? 640 : KS == 2 ? 256 : 192);
   if (a.share_keys) a.q_groups = tiles;
   const bool narrow = a.nq - (a.q_groups - 1) * (a.share_keys ? 1 : kQkWaves) * kNormTile <= 16;      // (as the kernel sees it)
   const int groups = a.q_groups - (narrow ? 1 : 0);
@@ -740,11 +742,14 @@ static void launch_qk(QkArgs a, hipStream_t s) {
     a.q_groups = (a.nq + Shape::kQueries - 1) / Shape::kQueries;
     hipLaunchKernelGGL(kern, dim3(xcd_padded_total(a.nb * a.q_groups * a.k_tiles)), dim3(Shape::kThreads), kLds, s, a);
   };
-  // Fewer than a workgroup of the wide form for every other compute unit: the heads of a tile are split instead
-  // (steps of 577 tokens, 16 heads, split and wide: two images, 90 workgroups, 40.0 and 43.8 us; three, 135 workgroups,
-  // 52.6 and 46.7; five, 225 workgroups, 54.9 and 49.1).
+  // Fewer than a workgroup of the wide form for every other compute unit: the heads of a tile are split instead, eight or more
+  // (with fewer, the sixteen wavefronts of a split tile cost more than the heads they share).  us of the two kernels, split and wide:
+  // one image of 577 tokens, 45 workgroups, 2 heads of 64 14.5 / 13.1, 8 15.8 / 16.7, 12 of 32 14.6 / 16.1; two images, 32 of 32
+  // 21.0 / 27.8; three, 135 workgroups, 8 of 64 25.6 / 19.2, 32 of 32 34.1 / 30.9.  Over 700 shapes, split relative to wide below 64 and
+  // at 64 to 128 workgroups: one head 1.20, 1.20; four 1.08, 1.08; six 1.06, 1.05; eight 1.00, 0.98; twelve 0.93, 0.90; 32 0.81, 0.77; at
+  // 160 and more wide is the better one up to twenty heads.
   const int wide = QkMeanShape<false>::kQueries;
-  const bool split = (int64_t)a.nb * ((a.nq + wide - 1) / wide) * a.k_tiles < 128;
+  const bool split = a.H >= 8 && (int64_t)a.nb * ((a.nq + wide - 1) / wide) * a.k_tiles < 128;
   if (split) mean(qk_mean_kernel<KS, DEC, true>, QkMeanShape<true>{});
   else mean(qk_mean_kernel<KS, DEC, false>, QkMeanShape<false>{});
 }

@@ -195,9 +195,9 @@ def test_unsupported_shapes_are_refused(ctx):
 @pytest.mark.parametrize("B,grid,H,d", [(1, 3, 2, 64), (2, 4, 9, 32), (1, 12, 3, 128), (2, 12, 8, 64), (16, 24, 3, 32), (40, 10, 2, 64),
                                         (3, 21, 5, 128)])
 def test_query_tiles_and_head_shares(ctx, B, grid, H, d):
-    """Edges of the two kernels' tiles (48 query rows, 96 and 192 side by side, 64 keys): one block of
-    queries in all, the [CLS] query alone behind whole tiles, fewer heads than shares, more than a
-    share's; few tiles (heads split over wavefronts) and many (not)."""
+    """Edges of the two kernels' tiles (48 query rows of the row normalisers, 64 or 128 of the head mean, 64 keys): one block of
+    queries in all, the [CLS] query alone behind whole tiles; few tiles (heads split over four groups of
+    wavefronts from eight heads on: 9 in shares of three, the last one without any, and 8) and many (not)."""
     full = _case(ctx, 300 + B + grid, B, grid, 72, H, d, "bf16", max(1, grid * grid // 3), 1.0)
     assert full >= (B + 1) // 2
 
@@ -205,15 +205,15 @@ def test_query_tiles_and_head_shares(ctx, B, grid, H, d):
 @pytest.mark.parametrize("B,grid,H,d", [(1, 8, 5, 64), (1, 9, 6, 128), (63, 9, 3, 64), (64, 9, 2, 128), (50, 16, 2, 64), (6, 18, 17, 128),
                                         (70, 10, 3, 32)])
 def test_tiles_of_64_and_128_queries_of_the_head_mean(ctx, B, grid, H, d):
-    """65 queries (a tile of 64 and one left), 82 (18 left, at 63 images the heads split, at 64 not), 257 (wide tiles and one
-    query left), 325 and 101 (a wide tile that is not full); fewer heads than shares, and a share that is shorter."""
+    """65 queries (a block of a wide tile and one query more), 82 (18 more), 257 (two wide tiles and one query left) and 101 (a wide
+    tile that is not full); 325 with 17 heads in tiles of 64, split (108 workgroups), of which 5 queries are left."""
     full = _case(ctx, 360 + B + grid, B, grid, 72, H, d, "bf16", max(1, grid * grid // 3), 1.0)
     assert full >= (B + 1) // 2
 
 
 @pytest.mark.parametrize("B,N,M,H,d", [(30, 230, 40, 2, 64), (1, 230, 40, 6, 128), (40, 100, 33, 3, 32)])
 def test_causal_tiles_of_64_and_128_queries(ctx, B, N, M, H, d):
-    """270 queries of which a block of 14 is left behind wide tiles, or behind tiles of 64 (split heads), and 133."""
+    """270 queries of which a block of 14 is left behind wide tiles, few heads on few tiles, and 133."""
     full = _case_l(ctx, 380 + B, B, 3, N, M, 72, H, d, N // 3, fc.R_ATTN_RECV, fc.C_ATTN)
     assert full >= (B + 1) // 2
 
@@ -221,8 +221,30 @@ def test_causal_tiles_of_64_and_128_queries(ctx, B, N, M, H, d):
 @pytest.mark.parametrize("B,grid,H,d", [(16, 24, 3, 64), (16, 24, 4, 64), (16, 14, 15, 32), (32, 14, 16, 32)])
 def test_keys_shared_by_the_wavefronts_or_not(ctx, B, grid, H, d):
     """192 and 256 workgroups of the row normalisers with heads of 64, 480 and 1024 with heads of 32: below 256
-    and 1024 the wavefronts of a workgroup share the keys of a query tile."""
+    and 640 the wavefronts of a workgroup share the keys of a query tile."""
     full = _case(ctx, 330 + B + H, B, grid, 72, H, d, "bf16", grid * grid // 3, 1.0)
+    assert full >= (B + 1) // 2
+
+
+@pytest.mark.parametrize("B,grid,H,d", [(16, 14, 5, 128), (16, 14, 6, 128), (13, 14, 24, 32), (20, 14, 16, 32)])
+def test_keys_shared_at_the_other_head_sizes(ctx, B, grid, H, d):
+    """160 and 192 workgroups with heads of 128 (shared below 192), 624 and 640 with heads of 32 (below 640)."""
+    full = _case(ctx, 350 + B + H, B, grid, 72, H, d, "bf16", grid * grid // 3, 1.0)
+    assert full >= (B + 1) // 2
+
+
+@pytest.mark.parametrize("B,grid,H,d", [(1, 8, 7, 64), (1, 8, 8, 64), (1, 8, 9, 64), (1, 9, 10, 128), (1, 16, 11, 64), (2, 10, 13, 32), (8, 18, 17, 128)])
+def test_heads_split_from_eight_on(ctx, B, grid, H, d):
+    """Few tiles: seven heads together, eight and more in four shares of two to four, the last one empty (9) or shorter (10, 11, 13);
+    65, 82, 257 and 101 queries in tiles of 64 (one, 18, one and 37 left); 144 workgroups (not split)."""
+    full = _case(ctx, 390 + B + H, B, grid, 72, H, d, "bf16", max(1, grid * grid // 3), 1.0)
+    assert full >= (B + 1) // 2
+
+
+@pytest.mark.parametrize("B,N,M,H,d", [(1, 230, 40, 9, 128), (2, 100, 33, 8, 32), (1, 61, 40, 13, 64)])
+def test_causal_heads_split(ctx, B, N, M, H, d):
+    """270 queries in tiles of 64 (a block of 14 left), 133 (5 left) and 101 (37 left), heads in shares."""
+    full = _case_l(ctx, 400 + B + H, B, 3, N, M, 72, H, d, N // 3, fc.R_ATTN_RECV, fc.C_ATTN)
     assert full >= (B + 1) // 2
 
 
