@@ -8,7 +8,7 @@ images, [CLS] + 24x24 patches (N = 576), D = 1024, 16 heads, bfloat16; keep 384 
 "step" is one call of ficoco_v_step / ficoco_l_step on the whole batch: attention reduction,
 score + local penalty, top-K filter, correlate / threshold / weights, compress.  Inputs are
 synthetic, seeded, resident in HBM before the timed region; steps rotate over several distinct
-input sets whose total size exceeds the 256 MB on-die cache, and alternate between two HIP
+input sets whose total size exceeds the 256 MB on-die cache, and go round three HIP
 streams (independent batches: the latency-bound tail of one step overlaps the bandwidth-bound
 head of the next; --streams 1 runs them strictly one after the other).
 
@@ -252,6 +252,10 @@ def _oracle_worker(job):
                          n_keep=kw["n_keep"], lam=kw["w_score"], eps=kw["eps"], grid=kw["grid"], window=2, coef=2.0,
                          recv_vec=sq["recv_vec"], sem_vec=sq["sem_vec"], red_src=job["red"], sem_src=job["sem"],
                          corr_src=job["cor"], **okw)
+            elif job["variant"] == "LQ":
+                O.l_step_qk(sq["X"], sq["Q"], sq["K"], job["qk_scale"], vis_begin=kw["vis_begin"], N=kw["N"], M=kw["M"],
+                            n_keep=kw["n_keep"], beta=kw["w_score"], gamma=kw["gamma"], eps=kw["eps"], red_src=job["red"],
+                            corr_src=job["cor"], **okw)
             else:
                 O.l_step(sq["X"], sq["A"], sq["A_text"], vis_begin=kw["vis_begin"], N=kw["N"], n_keep=kw["n_keep"],
                          beta=kw["w_score"], gamma=kw["gamma"], eps=kw["eps"], red_src=job["red"], corr_src=job["cor"], **okw)
@@ -298,9 +302,9 @@ def cpu_baseline(W, pool, n_workers, budget=7.0):
 
     seqs = [dict(X=host("X", b), A=host("A", b), A_text=host("A_text", b), recv_vec=host("recv_vec", b),
                  sem_vec=host("sem_vec", b), Q=host("Q", b), K=host("K", b)) for b in range(B)]
-    job = dict(variant=("VQ" if st.get("Q") is not None else "V") if W["variant"] == fc.VARIANT_V else "L",
+    job = dict(variant=("V" if W["variant"] == fc.VARIANT_V else "L") + ("Q" if st.get("Q") is not None else ""),
                qk_scale=float(W.get("d_head", 64)) ** -0.5,
-               kw={k: v for k, v in kw.items() if k in ("cls_index", "vis_begin", "N", "n_keep", "w_score", "eps", "grid", "gamma")},
+               kw={k: v for k, v in kw.items() if k in ("cls_index", "vis_begin", "N", "n_keep", "w_score", "eps", "grid", "gamma", "M")},
                red={fc.R_ATTN_RECV: "attn", fc.R_VECTOR: "vector", fc.R_SIM_MEAN: "sim_mean"}[kw.get("red_src", fc.R_ATTN_RECV)],
                sem={fc.G_CLS_ATTN: "cls", fc.G_VECTOR: "vector", fc.G_TEXT_ATTN: "cls"}[kw.get("sem_src", fc.G_CLS_ATTN)],
                cor={fc.C_ATTN: "attn", fc.C_COSINE: "cosine"}[kw.get("corr_src", fc.C_ATTN)],
