@@ -394,7 +394,7 @@ template <int KS, bool DEC, bool SPLIT>
 __global__ __launch_bounds__(QkMeanShape<SPLIT>::kThreads) __attribute__((amdgpu_waves_per_eu(SPLIT ? 4 : KS == 4 ? 2 : 3))) void qk_mean_kernel(QkArgs a) {
   constexpr int KSS = KS > 2 ? 2 : KS, NST = KS / KSS, CH = KSS * 4, KT = KSS * 2;     // 32-feature steps of a stage, stages of a head, instructions of a block and stage
   using Shape = QkMeanShape<SPLIT>;
-  constexpr int MB = Shape::kBlocks, QR = Shape::kQueries;                // query rows of a stage
+  constexpr int MB = Shape::kBlocks, QR = Shape::kQueries, kWaves = Shape::kThreads / kWave;    // QR: query rows of a stage
   constexpr int T = kQkWaves * kWave, RPI = T / CH, NL = (QR + kQkKeys) / RPI;   // rounds of RPI rows
   static_assert((QR + kQkKeys) % RPI == 0 && QR % RPI == 0, "whole rounds of queries and of keys");
   extern __shared__ u32x4_t stage_m[];                 // [2][shares][rows of a stage], then the queries' normalisers
@@ -413,7 +413,11 @@ __global__ __launch_bounds__(QkMeanShape<SPLIT>::kThreads) __attribute__((amdgpu
   const int band_w = min(kQkBand, a.k_tiles - band * kQkBand);
   const int kt0 = band * kQkBand + in_band % band_w;
   const int w0 = in_band / band_w * QR;
-  const bool narrow = a.nq - w0 <= kQkB;               // one block of queries in all (uniform)
+  // One block of queries in all (uniform): the wavefronts share its heads, with operands straight from memory, unless the tile is
+  // split anyway and a wavefront's share is four 32-feature steps or more: then rows through LDS are faster.  us, so and
+  // as any other tile: 8 x 16 text queries, 32 heads of 128 25.3 / 21.4, 24 queries 26.7 / 21.5, one image of 16 and 16 heads 15.6 / 13.9, 8 x 20 and
+  // 32 heads of 64 16.0 / 15.6; but 8 x 24 and 16 heads of 64 12.3 / 12.6, 8 heads 9.1 / 10.7, and not split 16 x 401 queries 19.9 / 20.9.
+  const bool narrow = a.nq - w0 <= kQkB && !(SPLIT && KS * ((a.H + kWaves - 1) / kWaves) >= 4);
   const int q0 = narrow ? 0 : wq * MB * kQkB, v0 = w0 + q0;
   const int wk0 = kt0 * kQkKeys, ik0 = wk0 + wk * kQkB;       // first visual key of the stage, of this wavefront
   const int per = (a.H + Shape::kShares - 1) / Shape::kShares;            // heads of a share (the last may have fewer)
@@ -639,7 +643,7 @@ __global__ __launch_bounds__(QkMeanShape<SPLIT>::kThreads) __attribute__((amdgpu
   if (narrow) {
     // The wavefronts take consecutive shares of the heads,
     // operands straight from memory, and their sums are added pairwise (a fixed tree).
-    constexpr int W = Shape::kThreads / kWave;
+    constexpr int W = kWaves;
     f32x16_t P1[2];
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb) P1[kb] = qk_zero();

@@ -248,6 +248,14 @@ def test_causal_heads_split(ctx, B, N, M, H, d):
     assert full >= (B + 1) // 2
 
 
+@pytest.mark.parametrize("M,H,d", [(1, 32, 128), (16, 16, 128), (17, 9, 128), (32, 32, 64), (31, 17, 64), (32, 16, 64), (5, 64, 32), (33, 40, 32)])
+def test_one_block_of_text_queries(ctx, M, H, d):
+    """At most 32 text queries alone, heads split: by wavefronts that share the heads, or (four 32-feature steps a wavefront and
+    more) as any other tile; one query more."""
+    full = _case_l(ctx, 420 + M + H, 2, 5, 90, M, 72, H, d, 30, fc.R_SIM_MEAN, fc.C_COSINE)
+    assert full >= 1
+
+
 @pytest.mark.parametrize("grid,H,d,where", [(24, 2, 64, 500), (24, 2, 64, 40), (12, 3, 32, 144), (30, 1, 128, 33), (3, 2, 64, 9)])
 def test_logits_far_above_those_of_the_first_keys(ctx, grid, H, d, where):
     """Rows whose largest logit lies 100 to 300 (units of e) above those of the keys the softmax
