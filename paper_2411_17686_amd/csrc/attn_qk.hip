@@ -424,13 +424,21 @@ __global__ __launch_bounds__(QkMeanShape<SPLIT>::kThreads) __attribute__((amdgpu
   const int h_lo = min(share * per, a.H), h_hi = min(h_lo + per, a.H);
   // (decoder: a tile all of whose keys lie behind its queries is zero)
   const bool wg_dead = DEC && a.vis0 + wk0 > a.row(min(w0 + QR, a.nq) - 1);
+  // Wavefronts of a last tile that have one block of queries (of 65 to 96: behind 576 visual ones the [CLS] query) add the heads up in
+  // quarters: the sums so far are kept in the registers of the other block, where nothing else is added.  With all heads one
+  // after the other in single precision the [CLS] row, which weighs most, had more error than in the forms before, where its heads
+  // were shared by wavefronts: scores against 64 bits, 16 heads of 64, 577 tokens 1.40e-7, before 1.23e-7, so 1.13e-7; 2881 1.57, 1.26 and
+  // 1.26e-7.  (That block as a tile of its own is a fifth more workgroups at 577 tokens: 16 images 27 -> 36 us instead of 27.4.)
+  const bool with_lone = !SPLIT && !DEC && !narrow && a.nq - w0 > kQkTile && a.nq - w0 <= kQkTile + kQkB;      // uniform in the workgroup
+  const bool lone = with_lone && q0 > 0;
   const bool active = v0 < a.nq && !(DEC && a.vis0 + ik0 > a.row(min(v0 + MB * kQkB, a.nq) - 1));
 
   f32x16_t P[MB];
 #pragma unroll
   for (int m = 0; m < MB; ++m) P[m] = qk_zero();
 
-  auto heads = [&]() __attribute__((always_inline)) {
+  auto heads = [&](auto fold) __attribute__((always_inline)) {
+    constexpr bool kFold = decltype(fold)::value;
     const int t = tid % T;
     u32x4_t* area = stage_m + share * kArea;
     constexpr int kBuf = Shape::kShares * kArea;
@@ -456,7 +464,14 @@ __global__ __launch_bounds__(QkMeanShape<SPLIT>::kThreads) __attribute__((amdgpu
         load_to_lds(src[i] + off, area + buf * kBuf + i * T + wv % kQkWaves * kWave);
     };
     auto load_nf = [&](int h) { next_nf = (nrm + (int64_t)h * a.nq)[nrm_at]; };
-    auto store_nf = [&](int par) { if (t < QR) nf_area[par * Shape::kShares * QR + t] = next_nf; };
+    const int counted = w0 + t < a.nq ? -1 : 0;        // (rows past the last query, staged as that one again, add nothing)
+    auto store_nf = [&](int par) {
+      if (t < QR) {
+        float2 v = next_nf;
+        if (kFold) v.y = __int_as_float(__float_as_int(v.y) & counted);
+        nf_area[par * Shape::kShares * QR + t] = v;
+      }
+    };
     const int cnt = h_hi - h_lo, last = max(cnt - 1, 0), h0 = min(h_lo, a.H - 1);
     auto head = [&](int i) { return h0 + min(i, last); };               // (past the last head: that one again)
 
@@ -564,16 +579,23 @@ __global__ __launch_bounds__(QkMeanShape<SPLIT>::kThreads) __attribute__((amdgpu
     store_nf(0);
     load_nf(head(1));
     loaded_to_lds();
+    const int quarter = kFold ? (per + 7) / 8 * 2 : per;      // even
+    int i = 0;
 #pragma unroll 1
-    for (int i = 0; i < per; i += 2) {
-      if (DEC) { }                                     // (as in the normalisers; causal maps 48.5 us without, 49.9 with)
-      else if (i == 0) __builtin_amdgcn_s_setprio(3);
-      else if (i == per / 4 * 2) __builtin_amdgcn_s_setprio(2);
-      else if (i == per * 3 / 8 * 2) __builtin_amdgcn_s_setprio(1);
-      else if (i == per * 7 / 16 * 2) __builtin_amdgcn_s_setprio(0);
-      step(i, std::integral_constant<int, 0>{});
-      if (i + 1 < per) step(i + 1, std::integral_constant<int, 1>{});
-    }
+    do {
+      const int to = min(i + quarter, per);
+#pragma unroll 1
+      for (; i < to; i += 2) {
+        if (DEC) { }                                   // (as in the normalisers; causal maps 48.5 us without, 49.9 with)
+        else if (i == 0) __builtin_amdgcn_s_setprio(3);
+        else if (i == per / 4 * 2) __builtin_amdgcn_s_setprio(2);
+        else if (i == per * 3 / 8 * 2) __builtin_amdgcn_s_setprio(1);
+        else if (i == per * 7 / 16 * 2) __builtin_amdgcn_s_setprio(0);
+        step(i, std::integral_constant<int, 0>{});
+        if (i + 1 < per) step(i + 1, std::integral_constant<int, 1>{});
+      }
+      if (kFold && lone) { P[MB - 1] += P[0]; P[0] = qk_zero(); }      // uniform in the wavefront
+    } while (i < per);
     if (active) {                                      // what is left: the last block, or the last head's blocks
       if constexpr (NST == 1 && MB == 2) {
         add(S[1][0], nf[1], P[1]);
@@ -697,7 +719,14 @@ __global__ __launch_bounds__(QkMeanShape<SPLIT>::kThreads) __attribute__((amdgpu
     return;
   }
 
-  if (!wg_dead) heads();                                // uniform in the workgroup
+  if (!wg_dead) {                                       // uniform in the workgroup
+    if constexpr (!SPLIT && !DEC) {
+      if (with_lone) heads(std::integral_constant<bool, true>{});      // (a copy of the loop: what it needs cost all others 4 % of the kernel)
+      else heads(std::integral_constant<bool, false>{});
+    } else {
+      heads(std::integral_constant<bool, false>{});
+    }
+  }
   if constexpr (SPLIT) {
     f32x16_t* sums = (f32x16_t*)stage_m;              // (the staging areas are free)
 #pragma unroll
@@ -714,6 +743,7 @@ __global__ __launch_bounds__(QkMeanShape<SPLIT>::kThreads) __attribute__((amdgpu
     if (share != 0 || wq != 0) return;
     write_out(std::integral_constant<int, 2>{}, w0, ik0, P[0], sums[wk * kWave + lane]);
   } else {
+    if (lone) P[0] += P[MB - 1];
     if (v0 < a.nq) write_out(std::integral_constant<int, 2>{}, v0, ik0, P[0], P[MB - 1]);
   }
 }
