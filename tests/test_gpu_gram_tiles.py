@@ -1,7 +1,7 @@
-"""Cosine correlation of batches whose products take the wide tiles (at least 128 tiles of 192 x 192, or of 256 x 192
-where those are one round of workgroups instead of two): rows and columns that fill a tile, miss it by one and pass it
-by one, and feature counts of less than a stage of 64, whole stages (one to five, three or two of them in flight) and
-stages with a remainder."""
+"""Cosine correlation of batches with many tiles of approximate values (128 x 128, 192 x 192 or 256 x 192, by an estimate of their
+time): rows and columns that fill a tile, miss it by one and pass it by one, feature counts of less than a stage, whole
+stages and stages with a remainder, several K ranges.  These are outputs of whole steps; the tiles' own values, which
+outputs need not show, are compared in test_gpu_gram_block.py."""
 import pytest
 
 from paper_2411_17686_amd import ficoco as fc
