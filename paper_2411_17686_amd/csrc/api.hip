@@ -30,14 +30,28 @@ struct ficoco_ctx {
 
 namespace ficoco {
 
-// With the head-mean map to store, a reduction workgroup has at most 8 row lanes and chunks of a
-// multiple of 8 rows (measured at the 576-token batched shape: 8 lanes x 32 rows, ~900 workgroups,
-// gives the best pipelined step; 10 lanes x 24 rows is 10 % slower alone).
-constexpr int kMapRowLanes = 8;
-constexpr int kMapRowsAlign = 8;
-// Workgroups the reduction aims at (half of it where the map tile is turned).  Measured: 1024 against
-// 2048 changes nothing at the batched ViT shapes and gives the decoder shape (8 sequences, 32 heads)
-// 32-row chunks instead of 16-row ones, 42.5 against 44.0 us.
+// Row lanes, 8-column groups (at most) and rows of a reduction workgroup with the head-mean map to store, whose chunks are
+// multiples of 8 rows (whole 32-byte sectors of the transposed map).  Chunks of 32 rows: their partials all pass through the
+// one workgroup of the filter, and the pieces of the transposed map are whole cache lines.  Then 32 lanes x 8 groups, a row a
+// thread, which takes one trip to memory for up to sixteen loads; 16 x 16, two rows, where a row's heads are fewer than eight loads
+// or more than sixteen and there are workgroups enough, and where there are very many (longer pieces of the rows).
+// us per step in bfloat16 before (8 x 24, rows for 512 workgroups) / 8 x 24 and 32 rows / 16 x 16 / 32 x 8:
+//   16 heads, 1 x 576 tokens 29.5 / 29.7 / 27.6 / 24.9, 5 x 576 35.2 / 36.1 / 33.8 / 33.5, 16 x 576 73.0 / 73.0 / 73.2 / 73.6, 4 x 2880 314 / 314 / 311 / 321;
+//   8 heads, 1 x 576 28.2 / 27.1 / 25.3 / 23.2, 8 x 576 34.6 / 34.7 / 34.0 / 33.3, 8 x 1200 95.2 / 95.5 / 94.1 / 93.6;
+//   4 heads, 1 x 576 28.3 / 25.7 / 25.1 / 23.9, 8 x 576 32.3 / 32.2 / 31.1 / 32.2, 40 x 576 74.1 / 74.2 / 73.1 / 76.0.
+// Short sequences have few chunks either way: 8 rows while every workgroup has a compute unit of its own, then 16 (3 images of
+// 221, 8 rows of 8 lanes / 16 of 16 / 32 of 32: 22.1 / 22.8 / 23.1; 8 images 24.4 / 23.5 / 25.2).
+struct MapShape { int lanes, groups, rows; };
+static MapShape map_shape(const ficoco_problem& p) {
+  const int groups = (p.N + kVec - 1) / kVec;
+  auto wgs = [&](int g, int r) { return (int64_t)p.B * ((groups + g - 1) / g) * ((p.N + r - 1) / r); };
+  if (p.N <= 256 && wgs(24, 8) <= 256) return {8, 24, 8};
+  if (p.N <= 256 && wgs(16, 16) <= 512) return {16, 16, 16};
+  const int64_t most = wgs(8, 32);
+  const int loads = p.dtype == FICOCO_BF16 ? p.H : 2 * p.H;
+  return most <= 700 || (loads >= 8 && loads <= 16 && most <= 6000) ? MapShape{32, 8, 32} : MapShape{16, 16, 32};
+}
+// Workgroups the reduction aims at where it has no such map to store.
 constexpr int64_t kWgTarget = 1024;
 
 static size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -150,27 +164,27 @@ int make_plan(const ficoco_problem& p, Plan& pl, const char** why, size_t scratc
   // (with the head-mean map to store, strips stay narrow at any width: the workgroup turns its
   // tile of the map in LDS, strip columns x chunk rows)
   const bool map_tile = p.corr_src == FICOCO_C_ATTN;
-  {
-    const int max_groups = groups <= 128 ? 24 : (map_tile ? 32 : kReduceThreads);
+  const MapShape ms = map_shape(p);
+  if (map_tile) {
+    pl.col_strips = (groups + ms.groups - 1) / ms.groups;
+    pl.strip_groups = (groups + pl.col_strips - 1) / pl.col_strips;
+    pl.row_lanes = ms.lanes;
+  } else {
+    const int max_groups = groups <= 128 ? 24 : kReduceThreads;
     const int s_min = std::max((groups + kReduceThreads - 1) / kReduceThreads, (groups + max_groups - 1) / max_groups);
     int best_busy = -1;
     for (int sN = s_min; sN < s_min + 8; ++sN) {
       const int sg = (groups + sN - 1) / sN;
-      int rl = kReduceThreads / sg;
-      if (map_tile) rl = std::min(rl, kMapRowLanes);
+      const int rl = kReduceThreads / sg;
       if (rl * sg > best_busy) { best_busy = rl * sg; pl.col_strips = sN; pl.strip_groups = sg; pl.row_lanes = rl; }
       if (best_busy * 5 >= kReduceThreads * 4) break;
     }
   }
   auto rows_per_wg = [&](int rows) {
-    // aim at ~kWgTarget workgroups; half as many where the map tile is turned (longer chunks make
-    // whole cache lines of the transposed pieces, and a reduction that does not fill every
-    // wavefront slot leaves room for the short kernels of the neighbouring streams)
-    const int64_t target = map_tile ? kWgTarget / 2 : kWgTarget;
-    int64_t want = ((int64_t)p.B * pl.col_strips * rows + target - 1) / target;
-    if (want < 1) want = 1;
-    int r = (int)((want + pl.row_lanes - 1) / pl.row_lanes) * pl.row_lanes;
-    return r;
+    if (map_tile) return ms.rows;
+    // aim at ~kWgTarget workgroups
+    const int64_t want = std::max<int64_t>(((int64_t)p.B * pl.col_strips * rows + kWgTarget - 1) / kWgTarget, 1);
+    return (int)((want + pl.row_lanes - 1) / pl.row_lanes) * pl.row_lanes;
   };
   pl.qk = qk;
   if (qk) {
@@ -196,7 +210,6 @@ int make_plan(const ficoco_problem& p, Plan& pl, const char** why, size_t scratc
       // The head-mean map is stored transposed, a chunk's rows of one key column as one piece:
       // chunks of a multiple of 8 rows that start at multiples of it, counted from visual row 0,
       // make every piece whole 32-byte sectors.
-      pl.rows_per_wg = std::min((pl.rows_per_wg + kMapRowsAlign - 1) / kMapRowsAlign * kMapRowsAlign, 32);    // the tile is at most 256 columns x that many rows
       const int lead = (p.vis_begin - p.a_q_begin) - lo;             // role rows before visual row 0 (the [CLS] query)
       pl.a_shift = (pl.rows_per_wg - lead % pl.rows_per_wg) % pl.rows_per_wg;
     }

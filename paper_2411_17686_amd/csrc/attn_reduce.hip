@@ -21,6 +21,8 @@ constexpr int kRowsAtOnce = 4;     // rows of one thread whose heads are added s
 constexpr int kHeadsAtOnce = 2;    // ... this many heads of each per batch of loads (more where the thread has fewer rows)
 
 
+__host__ __device__ __forceinline__ int reduce_pad(int N) { return N > kVec && N % kVec != 0 ? kVec : 0; }
+
 template <typename T>
 __device__ __forceinline__ void attn_reduce_block(const AttnArgs& a, int block, double* lds) {
   // Workgroups that read neighbouring strips of the same rows share the cache lines at the
@@ -33,18 +35,21 @@ __device__ __forceinline__ void attn_reduce_block(const AttnArgs& a, int block, 
   const int b = logical / (a.col_strips * a.n_chunks);
   const int tid = threadIdx.x;
   const int cg = tid % a.strip_groups, rl = tid / a.strip_groups;
-  const int col = (strip * a.strip_groups + cg) * kVec;
+  const int width = a.strip_groups * kVec;
+  const int col_own = (strip * a.strip_groups + cg) * kVec;
+  // The last group of a ragged map takes the last eight columns, some of them the neighbouring group's too (both leave
+  // the same bits there): column by column its loads are a chain of trips to memory, 60 of them at 12 heads and
+  // 13 x 17 columns, where the launch took 12.5 us and 7.3 so.  Only maps of fewer than eight columns go that way.
+  const int col = a.N >= kVec && col_own < a.N ? min(col_own, a.N - kVec) : col_own;
   const int ncol = min(kVec, a.N - col);
   const bool active = rl < a.row_lanes && ncol > 0;
-
-  // Where this thread leaves its column partial for the combination of the row lanes.
-  const int width = a.strip_groups * kVec;
-  double* mine = lds + (rl < a.row_lanes ? rl : 0) * width + cg * kVec;
+  const int pad = reduce_pad(a.N);                // columns before the strip's first that its first group may reach into
+  const int first = pad - strip * width, lpitch = width + pad;      // (column `col` lies at first + col of the workgroup's)
 
   // The head-mean map leaves transposed (abar[key token][query token], what the correlate stage
   // reads row by row): this workgroup's tile, strip columns x chunk rows, is turned in LDS and
   // written as one piece of rows_per_wg floats per key column.
-  float* tile = (float*)(lds + a.row_lanes * width);
+  float* tile = (float*)(lds + a.row_lanes * lpitch);
   const int tile_pitch = a.rows_per_wg + 1;           // odd: the 8 columns of a lane fall into different banks
   const int r_begin = a.row0 + chunk * a.rows_per_wg - a.shift;   // chunk 0 may begin before row0
   const int r_end = min(r_begin + a.rows_per_wg, a.row0 + a.nrows);
@@ -63,7 +68,7 @@ __device__ __forceinline__ void attn_reduce_block(const AttnArgs& a, int block, 
 #pragma unroll
       for (int k = 0; k < kVec; ++k) colsum[k] += p[k];
       if (a.abar) {
-        float* dst = tile + (cg * kVec) * tile_pitch + (r - r_begin);
+        float* dst = tile + (first + col) * tile_pitch + (r - r_begin);
 #pragma unroll
         for (int k = 0; k < kVec; ++k) dst[k * tile_pitch] = (float)p[k];   // columns past N are never read back
       }
@@ -88,7 +93,7 @@ __device__ __forceinline__ void attn_reduce_block(const AttnArgs& a, int block, 
       // ROWS = rows of this thread (compile time: the accumulators are registers)
       auto run = [&](auto rows_c) __attribute__((always_inline)) {
         constexpr int ROWS = decltype(rows_c)::value;
-        constexpr int HEADS = ROWS >= 3 ? kHeadsAtOnce : kHeadBatch / ROWS;   // about kHeadBatch loads in flight
+        constexpr int HEADS = ROWS >= 3 ? kHeadsAtOnce : ROWS == 2 ? 4 : 16;   // loads in flight: 8 (16 with two rows spill), with one row 16
         double p[ROWS][kVec];
         const T* base[ROWS];
 #pragma unroll
@@ -98,22 +103,34 @@ __device__ __forceinline__ void attn_reduce_block(const AttnArgs& a, int block, 
 #pragma unroll
           for (int k = 0; k < kVec; ++k) p[q][k] = 0.0;
         }
-        for (int h0 = 0; h0 < a.H; h0 += HEADS) {
-          Raw8<T> raw[HEADS][ROWS];
+        auto add_heads = [&](auto heads_c, int h0) __attribute__((always_inline)) {
+          constexpr int N_H = decltype(heads_c)::value;
+          Raw8<T> raw[N_H][ROWS];
 #pragma unroll
-          for (int u = 0; u < HEADS; ++u) {
+          for (int u = 0; u < N_H; ++u) {
             const int64_t hoff = (int64_t)min(h0 + u, a.H - 1) * a.sh;
 #pragma unroll
             for (int q = 0; q < ROWS; ++q) load_raw(base[q] + hoff, raw[u][q]);
           }
           issue_fence();
 #pragma unroll
-          for (int u = 0; u < HEADS; ++u)
+          for (int u = 0; u < N_H; ++u)
 #pragma unroll
             for (int q = 0; q < ROWS; ++q) {
               keep_raw_if(raw[u][q], h0 + u < a.H);
               add_raw(raw[u][q], p[q]);
             }
+        };
+        // (what is left over is a batch of about its own size: heads past the last would be loads for nothing)
+        int h0 = 0;
+        if constexpr (ROWS >= 3) {
+          for (; h0 < a.H; h0 += HEADS) add_heads(std::integral_constant<int, HEADS>{}, h0);
+        } else {
+          constexpr int Q = HEADS / 4;
+          for (; a.H - h0 > 3 * Q; h0 += HEADS) add_heads(std::integral_constant<int, HEADS>{}, h0);
+          if (a.H - h0 > 2 * Q) add_heads(std::integral_constant<int, 3 * Q>{}, h0);
+          else if (a.H - h0 > Q) add_heads(std::integral_constant<int, 2 * Q>{}, h0);
+          else if (a.H - h0 > 0) add_heads(std::integral_constant<int, Q>{}, h0);
         }
 #pragma unroll
         for (int q = 0; q < ROWS; ++q) {
@@ -127,7 +144,7 @@ __device__ __forceinline__ void attn_reduce_block(const AttnArgs& a, int block, 
 #pragma unroll
               for (int k = 0; k < kVec; ++k) colsum[k] += p[q][k];      // rows in ascending order, from zero
               if (a.abar) {
-                float* dst = tile + (cg * kVec) * tile_pitch + (r - r_begin);
+                float* dst = tile + (first + col) * tile_pitch + (r - r_begin);
 #pragma unroll
                 for (int k = 0; k < kVec; ++k) dst[k * tile_pitch] = (float)p[q][k];
               }
@@ -192,7 +209,8 @@ __device__ __forceinline__ void attn_reduce_block(const AttnArgs& a, int block, 
     }
   }
 
-  if (rl < a.row_lanes) {
+  if (rl < a.row_lanes) {      // this thread's column partial, for the combination of the row lanes
+    double* mine = lds + rl * lpitch + first + col;
 #pragma unroll
     for (int k = 0; k < kVec; ++k) mine[k] = colsum[k];
   }
@@ -207,7 +225,7 @@ __device__ __forceinline__ void attn_reduce_block(const AttnArgs& a, int block, 
     const int n_cols = min(width, a.N - strip_col0);
     for (int q = tid; q < n_cols * pieces; q += (int)blockDim.x) {
       const int c = q / pieces, v0 = (q % pieces) * 4;
-      const float* src = tile + c * tile_pitch + v0;
+      const float* src = tile + (pad + c) * tile_pitch + v0;
       float* dst = a.abar + ((int64_t)b * a.N + strip_col0 + c) * a.map_pitch + v_begin + v0;
       if (v_begin + v0 >= 0 && v_begin + v0 + 4 <= v_end) {
         const float4 o = make_float4(src[0], src[1], src[2], src[3]);
@@ -225,15 +243,15 @@ __device__ __forceinline__ void attn_reduce_block(const AttnArgs& a, int block, 
   const int strip_col0 = strip * width;
   for (int c = tid; c < width && strip_col0 + c < a.N; c += (int)blockDim.x) {
     double s = 0.0;
-    for (int l = 0; l < a.row_lanes; ++l) s += lds[l * width + c];
+    for (int l = 0; l < a.row_lanes; ++l) s += lds[l * lpitch + pad + c];
     a.recv_part[((int64_t)b * a.n_chunks + chunk) * a.N + strip_col0 + c] = s;
   }
 }
 
-// Three wavefronts per SIMD (170 registers): the four-row form keeps 32 double accumulators and 8
-// raw vectors per thread, and its grids hold about three wavefronts per SIMD anyway.
+// bfloat16: four wavefronts per SIMD (128 registers: in the four-row form 32 double accumulators and 8 raw vectors per
+// thread; one more left 64 maps of 288 tokens, four heads, 6 % slower).
 template <typename T>
-__global__ __launch_bounds__(kReduceThreads) __attribute__((amdgpu_waves_per_eu(3))) void attn_reduce_kernel(AttnArgs a) {
+__global__ __launch_bounds__(kReduceThreads) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 2 ? 4 : 3))) void attn_reduce_kernel(AttnArgs a) {
   extern __shared__ double lds[];
   attn_reduce_block<T>(a, blockIdx.x, lds);
 }
@@ -253,7 +271,7 @@ __global__ __launch_bounds__(256) void text_reduce_kernel(AttnArgs a) {
 // still the faster (step, one launch against two: 8 x 32 heads x 640 x 576 144 and 145 us, 2 such images 54 and
 // 59, 8 x 32 x 656 x 400 88 and 95, one image 46 and 51); at four, with spills, it is not (151, 58, 105, 51).
 template <typename T>
-__global__ __launch_bounds__(kReduceThreads) __attribute__((amdgpu_waves_per_eu(3))) void attn_text_reduce_kernel(AttnArgs a, AttnArgs t, int tx, int ty, int text_blocks) {
+__global__ __launch_bounds__(kReduceThreads) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 2 ? 4 : 3))) void attn_text_reduce_kernel(AttnArgs a, AttnArgs t, int tx, int ty, int text_blocks) {
   extern __shared__ double lds[];
   const int block = blockIdx.x;
   if (block >= text_blocks) {
@@ -268,8 +286,9 @@ static void launch_block(const ficoco_problem& p, const AttnArgs& a, const AttnA
   AttnArgs g = a;
   g.col_strips = col_strips; g.B = B;
   dim3 grid(xcd_padded_total(a.n_chunks * col_strips * B)), block(std::min(kReduceThreads, (a.row_lanes * a.strip_groups + kWave - 1) / kWave * kWave));
-  size_t lds = (size_t)a.row_lanes * a.strip_groups * kVec * sizeof(double);
-  if (a.abar) lds += (size_t)a.strip_groups * kVec * (a.rows_per_wg + 1) * sizeof(float);   // the tile that is turned
+  const size_t columns = (size_t)a.strip_groups * kVec + reduce_pad(a.N);
+  size_t lds = a.row_lanes * columns * sizeof(double);
+  if (a.abar) lds += columns * (a.rows_per_wg + 1) * sizeof(float);   // the tile that is turned
   if (text) {
     const dim3 tgrid = text_grid(p);
     const int blocks = xcd_padded_total((int)(tgrid.x * tgrid.y * tgrid.z));

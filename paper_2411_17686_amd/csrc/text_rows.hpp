@@ -41,15 +41,18 @@ constexpr int kTextHeadBatch = 16;
 constexpr int kTextRows = 8;
 using TextTile = double[kTextRows + 1];           // one column's rows; +1: the rows of one column in different banks
 constexpr int kTextGroups = 256 / kTextRows;      // 8-column groups per workgroup
-constexpr int kTextTiles = kTextGroups * kVec;    // the LDS it needs: TextTile[kTextTiles]
+constexpr int kTextTiles = kTextGroups * kVec + kVec;    // the LDS it needs: TextTile[kTextTiles], the first kVec for columns before the strip
 template <typename T>
 __device__ __forceinline__ void text_reduce_block(const AttnArgs& a, int chunk, int strip, int64_t b, TextTile* tile) {
   const int tid = threadIdx.x;
   const int cg = tid % kTextGroups, rl = tid / kTextGroups;
   const int row = chunk * kTextRows + rl;
   const int col0 = strip * kTextGroups * kVec;
-  const int col = col0 + cg * kVec;
+  // (the last group of a ragged block takes the last eight columns, as in the kernel above)
+  const int col_own = col0 + cg * kVec;
+  const int col = a.N >= kVec && col_own < a.N ? min(col_own, a.N - kVec) : col_own;
   const int ncol = max(min(kVec, a.N - col), 0);
+  tile += kVec;
   if (row < a.M && ncol > 0) {
     const T* base = (const T*)a.A + b * a.sb + (int64_t)row * a.sq + a.col0 + col;
     double p[kVec];
@@ -84,7 +87,7 @@ __device__ __forceinline__ void text_reduce_block(const AttnArgs& a, int chunk, 
         for (int k = 0; k < ncol; ++k) p[k] += widen(base[(int64_t)h * a.sh + k]);
     }
 #pragma unroll
-    for (int k = 0; k < kVec; ++k) tile[cg * kVec + k][rl] = p[k] * a.invH;
+    for (int k = 0; k < kVec; ++k) tile[col - col0 + k][rl] = p[k] * a.invH;
   }
   __syncthreads();
   const int c = col0 + tid;                        // this thread's column
