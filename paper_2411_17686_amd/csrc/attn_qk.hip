@@ -108,6 +108,10 @@ static_assert(kQkKeys == 2 * kNormKB * 16, "two steps of keys");
 //
 // Bound by the vector unit: exponential, multiply-add and add per logit, and by the matrix instructions, which hardly
 // run beside them (4 x 2881 tokens, 16 heads of 64: 112 us; with operands straight from memory 165-205 us).
+template <bool DEC>
+__host__ __device__ __forceinline__ int norm_grid(const QkArgs& a, int heads, int groups) {
+  return DEC && !a.share_keys ? xcd_padded_total(heads) * groups : xcd_padded_total(heads * groups);
+}
 template <int KS, bool DEC>
 __global__ __launch_bounds__(kQkWaves * kWave) __attribute__((amdgpu_waves_per_eu(2))) void qk_norm_kernel(QkArgs a) {
   constexpr int CH = KS * 4, T = kQkWaves * kWave, RPI = T / CH, NL = kQkKeys / RPI;
@@ -116,13 +120,27 @@ __global__ __launch_bounds__(kQkWaves * kWave) __attribute__((amdgpu_waves_per_e
   // others: in their places between them they left every q_groups-th compute unit without work (a quarter of the chip at
   // 16 x 577 tokens: 29.8 us, and 24.3 with the order of precedence below).
   const bool last_narrow = a.nq - (a.q_groups - 1) * (a.share_keys ? 1 : kQkWaves) * kNormTile <= 16;
-  const int groups = a.q_groups - (last_narrow ? 1 : 0), units = a.nb * a.H * groups, first = xcd_padded_total(units);
+  const int groups = a.q_groups - (last_narrow ? 1 : 0), all_heads = a.nb * a.H, first = norm_grid<DEC>(a, all_heads, groups);
   const bool behind = (int)blockIdx.x >= first;
-  const int unit = xcd_logical_id(behind ? blockIdx.x - first : blockIdx.x, behind ? a.nb * a.H : units);
-  if (unit >= (behind ? a.nb * a.H : units)) return;
+  // Causal maps: the groups that see most keys come first, one group of every head after the other.  (Group by group of a head
+  // the workgroups that meet on a compute unit are of one length wherever the groups divide the 32 units of an XCD: 8 x 675 tokens, 32
+  // heads of 128 45.7 us, and 38.3 so.  With shared keys the short ones go first: 16 heads, one image of 675 32.3, else 36.2 for the stage.)
+  int in_head, head;
+  if (behind) {
+    in_head = groups;
+    head = xcd_logical_id(blockIdx.x - first, all_heads);
+  } else if (DEC && !a.share_keys) {
+    const int per = (all_heads + kXcds - 1) / kXcds, at = blockIdx.x / kXcds;
+    in_head = groups - 1 - at / per;
+    head = at % per + blockIdx.x % kXcds * per;
+  } else {
+    const int unit = xcd_logical_id(blockIdx.x, all_heads * groups);
+    in_head = unit % groups;
+    head = unit / groups;
+  }
+  if (head >= all_heads) return;
   const int tid = threadIdx.x, lane = tid % kWave, l16 = lane % 16, lg = lane / 16;
   const int wv = __builtin_amdgcn_readfirstlane(tid / kWave);
-  const int in_head = behind ? groups : unit % groups, head = behind ? unit : unit / groups;
   const int w0 = in_head * (a.share_keys ? 1 : kQkWaves) * kNormTile;
   const bool narrow = a.nq - w0 <= 16;     // one block of queries in all (the [CLS] query behind 576 visual ones)
   const bool share_keys = a.share_keys || narrow;
@@ -383,13 +401,102 @@ __device__ __forceinline__ double sums_of_16(const double (&x)[16], int l) {
 // on its own 180 / 44 / 56; 96 x 64 by four wavefronts with 16 x 16 products, the next head's beside this head's
 // exponentials 170 / 40 / 51; normalisers through LDS, whole tiles written without tests 158 / 34 / 49; 32 x 32 products
 // 157 / 33 / 51; rows straight into LDS, order of precedence among the wavefronts 142 / 28.6 / 48.
+// Causal maps: key tiles that some query of group g (of qr rows) sees, and all of them.  (Queries behind the visual span see all.)
+__host__ __device__ __forceinline__ int causal_keys(int g, int k_tiles, int qr, int n_visq) {
+  return (g + 1) * qr > n_visq ? k_tiles : min(k_tiles, ((g + 1) * qr + kQkKeys - 1) / kQkKeys);
+}
+__host__ __device__ __forceinline__ int causal_tiles(int groups, int k_tiles, int qr, int n_visq) {
+  int sum = 0;
+  for (int g = 0; g < groups; ++g) sum += causal_keys(g, k_tiles, qr, n_visq);
+  return sum;
+}
 constexpr int kQkBand = 8;                          // key tiles side by side in the order of the workgroups
+// Tile number `unit` of an image (qr queries x kQkKeys keys): in columns kQkBand key tiles wide, so that the workgroups that run
+// together on an XCD need few rows of either side, which its L2 holds for all heads.  live_first (causal maps of more tiles
+// than there are compute units): first the tiles that hold a key some query sees, last queries first, then the others, which are
+// zero.  In between, the latter took places on the chip from which others were missing (16 heads of 64, 270 tiles: 37.9 us for the two kernels, 34.8
+// so; where every tile has a place at once the search costs more: 135 tiles 27.4, and 28.1 so).
+constexpr int kCausalTiles = 256;
+__device__ __forceinline__ void qk_tile(const QkArgs& a, int unit, bool live_first, int qr, int& kt0, int& w0) {
+  if (live_first) {
+    const int live_all = causal_tiles(a.q_groups, a.k_tiles, qr, a.n_visq);
+    const bool dead = unit >= live_all;
+    int left = dead ? unit - live_all : unit, g = a.q_groups - 1;
+    for (; g > 0; --g) {
+      const int live = causal_keys(g, a.k_tiles, qr, a.n_visq), here = dead ? a.k_tiles - live : live;
+      if (left < here) break;
+      left -= here;
+    }
+    kt0 = dead ? causal_keys(g, a.k_tiles, qr, a.n_visq) + left : left;
+    w0 = g * qr;
+  } else {
+    const int band = unit / (kQkBand * a.q_groups), in_band = unit - band * kQkBand * a.q_groups;
+    const int band_w = min(kQkBand, a.k_tiles - band * kQkBand);
+    kt0 = band * kQkBand + in_band % band_w;
+    w0 = in_band / band_w * qr;
+  }
+}
 template <bool SPLIT> struct QkMeanShape {
   static constexpr int kBlocks = SPLIT ? 1 : 2;       // of queries per wavefront
   static constexpr int kQueries = 2 * kBlocks * kQkB; // of a workgroup
   static constexpr int kShares = SPLIT ? 4 : 1;       // shares of the heads
   static constexpr int kThreads = kQkWaves * kShares * kWave;
 };
+// Outputs of 64 queries (32: one block) from v0 and 32 visual keys from ik0 on, of the sums over the heads.
+template <bool DEC, int blocks>
+__device__ __forceinline__ void qk_write_out(const QkArgs& a, int64_t b, int v0, int ik0, const f32x16_t& s0, const f32x16_t& s1) {
+  // (again from the thread's number: kept over the heads, these took registers that heads of 128, split, do not have)
+  int here = threadIdx.x;
+  asm volatile("" : "+v"(here));
+  const int l32 = here % kQkB, hi = here % kWave / kQkB;
+  const float invH = 1.0f / (float)a.H;
+  const int qt = v0 / kQkTile;
+  const bool recv = a.recv_part && qt < a.n_tiles;    // uniform
+  double cs[kQkE];                                    // received from this tile's visual queries
+  if (blocks == 2 && a.abar && ik0 + kQkB <= a.N && v0 + kQkTile <= a.n_visq && !(DEC && ik0 + kQkB - 1 > v0)) {     // uniform
+    // Whole blocks of visual queries that all count (all but the edges): no test per value, the rows' addresses in
+    // scalar registers.
+    const uint32_t at = (uint32_t)(hi * 4 * a.map_pitch + l32);
+#pragma unroll
+    for (int v = 0; v < kQkE; ++v) {
+      float* row = a.abar + (b * a.N + ik0 + key_of(v)) * a.map_pitch + v0;
+      const float p0 = s0[v] * invH, p1 = s1[v] * invH;      // head-mean probabilities
+      row[at] = p0;
+      row[at + kQkB] = p1;
+      cs[v] = (double)p0 + (double)p1;
+    }
+  } else {
+#pragma unroll
+    for (int v = 0; v < kQkE; ++v) cs[v] = 0.0;
+#pragma unroll
+    for (int m = 0; m < blocks; ++m) {
+      const int vq = v0 + m * kQkB + l32, k_first = ik0 + 4 * hi, n_k = a.N - k_first;
+      const bool q_vis = vq < a.n_visq, q_in = vq < a.nq;
+      const int behind = DEC ? a.row(vq) - a.vis0 - k_first : 0;     // keys from there on lie behind the query
+      const int64_t key = b * a.N + k_first;
+      float* map = a.abar + key * a.map_pitch + vq;
+      double* other = DEC ? a.ttext + key * a.M + (vq - a.n_visq) : a.cls + key;
+      const int64_t other_pitch = DEC ? a.M : 1;
+#pragma unroll
+      for (int v = 0; v < kQkE; ++v) {
+        const int k = key_of(v);
+        float pm = (m == 0 ? s0[v] : s1[v]) * invH;
+        if (DEC && k > behind) pm = 0.0f;
+        if (k < n_k) {
+          if (q_vis) { if (a.abar) map[k * (int64_t)a.map_pitch] = pm; }
+          else if (q_in) other[k * other_pitch] = (double)pm;
+        }
+        cs[v] += q_vis ? (double)pm : 0.0;
+      }
+    }
+  }
+  if (recv) {
+    const double mine = sums_of_16(cs, l32);
+    const int i = sum_index(l32), ik = ik0 + i / 4 * 8 + i % 4 + 4 * hi;
+    if (l32 < 16 && ik < a.N) a.recv_part[(b * a.n_tiles + qt) * a.N + ik] = mine;
+  }
+}
+
 template <int KS, bool DEC, bool SPLIT>
 __global__ __launch_bounds__(QkMeanShape<SPLIT>::kThreads) __attribute__((amdgpu_waves_per_eu(SPLIT ? 4 : KS == 4 ? 2 : 3))) void qk_mean_kernel(QkArgs a) {
   constexpr int KSS = KS > 2 ? 2 : KS, NST = KS / KSS, CH = KSS * 4, KT = KSS * 2;     // 32-feature steps of a stage, stages of a head, instructions of a block and stage
@@ -405,14 +512,10 @@ __global__ __launch_bounds__(QkMeanShape<SPLIT>::kThreads) __attribute__((amdgpu
   const int tid = threadIdx.x, lane = tid % kWave, l32 = lane % kQkB, hi = lane / kQkB;
   const int wv = __builtin_amdgcn_readfirstlane(tid / kWave);
   const int share = wv / kQkWaves, wq = wv % kQkWaves / 2, wk = wv % 2;
-  // the tiles of an image in columns kQkBand key tiles wide: the workgroups that run together on an
-  // XCD then need few rows of either side, which its L2 holds for all heads
   const int64_t bi = unit / (a.k_tiles * a.q_groups), b = a.b0 + bi;
   const int in_img = unit - (int)bi * a.k_tiles * a.q_groups;
-  const int band = in_img / (kQkBand * a.q_groups), in_band = in_img - band * kQkBand * a.q_groups;
-  const int band_w = min(kQkBand, a.k_tiles - band * kQkBand);
-  const int kt0 = band * kQkBand + in_band % band_w;
-  const int w0 = in_band / band_w * QR;
+  int kt0, w0;
+  qk_tile(a, in_img, DEC && !SPLIT && units > kCausalTiles, QR, kt0, w0);
   // One block of queries in all (uniform): the wavefronts share its heads, with operands straight from memory, unless the tile is
   // split anyway and a wavefront's share is four 32-feature steps or more: then rows through LDS are faster.  us, so and
   // as any other tile: 8 x 16 text queries, 32 heads of 128 25.3 / 21.4, 24 queries 26.7 / 21.5, one image of 16 and 16 heads 15.6 / 13.9, 8 x 20 and
@@ -607,61 +710,6 @@ __global__ __launch_bounds__(QkMeanShape<SPLIT>::kThreads) __attribute__((amdgpu
       }
     }
   };
-  // outputs of 64 queries (32: one block) from v0 and 32 visual keys from ik0 on, of the sums over the heads
-  auto write_out = [&](auto blocks_c, int v0, int ik0, const f32x16_t& s0, const f32x16_t& s1) __attribute__((always_inline)) {
-    constexpr int blocks = decltype(blocks_c)::value;
-    // (again from the thread's number: kept over the heads, these took registers that heads of 128, split, do not have)
-    int here = threadIdx.x;
-    asm volatile("" : "+v"(here));
-    const int l32 = here % kQkB, hi = here % kWave / kQkB;
-    const float invH = 1.0f / (float)a.H;
-    const int qt = v0 / kQkTile;
-    const bool recv = a.recv_part && qt < a.n_tiles;    // uniform
-    double cs[kQkE];                                    // received from this tile's visual queries
-    if (blocks == 2 && a.abar && ik0 + kQkB <= a.N && v0 + kQkTile <= a.n_visq && !(DEC && ik0 + kQkB - 1 > v0)) {     // uniform
-      // Whole blocks of visual queries that all count (all but the edges): no test per value, the rows' addresses in
-      // scalar registers.
-      const uint32_t at = (uint32_t)(hi * 4 * a.map_pitch + l32);
-#pragma unroll
-      for (int v = 0; v < kQkE; ++v) {
-        float* row = a.abar + (b * a.N + ik0 + key_of(v)) * a.map_pitch + v0;
-        const float p0 = s0[v] * invH, p1 = s1[v] * invH;      // head-mean probabilities
-        row[at] = p0;
-        row[at + kQkB] = p1;
-        cs[v] = (double)p0 + (double)p1;
-      }
-    } else {
-#pragma unroll
-      for (int v = 0; v < kQkE; ++v) cs[v] = 0.0;
-#pragma unroll
-      for (int m = 0; m < blocks; ++m) {
-        const int vq = v0 + m * kQkB + l32, k_first = ik0 + 4 * hi, n_k = a.N - k_first;
-        const bool q_vis = vq < a.n_visq, q_in = vq < a.nq;
-        const int behind = DEC ? a.row(vq) - a.vis0 - k_first : 0;     // keys from there on lie behind the query
-        const int64_t key = b * a.N + k_first;
-        float* map = a.abar + key * a.map_pitch + vq;
-        double* other = DEC ? a.ttext + key * a.M + (vq - a.n_visq) : a.cls + key;
-        const int64_t other_pitch = DEC ? a.M : 1;
-#pragma unroll
-        for (int v = 0; v < kQkE; ++v) {
-          const int k = key_of(v);
-          float pm = (m == 0 ? s0[v] : s1[v]) * invH;
-          if (DEC && k > behind) pm = 0.0f;
-          if (k < n_k) {
-            if (q_vis) { if (a.abar) map[k * (int64_t)a.map_pitch] = pm; }
-            else if (q_in) other[k * other_pitch] = (double)pm;
-          }
-          cs[v] += q_vis ? (double)pm : 0.0;
-        }
-      }
-    }
-    if (recv) {
-      const double mine = sums_of_16(cs, l32);
-      const int i = sum_index(l32), ik = ik0 + i / 4 * 8 + i % 4 + 4 * hi;
-      if (l32 < 16 && ik < a.N) a.recv_part[(b * a.n_tiles + qt) * a.N + ik] = mine;
-    }
-  };
-
   if (narrow) {
     // The wavefronts take consecutive shares of the heads,
     // operands straight from memory, and their sums are added pairwise (a fixed tree).
@@ -715,7 +763,7 @@ __global__ __launch_bounds__(QkMeanShape<SPLIT>::kThreads) __attribute__((amdgpu
     __syncthreads();
     if (wv >= 2) return;
     const f32x16_t mine = wv == 0 ? P1[0] + sums[kWave + lane] : sums[lane] + P1[1];
-    write_out(std::integral_constant<int, 1>{}, w0, wk0 + wv * kQkB, mine, mine);
+    qk_write_out<DEC, 1>(a, b, w0, wk0 + wv * kQkB, mine, mine);
     return;
   }
 
@@ -741,11 +789,186 @@ __global__ __launch_bounds__(QkMeanShape<SPLIT>::kThreads) __attribute__((amdgpu
     if (share == 0 && wq == 1) sums[wk * kWave + lane] = P[0];
     __syncthreads();
     if (share != 0 || wq != 0) return;
-    write_out(std::integral_constant<int, 2>{}, w0, ik0, P[0], sums[wk * kWave + lane]);
+    qk_write_out<DEC, 2>(a, b, w0, ik0, P[0], sums[wk * kWave + lane]);
   } else {
     if (lone) P[0] += P[MB - 1];
-    if (v0 < a.nq) write_out(std::integral_constant<int, 2>{}, v0, ik0, P[0], P[MB - 1]);
+    if (v0 < a.nq) qk_write_out<DEC, 2>(a, b, v0, ik0, P[0], P[MB - 1]);
   }
+}
+
+// ---- the same for causal maps with heads of 128 -----------------------------------------------------
+// Tiles, products and sums of the kernel above in its wide form, in the same order (the same bits).  Few wavefronts share a SIMD: 232 of
+// the 360 tiles of 8 x 675 tokens hold a key that some query sees, fewer than there are compute units, and then nothing
+// hides a wavefront's trips.  So the fragments of a stage are read into a second set of registers while the products of the one
+// before are formed, rows are loaded three stages ahead (three buffers, one barrier a stage, no wait for loads just issued),
+// and reads and loads are spread over the stage's products and exponentials.  The buffers are arrays of their own: the
+// compiler then knows that a read of one need not wait for the loads into the others.
+//
+// 8 x 675 tokens, 32 heads (64 stages a workgroup): kernel above 47.2 us; this one with all reads and loads at the head of a stage
+// 34.8, spread 30.8.  Bound by what one wavefront issues per stage (850 cycles), loads alone take 540.  With the heads in two
+// shares of four wavefronts each (two a SIMD) 37.7 and 33.0: LDS, and the zero tiles wait for a place.
+constexpr int kDeepRows = 2 * 2 * kQkB + kQkKeys, kDeepCh = 8;      // queries, then keys, of a stage of 64 features
+__global__ __launch_bounds__(kQkWaves * kWave) __attribute__((amdgpu_waves_per_eu(2, 2))) void qk_mean_deep_kernel(QkArgs a) {
+  constexpr int QR = 4 * kQkB, CH = kDeepCh, T = kQkWaves * kWave, RPI = T / CH, NL = kDeepRows / RPI, KT = 4;
+  static_assert(kDeepRows % RPI == 0 && QR % RPI == 0 && NL == 6, "whole rounds of queries and of keys; the loads that are waited for");
+  __shared__ u32x4_t buf0[kDeepRows * CH], buf1[kDeepRows * CH], buf2[kDeepRows * CH];
+  const int units = a.nb * a.q_groups * a.k_tiles;
+  const int unit = xcd_logical_id(blockIdx.x, units);
+  if (unit >= units) return;
+  const int tid = threadIdx.x, lane = tid % kWave, l32 = lane % kQkB, hi = lane / kQkB;
+  const int wv = __builtin_amdgcn_readfirstlane(tid / kWave), wq = wv / 2, wk = wv % 2;
+  const int64_t bi = unit / (a.k_tiles * a.q_groups), b = a.b0 + bi;
+  int kt0, w0;
+  qk_tile(a, unit - (int)bi * a.k_tiles * a.q_groups, units > kCausalTiles, QR, kt0, w0);
+  const int q0 = wq * 2 * kQkB, v0 = w0 + q0, wk0 = kt0 * kQkKeys, ik0 = wk0 + wk * kQkB;
+  f32x16_t P[2] = {qk_zero(), qk_zero()};
+  if (a.vis0 + wk0 <= a.row(min(w0 + QR, a.nq) - 1)) {  // uniform in the workgroup: some query sees some key
+    const bf16_t* src[NL];                             // this thread's chunk of the stage's rows: queries, then keys
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      const int r = tid / CH + i * RPI;
+      const int row = r < QR ? a.row(min(w0 + r, a.nq - 1)) : a.vis0 + min(wk0 + r - QR, a.N - 1);
+      src[i] = (i * RPI < QR ? a.Q : a.K) + b * a.sb + (int64_t)row * a.sn + (tid % CH ^ (tid / 16 & (CH - 1))) * 8;
+    }
+    float scale = a.scale_log2e;
+    asm volatile("" : "+s"(scale));
+    const float2* nrm = a.norm + bi * a.H * a.nq;
+    uint32_t nrm_at[2];
+#pragma unroll
+    for (int m = 0; m < 2; ++m) nrm_at[m] = (uint32_t)min(v0 + m * kQkB + l32, a.nq - 1);
+    auto load_stage = [&](int h, int part, u32x4_t* buf, int only = -1) __attribute__((always_inline)) {
+      int64_t off = (int64_t)min(h, a.H - 1) * a.sh + part * 64;      // (past the last head: that one again)
+      asm volatile("" : "+s"(off));
+#pragma unroll
+      for (int i = 0; i < NL; ++i) {
+        if (only >= 0 && i != only) continue;
+        asm volatile("" : "+v"(src[i]));
+        load_to_lds(src[i] + off, buf + i * T + wv * kWave);
+      }
+    };
+    auto load_nf = [&](int h, float2 (&n)[2]) __attribute__((always_inline)) {
+#pragma unroll
+      for (int m = 0; m < 2; ++m) n[m] = (nrm + (int64_t)min(h, a.H - 1) * a.nq)[nrm_at[m]];
+      issue_fence();
+    };
+    // Where a lane's fragments lie in a buffer: with the same swizzle for every 32 rows they differ by constants.  (Taken anew for
+    // every stage: formed ahead of the loop for each buffer, the addresses spill.)
+    int at_q[KT], at_k[KT];                            // in bytes
+#pragma unroll
+    for (int kt = 0; kt < KT; ++kt) {
+      at_q[kt] = lds_chunk<CH>(q0 + l32, kt * 2 + hi) * 16;
+      at_k[kt] = lds_chunk<CH>(QR + wk * kQkB + l32, kt * 2 + hi) * 16;
+    }
+    struct Frags { bf16x8_t k[KT], q[2][KT]; };
+    auto read = [&](const u32x4_t* buf, Frags& f, int only = -1) __attribute__((always_inline)) {
+      const char* st = (const char*)buf;
+#pragma unroll
+      for (int kt = 0; kt < KT; ++kt) {
+#pragma unroll
+        for (int r = 0; r < 3; ++r) {
+          if (only >= 0 && kt * 3 + r != only) continue;
+          if (r == 0) {
+            asm volatile("" : "+v"(at_k[kt]));
+            f.k[kt] = *(const bf16x8_t*)(st + at_k[kt]);
+          } else {
+            asm volatile("" : "+v"(at_q[kt]));
+            f.q[r - 1][kt] = *(const bf16x8_t*)(st + at_q[kt] + (r - 1) * kQkB * CH * 16);
+          }
+        }
+      }
+    };
+    f32x16_t S[2][2];                                  // logits of even and odd heads
+    S[1][0] = S[1][1] = qk_zero();
+    float2 nf[3][2];                                   // normalisers of three heads in turn
+#pragma unroll
+    for (int m = 0; m < 2; ++m) nf[2][m] = make_float2(__builtin_huge_valf(), 0.0f);    // (nothing before the first head: 2^-inf, times zero)
+    auto x_of = [&](const f32x16_t& Sd, float2 n, int v) { return fmaf(Sd[v], scale, -n.x); };
+    // The products of one stage beside the exponentials of one block of the head before, the reads of the next stage's
+    // fragments and the loads of a stage further on (`side`, in seventeen parts): all in one stream, as a wavefront whose reads
+    // stand at the head waits there until LDS has taken those of the others.
+    auto multiply = [&](const Frags& f, f32x16_t (&Sn)[2], bool fresh, const f32x16_t& Sd, float2 n, f32x16_t& Pd, auto side) __attribute__((always_inline)) {
+      constexpr int E = kQkE, M = 2 * KT;
+      float x[2] = {x_of(Sd, n, 0), x_of(Sd, n, 1)}, e_prev = 0.0f;
+      issue_fence();
+#pragma unroll
+      for (int i = 0; i <= E; ++i) {
+        float e = 0.0f;
+#pragma unroll
+        for (int m = 0; m < M; ++m)
+          if (m * E / M == i) {
+            const int kt = m / 2, blk = m % 2;
+            Sn[blk] = qk_mfma(f.k[kt], f.q[blk][kt], fresh && kt == 0 ? qk_zero() : Sn[blk]);
+          }
+        if (i < E) e = __builtin_amdgcn_exp2f(x[i % 2]);
+        if (i + 2 < E) x[i % 2] = x_of(Sd, n, i + 2);
+        side(i);
+        if (i > 0) Pd[i - 1] = fmaf(e_prev, n.y, Pd[i - 1]);
+        issue_fence();
+        e_prev = e;
+      }
+    };
+    Frags fr[2];
+    // Stage 2 h + part (j: h modulo 6, the turn of buffers and registers): its fragments have been read.  The next stage's rows
+    // have arrived once all but the last eight loads have (the six of the stage after it and two normalisers); the buffer of this
+    // stage, whose fragments every wavefront has by the barrier, is filled three stages ahead.
+    auto buf = [&](auto s_c) { constexpr int s = decltype(s_c)::value % 3; return s == 0 ? buf0 : s == 1 ? buf1 : buf2; };
+    auto stage = [&](int h, auto j_c, auto part_c) __attribute__((always_inline)) {
+      constexpr int j = decltype(j_c)::value, part = decltype(part_c)::value, s = 2 * j + part;
+      issue_fence();
+      __builtin_amdgcn_s_waitcnt(0x0078);              // lgkmcnt(0), vmcnt(8)
+      asm volatile("s_barrier" ::: "memory");
+      const u32x4_t* after = buf(std::integral_constant<int, s + 1>{});
+      u32x4_t* own = buf(std::integral_constant<int, s>{});
+      multiply(fr[part], S[j % 2], part == 0, S[1 - j % 2][part], nf[(j + 2) % 3][part], P[part], [&](int i) __attribute__((always_inline)) {
+        if (i < 12) read(after, fr[1 - part], i);
+        if (i >= 1 && i <= 11 && i % 2 == 1) load_stage(h + (part + 3) / 2, (part + 1) % 2, own, i / 2);
+        if (part == 1 && i == 13) load_nf(h + 1, nf[(j + 1) % 3]);
+      });
+    };
+    auto head = [&](int h, auto j_c) __attribute__((always_inline)) {
+      stage(h, j_c, std::integral_constant<int, 0>{});
+      stage(h, j_c, std::integral_constant<int, 1>{});
+    };
+    load_stage(0, 0, buf0);
+    load_stage(0, 1, buf1);
+    load_stage(1, 0, buf2);
+    load_nf(0, nf[0]);
+    __builtin_amdgcn_s_waitcnt(0x0f7e);                // vmcnt(14): the first stage's loads
+    asm volatile("s_barrier" ::: "memory");
+    read(buf0, fr[0]);
+    int h = 0;
+    // Whole turns with no way out in between: the compiler would wait for every load at the loop's head.
+#pragma unroll 1
+    for (; h + 6 <= a.H; h += 6) {
+      head(h, std::integral_constant<int, 0>{});
+      head(h + 1, std::integral_constant<int, 1>{});
+      head(h + 2, std::integral_constant<int, 2>{});
+      head(h + 3, std::integral_constant<int, 3>{});
+      head(h + 4, std::integral_constant<int, 4>{});
+      head(h + 5, std::integral_constant<int, 5>{});
+    }
+    if (h < a.H) head(h, std::integral_constant<int, 0>{});
+    if (h + 1 < a.H) head(h + 1, std::integral_constant<int, 1>{});
+    if (h + 2 < a.H) head(h + 2, std::integral_constant<int, 2>{});
+    if (h + 3 < a.H) head(h + 3, std::integral_constant<int, 3>{});
+    if (h + 4 < a.H) head(h + 4, std::integral_constant<int, 4>{});
+    __builtin_amdgcn_s_waitcnt(0x0f70);                // vmcnt(0): nothing may arrive in LDS after the workgroup's end
+    auto last = [&](auto j_c) __attribute__((always_inline)) {
+      constexpr int j = decltype(j_c)::value;
+      if ((a.H - 1) % 6 != j) return;                  // uniform
+#pragma unroll
+      for (int m = 0; m < 2; ++m)
+#pragma unroll
+        for (int v = 0; v < kQkE; ++v) P[m][v] = fmaf(__builtin_amdgcn_exp2f(x_of(S[j % 2][m], nf[j % 3][m], v)), nf[j % 3][m].y, P[m][v]);
+    };
+    last(std::integral_constant<int, 0>{});
+    last(std::integral_constant<int, 1>{});
+    last(std::integral_constant<int, 2>{});
+    last(std::integral_constant<int, 3>{});
+    last(std::integral_constant<int, 4>{});
+    last(std::integral_constant<int, 5>{});
+  }
+  if (v0 < a.nq) qk_write_out<true, 2>(a, b, v0, ik0, P[0], P[1]);
 }
 
 template <int KS, bool DEC>
@@ -764,7 +987,7 @@ static void launch_qk(QkArgs a, hipStream_t s) {
   if (a.share_keys) a.q_groups = tiles;
   const bool narrow = a.nq - (a.q_groups - 1) * (a.share_keys ? 1 : kQkWaves) * kNormTile <= 16;      // (as the kernel sees it)
   const int groups = a.q_groups - (narrow ? 1 : 0);
-  hipLaunchKernelGGL((qk_norm_kernel<KS, DEC>), dim3(xcd_padded_total(a.nb * a.H * groups) + (narrow ? xcd_padded_total(a.nb * a.H) : 0)), dim3(kQkWaves * kWave), 0, s, a);
+  hipLaunchKernelGGL((qk_norm_kernel<KS, DEC>), dim3(norm_grid<DEC>(a, a.nb * a.H, groups) + (narrow ? xcd_padded_total(a.nb * a.H) : 0)), dim3(kQkWaves * kWave), 0, s, a);
   auto mean = [&](auto kern, auto shape) {
     using Shape = decltype(shape);
     // two stages of (queries + keys) rows per share of the heads, and the queries' normalisers of two heads
@@ -782,8 +1005,21 @@ static void launch_qk(QkArgs a, hipStream_t s) {
   // 21.0 / 27.8; three, 135 workgroups, 8 of 64 25.6 / 19.2, 32 of 32 34.1 / 30.9.  Over 700 shapes, split relative to wide below 64 and
   // at 64 to 128 workgroups: one head 1.20, 1.20; four 1.08, 1.08; six 1.06, 1.05; eight 1.00, 0.98; twelve 0.93, 0.90; 32 0.81, 0.77; at
   // 160 and more wide is the better one up to twenty heads.
-  const int wide = QkMeanShape<false>::kQueries;
-  const bool split = a.H >= 8 && (int64_t)a.nb * ((a.nq + wide - 1) / wide) * a.k_tiles < 128;
+  const int wide = QkMeanShape<false>::kQueries, q_tiles = (a.nq + wide - 1) / wide;
+  const bool split = a.H >= 8 && (int64_t)a.nb * q_tiles * a.k_tiles < 128;
+  if constexpr (DEC && KS == 4) {
+    // Heads of 128: the form with rows three stages ahead, but for one block of queries (whose heads the wavefronts share), and for
+    // sixteen tiles or fewer with many heads, which keep the shares of four.  us of the two kernels, this form and the other one chosen:
+    // 32 heads, 8 x (576 + 64) queries (232 tiles) 64.5 / 78.8, 4 images 45.2 / 66.8 (split), one 38.0 / 39.0 (split); 16 heads, 8 images 40.2 /
+    // 45.8, 12 x (300 + 40) 32.1 / 43.9 (split); 8 heads 31.4 / 32.8; 8 x (96 + 17), 32 heads (16 tiles) 31.9 / 29.1 (split); 8 text queries
+    // alone, 16 heads 23.5 / 21.3.
+    const int64_t live = (int64_t)a.nb * causal_tiles(q_tiles, a.k_tiles, wide, a.n_visq);
+    if (a.nq > kQkB && (live > 16 || a.H < 16)) {
+      a.q_groups = q_tiles;
+      hipLaunchKernelGGL(qk_mean_deep_kernel, dim3(xcd_padded_total(a.nb * a.q_groups * a.k_tiles)), dim3(kQkWaves * kWave), 0, s, a);
+      return;
+    }
+  }
   if (split) mean(qk_mean_kernel<KS, DEC, true>, QkMeanShape<true>{});
   else mean(qk_mean_kernel<KS, DEC, false>, QkMeanShape<false>{});
 }

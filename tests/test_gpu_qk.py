@@ -248,6 +248,22 @@ def test_causal_heads_split(ctx, B, N, M, H, d):
     assert full >= (B + 1) // 2
 
 
+@pytest.mark.parametrize("B,N,M,H", [(1, 70, 5, 1), (2, 64, 64, 2), (1, 130, 33, 3), (2, 200, 9, 4), (1, 129, 128, 5), (1, 61, 70, 6), (3, 128, 1, 7),
+                                     (1, 193, 64, 12), (2, 33, 31, 13), (9, 250, 40, 17), (1, 200, 33, 16), (1, 20, 20, 18)])
+def test_causal_heads_of_128(ctx, monkeypatch, B, N, M, H):
+    """Heads that leave every remainder of a turn of six; one tile, tiles of zeros, tiles with one wavefront's queries, sixteen tiles
+    and fewer with many heads (not that form).  The workspace holds NaN first: every entry of the maps has to be written."""
+    make = fc.Buffers
+
+    def filled(*args):
+        buf = make(*args)
+        buf.ws.fill_(255)
+        return buf
+    monkeypatch.setattr(fc, "Buffers", filled)
+    full = _case_l(ctx, 440 + B + H + N, B, 3, N, M, 72, H, 128, max(1, N // 3), fc.R_ATTN_RECV, fc.C_ATTN)
+    assert full >= (B + 1) // 2
+
+
 @pytest.mark.parametrize("M,H,d", [(1, 32, 128), (16, 16, 128), (17, 9, 128), (32, 32, 64), (31, 17, 64), (32, 16, 64), (5, 64, 32), (33, 40, 32)])
 def test_one_block_of_text_queries(ctx, M, H, d):
     """At most 32 text queries alone, heads split: by wavefronts that share the heads, or (four 32-feature steps a wavefront and
