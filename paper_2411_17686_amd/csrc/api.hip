@@ -235,7 +235,8 @@ int make_plan(const ficoco_problem& p, Plan& pl, const char** why, size_t scratc
 
   // feature pass geometry (column sums over the tokens)
   if (pl.need_features) {
-    pl.f_rows_per_wg = 64;      // two batches of 8 rows per wavefront: half the workgroups (one round on the chip) and half the partials
+    // two batches of 8 rows per wavefront: half the workgroups (one round on the chip) and half the partials
+    pl.f_rows_per_wg = unit_rows_summed(p, pl.Df) ? unit_rows_per_wg(p) : 64;
     pl.f_chunks = (p.N + pl.f_rows_per_wg - 1) / pl.f_rows_per_wg;
   }
 
@@ -249,7 +250,7 @@ int make_plan(const ficoco_problem& p, Plan& pl, const char** why, size_t scratc
   pl.ttext = take(L ? B * N * (size_t)p.M * sizeof(double) : 0);
   pl.inv_norm = take(pl.need_features ? B * N * sizeof(double) : 0);
   pl.xhat = take(p.corr_src == FICOCO_C_COSINE ? B * N * (size_t)pl.Df * sizeof(bf16_t) : 0);
-  pl.colsum_part = take(pl.need_features ? 2 * B * (size_t)pl.f_chunks * pl.Df * sizeof(double) : 0);
+  pl.colsum_part = take(pl.need_features ? (unit_rows_summed(p, pl.Df) ? 1 : 2) * B * (size_t)pl.f_chunks * pl.Df * sizeof(double) : 0);
   pl.colmean = take(pl.need_features ? (2 * B * (size_t)pl.Df + B * (size_t)((pl.Df + 255) / 256)) * sizeof(double) : 0);   // two means, then |mu|^2 in parts
   pl.fterm = take(B * N * sizeof(double));
   pl.fterm2 = take(B * N * sizeof(double));

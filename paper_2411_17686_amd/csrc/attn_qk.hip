@@ -361,14 +361,6 @@ __global__ __launch_bounds__(kQkWaves * kWave) __attribute__((amdgpu_waves_per_e
   }
 }
 
-// The value of lane ^ 4: rows shifted by four lanes up for the first quad of a pair, down for the second.
-__device__ __forceinline__ int lane_xor_4(int v) {
-  const int up = __builtin_amdgcn_update_dpp(v, v, 0x104, 0xF, 0x5, false);      // row_shl:4 into quads 0 and 2
-  return __builtin_amdgcn_update_dpp(up, v, 0x114, 0xF, 0xA, false);             // row_shr:4 into quads 1 and 3
-}
-__device__ __forceinline__ double lane_xor_4(double v) {
-  return __hiloint2double(lane_xor_4(__double2hiint(v)), lane_xor_4(__double2loint(v)));
-}
 // Sixteen values of every lane, each summed over 32 lanes: the tree of the steps lane ^ 1, ^ 2, ^ 4, ^ 8, ^ 16.
 // The first four hand half of the values to the other lane of the pair, so lane l is left with value
 // sum_index(l) alone: 16 additions instead of 80.

@@ -117,6 +117,17 @@ inline bool text_stats_in_score(const ficoco_problem& p) {
 inline bool text_with_features(const ficoco_problem& p, const Plan& pl) {
   return text_stats_in_score(p) && p.A_text != nullptr && pl.need_features && !rows_with_filter(p, pl);
 }
+// FiCoCo-L whose redundancy term is the mean cosine, in bfloat16: norms, unit rows and their column sums in one pass over the
+// tokens (features.hip), where a row fills four to sixteen wavefronts with 16 bytes a lane: 2048 to 8192 features (narrower
+// rows leave a workgroup too few wavefronts; FiCoCo-V keeps its workspace, which the static scratch bounds).
+inline bool unit_rows_summed(const ficoco_problem& p, int Df) {
+  return p.variant == FICOCO_VARIANT_L && p.dtype == FICOCO_BF16 && p.red_src == FICOCO_R_SIM_MEAN && Df % kVec == 0 &&
+         Df >= 2048 && Df <= 8192;
+}
+// Rows of a workgroup there: 16, or 8 where those would be fewer than half as many workgroups as there are compute units.  us per step with
+// 16, with 8 and in the separate passes before: one sequence of 576 tokens, 5120 features 73.2 / 66.0 / 71.6, four of 200 82.2 / 74.2 /
+// 79.1; four of 576 91.9 / 97.3 / 97.8, eight of 690 172 / 183 / 187.
+inline int unit_rows_per_wg(const ficoco_problem& p) { return (int64_t)p.B * ((p.N + 15) / 16) >= 128 ? 16 : 8; }
 // text_stats_done: the text statistics were formed by the feature stage's launches
 void launch_score(const ficoco_problem& p, const Plan& pl, char* ws, double* scores, hipStream_t s,
                   bool text_stats_done = false);
@@ -276,6 +287,14 @@ __device__ __forceinline__ int wave_scan_inclusive(int v) {
   return v + (row >= 1 ? r0 : 0) + (row >= 2 ? r1 : 0) + (row >= 3 ? r2 : 0);
 }
 
+// The value of lane ^ 4: rows shifted by four lanes up for the first quad of a pair, down for the second.
+__device__ __forceinline__ int lane_xor_4(int v) {
+  const int up = __builtin_amdgcn_update_dpp(v, v, 0x104, 0xF, 0x5, false);      // row_shl:4 into quads 0 and 2
+  return __builtin_amdgcn_update_dpp(up, v, 0x114, 0xF, 0xA, false);             // row_shr:4 into quads 1 and 3
+}
+__device__ __forceinline__ double lane_xor_4(double v) {
+  return __hiloint2double(lane_xor_4(__double2hiint(v)), lane_xor_4(__double2loint(v)));
+}
 // all bits cleared (eight zeros) unless `keep`: selects, no branch
 __device__ __forceinline__ void keep_raw_if(Raw8<bf16_t>& r, bool keep) {
   r.a.x = keep ? r.a.x : 0u; r.a.y = keep ? r.a.y : 0u; r.a.z = keep ? r.a.z : 0u; r.a.w = keep ? r.a.w : 0u;
