@@ -278,9 +278,13 @@ int make_plan(const ficoco_problem& p, Plan& pl, const char** why, size_t scratc
     // Few output tiles: cut K so that the matrix-core kernel still fills the chip (about two
     // workgroups per compute unit), each range at least 256 features long; the partial blocks are
     // added, in a fixed order, where they are read.
+    // At most 8 ranges, or 16 of a decoder's layer as long as they are one workgroup per compute unit: a tile's time is its
+    // stages, but every range is also a block to write and to read.  Stage of 8 / 16 ranges, 4096 features: 1 image of 432 x 144
+    // (8 tiles) 22.2 / 21.4 us, 8 of 256 x 128 (16) 27.7 / 26.8, 3 of 432 x 144 (24) 26.9 / 27.9; 5120: 24.6 / 22.5, 29.8 / 29.3,
+    // 1 of 800 x 384 (21 tiles) 29.3 / 31.0.  (The other variant keeps to 8: what its scratch may hold is a fixed size.)
     const int64_t tiles = (int64_t)p.B * ((pl.n_disc + 127) / 128) * ((p.n_keep + 127) / 128);
     int splits = (int)((512 + tiles - 1) / tiles);
-    splits = std::min(splits, std::min(8, pl.Df / 256));
+    splits = std::min(splits, std::min(L && tiles <= 16 ? 16 : 8, pl.Df / 256));
     if (splits < 1) splits = 1;
     const int st_all = (pl.Df + kGramStage - 1) / kGramStage;
     pl.gram_st_per_split = (st_all + splits - 1) / splits;

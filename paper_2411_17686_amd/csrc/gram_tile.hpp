@@ -9,12 +9,17 @@
 // v_mfma_f32_32x32x16_bf16), K staged through LDS 32 at a time,
 // double buffered, rows gathered by index.  LDS rows are padded by 16 bytes so that the
 // 16-byte fragment reads of a quarter wavefront fall on distinct banks.
+//
+// What bounds it: with few tiles the chain of a stage (fragments, eight products, stores to LDS, barrier: 850 cycles of a lone
+// workgroup), with many the rows and the partial blocks, about 7 TB/s between 8 and 16 images of 432 x 144 with 4096 features
+// (17.2 and 25.0 us).  Of 1 image, in 16 ranges of K: 8.7 us; in 8 ranges 11.6, and 12.7 while its loads were under a condition.
 #pragma once
 #include "common.hpp"
 
 namespace ficoco {
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 
 constexpr int kGT = 128;           // tile rows = tile columns
@@ -22,6 +27,8 @@ constexpr int kGK = kGramStage;    // K elements per stage (32 measured best at 
 constexpr int kGChunks = kGK / 16;  // 16-byte chunks per thread, operand and stage
 constexpr int kGStride = kGK + 8;  // LDS row pitch in elements (row + 16 bytes)
 constexpr int kGStages = 2;   // K-stages in flight per thread (register ring)
+
+static __device__ const uint4 g_zero_chunk = {0, 0, 0, 0};
 
 struct GramArgs {
   const bf16_t* xhat;  // [B][N][Df]
@@ -62,39 +69,43 @@ __global__ __launch_bounds__(256) void gram_tile_kernel(GramArgs a) {
   // this split's K range, [k_begin, k_begin + k_len)
   const int k_begin = split * a.st_per_split * kGK;
   const int k_len = max(min(a.Df - k_begin, a.st_per_split * kGK), 0);
-  // loader: the stage is 128 rows x kGK/8 chunks of 8 elements per operand; thread -> kGChunks chunks each
-  const bf16_t* Xb = a.xhat + b * a.N * (int64_t)a.Df + k_begin;
-  int lrow[kGChunks], lkc[kGChunks];
-  const bf16_t* srcA[kGChunks];
-  const bf16_t* srcB[kGChunks];
+  // loader: the stage is 128 rows x kGK/8 chunks of 8 elements per operand; thread -> one chunk of kGChunks rows each.
+  // A row of no token, and a chunk past the range, is loaded from a chunk of zeros: with the loads under a condition the compiler
+  // waited for each where its values joined the zeros of the other way, one latency of memory a stage.
+  const uint64_t xb = (uint64_t)(a.xhat + b * a.N * (int64_t)a.Df + k_begin), zeros = (uint64_t)&g_zero_chunk;
+  const int lkc = tid % (kGK / 8) * 8;
+  int lrow[kGChunks];
+  uint64_t srcA[kGChunks], srcB[kGChunks];        // of the next stage to fetch
+  uint32_t stepA[kGChunks], stepB[kGChunks];
 #pragma unroll
   for (int u = 0; u < kGChunks; ++u) {
-    const int q = tid + 256 * u;
-    lrow[u] = q / (kGK / 8);
-    lkc[u] = (q % (kGK / 8)) * 8;
-    srcA[u] = rowA[lrow[u]] >= 0 ? Xb + (int64_t)rowA[lrow[u]] * a.Df + lkc[u] : nullptr;
-    srcB[u] = rowB[lrow[u]] >= 0 ? Xb + (int64_t)rowB[lrow[u]] * a.Df + lkc[u] : nullptr;
+    lrow[u] = (tid + 256 * u) / (kGK / 8);
+    const int ia = rowA[lrow[u]], ib = rowB[lrow[u]];
+    srcA[u] = ia >= 0 ? xb + 2 * ((int64_t)ia * a.Df + lkc) : zeros;
+    srcB[u] = ib >= 0 ? xb + 2 * ((int64_t)ib * a.Df + lkc) : zeros;
+    stepA[u] = ia >= 0 ? 2 * kGK : 0;
+    stepB[u] = ib >= 0 ? 2 * kGK : 0;
   }
   // Register ring of kGStages K-stages in flight per thread: a stage is fetched kGStages
   // iterations before it is stashed into LDS.
-  uint4 ra[kGStages][kGChunks], rb[kGStages][kGChunks];
+  u32x4_t ra[kGStages][kGChunks], rb[kGStages][kGChunks];
   const int n_st = (k_len + kGK - 1) / kGK;
+  auto get = [](uint64_t at) { return *(const __attribute__((address_space(1))) u32x4_t*)at; };
   auto fetch = [&](int slot, int st) {
-    const int k0 = st * kGK;
+    const bool in = st * kGK + lkc + 8 <= k_len;   // Df is a multiple of 8 on this path
 #pragma unroll
     for (int u = 0; u < kGChunks; ++u) {
-      const bool in = st < n_st && k0 + lkc[u] + 8 <= k_len;   // Df is a multiple of 8 on this path
-      ra[slot][u] = make_uint4(0, 0, 0, 0);
-      rb[slot][u] = make_uint4(0, 0, 0, 0);
-      if (in && srcA[u]) __builtin_memcpy(&ra[slot][u], srcA[u] + k0, 16);
-      if (in && srcB[u]) __builtin_memcpy(&rb[slot][u], srcB[u] + k0, 16);
+      ra[slot][u] = get(in ? srcA[u] : zeros);
+      rb[slot][u] = get(in ? srcB[u] : zeros);
+      srcA[u] += stepA[u];
+      srcB[u] += stepB[u];
     }
   };
   auto stash = [&](int slot, int buf) {
 #pragma unroll
     for (int u = 0; u < kGChunks; ++u) {
-      *reinterpret_cast<uint4*>(&As[buf][lrow[u] * kGStride + lkc[u]]) = ra[slot][u];
-      *reinterpret_cast<uint4*>(&Bs[buf][lrow[u] * kGStride + lkc[u]]) = rb[slot][u];
+      *reinterpret_cast<u32x4_t*>(&As[buf][lrow[u] * kGStride + lkc]) = ra[slot][u];
+      *reinterpret_cast<u32x4_t*>(&Bs[buf][lrow[u] * kGStride + lkc]) = rb[slot][u];
     }
   };
 
@@ -178,7 +189,6 @@ __global__ __launch_bounds__(256) void gram_tile_kernel(GramArgs a) {
 constexpr int kG2M = 192, kG2N = 192, kG2K = 64;
 constexpr int kG2Threads = 256;
 constexpr int kG2Chunks = kG2K / 8;        // 16-byte chunks per operand row and stage
-static __device__ const uint4 g_zero_chunk = {0, 0, 0, 0};
 __device__ __forceinline__ int g2_slot(int row, int chunk) { return row * kG2Chunks + (chunk ^ ((row >> 1) & 7)); }
 
 __global__ __launch_bounds__(kG2Threads) __attribute__((amdgpu_waves_per_eu(1, 1))) void gram_tile2_kernel(GramArgs a) {

@@ -113,3 +113,20 @@ def test_rows_and_columns_of_no_token_are_zero(ctx, B, n_disc, n_keep, D, M, for
     _check(p, buf, plan, buf.discard_idx, buf.keep_idx)
     for b, a in ((0, 0), (0, n_disc - 1), (B - 1, n_disc // 2), (B // 2, 1)):
         assert int(buf.edge_cnt[b, a]) == 0
+
+
+# images, discarded, kept tokens, features, text queries, K ranges: up to 16 tiles of a decoder's layer with long rows are cut into up to
+# 16 ranges (the last one shorter, or less than a stage), 17 of them into 8, as the other variant's are
+RANGES = [(1, 432, 144, 4096, 64, 16), (1, 128, 128, 4104, 3, 15), (1, 100, 60, 5120, 9, 16), (16, 100, 60, 4096, 2, 16), (17, 100, 60, 4096, 2, 8),
+          (1, 129, 129, 2304, 5, 9), (1, 432, 144, 4096, 0, 8)]
+
+
+@pytest.mark.parametrize("B,n_disc,n_keep,D,M,splits", RANGES)
+def test_ranges_of_long_rows(ctx, B, n_disc, n_keep, D, M, splits):
+    p, buf, alive = _problem(B, n_disc, n_keep, D, M)
+    plan = H.gram_plan(p)
+    assert plan.use_gram and plan.form == H.SQUARE and plan.splits == splits
+    assert (splits - 1) * plan.st_per_split * 32 < D <= splits * plan.st_per_split * 32
+    (fc.ficoco_l_step if M else fc.ficoco_v_step)(ctx, p, buf)
+    torch.cuda.synchronize()
+    _check(p, buf, plan, buf.discard_idx, buf.keep_idx)
