@@ -394,10 +394,10 @@ __device__ __forceinline__ double sums_of_16(const double (&x)[16], int l) {
 // exponentials 170 / 40 / 51; normalisers through LDS, whole tiles written without tests 158 / 34 / 49; 32 x 32 products
 // 157 / 33 / 51; rows straight into LDS, order of precedence among the wavefronts 142 / 28.6 / 48.
 // Causal maps: key tiles that some query of group g (of qr rows) sees, and all of them.  (Queries behind the visual span see all.)
-__host__ __device__ __forceinline__ int causal_keys(int g, int k_tiles, int qr, int n_visq) {
+__device__ __forceinline__ int causal_keys(int g, int k_tiles, int qr, int n_visq) {
   return (g + 1) * qr > n_visq ? k_tiles : min(k_tiles, ((g + 1) * qr + kQkKeys - 1) / kQkKeys);
 }
-__host__ __device__ __forceinline__ int causal_tiles(int groups, int k_tiles, int qr, int n_visq) {
+__device__ __forceinline__ int causal_tiles(int groups, int k_tiles, int qr, int n_visq) {
   int sum = 0;
   for (int g = 0; g < groups; ++g) sum += causal_keys(g, k_tiles, qr, n_visq);
   return sum;
@@ -1000,13 +1000,13 @@ static void launch_qk(QkArgs a, hipStream_t s) {
   const int wide = QkMeanShape<false>::kQueries, q_tiles = (a.nq + wide - 1) / wide;
   const bool split = a.H >= 8 && (int64_t)a.nb * q_tiles * a.k_tiles < 128;
   if constexpr (DEC && KS == 4) {
-    // Heads of 128: the form with rows three stages ahead, but for one block of queries (whose heads the wavefronts share), and for
-    // sixteen tiles or fewer with many heads, which keep the shares of four.  us of the two kernels, this form and the other one chosen:
-    // 32 heads, 8 x (576 + 64) queries (232 tiles) 64.5 / 78.8, 4 images 45.2 / 66.8 (split), one 38.0 / 39.0 (split); 16 heads, 8 images 40.2 /
-    // 45.8, 12 x (300 + 40) 32.1 / 43.9 (split); 8 heads 31.4 / 32.8; 8 x (96 + 17), 32 heads (16 tiles) 31.9 / 29.1 (split); 8 text queries
-    // alone, 16 heads 23.5 / 21.3.
-    const int64_t live = (int64_t)a.nb * causal_tiles(q_tiles, a.k_tiles, wide, a.n_visq);
-    if (a.nq > kQkB && (live > 16 || a.H < 16)) {
+    // Heads of 128: the form with rows three stages ahead in place of the wide one, the same bits, but for one block of queries, whose heads
+    // the wavefronts share.  us of the two kernels, this form and the wide one: 32 heads, 8 x (576 + 64) queries 61.3 / 87.5, 4
+    // images (180 tiles) 44.5 / 68.0, 2 x (630 + 200) (140) 46.4 / 71.3; 16 heads, 8 x (576 + 64) 38.0 / 50.6.  Not in place of split
+    // heads: about as fast there (32 heads, one image of 576 + 64 38.0 / 39.0, 8 x (96 + 17) 31.9 / 29.1), but all heads in line take the
+    // error of the scores against 64 bits from 3.20e-8 to 3.56e-8 (32 heads, 576 + 64), and with sums of three heads, which keep it, 42.9 us
+    // instead of 40.9 at one image and 44.7 instead of 43.0 at two.
+    if (a.nq > kQkB && !split) {
       a.q_groups = q_tiles;
       hipLaunchKernelGGL(qk_mean_deep_kernel, dim3(xcd_padded_total(a.nb * a.q_groups * a.k_tiles)), dim3(kQkWaves * kWave), 0, s, a);
       return;

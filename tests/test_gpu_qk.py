@@ -249,10 +249,10 @@ def test_causal_heads_split(ctx, B, N, M, H, d):
 
 
 @pytest.mark.parametrize("B,N,M,H", [(1, 70, 5, 1), (2, 64, 64, 2), (1, 130, 33, 3), (2, 200, 9, 4), (1, 129, 128, 5), (1, 61, 70, 6), (3, 128, 1, 7),
-                                     (1, 193, 64, 12), (2, 33, 31, 13), (9, 250, 40, 17), (1, 200, 33, 16), (1, 20, 20, 18)])
+                                     (1, 193, 64, 12), (2, 33, 31, 13), (9, 250, 40, 17), (11, 250, 40, 12), (22, 130, 33, 17), (1, 20, 20, 18)])
 def test_causal_heads_of_128(ctx, monkeypatch, B, N, M, H):
-    """Heads that leave every remainder of a turn of six; one tile, tiles of zeros, tiles with one wavefront's queries, sixteen tiles
-    and fewer with many heads (not that form).  The workspace holds NaN first: every entry of the maps has to be written."""
+    """Heads that leave every remainder of a turn of six; one tile, tiles of zeros, tiles with one wavefront's queries; eight heads and
+    more with 132 tiles, and with fewer (split, not that form).  The workspace holds NaN first: every entry of the maps has to be written."""
     make = fc.Buffers
 
     def filled(*args):
