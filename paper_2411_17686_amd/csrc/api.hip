@@ -32,9 +32,13 @@ namespace ficoco {
 
 // Row lanes, 8-column groups (at most) and rows of a reduction workgroup with the head-mean map to store, whose chunks are
 // multiples of 8 rows (whole 32-byte sectors of the transposed map).  Chunks of 32 rows: their partials all pass through the
-// one workgroup of the filter, and the pieces of the transposed map are whole cache lines.  Then 32 lanes x 8 groups, a row a
-// thread, which takes one trip to memory for up to sixteen loads; 16 x 16, two rows, where a row's heads are fewer than eight loads
-// or more than sixteen and there are workgroups enough, and where there are very many (longer pieces of the rows).
+// one workgroup of the filter, and the pieces of the transposed map are whole cache lines.  Up to 1300 workgroups (five a compute unit)
+// 32 lanes x 8 groups, a row a thread, which takes one trip to memory for up to sixteen loads; beyond 700 of them 16 x 16, two rows,
+// where a row's heads are fewer than eight loads (with sixteen 1150: launch at 5 / 8 x 576 tokens, 810 / 1296 workgroups, 8 x 24 13.8 / 23.4 us, 32 x 8 13.1 /
+// 25.2; 8 heads, 1296 13.0 and 12.2).  More workgroups than that: 8 x 24, four rows, whose loads lie closer together in memory and
+// whose few, long workgroups leave room for those of other streams: 16 x 577 tokens, 16 heads, four inputs in turn, 38.3 us
+// a launch (32 x 8 42.6), 67.0 us per step alone (70.7), 50 to 53 with three in flight (55 to 56); decoder's maps, 8 x 576 of 32 heads, three in
+// flight 59.0 (16 x 16 60.8).  Above 6000 workgroups 16 x 16 (4 x 2880: 247 us a launch, 251 with 8 x 24).
 // us per step in bfloat16 before (8 x 24, rows for 512 workgroups) / 8 x 24 and 32 rows / 16 x 16 / 32 x 8:
 //   16 heads, 1 x 576 tokens 29.5 / 29.7 / 27.6 / 24.9, 5 x 576 35.2 / 36.1 / 33.8 / 33.5, 16 x 576 73.0 / 73.0 / 73.2 / 73.6, 4 x 2880 314 / 314 / 311 / 321;
 //   8 heads, 1 x 576 28.2 / 27.1 / 25.3 / 23.2, 8 x 576 34.6 / 34.7 / 34.0 / 33.3, 8 x 1200 95.2 / 95.5 / 94.1 / 93.6;
@@ -49,7 +53,8 @@ static MapShape map_shape(const ficoco_problem& p) {
   if (p.N <= 256 && wgs(16, 16) <= 512) return {16, 16, 16};
   const int64_t most = wgs(8, 32);
   const int loads = p.dtype == FICOCO_BF16 ? p.H : 2 * p.H;
-  return most <= 700 || (loads >= 8 && loads <= 16 && most <= 6000) ? MapShape{32, 8, 32} : MapShape{16, 16, 32};
+  if (most <= 700 || (loads >= 8 && loads <= 16 && most <= 1300 && most * loads <= 19000)) return {32, 8, 32};
+  return loads < 8 || most > 6000 ? MapShape{16, 16, 32} : MapShape{8, 24, 32};
 }
 // Workgroups the reduction aims at where it has no such map to store.
 constexpr int64_t kWgTarget = 1024;
