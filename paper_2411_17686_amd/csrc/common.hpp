@@ -128,6 +128,13 @@ inline bool unit_rows_summed(const ficoco_problem& p, int Df) {
 // 16, with 8 and in the separate passes before: one sequence of 576 tokens, 5120 features 73.2 / 66.0 / 71.6, four of 200 82.2 / 74.2 /
 // 79.1; four of 576 91.9 / 97.3 / 97.8, eight of 690 172 / 183 / 187.
 inline int unit_rows_per_wg(const ficoco_problem& p) { return (int64_t)p.B * ((p.N + 15) / 16) >= 128 ? 16 : 8; }
+// The column partials of the reduction are added by a launch of their own (combine_partials_kernel) instead of by the one workgroup of
+// an image's filter: from 48 partials a thread of that workgroup (chunks x columns a thread) on.  us behind the reduction, added by the filter and
+// so: 33 partials of 1024 columns 25.0 / 23.9 and, four images, 27.7 / 26.7; 66 of 1025 columns 28.1 / 27.4, 82 (1296) 31.4 / 28.4, 108 (1728)
+// 36.5 / 30.2, 126 (2000) 41.5 / 30.6; without a map 58 (576) 30.8 / 29.9; from queries and keys 46 (1440) 27.9 / 27.9, 54 (1728) 31.6 / 28.8, 108 (2304) 47.6 / 40.5.
+inline bool partials_combined(const ficoco_problem& p, const Plan& pl) {
+  return p.red_src == FICOCO_R_ATTN_RECV && (int64_t)pl.n_chunks * ((p.N + kSelectThreads - 1) / kSelectThreads) > 48;
+}
 // text_stats_done: the text statistics were formed by the feature stage's launches
 void launch_score(const ficoco_problem& p, const Plan& pl, char* ws, double* scores, hipStream_t s,
                   bool text_stats_done = false);

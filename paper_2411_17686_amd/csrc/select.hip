@@ -819,7 +819,7 @@ __global__ __launch_bounds__(kSelectThreads) void select_kernel(SelectArgs a) {
   }
 }
 
-// Large problems (many row chunks and more columns than one workgroup has threads): the
+// Large problems (partials_combined: many row chunks, or more columns than one workgroup has threads): the
 // per-column partial sums are added up by a grid of workgroups first, in chunk order, so the
 // single per-image workgroup of select_kernel reads one value per column.
 constexpr int kCombineThreads = 64;
@@ -963,8 +963,7 @@ void launch_select(const ficoco_problem& p, const Plan& pl, char* ws, double* sc
   a.red_src = p.red_src; a.sem_src = p.sem_src;
   a.do_score = do_score; a.do_filter = do_filter;
   a.recv_part = (const double*)(ws + pl.recv_part);
-  if (do_score && p.red_src == FICOCO_R_ATTN_RECV &&
-      (int64_t)pl.n_chunks * ((p.N + kSelectThreads - 1) / kSelectThreads) > 128) {
+  if (do_score && partials_combined(p, pl)) {
     double* sums = (double*)(ws + pl.fterm);     // free in this mode (it holds the mean-cosine term otherwise)
     hipLaunchKernelGGL(combine_partials_kernel, dim3((p.N + kCombineThreads - 1) / kCombineThreads, p.B), dim3(kCombineThreads), 0, s, a.recv_part, sums,
                        p.N, pl.n_chunks);

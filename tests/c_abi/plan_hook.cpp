@@ -1,5 +1,6 @@
 // What a test may ask about the plan of a problem: where the block of approximate cosines, the unit rows, the text
-// profiles and their maxima lie in the workspace, how the block is cut, and the error its readers allow for.  (Host code only.)
+// profiles and their maxima lie in the workspace, how the block is cut, and the error its readers allow for; how the reduction
+// of the maps is cut.  (Host code only.)
 #include "../../paper_2411_17686_amd/csrc/common.hpp"
 
 extern "C" {
@@ -19,6 +20,21 @@ int plan_hook_gram(const ficoco_problem* p, gram_plan* out) {
   if (rc != FICOCO_OK) return rc;
   *out = gram_plan{(int64_t)pl.ct, (int64_t)pl.xhat, (int64_t)pl.ttext, (int64_t)pl.cmax, pl.use_gram, pl.gram_splits, pl.gram_st_per_split,
                    pl.use_gram ? (int32_t)ficoco::gram_form(*p, pl) : 0, pl.Df, ficoco::gram_delta(pl)};
+  return rc;
+}
+
+struct reduce_plan {
+  int64_t total, beyond;     // bytes of the workspace; those that the limit of the static scratch does not count
+  int32_t row_lanes, strip_groups, rows, chunks, combined;
+};
+
+// scratch: as in make_plan
+int plan_hook_reduce(const ficoco_problem* p, uint64_t scratch, reduce_plan* out) {
+  ficoco::Plan pl{};
+  const char* why = nullptr;
+  const int rc = ficoco::make_plan(*p, pl, &why, scratch);
+  if (rc != FICOCO_OK) return rc;
+  *out = reduce_plan{(int64_t)pl.total, (int64_t)pl.beyond, pl.row_lanes, pl.strip_groups, pl.rows_per_wg, pl.n_chunks, ficoco::partials_combined(*p, pl)};
   return rc;
 }
 

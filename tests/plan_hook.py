@@ -1,5 +1,5 @@
-"""ctypes view of tests/c_abi/plan_hook.cpp: how the library lays out and cuts the block of approximate cosines, and
-where the text profiles lie."""
+"""ctypes view of tests/c_abi/plan_hook.cpp: how the library lays out and cuts the block of approximate cosines and
+the reduction of maps, and where the text profiles lie."""
 import ctypes as C
 import os
 
@@ -12,9 +12,25 @@ class GramPlan(C.Structure):
                 ("st_per_split", C.c_int32), ("form", C.c_int32), ("Df", C.c_int32), ("delta", C.c_float)]
 
 
-def gram_plan(p):
+class ReducePlan(C.Structure):
+    _fields_ = [("total", C.c_int64), ("beyond", C.c_int64), ("row_lanes", C.c_int32), ("strip_groups", C.c_int32), ("rows", C.c_int32),
+                ("chunks", C.c_int32), ("combined", C.c_int32)]
+
+
+def _lib():
     assert os.path.exists(_SO), "tests/c_abi/libplan_hook.so is not built: run `python -m paper_2411_17686_amd.build`"
+    return C.CDLL(_SO)
+
+
+def gram_plan(p):
     g = GramPlan()
-    rc = C.CDLL(_SO).plan_hook_gram(C.byref(p), C.byref(g))
+    rc = _lib().plan_hook_gram(C.byref(p), C.byref(g))
     assert rc == 0, rc
     return g
+
+
+def reduce_plan(p, scratch=2 ** 64 - 1):
+    r = ReducePlan()
+    rc = _lib().plan_hook_reduce(C.byref(p), C.c_uint64(scratch), C.byref(r))
+    assert rc == 0, rc
+    return r
