@@ -45,12 +45,17 @@ namespace ficoco {
 //   4 heads, 1 x 576 28.3 / 25.7 / 25.1 / 23.9, 8 x 576 32.3 / 32.2 / 31.1 / 32.2, 40 x 576 74.1 / 74.2 / 73.1 / 76.0.
 // Short sequences have few chunks either way: 8 rows while every workgroup has a compute unit of its own, then 16 (3 images of
 // 221, 8 rows of 8 lanes / 16 of 16 / 32 of 32: 22.1 / 22.8 / 23.1; 8 images 24.4 / 23.5 / 25.2).
+//
+// What the static scratch may hold is a fixed size, so no shape has fewer rows (more partials) than the 8 x 24 lanes for 512 workgroups whose
+// partials it has always had room for: the 16 rows end where those would take 24.
+static int rows_for_512(int64_t strip_rows) { return (int)std::min<int64_t>(((strip_rows + 511) / 512 + 7) / 8 * 8, 32); }
 struct MapShape { int lanes, groups, rows; };
-static MapShape map_shape(const ficoco_problem& p) {
+static MapShape map_shape(const ficoco_problem& p, int rows) {
   const int groups = (p.N + kVec - 1) / kVec;
   auto wgs = [&](int g, int r) { return (int64_t)p.B * ((groups + g - 1) / g) * ((p.N + r - 1) / r); };
   if (p.N <= 256 && wgs(24, 8) <= 256) return {8, 24, 8};
-  if (p.N <= 256 && wgs(16, 16) <= 512) return {16, 16, 16};
+  const int for_512 = rows_for_512((int64_t)p.B * ((groups + 23) / 24) * rows);
+  if (p.N <= 256 && wgs(16, 16) <= 512 && for_512 <= 16) return {16, 16, 16};
   const int64_t most = wgs(8, 32);
   const int loads = p.dtype == FICOCO_BF16 ? p.H : 2 * p.H;
   if (most <= 700 || (loads >= 8 && loads <= 16 && most <= 1300 && most * loads <= 19000)) return {32, 8, 32};
@@ -169,7 +174,19 @@ int make_plan(const ficoco_problem& p, Plan& pl, const char** why, size_t scratc
   // (with the head-mean map to store, strips stay narrow at any width: the workgroup turns its
   // tile of the map in LDS, strip columns x chunk rows)
   const bool map_tile = p.corr_src == FICOCO_C_ATTN;
-  const MapShape ms = map_shape(p);
+  const bool vis_rows = p.red_src == FICOCO_R_ATTN_RECV || p.corr_src == FICOCO_C_ATTN;
+  if (need_A && !qk) {
+    int lo = p.vis_begin - p.a_q_begin, hi = lo + p.N;  // visual query rows
+    if (!vis_rows) { lo = hi = p.cls_index - p.a_q_begin; ++hi; }
+    if (p.sem_src == FICOCO_G_CLS_ATTN) {
+      const int c = p.cls_index - p.a_q_begin;
+      if (c < lo) lo = c;
+      if (c + 1 > hi) hi = c + 1;
+    }
+    pl.a_row0 = lo;
+    pl.a_rows = hi - lo;
+  }
+  const MapShape ms = map_shape(p, pl.a_rows);
   if (map_tile) {
     pl.col_strips = (groups + ms.groups - 1) / ms.groups;
     pl.strip_groups = (groups + pl.col_strips - 1) / pl.col_strips;
@@ -199,23 +216,13 @@ int make_plan(const ficoco_problem& p, Plan& pl, const char** why, size_t scratc
     pl.qk_nq = pl.qk_visq + (L ? p.M : p.sem_src == FICOCO_G_CLS_ATTN ? 1 : 0);
     pl.n_chunks = (pl.qk_visq + kQkTile - 1) / kQkTile;
   } else if (need_A) {
-    int lo = p.vis_begin - p.a_q_begin, hi = lo + p.N;  // visual query rows
-    const bool vis_rows = p.red_src == FICOCO_R_ATTN_RECV || p.corr_src == FICOCO_C_ATTN;
-    if (!vis_rows) { lo = hi = p.cls_index - p.a_q_begin; ++hi; }
-    if (p.sem_src == FICOCO_G_CLS_ATTN) {
-      const int c = p.cls_index - p.a_q_begin;
-      if (c < lo) lo = c;
-      if (c + 1 > hi) hi = c + 1;
-    }
-    pl.a_row0 = lo;
-    pl.a_rows = hi - lo;
     pl.rows_per_wg = rows_per_wg(pl.a_rows);
     pl.a_shift = 0;
     if (p.corr_src == FICOCO_C_ATTN && vis_rows) {
       // The head-mean map is stored transposed, a chunk's rows of one key column as one piece:
       // chunks of a multiple of 8 rows that start at multiples of it, counted from visual row 0,
       // make every piece whole 32-byte sectors.
-      const int lead = (p.vis_begin - p.a_q_begin) - lo;             // role rows before visual row 0 (the [CLS] query)
+      const int lead = (p.vis_begin - p.a_q_begin) - pl.a_row0;      // role rows before visual row 0 (the [CLS] query)
       pl.a_shift = (pl.rows_per_wg - lead % pl.rows_per_wg) % pl.rows_per_wg;
     }
     pl.n_chunks = (pl.a_rows + pl.a_shift + pl.rows_per_wg - 1) / pl.rows_per_wg;

@@ -34,3 +34,16 @@ PARTIALS = [(1, 640, 4, True, (16.3, 16.4)), (4, 1025, 4, True, (30.9, 29.9)), (
 def test_many_partials_are_added_by_a_launch_of_their_own(B, N, heads, maps, us):
     r = H.reduce_plan(problem(B, N, heads, maps=maps))
     assert us[r.combined] <= 1.02 * min(us)
+
+
+# images, tokens, edges a token at most: just within the limit with chunks of 24 rows, beyond it with 16
+LARGEST = [(64, 128, 580), (16, 256, 1167), (85, 96, 586)]
+
+
+@pytest.mark.parametrize("B,N,k_max", LARGEST)
+def test_static_scratch_holds_the_partials_of_small_maps(B, N, k_max):
+    """A step's workspace, without its lists, is within the limit of the allocation-free entry point."""
+    p = problem(B, N, 8)
+    p.k_max = k_max
+    r = H.reduce_plan(p, 48 << 20)
+    assert r.total - r.beyond <= fc.STATIC_SCRATCH_BYTES
