@@ -31,35 +31,38 @@ struct ficoco_ctx {
 namespace ficoco {
 
 // Row lanes, 8-column groups (at most) and rows of a reduction workgroup with the head-mean map to store, whose chunks are
-// multiples of 8 rows (whole 32-byte sectors of the transposed map).  Chunks of 32 rows: their partials all pass through the
-// one workgroup of the filter, and the pieces of the transposed map are whole cache lines.  Up to 1300 workgroups (five a compute unit)
-// 32 lanes x 8 groups, a row a thread, which takes one trip to memory for up to sixteen loads; beyond 700 of them 16 x 16, two rows,
-// where a row's heads are fewer than eight loads (with sixteen 1150: launch at 5 / 8 x 576 tokens, 810 / 1296 workgroups, 8 x 24 13.8 / 23.4 us, 32 x 8 13.1 /
-// 25.2; 8 heads, 1296 13.0 and 12.2).  More workgroups than that: 8 x 24, four rows, whose loads lie closer together in memory and
-// whose few, long workgroups leave room for those of other streams: 16 x 577 tokens, 16 heads, four inputs in turn, 38.3 us
-// a launch (32 x 8 42.6), 67.0 us per step alone (70.7), 50 to 53 with three in flight (55 to 56); decoder's maps, 8 x 576 of 32 heads, three in
-// flight 59.0 (16 x 16 60.8).  Above 6000 workgroups 16 x 16 (4 x 2880: 247 us a launch, 251 with 8 x 24).
-// us per step in bfloat16 before (8 x 24, rows for 512 workgroups) / 8 x 24 and 32 rows / 16 x 16 / 32 x 8:
-//   16 heads, 1 x 576 tokens 29.5 / 29.7 / 27.6 / 24.9, 5 x 576 35.2 / 36.1 / 33.8 / 33.5, 16 x 576 73.0 / 73.0 / 73.2 / 73.6, 4 x 2880 314 / 314 / 311 / 321;
-//   8 heads, 1 x 576 28.2 / 27.1 / 25.3 / 23.2, 8 x 576 34.6 / 34.7 / 34.0 / 33.3, 8 x 1200 95.2 / 95.5 / 94.1 / 93.6;
-//   4 heads, 1 x 576 28.3 / 25.7 / 25.1 / 23.9, 8 x 576 32.3 / 32.2 / 31.1 / 32.2, 40 x 576 74.1 / 74.2 / 73.1 / 76.0.
-// Short sequences have few chunks either way: 8 rows while every workgroup has a compute unit of its own, then 16 (3 images of
-// 221, 8 rows of 8 lanes / 16 of 16 / 32 of 32: 22.1 / 22.8 / 23.1; 8 images 24.4 / 23.5 / 25.2).
+// multiples of 8 rows (whole 32-byte sectors of the transposed map).
 //
-// What the static scratch may hold is a fixed size, so no shape has fewer rows (more partials) than the 8 x 24 lanes for 512 workgroups whose
-// partials it has always had room for: the 16 rows end where those would take 24.
+// The usual shape is 8 lanes x 24 groups (32 beyond 1024 columns) with rows for about 512 workgroups: its loads lie close together in
+// memory, and few, long workgroups leave room for those of other streams.  Others take its place where they are faster, by the 16-byte loads that a
+// row and a column group take (`loads`: heads, twice as many in float32).  Step in us, usual / taken:
+//   16 x 16 lanes, 16 rows: up to sixteen loads, short sequences, at most 512 workgroups.  8 x 256 tokens, 16 heads 26.9 / 25.4.
+//   32 x 8, 32 rows, a row a thread: up to sixteen loads in flight, and few partials for the one workgroup of the filter.  1 x 576 tokens, 8 heads
+//     25.9 / 24.1, 3 x 576 28.7 / 27.1.  As far as 1300 workgroups (five a compute unit: 8 x 576, 12 heads 39.7 / 39.6; with sixteen loads 1187; few heads
+//     700, from where two rows a thread are better).  Beyond sixteen loads a thread makes several trips with one row in hand: up to 512 workgroups (1 x 576,
+//     float32, 16 heads 28.3 / 26.3), with more than forty loads one a compute unit (the second is half a launch there: 3 x 400, 32 heads of float32
+//     with 273: launch 12.5 us usual, 17.1 so), for short sequences none (46 x 144, 40 heads of float32 56.4 / 63.1, 16 x 144 of a decoder in bfloat16 35.8 / 38.5).
+//   16 x 16, 32 rows, two a thread: few heads up to 2500 workgroups (8 x 576, 4 heads 31.1 / 30.2; beyond, several steps in flight lose by it: 48 x 576, one
+//     head 54.6 / 59.2), others from 6000 on (4 x 2880, 16 heads 314 / 311).
+// Of 2500 problems (60 to 2900 tokens, 1 to 80 images, 1 to 40 heads) the step is 1.018 times as fast as with the usual shape alone, four are more than 3 %
+// slower (none 6 %), three steps in flight 1.005 times.  (With 8 x 24 lanes and 32 rows for all calls beyond 700 workgroups 119 were, by up to 16 %: 11 x 348,
+// 32 heads, launch 22.1 usual, 30.9.)
+//
+// What the static scratch may hold is a fixed size, so no shape has fewer rows (more partials) than the usual one, whose
+// partials it has always had room for: the 16 rows end where that takes 24.
 static int rows_for_512(int64_t strip_rows) { return (int)std::min<int64_t>(((strip_rows + 511) / 512 + 7) / 8 * 8, 32); }
 struct MapShape { int lanes, groups, rows; };
 static MapShape map_shape(const ficoco_problem& p, int rows) {
-  const int groups = (p.N + kVec - 1) / kVec;
+  const int groups = (p.N + kVec - 1) / kVec, wide = groups > 128 ? 32 : 24;
   auto wgs = [&](int g, int r) { return (int64_t)p.B * ((groups + g - 1) / g) * ((p.N + r - 1) / r); };
-  if (p.N <= 256 && wgs(24, 8) <= 256) return {8, 24, 8};
-  const int for_512 = rows_for_512((int64_t)p.B * ((groups + 23) / 24) * rows);
-  if (p.N <= 256 && wgs(16, 16) <= 512 && for_512 <= 16) return {16, 16, 16};
-  const int64_t most = wgs(8, 32);
+  const MapShape usual{8, wide, rows_for_512((int64_t)p.B * ((groups + wide - 1) / wide) * rows)};
   const int loads = p.dtype == FICOCO_BF16 ? p.H : 2 * p.H;
-  if (most <= 700 || (loads >= 8 && loads <= 16 && most <= 1300 && most * loads <= 19000)) return {32, 8, 32};
-  return loads < 8 || most > 6000 ? MapShape{16, 16, 32} : MapShape{8, 24, 32};
+  const bool is_short = p.N <= 256;
+  if (is_short && wgs(24, 8) <= 256) return usual;         // every workgroup has a compute unit of its own
+  if (is_short && loads <= 16 && wgs(16, 16) <= 512 && usual.rows <= 16) return {16, 16, 16};
+  const int64_t most = wgs(8, 32);
+  if (most <= (loads < 8 ? 700 : loads <= 16 ? std::min(1300, 19000 / loads) : is_short ? 0 : loads <= 40 ? 512 : 256)) return {32, 8, 32};
+  return (loads < 8 ? most <= 2500 : most > 6000) ? MapShape{16, 16, 32} : usual;
 }
 // Workgroups the reduction aims at where it has no such map to store.
 constexpr int64_t kWgTarget = 1024;
@@ -164,15 +167,13 @@ int make_plan(const ficoco_problem& p, Plan& pl, const char** why, size_t scratc
   if (p.k_mode == FICOCO_K_CONVERGENT) pl.fixed_k = 0;
 
   // attention reduction geometry
-  // Column strips.  Up to 1024 key columns a strip has at most 24 8-column groups: a workgroup
-  // is then (row lanes) x (groups of the strip) with several row lanes, covers many query rows
-  // and leaves few per-chunk column partials behind (measured: 3 strips of 24 groups beat 1 strip
-  // of 72 at 576 columns by 4 %).  Wider maps without a head-mean map to store take wide strips
-  // (their partials are a small share of the traffic).  From there the fewest strips that keep at
-  // least 80 % of the threads busy, else the busiest of the next 8 choices.
+  // Column strips.  With the head-mean map to store they are narrow at any width: the workgroup turns its
+  // tile of the map in LDS, strip columns x chunk rows (map_shape).  Without it, up to 1024 key columns, a strip has
+  // at most 24 8-column groups: a workgroup is then (row lanes) x (groups of the strip) with several row lanes, covers many
+  // query rows and leaves few per-chunk column partials behind (measured: 3 strips of 24 groups beat 1 strip
+  // of 72 at 576 columns by 4 %).  Wider maps take wide strips (their partials are a small share of the traffic): the
+  // fewest strips that keep at least 80 % of the threads busy, else the busiest of the next 8 choices.
   const int groups = (p.N + kVec - 1) / kVec;
-  // (with the head-mean map to store, strips stay narrow at any width: the workgroup turns its
-  // tile of the map in LDS, strip columns x chunk rows)
   const bool map_tile = p.corr_src == FICOCO_C_ATTN;
   const bool vis_rows = p.red_src == FICOCO_R_ATTN_RECV || p.corr_src == FICOCO_C_ATTN;
   if (need_A && !qk) {

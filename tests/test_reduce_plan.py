@@ -47,3 +47,24 @@ def test_static_scratch_holds_the_partials_of_small_maps(B, N, k_max):
     p.k_max = k_max
     r = H.reduce_plan(p, 48 << 20)
     assert r.total - r.beyond <= fc.STATIC_SCRATCH_BYTES
+
+
+# images, tokens, heads, type, us of the step with the usual shape (8 lanes, rows for 512 workgroups), 32 x 8 lanes and 32 rows, 16 x 16 and 16 / 32 rows
+# and 8 x 24 lanes and 32 rows
+SHAPES = [
+    # up to sixteen loads
+    (1, 576, 8, fc.BF16, (25.9, 24.1, 25.1, 25.6, 27.2)), (3, 576, 8, fc.BF16, (28.7, 27.1, 28.1, 27.6, 28.1)), (8, 576, 12, fc.BF16, (39.7, 39.6, 40.5, 39.8, 39.7)),
+    (16, 576, 16, fc.BF16, (68.9, 69.2, 70.2, 68.3, 68.9)), (8, 256, 16, fc.BF16, (26.9, 25.5, 25.4, 25.9, 28.6)),
+    (8, 576, 4, fc.BF16, (31.1, 31.2, 32.5, 30.2, 31.1)), (47, 400, 4, fc.BF16, (56.2, 58.1, 59.6, 55.6, 56.2)), (48, 576, 1, fc.BF16, (71.5, 86.4, 89.8, 72.6, 71.5)),
+    # more
+    (1, 576, 16, fc.F32, (28.3, 26.3, 27.9, 27.8, 30.3)), (3, 400, 32, fc.F32, (33.2, 36.3, 34.7, 34.6, 37.8)), (46, 144, 40, fc.F32, (56.4, 63.1, 58.9, 63.5, 68.3)),
+    (5, 428, 40, fc.F32, (52.5, 58.2, 55.3, 60.8, 53.6)), (5, 576, 40, fc.F32, (78.3, 76.5, 74.5, 73.2, 87.6)), (11, 348, 32, fc.BF16, (42.8, 45.5, 42.5, 45.6, 50.9)),
+    (49, 144, 40, fc.BF16, (45.4, 48.1, 45.4, 52.6, 54.4)), (7, 465, 40, fc.BF16, (57.8, 56.9, 57.0, 56.9, 65.1)), (6, 549, 32, fc.BF16, (56.6, 55.3, 57.2, 60.5, 63.2)),
+]
+
+
+@pytest.mark.parametrize("B,N,heads,dtype,us", SHAPES)
+def test_shape_is_no_slower_than_the_usual(B, N, heads, dtype, us):
+    r = H.reduce_plan(problem(B, N, heads, dtype))
+    got = us[4 if r.rows == 32 else 0] if r.row_lanes == 8 else us[1] if r.row_lanes == 32 else us[2 if r.rows == 16 else 3]
+    assert got <= 1.03 * us[0]
