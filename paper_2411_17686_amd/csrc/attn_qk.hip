@@ -15,6 +15,7 @@
 //
 // Single precision (products of bfloat16 values are exact in it), row sums and column sums in double.
 #include "common.hpp"
+#include "causal_tiles.hpp"
 
 #include <algorithm>
 
@@ -393,33 +394,14 @@ __device__ __forceinline__ double sums_of_16(const double (&x)[16], int l) {
 // on its own 180 / 44 / 56; 96 x 64 by four wavefronts with 16 x 16 products, the next head's beside this head's
 // exponentials 170 / 40 / 51; normalisers through LDS, whole tiles written without tests 158 / 34 / 49; 32 x 32 products
 // 157 / 33 / 51; rows straight into LDS, order of precedence among the wavefronts 142 / 28.6 / 48.
-// Causal maps: key tiles that some query of group g (of qr rows) sees, and all of them.  (Queries behind the visual span see all.)
-__device__ __forceinline__ int causal_keys(int g, int k_tiles, int qr, int n_visq) {
-  return (g + 1) * qr > n_visq ? k_tiles : min(k_tiles, ((g + 1) * qr + kQkKeys - 1) / kQkKeys);
-}
-__device__ __forceinline__ int causal_tiles(int groups, int k_tiles, int qr, int n_visq) {
-  int sum = 0;
-  for (int g = 0; g < groups; ++g) sum += causal_keys(g, k_tiles, qr, n_visq);
-  return sum;
-}
 constexpr int kQkBand = 8;                          // key tiles side by side in the order of the workgroups
 // Tile number `unit` of an image (qr queries x kQkKeys keys): in columns kQkBand key tiles wide, so that the workgroups that run
-// together on an XCD need few rows of either side, which its L2 holds for all heads.  live_first (causal maps of more tiles
-// than there are compute units): first the tiles that hold a key some query sees, last queries first, then the others, which are
-// zero.  In between, the latter took places on the chip from which others were missing (16 heads of 64, 270 tiles: 37.9 us for the two kernels, 34.8
-// so; where every tile has a place at once the search costs more: 135 tiles 27.4, and 28.1 so).
-constexpr int kCausalTiles = 256;
+// together on an XCD need few rows of either side, which its L2 holds for all heads.  live_first: first the tiles that hold a key
+// some query sees, then the others, which are zero and took places on the chip from which others were missing in between.
 __device__ __forceinline__ void qk_tile(const QkArgs& a, int unit, bool live_first, int qr, int& kt0, int& w0) {
   if (live_first) {
-    const int live_all = causal_tiles(a.q_groups, a.k_tiles, qr, a.n_visq);
-    const bool dead = unit >= live_all;
-    int left = dead ? unit - live_all : unit, g = a.q_groups - 1;
-    for (; g > 0; --g) {
-      const int live = causal_keys(g, a.k_tiles, qr, a.n_visq), here = dead ? a.k_tiles - live : live;
-      if (left < here) break;
-      left -= here;
-    }
-    kt0 = dead ? causal_keys(g, a.k_tiles, qr, a.n_visq) + left : left;
+    int g;
+    causal_tile(unit, a.q_groups, a.k_tiles, qr / kQkKeys, a.n_visq / qr, g, kt0);
     w0 = g * qr;
   } else {
     const int band = unit / (kQkBand * a.q_groups), in_band = unit - band * kQkBand * a.q_groups;
@@ -507,7 +489,7 @@ __global__ __launch_bounds__(QkMeanShape<SPLIT>::kThreads) __attribute__((amdgpu
   const int64_t bi = unit / (a.k_tiles * a.q_groups), b = a.b0 + bi;
   const int in_img = unit - (int)bi * a.k_tiles * a.q_groups;
   int kt0, w0;
-  qk_tile(a, in_img, DEC && !SPLIT && units > kCausalTiles, QR, kt0, w0);
+  qk_tile(a, in_img, DEC && !SPLIT && causal_live_first(units, a.k_tiles), QR, kt0, w0);
   // One block of queries in all (uniform): the wavefronts share its heads, with operands straight from memory, unless the tile is
   // split anyway and a wavefront's share is four 32-feature steps or more: then rows through LDS are faster.  us, so and
   // as any other tile: 8 x 16 text queries, 32 heads of 128 25.3 / 21.4, 24 queries 26.7 / 21.5, one image of 16 and 16 heads 15.6 / 13.9, 8 x 20 and
@@ -811,7 +793,7 @@ __global__ __launch_bounds__(kQkWaves * kWave) __attribute__((amdgpu_waves_per_e
   const int wv = __builtin_amdgcn_readfirstlane(tid / kWave), wq = wv / 2, wk = wv % 2;
   const int64_t bi = unit / (a.k_tiles * a.q_groups), b = a.b0 + bi;
   int kt0, w0;
-  qk_tile(a, unit - (int)bi * a.k_tiles * a.q_groups, units > kCausalTiles, QR, kt0, w0);
+  qk_tile(a, unit - (int)bi * a.k_tiles * a.q_groups, causal_live_first(units, a.k_tiles), QR, kt0, w0);
   const int q0 = wq * 2 * kQkB, v0 = w0 + q0, wk0 = kt0 * kQkKeys, ik0 = wk0 + wk * kQkB;
   f32x16_t P[2] = {qk_zero(), qk_zero()};
   if (a.vis0 + wk0 <= a.row(min(w0 + QR, a.nq) - 1)) {  // uniform in the workgroup: some query sees some key

@@ -1,7 +1,8 @@
 // What a test may ask about the plan of a problem: where the block of approximate cosines, the unit rows, the text
 // profiles and their maxima lie in the workspace, how the block is cut, and the error its readers allow for; how the reduction
-// of the maps is cut.  (Host code only.)
+// of the maps is cut; the order of causal tiles.  (Host code only.)
 #include "../../paper_2411_17686_amd/csrc/common.hpp"
+#include "../../paper_2411_17686_amd/csrc/causal_tiles.hpp"
 
 extern "C" {
 
@@ -36,6 +37,13 @@ int plan_hook_reduce(const ficoco_problem* p, uint64_t scratch, reduce_plan* out
   if (rc != FICOCO_OK) return rc;
   *out = reduce_plan{(int64_t)pl.total, (int64_t)pl.beyond, pl.row_lanes, pl.strip_groups, pl.rows_per_wg, pl.n_chunks, ficoco::partials_combined(*p, pl)};
   return rc;
+}
+
+int plan_hook_causal_live_first(int units, int k_tiles) { return ficoco::causal_live_first(units, k_tiles); }
+
+// The order of all groups x k_tiles tiles: group and key tile of each.
+void plan_hook_causal_tiles(int groups, int k_tiles, int per, int full, int32_t* out) {
+  for (int unit = 0; unit < groups * k_tiles; ++unit) ficoco::causal_tile(unit, groups, k_tiles, per, full, out[2 * unit], out[2 * unit + 1]);
 }
 
 }  // extern "C"

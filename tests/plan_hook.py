@@ -1,5 +1,5 @@
 """ctypes view of tests/c_abi/plan_hook.cpp: how the library lays out and cuts the block of approximate cosines and
-the reduction of maps, and where the text profiles lie."""
+the reduction of maps, where the text profiles lie, and the order of causal tiles."""
 import ctypes as C
 import os
 
@@ -34,3 +34,13 @@ def reduce_plan(p, scratch=2 ** 64 - 1):
     rc = _lib().plan_hook_reduce(C.byref(p), C.c_uint64(scratch), C.byref(r))
     assert rc == 0, rc
     return r
+
+
+def causal_tiles(groups, k_tiles, per, full):
+    out = (C.c_int32 * (2 * groups * k_tiles))()
+    _lib().plan_hook_causal_tiles(groups, k_tiles, per, full, out)
+    return list(zip(out[::2], out[1::2]))
+
+
+def causal_live_first(units, k_tiles):
+    return bool(_lib().plan_hook_causal_live_first(units, k_tiles))
