@@ -53,7 +53,8 @@ struct QkArgs {
   int b0, nb;           // images of this launch
   int q_groups, k_tiles; // workgroups of one image: query tiles or groups of them, key tiles
   bool share_keys;      // row normalisers: one query tile per workgroup, whose wavefronts share its keys
-  __device__ __forceinline__ int row(int v) const { return v < n_visq ? vis0 + v : x0 + (v - n_visq); }
+  bool long_first;      // row normalisers: one group of every head after the other, those that see most keys first
+  __host__ __device__ __forceinline__ int row(int v) const { return v < n_visq ? vis0 + v : x0 + (v - n_visq); }
 };
 
 // Rows of a product are keys here, columns queries.  Head mean: v_mfma_f32_32x32x16_bf16, operand A 32 rows x 16
@@ -109,9 +110,8 @@ static_assert(kQkKeys == 2 * kNormKB * 16, "two steps of keys");
 //
 // Bound by the vector unit: exponential, multiply-add and add per logit, and by the matrix instructions, which hardly
 // run beside them (4 x 2881 tokens, 16 heads of 64: 112 us; with operands straight from memory 165-205 us).
-template <bool DEC>
 __host__ __device__ __forceinline__ int norm_grid(const QkArgs& a, int heads, int groups) {
-  return DEC && !a.share_keys ? xcd_padded_total(heads) * groups : xcd_padded_total(heads * groups);
+  return a.long_first ? xcd_padded_total(heads) * groups : xcd_padded_total(heads * groups);
 }
 template <int KS, bool DEC>
 __global__ __launch_bounds__(kQkWaves * kWave) __attribute__((amdgpu_waves_per_eu(2))) void qk_norm_kernel(QkArgs a) {
@@ -121,16 +121,13 @@ __global__ __launch_bounds__(kQkWaves * kWave) __attribute__((amdgpu_waves_per_e
   // others: in their places between them they left every q_groups-th compute unit without work (a quarter of the chip at
   // 16 x 577 tokens: 29.8 us, and 24.3 with the order of precedence below).
   const bool last_narrow = a.nq - (a.q_groups - 1) * (a.share_keys ? 1 : kQkWaves) * kNormTile <= 16;
-  const int groups = a.q_groups - (last_narrow ? 1 : 0), all_heads = a.nb * a.H, first = norm_grid<DEC>(a, all_heads, groups);
+  const int groups = a.q_groups - (last_narrow ? 1 : 0), all_heads = a.nb * a.H, first = norm_grid(a, all_heads, groups);
   const bool behind = (int)blockIdx.x >= first;
-  // Causal maps: the groups that see most keys come first, one group of every head after the other.  (Group by group of a head
-  // the workgroups that meet on a compute unit are of one length wherever the groups divide the 32 units of an XCD: 8 x 675 tokens, 32
-  // heads of 128 45.7 us, and 38.3 so.  With shared keys the short ones go first: 16 heads, one image of 675 32.3, else 36.2 for the stage.)
   int in_head, head;
   if (behind) {
     in_head = groups;
     head = xcd_logical_id(blockIdx.x - first, all_heads);
-  } else if (DEC && !a.share_keys) {
+  } else if (DEC && a.long_first) {
     const int per = (all_heads + kXcds - 1) / kXcds, at = blockIdx.x / kXcds;
     in_head = groups - 1 - at / per;
     head = at % per + blockIdx.x % kXcds * per;
@@ -961,7 +958,12 @@ static void launch_qk(QkArgs a, hipStream_t s) {
   if (a.share_keys) a.q_groups = tiles;
   const bool narrow = a.nq - (a.q_groups - 1) * (a.share_keys ? 1 : kQkWaves) * kNormTile <= 16;      // (as the kernel sees it)
   const int groups = a.q_groups - (narrow ? 1 : 0);
-  hipLaunchKernelGGL((qk_norm_kernel<KS, DEC>), dim3(norm_grid<DEC>(a, a.nb * a.H, groups) + (narrow ? xcd_padded_total(a.nb * a.H) : 0)), dim3(kQkWaves * kWave), 0, s, a);
+  // Causal maps: the groups that see most keys come first, one group of every head after the other.  (Group by group of a head
+  // the workgroups that meet on a compute unit are of one length wherever the groups divide the 32 units of an XCD: 8 x 675 tokens, 32
+  // heads of 128 45.7 us, and 38.3 so.  With shared keys the short ones go first: 16 heads, one image of 675 32.3, else 36.2 for the stage.)
+  auto keys_seen = [&](int g) { return a.row(std::min((g + 1) * kQkWaves * kNormTile, a.nq) - 1) + 1; };
+  a.long_first = DEC && !a.share_keys && groups > 1 && causal_long_first(keys_seen(0), keys_seen(groups - 1));
+  hipLaunchKernelGGL((qk_norm_kernel<KS, DEC>), dim3(norm_grid(a, a.nb * a.H, groups) + (narrow ? xcd_padded_total(a.nb * a.H) : 0)), dim3(kQkWaves * kWave), 0, s, a);
   auto mean = [&](auto kern, auto shape) {
     using Shape = decltype(shape);
     // two stages of (queries + keys) rows per share of the heads, and the queries' normalisers of two heads

@@ -39,6 +39,7 @@ int plan_hook_reduce(const ficoco_problem* p, uint64_t scratch, reduce_plan* out
   return rc;
 }
 
+int plan_hook_causal_long_first(int first, int last) { return ficoco::causal_long_first(first, last); }
 int plan_hook_causal_live_first(int units, int k_tiles) { return ficoco::causal_live_first(units, k_tiles); }
 
 // The order of all groups x k_tiles tiles: group and key tile of each.

@@ -44,3 +44,7 @@ def causal_tiles(groups, k_tiles, per, full):
 
 def causal_live_first(units, k_tiles):
     return bool(_lib().plan_hook_causal_live_first(units, k_tiles))
+
+
+def causal_long_first(keys_of_first, keys_of_last):
+    return bool(_lib().plan_hook_causal_long_first(keys_of_first, keys_of_last))

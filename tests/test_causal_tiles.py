@@ -1,4 +1,4 @@
-"""The order of the tiles of a causal map (host code; nothing is launched): every tile once, those that some query sees first."""
+"""Orders of the workgroups of causal maps (host code; nothing is launched): every tile once, those that some query sees first; which order is taken."""
 import pytest
 
 from tests import plan_hook as H
@@ -27,3 +27,18 @@ MEASURED = [(8, 576, 17, (76.7, 63.4)), (8, 576, 64, (80.8, 69.8)), (8, 690, 64,
 def test_live_first_where_it_is_faster(B, N, M, us):
     k_tiles = -(-N // KEYS)
     assert us[H.causal_live_first(B * k_tiles * -(-(N + M) // 128), k_tiles)] <= 1.01 * min(us)
+
+
+# images, visual tokens, text queries behind 35 others (heads of 128, 40 and 32; of 64, 32), us of the two kernels, normalisers head by head and long first
+NORMALISERS = [(16, 64, 200, (58.3, 64.1)), (16, 100, 200, (63.2, 67.6)), (8, 576, 64, (86.8, 77.8)), (6, 432, 64, (48.8, 45.6)), (8, 432, 64, (44.7, 42.3)),
+               (16, 576, 17, (94.6, 82.3)), (6, 690, 64, (72.8, 63.5))]
+
+
+@pytest.mark.parametrize("B,N,M,us", NORMALISERS)
+def test_long_groups_first_where_it_is_faster(B, N, M, us):
+    def keys(query):                       # seen by it: all up to itself
+        return 35 + query + 1
+    first, groups = keys(191), -(-(N + M) // 192)
+    if N + M - (groups - 1) * 192 <= 16:   # such a group comes behind all others
+        groups -= 1
+    assert us[H.causal_long_first(first, keys(min(groups * 192, N + M) - 1))] <= 1.01 * min(us)

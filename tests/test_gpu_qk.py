@@ -264,6 +264,14 @@ def test_causal_heads_of_128(ctx, monkeypatch, B, N, M, H):
     assert full >= (B + 1) // 2
 
 
+@pytest.mark.parametrize("B,N,M,H,d", [(16, 64, 200, 16, 64), (13, 50, 200, 13, 64), (8, 64, 200, 25, 128), (7, 30, 400, 31, 128), (5, 500, 60, 21, 64)])
+def test_causal_normalisers_head_by_head_or_long_first(ctx, B, N, M, H, d):
+    """Two groups of queries that see about the same keys (head by head), three and four (long first, a number of heads that does not divide among
+    the XCDs)."""
+    full = _case_l(ctx, 470 + B + H, B, 3, N, M, 72, H, d, N // 3, fc.R_ATTN_RECV, fc.C_ATTN)
+    assert full >= (B + 1) // 2
+
+
 @pytest.mark.parametrize("M,H,d", [(1, 32, 128), (16, 16, 128), (17, 9, 128), (32, 32, 64), (31, 17, 64), (32, 16, 64), (5, 64, 32), (33, 40, 32)])
 def test_one_block_of_text_queries(ctx, M, H, d):
     """At most 32 text queries alone, heads split: by wavefronts that share the heads, or (four 32-feature steps a wavefront and
