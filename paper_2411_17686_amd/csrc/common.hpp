@@ -120,9 +120,14 @@ inline bool text_with_features(const ficoco_problem& p, const Plan& pl) {
 // FiCoCo-L whose redundancy term is the mean cosine, in bfloat16: norms, unit rows and their column sums in one pass over the
 // tokens (features.hip), where a row fills four to sixteen wavefronts with 16 bytes a lane: 2048 to 8192 features (narrower
 // rows leave a workgroup too few wavefronts; FiCoCo-V keeps its workspace, which the static scratch bounds).
+// Not where its workgroups fill the chip badly and the separate passes are faster.  Step in us, one pass / separate: nine or ten wavefronts, of which one
+// workgroup has a compute unit of sixteen to itself, above 8192 rows (5120 features, 64 text tokens: 8 x 690 145.8 / 151.8, 12 x 690 184.5 / 183.9, 8 x 1152
+// 221.2 / 214.6, with 200 252.3 / 241.1; 4096 features 170.8 / 179.7); thirteen and more with over four workgroups of text profiles a compute unit in
+// the launch (8192 features, 200 text tokens: 32 x 200 253.3 / 263.6, 24 x 576 455.7 / 486.7, 64 x 64 263.6 / 251.2, 128 x 33 414.4 / 393.4).
 inline bool unit_rows_summed(const ficoco_problem& p, int Df) {
-  return p.variant == FICOCO_VARIANT_L && p.dtype == FICOCO_BF16 && p.red_src == FICOCO_R_SIM_MEAN && Df % kVec == 0 &&
-         Df >= 2048 && Df <= 8192;
+  if (p.variant != FICOCO_VARIANT_L || p.dtype != FICOCO_BF16 || p.red_src != FICOCO_R_SIM_MEAN || Df % kVec != 0 || Df < 2048 || Df > 8192) return false;
+  if (Df > 4096 && Df <= 5120 && (int64_t)p.B * p.N > 8192) return false;
+  return !(Df > 6144 && p.A_text != nullptr && (int64_t)p.B * ((p.M + 7) / 8) > 1024);
 }
 // Rows of a workgroup there: 16, or 8 where those would be fewer than half as many workgroups as there are compute units.  us per step with
 // 16, with 8 and in the separate passes before: one sequence of 576 tokens, 5120 features 73.2 / 66.0 / 71.6, four of 200 82.2 / 74.2 /

@@ -1,6 +1,6 @@
 // What a test may ask about the plan of a problem: where the block of approximate cosines, the unit rows, the text
 // profiles and their maxima lie in the workspace, how the block is cut, and the error its readers allow for; how the reduction
-// of the maps is cut; the order of causal tiles.  (Host code only.)
+// of the maps is cut; the order of causal tiles; the form of the feature passes.  (Host code only.)
 #include "../../paper_2411_17686_amd/csrc/common.hpp"
 #include "../../paper_2411_17686_amd/csrc/causal_tiles.hpp"
 
@@ -39,6 +39,7 @@ int plan_hook_reduce(const ficoco_problem* p, uint64_t scratch, reduce_plan* out
   return rc;
 }
 
+int plan_hook_unit_rows_summed(const ficoco_problem* p) { return ficoco::unit_rows_summed(*p, p->F ? p->Df : p->D); }
 int plan_hook_causal_long_first(int first, int last) { return ficoco::causal_long_first(first, last); }
 int plan_hook_causal_live_first(int units, int k_tiles) { return ficoco::causal_live_first(units, k_tiles); }
 

@@ -48,3 +48,7 @@ def causal_live_first(units, k_tiles):
 
 def causal_long_first(keys_of_first, keys_of_last):
     return bool(_lib().plan_hook_causal_long_first(keys_of_first, keys_of_last))
+
+
+def unit_rows_summed(p):
+    return bool(_lib().plan_hook_unit_rows_summed(C.byref(p)))
