@@ -412,6 +412,8 @@ template <bool SPLIT> struct QkMeanShape {
   static constexpr int kQueries = 2 * kBlocks * kQkB; // of a workgroup
   static constexpr int kShares = SPLIT ? 4 : 1;       // shares of the heads
   static constexpr int kThreads = kQkWaves * kShares * kWave;
+  // Causal maps with heads of 128, not split: only launched with one block of queries in all (qk_mean_deep_kernel takes the others).
+  static constexpr bool narrow_only(int ks, bool dec) { return dec && ks == 4 && !SPLIT; }
 };
 // Outputs of 64 queries (32: one block) from v0 and 32 visual keys from ik0 on, of the sums over the heads.
 template <bool DEC, int blocks>
@@ -737,6 +739,7 @@ __global__ __launch_bounds__(QkMeanShape<SPLIT>::kThreads) __attribute__((amdgpu
     qk_write_out<DEC, 1>(a, b, w0, wk0 + wv * kQkB, mine, mine);
     return;
   }
+  if constexpr (QkMeanShape<SPLIT>::narrow_only(KS, DEC)) return;
 
   if (!wg_dead) {                                       // uniform in the workgroup
     if constexpr (!SPLIT && !DEC) {
@@ -969,7 +972,7 @@ static void launch_qk(QkArgs a, hipStream_t s) {
     // two stages of (queries + keys) rows per share of the heads, and the queries' normalisers of two heads
     constexpr size_t kStages = 2 * Shape::kShares * ((size_t)(Shape::kQueries + kQkKeys) * CH * sizeof(u32x4_t) + Shape::kQueries * sizeof(float2));
     constexpr size_t kSums = (size_t)Shape::kThreads * sizeof(f32x16_t);      // (of a narrow tile, at most)
-    constexpr size_t kLds = kStages > kSums ? kStages : kSums;
+    constexpr size_t kLds = kStages > kSums && !Shape::narrow_only(KS, DEC) ? kStages : kSums;
     if (kLds > 32768)
       (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLds);
     a.q_groups = (a.nq + Shape::kQueries - 1) / Shape::kQueries;

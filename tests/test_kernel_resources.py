@@ -13,7 +13,7 @@ LLVM = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "llvm", "bin")
 
 @pytest.fixture(scope="module")
 def kernels(tmp_path_factory):
-    """{name: {sgpr_spill_count, vgpr_spill_count, private_segment_fixed_size}} of every kernel."""
+    """{name: {vgpr_count, sgpr_spill_count, vgpr_spill_count, private_segment_fixed_size}} of every kernel."""
     d = tmp_path_factory.mktemp("objects")
     lib = d / "libficoco.so"
     lib.symlink_to(fc.LIB_PATH)
@@ -26,7 +26,7 @@ def kernels(tmp_path_factory):
         for k in re.split(r"\n\s+- \.agpr_count:", notes)[1:]:
             name = re.search(r"\.name:\s+(\S+)", k).group(1)
             found[name] = {n: int(re.search(r"\.%s:\s+(\d+)" % n, k).group(1))
-                           for n in ("sgpr_spill_count", "vgpr_spill_count", "private_segment_fixed_size")}
+                           for n in ("vgpr_count", "sgpr_spill_count", "vgpr_spill_count", "private_segment_fixed_size")}
     assert len(found) > 60
     return found
 
@@ -45,3 +45,9 @@ def test_candidate_rows_keep_their_scalars(kernels):
 def test_head_mean_of_queries_and_keys_uses_no_scratch(kernels):
     for n, r in _all(kernels, "qk_mean_kernel").items():
         assert r["vgpr_spill_count"] == r["private_segment_fixed_size"] == 0, (n, r)
+
+
+def test_head_mean_of_one_block_has_nothing_else(kernels):
+    """Causal heads of 128, not split: launched with one block of queries only, without the registers of whole tiles."""
+    (n, r), = _all(kernels, "qk_mean_kernelILi4ELb1ELb0E").items()
+    assert r["vgpr_count"] <= 128, (n, r)
