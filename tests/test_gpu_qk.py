@@ -272,6 +272,50 @@ def test_causal_normalisers_head_by_head_or_long_first(ctx, B, N, M, H, d):
     assert full >= (B + 1) // 2
 
 
+def _same_bits(ctx, kw, Q, K, X):
+    """One step from contiguous queries and keys, and from the same ones as a projection leaves them ([B][n][H][d], with room behind a row)."""
+    B, H, n, d = Q.shape
+    outs = []
+    for apart in (False, True):
+        q, k = Q.to("cuda"), K.to("cuda")
+        if apart:
+            both = torch.full((B, n, 2 * H * d + 8), float("nan"), dtype=torch.bfloat16, device="cuda")
+            at_q, at_k = both[..., :H * d].unflatten(-1, (H, d)), both[..., H * d:2 * H * d].unflatten(-1, (H, d))
+            at_q.copy_(q.transpose(1, 2))
+            at_k.copy_(k.transpose(1, 2))
+            q, k = at_q.transpose(1, 2), at_k.transpose(1, 2)
+        p = fc.make_problem(X, Q=q, K=k, qk_begin=0, **kw)
+        assert not apart or (p.qk_stride_h, p.qk_stride_n) == (d, 2 * H * d + 8)
+        buf = fc.Buffers(p, "cuda", X.dtype)
+        buf.ws.fill_(255)
+        (fc.ficoco_l_step if kw["variant"] == fc.VARIANT_L else fc.ficoco_v_step)(ctx, p, buf)
+        torch.cuda.synchronize()
+        outs.append([getattr(buf, name) for name in ("scores", "keep_idx", "edge_cnt", "X_out")])
+    for a, b in zip(*outs):
+        assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("B,N,M,H,d", [(1, 130, 33, 3, 128), (5, 600, 60, 7, 128), (2, 129, 70, 17, 128), (3, 200, 20, 13, 64), (2, 90, 150, 8, 32), (1, 60, 17, 32, 128),
+                                       (16, 64, 200, 16, 64)])
+def test_causal_queries_and_keys_as_a_projection_leaves_them(ctx, B, N, M, H, d):
+    """Heads of 128 in whole tiles (of 163 and 660 queries: 300 tiles, live ones first, a whole turn of six heads and one more), split, text queries
+    shared by wavefronts, normalisers long first and head by head."""
+    g = torch.Generator().manual_seed(B + N + H)
+    n = 3 + N + M
+    Q, K = draw_qk(B + N + H, B, H, n, d, 1.0)
+    X = torch.randn(B, n, 72, generator=g).to(torch.bfloat16).to("cuda")
+    _same_bits(ctx, dict(variant=fc.VARIANT_L, vis_begin=3, N=N, n_keep=max(1, N // 3), w_score=0.6, gamma=0.6, eps=0.998, window=0, M=M,
+                         red_src=fc.R_ATTN_RECV, sem_src=fc.G_TEXT_ATTN, corr_src=fc.C_ATTN), Q, K, X)
+
+
+@pytest.mark.parametrize("B,N,H,d", [(1, 64, 3, 64), (16, 196, 9, 32), (2, 289, 8, 64), (3, 400, 17, 128)])
+def test_queries_and_keys_as_a_projection_leaves_them(ctx, B, N, H, d):
+    g = torch.Generator().manual_seed(B + N + H)
+    Q, K = draw_qk(B + N + H + 1, B, H, N + 1, d, 1.0)
+    X = torch.randn(B, N + 1, 72, generator=g).to(torch.bfloat16).to("cuda")
+    _same_bits(ctx, dict(variant=fc.VARIANT_V, vis_begin=1, N=N, n_keep=N // 2, cls_index=0, window=0, eps=0.998), Q, K, X)
+
+
 @pytest.mark.parametrize("M,H,d", [(1, 32, 128), (16, 16, 128), (17, 9, 128), (32, 32, 64), (31, 17, 64), (32, 16, 64), (5, 64, 32), (33, 40, 32)])
 def test_one_block_of_text_queries(ctx, M, H, d):
     """At most 32 text queries alone, heads split: by wavefronts that share the heads, or (four 32-feature steps a wavefront and

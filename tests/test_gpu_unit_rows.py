@@ -54,3 +54,77 @@ def test_unit_rows_and_terms(ctx, B, system, N, M, D):
     s = w * R - (1.0 - w) * Ad.double().mean(1).mean(1)
     # sums of at most D + N double terms whose magnitudes add up to one
     assert (buf.scores - s).abs().max().item() <= 4 * (D + N) * 2.0 ** -53 + 1e-13 * s.abs().max().item()
+
+
+def _problem(Xd, Ad, system, N, F=None):
+    return fc.make_problem(Xd, variant=fc.VARIANT_L, vis_begin=system, N=N, n_keep=max(1, N // 2), w_score=0.6, gamma=0.6, eps=0.998, window=0,
+                           red_src=fc.R_SIM_MEAN, sem_src=fc.G_TEXT_ATTN, corr_src=fc.C_COSINE, H=2, A_text=Ad, F=F,
+                           a_q_begin=system, a_k_begin=system, at_k_begin=system)
+
+
+def _unit_rows(p, buf):
+    at = H.gram_plan(p).xhat + buf.ws_ptr - buf.ws.data_ptr()
+    return buf.ws[at:at + p.B * p.N * H.gram_plan(p).Df * 2].view(torch.bfloat16).view(p.B, p.N, -1)
+
+
+# sequences, visual tokens, text tokens, features, room behind a row and behind a sequence (odd: rows at any 2-byte address)
+STRIDES = [(1, 40, 5, 2048, 1, 0), (3, 65, 40, 2056, 7, 3), (2, 129, 33, 4096, 8, 1), (16, 131, 36, 5120, 3, 2), (2, 33, 64, 8192, 5, 0)]
+
+
+@pytest.mark.parametrize("separate", [False, True])
+@pytest.mark.parametrize("B,N,M,D,room,behind", STRIDES)
+def test_rows_with_room_behind_them(ctx, B, N, M, D, room, behind, separate):
+    """The same bits from rows and sequences apart in memory, with NaN between, as from contiguous ones; as tokens and as features of their own."""
+    assert (B * ((N + 15) // 16) >= 128) == (B == 16)          # both numbers of rows a workgroup
+    system, n = 3, 3 + N + M
+    g = torch.Generator().manual_seed(N + D)
+    X = torch.randn(B, n, D, generator=g).to(torch.bfloat16).to("cuda")
+    A = torch.softmax(torch.randn(B, 2, M, N, generator=g), -1).to(torch.bfloat16).to("cuda")
+    flat = torch.full((B * (n * (D + room) + behind) + 1,), float("nan"), dtype=torch.bfloat16, device="cuda")
+    apart = flat.as_strided((B, n, D), (n * (D + room) + behind, D + room, 1), 1 if room % 2 else 0)
+    apart.copy_(X)
+    tokens = torch.randn(B, n, 64, generator=g).to(torch.bfloat16).to("cuda")
+    outs = []
+    for f in (X, apart):
+        p = _problem(tokens, A, system, N, F=f[:, system:system + N]) if separate else _problem(f, A, system, N)
+        assert p.D >= 2048 or p.Df >= 2048
+        buf = fc.Buffers(p, "cuda", torch.bfloat16)
+        buf.ws.fill_(255)
+        fc.ficoco_l_step(ctx, p, buf)
+        torch.cuda.synchronize()
+        outs.append([_unit_rows(p, buf).clone().view(torch.int16)] + [getattr(buf, k) for k in ("scores", "keep_idx", "edge_cnt", "X_out")])
+    for a, b in zip(*outs):
+        assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("D,N", [(2048, 20), (4104, 65)])
+def test_infinities_and_nan_stay_in_their_sequence(ctx, D, N):
+    """A row with an infinity has no direction but where it is infinite, one with NaN none at all: zeros and NaN there, and every other
+    sequence's rows and scores as without them."""
+    B, M, system = 3, 40, 2
+    g = torch.Generator().manual_seed(D)
+    X = torch.randn(B, system + N + M, D, generator=g).to(torch.bfloat16)
+    A = torch.softmax(torch.randn(B, 2, M, N, generator=g), -1).to(torch.bfloat16).to("cuda")
+    bad = X.clone()
+    bad[1, system + 3, 5], bad[1, system + 3, D - 1] = float("inf"), float("-inf")
+    bad[1, system + N - 1, 0] = float("nan")
+    got = []
+    for x in (X, bad):
+        xd = x.to("cuda")
+        p = _problem(xd, A, system, N)
+        buf = fc.Buffers(p, "cuda", torch.bfloat16)
+        fc.ficoco_score(ctx, p, buf)
+        torch.cuda.synchronize()
+        got.append((_unit_rows(p, buf).clone(), buf.scores.clone()))
+    (u, s), (ub, sb) = got
+    for b in (0, 2):
+        assert torch.equal(u[b].view(torch.int16), ub[b].view(torch.int16)) and torch.equal(s[b], sb[b])
+    # the mean unit row has the NaN, and with it every product but that of the row whose norm is no number: like a zero row it has no cosine
+    assert torch.isnan(sb[1, :N - 1]).all() and torch.isfinite(sb[1, N - 1])
+    nan = torch.zeros(N, D, dtype=torch.bool)
+    nan[3, 5] = nan[3, D - 1] = nan[N - 1, 0] = True
+    assert torch.equal(torch.isnan(ub[1]).cpu(), nan)
+    rows = [3, N - 1]
+    assert bool((ub[1][rows][~nan[rows].to("cuda")] == 0).all())
+    keep = [i for i in range(N) if i not in rows]
+    assert torch.equal(ub[1][keep].view(torch.int16), u[1][keep].view(torch.int16))

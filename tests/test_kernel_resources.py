@@ -47,6 +47,20 @@ def test_head_mean_of_queries_and_keys_uses_no_scratch(kernels):
         assert r["vgpr_spill_count"] == r["private_segment_fixed_size"] == 0, (n, r)
 
 
+@pytest.mark.parametrize("part", ["qk_mean_deep_kernel", "qk_norm_kernel", "unit_rows_kernel", "unit_terms_kernel", "unit_mean_kernel",
+                                  "attn_reduce_kernel", "attn_text_reduce_kernel", "gram_tile_kernel"])
+def test_other_kernels_use_no_scratch(kernels, part):
+    for n, r in _all(kernels, part).items():
+        assert r["vgpr_spill_count"] == r["private_segment_fixed_size"] == 0, (n, r)
+
+
+def test_reduction_of_bfloat16_maps_keeps_four_wavefronts_a_simd(kernels):
+    """The instances with 16-byte rows of bfloat16 (one more register than 128 is a quarter of the wavefronts)."""
+    for part in ("18attn_reduce_kernelIt", "23attn_text_reduce_kernelIt"):
+        for n, r in _all(kernels, part).items():
+            assert r["vgpr_count"] <= 128, (n, r)
+
+
 def test_head_mean_of_one_block_has_nothing_else(kernels):
     """Causal heads of 128, not split: launched with one block of queries only, without the registers of whole tiles."""
     (n, r), = _all(kernels, "qk_mean_kernelILi4ELb1ELb0E").items()
