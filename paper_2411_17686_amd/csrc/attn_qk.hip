@@ -101,18 +101,20 @@ constexpr int kNormQB = kNormTile / 16;             // in blocks of 16
 constexpr int kNormKB = 2;                          // 16-key blocks a wavefront takes together
 static_assert(kQkKeys == 2 * kNormKB * 16, "two steps of keys");
 
-// A workgroup takes 4 x 48 queries of one head and walks its keys 64 at a time, the next 64 being
-// loaded while the current ones are added (few workgroups: 48 queries, the keys shared by its wavefronts).
-// (Keys loaded straight into LDS: no change.)  The exponentials are taken relative to a whole number (units of log2) at the largest logit of the first 32 keys, not of the whole row: any reference
-// serves as long as nothing overflows, and then the sums need no running maximum.  A row whose sum
-// does overflow (its largest logit more than ~70 above those of the first 32 keys) is seen in the
-// sum and done again with its own maximum.
-//
-// Bound by the vector unit: exponential, multiply-add and add per logit, and by the matrix instructions, which hardly
-// run beside them (4 x 2881 tokens, 16 heads of 64: 112 us; with operands straight from memory 165-205 us).
+// Workgroups of the heads' groups, without the narrow last ones.
 __host__ __device__ __forceinline__ int norm_grid(const QkArgs& a, int heads, int groups) {
   return a.long_first ? xcd_padded_total(heads) * groups : xcd_padded_total(heads * groups);
 }
+
+// A workgroup takes 4 x 48 queries of one head and walks its keys 64 at a time, the next 64 being
+// loaded while the current ones are added (few workgroups: 48 queries, the keys shared by its wavefronts).
+// (Keys loaded straight into LDS: no change.)  The exponentials are taken relative to a whole number (units of log2) at the
+// largest logit of the first 32 keys, not of the whole row: any reference serves as long as nothing overflows, and then the
+// sums need no running maximum.  A row whose sum does overflow (its largest logit more than ~70 above those of the first 32
+// keys) is seen in the sum and done again with its own maximum.
+//
+// Bound by the vector unit: exponential, multiply-add and add per logit, and by the matrix instructions, which hardly
+// run beside them (4 x 2881 tokens, 16 heads of 64: 112 us; with operands straight from memory 165-205 us).
 template <int KS, bool DEC>
 __global__ __launch_bounds__(kQkWaves * kWave) __attribute__((amdgpu_waves_per_eu(2))) void qk_norm_kernel(QkArgs a) {
   constexpr int CH = KS * 4, T = kQkWaves * kWave, RPI = T / CH, NL = kQkKeys / RPI;
@@ -377,20 +379,6 @@ __device__ __forceinline__ double sums_of_16(const double (&x)[16], int l) {
 }
 
 // ---- probabilities, head mean, outputs -----------------------------------------------------------
-// A wavefront forms 64 queries x 32 visual keys of an image, the heads added in order in registers.
-// SPLIT = false: the four wavefronts of a workgroup sit two by two on 128 queries x 64 keys and
-// share the staged rows.  SPLIT = true (few tiles): 64 x 64 by four wavefronts of one block each, and four such groups
-// take consecutive shares of the heads, each with a staging area of its own; their sums are added
-// pairwise (a fixed tree) in LDS.  Rows are staged 64 features at a time in two buffers, loaded straight into LDS
-// a stage ahead; the normalisers of a head come through LDS as well; the exponentials of a block are computed beside
-// the matrix instructions and LDS reads of the next one, in a fixed order.
-//
-// Bound by the vector unit (exponential, two multiply-adds per logit) and the trips between
-// barriers.  Measured at 4 x 2881 tokens, 16 heads of 64 / 16 x 577, 16 of 64 / 8 x 675 causal, 32
-// of 128: operands straight from memory 314 / 70 / 99 us; staged through registers, 192 x 64 by eight wavefronts, each head
-// on its own 180 / 44 / 56; 96 x 64 by four wavefronts with 16 x 16 products, the next head's beside this head's
-// exponentials 170 / 40 / 51; normalisers through LDS, whole tiles written without tests 158 / 34 / 49; 32 x 32 products
-// 157 / 33 / 51; rows straight into LDS, order of precedence among the wavefronts 142 / 28.6 / 48.
 constexpr int kQkBand = 8;                          // key tiles side by side in the order of the workgroups
 // Tile number `unit` of an image (qr queries x kQkKeys keys): in columns kQkBand key tiles wide, so that the workgroups that run
 // together on an XCD need few rows of either side, which its L2 holds for all heads.  live_first: first the tiles that hold a key
@@ -470,6 +458,20 @@ __device__ __forceinline__ void qk_write_out(const QkArgs& a, int64_t b, int v0,
   }
 }
 
+// A wavefront forms 64 queries x 32 visual keys of an image, the heads added in order in registers.
+// SPLIT = false: the four wavefronts of a workgroup sit two by two on 128 queries x 64 keys and
+// share the staged rows.  SPLIT = true (few tiles): 64 x 64 by four wavefronts of one block each, and four such groups
+// take consecutive shares of the heads, each with a staging area of its own; their sums are added
+// pairwise (a fixed tree) in LDS.  Rows are staged 64 features at a time in two buffers, loaded straight into LDS
+// a stage ahead; the normalisers of a head come through LDS as well; the exponentials of a block are computed beside
+// the matrix instructions and LDS reads of the next one, in a fixed order.
+//
+// Bound by the vector unit (exponential, two multiply-adds per logit) and the trips between
+// barriers.  Measured at 4 x 2881 tokens, 16 heads of 64 / 16 x 577, 16 of 64 / 8 x 675 causal, 32
+// of 128: operands straight from memory 314 / 70 / 99 us; staged through registers, 192 x 64 by eight wavefronts, each head
+// on its own 180 / 44 / 56; 96 x 64 by four wavefronts with 16 x 16 products, the next head's beside this head's
+// exponentials 170 / 40 / 51; normalisers through LDS, whole tiles written without tests 158 / 34 / 49; 32 x 32 products
+// 157 / 33 / 51; rows straight into LDS, order of precedence among the wavefronts 142 / 28.6 / 48.
 template <int KS, bool DEC, bool SPLIT>
 __global__ __launch_bounds__(QkMeanShape<SPLIT>::kThreads) __attribute__((amdgpu_waves_per_eu(SPLIT ? 4 : KS == 4 ? 2 : 3))) void qk_mean_kernel(QkArgs a) {
   constexpr int KSS = KS > 2 ? 2 : KS, NST = KS / KSS, CH = KSS * 4, KT = KSS * 2;     // 32-feature steps of a stage, stages of a head, instructions of a block and stage

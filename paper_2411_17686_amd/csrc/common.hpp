@@ -43,7 +43,7 @@ struct Plan {
   size_t ttext;          // double [B][N][M]      head-mean text->visual map, transposed
   size_t inv_norm;       // double [B][N]         1/|F_i| (0 for a zero row)
   size_t xhat;           // bf16   [B][N][Df]     unit rows rounded to bfloat16
-  size_t colsum_part;    // double [B][f_chunks][Df]
+  size_t colsum_part;    // double [2][B][f_chunks][Df] column sums of unit rows and of rows (unit_rows_summed: [B][f_chunks][Df], of unit rows)
   size_t colmean;        // double [2][B][Df] (mean unit row, mean raw row), then the parts of |mean raw row|^2
   size_t fterm;          // double [B][N]         feature-derived score term
   size_t fterm2;         // double [B][N]

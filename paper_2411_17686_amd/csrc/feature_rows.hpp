@@ -12,7 +12,7 @@ struct FeatArgs {
   int N, Df, f_chunks, f_rows_per_wg;
   double* norm;         // [B][N]
   bf16_t* xhat;         // [B][N][Df] or null
-  double* colsum_part;  // [2][B][f_chunks][Df]  (0: unit rows, 1: raw rows)
+  double* colsum_part;  // [2][B][f_chunks][Df]  (0: unit rows, 1: raw rows; where unit_rows_summed: unit rows alone)
   double* colmean;      // [2][B][Df]
   double* fterm_r;      // [B][N]
   double* fterm_g;      // [B][N]

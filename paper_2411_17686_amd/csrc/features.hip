@@ -152,7 +152,7 @@ __global__ __launch_bounds__(kUnitWaves * kWave) __attribute__((amdgpu_waves_per
   const int q = (int)blockIdx.x - a.f_chunks * a.B;
   if (q < 0) {
     unit_rows_block<ROWS>(a, blockIdx.x % a.f_chunks, blockIdx.x / a.f_chunks, lds.part);
-  } else if (threadIdx.x < 256) {
+  } else if (threadIdx.x < 256) {       // whole wavefronts; the others end here, and the barrier inside waits for none that has ended
     text_reduce_block<bf16_t>(t, q % tgx, (q / tgx) % tgy, q / (tgx * tgy), lds.tile);
   }
 }
@@ -526,11 +526,6 @@ void launch_features(const ficoco_problem& p, const Plan& pl, char* ws, hipStrea
     else hipLaunchKernelGGL((row_norm_kernel<float, 4>), rows, block, 0, s, a);
   }
   if (!a.want_sim && !a.want_eq) return;
-  const dim3 trows((p.N + kFtRows - 1) / kFtRows, p.B);
-  auto terms = [&] {
-    if (bf16) hipLaunchKernelGGL(feature_terms_kernel<bf16_t>, trows, block, 0, s, a);
-    else hipLaunchKernelGGL(feature_terms_kernel<float>, trows, block, 0, s, a);
-  };
   if (summed) {
     auto go = [&](auto kern) { hipLaunchKernelGGL(kern, dim3(pl.f_chunks * p.B), dim3((pl.Df + kWave * kVec - 1) / (kWave * kVec) * kWave), 0, s, a); };
     if (pl.f_rows_per_wg == 16) go(unit_terms_kernel<16>); else go(unit_terms_kernel<8>);
@@ -549,7 +544,9 @@ void launch_features(const ficoco_problem& p, const Plan& pl, char* ws, hipStrea
     else hipLaunchKernelGGL(col_sum_kernel<float>, cgrid, block, 0, s, a);
   }
   hipLaunchKernelGGL(col_mean_kernel, dim3((pl.Df + 255) / 256, p.B), block, 0, s, a);
-  terms();
+  const dim3 trows((p.N + kFtRows - 1) / kFtRows, p.B);
+  if (bf16) hipLaunchKernelGGL(feature_terms_kernel<bf16_t>, trows, block, 0, s, a);
+  else hipLaunchKernelGGL(feature_terms_kernel<float>, trows, block, 0, s, a);
 }
 
 }  // namespace ficoco
