@@ -189,17 +189,17 @@ __device__ __forceinline__ void attn_reduce_block(const AttnArgs& a, int block, 
         // kHeadBatch independent 16-byte loads are issued before the first add; the adds
         // then run in head order.
         int h0 = 0;
+        int64_t at = 0;
         for (; h0 + kHeadBatch <= a.H; h0 += kHeadBatch) {
           Raw8<T> raw[kHeadBatch];
-#pragma unroll
-          for (int u = 0; u < kHeadBatch; ++u) load_raw(base + (int64_t)(h0 + u) * a.sh, raw[u]);
+          load_heads(base, at, a.sh, raw);
 #pragma unroll
           for (int u = 0; u < kHeadBatch; ++u) add_raw(raw[u], p);
         }
         for (; h0 < a.H; ++h0) {
-          Raw8<T> raw;
-          load_raw(base + (int64_t)h0 * a.sh, raw);
-          add_raw(raw, p);
+          Raw8<T> raw[1];
+          load_heads(base, at, a.sh, raw);
+          add_raw(raw[0], p);
         }
       } else {
         for (int h = 0; h < a.H; ++h)

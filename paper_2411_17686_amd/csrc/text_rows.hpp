@@ -32,6 +32,18 @@ struct AttnArgs {
 void fill_text_args(const ficoco_problem& p, const Plan& pl, char* ws, AttnArgs& a);
 inline dim3 text_grid(const ficoco_problem& p);
 
+// The next heads of eight columns of one row, the first of them `at` elements behind base; moves on.  The offset is opaque: where
+// the compiler forms it from the head's number, each load of a batch has a multiplication of its own, and the first one of a
+// float32 batch comes apart into three.  The map kernel alone, float32 and 32 heads: 7.6 us with such loads and 7.2 so (three
+// maps of 144 tokens), with eight text rows 6.2 and 5.85 (one map).
+template <typename T, int HEADS>
+__device__ __forceinline__ void load_heads(const T* base, int64_t& at, int64_t sh, Raw8<T> (&raw)[HEADS]) {
+  asm volatile("" : "+s"(at));
+#pragma unroll
+  for (int u = 0; u < HEADS; ++u) load_raw(base + (at + u * sh), raw[u]);
+  at += HEADS * sh;
+}
+
 // Text-query block of FiCoCo-L (task term of Eq. 3, profiles of Eq. 4): the head mean of
 // A_text[b][h][k][i], stored TRANSPOSED as the token's profile ttext[b][i][k].  A workgroup
 // owns 8 consecutive text rows x 256 key columns: a thread forms the head mean of one row and
@@ -62,25 +74,24 @@ __device__ __forceinline__ void text_reduce_block(const AttnArgs& a, int chunk, 
       int h0 = 0;
       // the grid of this kernel is small (8 rows x 256 keys per workgroup), so each thread keeps
       // more loads in flight than the map kernel does: kTextHeadBatch heads at a time
+      int64_t at = 0;
       for (; h0 + kTextHeadBatch <= a.H; h0 += kTextHeadBatch) {
         Raw8<T> raw[kTextHeadBatch];
-#pragma unroll
-        for (int u = 0; u < kTextHeadBatch; ++u) load_raw(base + (int64_t)(h0 + u) * a.sh, raw[u]);
+        load_heads(base, at, a.sh, raw);
         issue_fence();
 #pragma unroll
         for (int u = 0; u < kTextHeadBatch; ++u) add_raw(raw[u], p);
       }
       for (; h0 + kHeadBatch <= a.H; h0 += kHeadBatch) {
         Raw8<T> raw[kHeadBatch];
-#pragma unroll
-        for (int u = 0; u < kHeadBatch; ++u) load_raw(base + (int64_t)(h0 + u) * a.sh, raw[u]);
+        load_heads(base, at, a.sh, raw);
 #pragma unroll
         for (int u = 0; u < kHeadBatch; ++u) add_raw(raw[u], p);
       }
       for (; h0 < a.H; ++h0) {
-        Raw8<T> raw;
-        load_raw(base + (int64_t)h0 * a.sh, raw);
-        add_raw(raw, p);
+        Raw8<T> raw[1];
+        load_heads(base, at, a.sh, raw);
+        add_raw(raw[0], p);
       }
     } else {
       for (int h = 0; h < a.H; ++h)

@@ -41,3 +41,28 @@ def test_ragged_columns(ctx, N, B, H, dtype):
         out, _ = P.run_v(cfg, cfg["A"], ctx=ctx, **kw)
         for b in {0, B // 2, B - 1}:
             P.compare_image(out, b, P.oracle_v(cfg, cfg["A"], b, **kw), dtype, cfg["vis_begin"], corr == fc.C_ATTN)
+
+
+# Heads of one row a thread: whole batches of eight and sixteen, one head past them, what is left of each size; text rows alike.
+HEADS = [16, 17, 20, 23, 24, 25, 29, 33, 40]
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("H", HEADS)
+def test_heads_of_one_row(ctx, H, dtype):
+    cfg = case(72, 2, H, dtype)
+    for corr in (fc.C_ATTN, fc.C_COSINE):
+        kw = dict(red_src=fc.R_ATTN_RECV, sem_src=fc.G_CLS_ATTN, corr_src=corr)
+        out, _ = P.run_v(cfg, cfg["A"], ctx=ctx, **kw)
+        for b in range(2):
+            P.compare_image(out, b, P.oracle_v(cfg, cfg["A"], b, **kw), dtype, cfg["vis_begin"], corr == fc.C_ATTN)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("H", HEADS)
+def test_heads_of_text_rows(ctx, H, dtype):
+    cfg = synth.ficoco_l_decoder(seed=H, B=2, n_sys=3, N=72, M=9, D=32, H=H, centres=7, n_keep=24, dtype=dtype, with_vv=True)
+    for red, corr in ((fc.R_ATTN_RECV, fc.C_ATTN), (fc.R_SIM_MEAN, fc.C_COSINE)):
+        out, _ = P.run_l(cfg, red, corr, ctx=ctx)
+        for b in range(2):
+            P.compare_image(out, b, P.oracle_l(cfg, b, red, corr), dtype, cfg["vis_begin"], False)
