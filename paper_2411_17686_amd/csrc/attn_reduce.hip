@@ -93,7 +93,7 @@ __device__ __forceinline__ void attn_reduce_block(const AttnArgs& a, int block, 
       // ROWS = rows of this thread (compile time: the accumulators are registers)
       auto run = [&](auto rows_c) __attribute__((always_inline)) {
         constexpr int ROWS = decltype(rows_c)::value;
-        constexpr int HEADS = ROWS >= 3 ? kHeadsAtOnce : ROWS == 2 ? 4 : 16;   // loads in flight: 8 (16 with two rows spill), with one row and up to 16 heads all of them
+        constexpr int HEADS = ROWS >= 3 ? kHeadsAtOnce : ROWS == 2 ? 4 : 16;   // loads in flight: 8 (16 with two rows spill), with one row and up to 15 heads all of them
         double p[ROWS][kVec];
         const T* base[ROWS];
 #pragma unroll
@@ -127,10 +127,12 @@ __device__ __forceinline__ void attn_reduce_block(const AttnArgs& a, int block, 
           for (; h0 < a.H; h0 += HEADS) add_heads(std::integral_constant<int, HEADS>{}, h0);
         } else {
           if constexpr (ROWS == 1) {
-            // More heads than one batch of sixteen holds: whole batches of eight first, nothing to clamp or clear.
-            // (Sixteen at a time, us a launch, one row a thread: 8 maps of 64 tokens, 32 heads 7.8, so 6.3, as one batch of
-            // eight after another with clamps 7.3; 40 heads 8.4, 6.9, 8.2; 5 x 400 tokens, 32 heads 13.2, 12.1, 11.8.)
-            if (a.H > HEADS) {
+            // From sixteen heads on: whole batches of eight first, nothing to clamp or clear.  (Sixteen at a time and so, us a
+            // launch: 8 maps of 64 tokens, 32 heads 7.8 and 6.3, 40 heads 8.4 and 6.9; 5 x 400 tokens, 32 heads 13.2 and 12.1; 16
+            // heads, 3 x 64 tokens 5.7 and 5.0, 2 x 144 5.9 and 5.2, 576 with the map 6.85 and 6.7; whole batches of sixteen 5.35
+            // and 5.55 there, 7.0 at 32 heads.)  Up to fifteen all heads at once: twelve, seven maps of 576 tokens 15.7, and 16.8 as
+            // eight and four.
+            if (a.H >= HEADS) {
               int64_t at = 0;
               for (; a.H - h0 >= kHeadBatch; h0 += kHeadBatch) {
                 Raw8<T> raw[kHeadBatch];
