@@ -40,8 +40,12 @@ namespace ficoco {
 //   32 x 8, 32 rows, a row a thread: up to sixteen loads in flight, and few partials for the one workgroup of the filter.  1 x 576 tokens, 8 heads
 //     25.9 / 24.1, 3 x 576 28.7 / 27.1.  As far as 1300 workgroups (five a compute unit: 8 x 576, 12 heads 39.7 / 39.6; with sixteen loads 1187; few heads
 //     700, from where two rows a thread are better).  Beyond sixteen loads a thread makes several trips with one row in hand: up to 512 workgroups (1 x 576,
-//     float32, 16 heads 28.3 / 26.3), with more than forty loads one a compute unit (the second is half a launch there: 3 x 400, 32 heads of float32
-//     with 273: launch 12.5 us usual, 17.1 so), for short sequences none (46 x 144, 40 heads of float32 56.4 / 63.1, 16 x 144 of a decoder in bfloat16 35.8 / 38.5).
+//     float32, 16 heads 28.3 / 26.3), with more than forty loads one a compute unit, the [CLS] rows' among them (the second is half a launch there: 2 x 488,
+//     40 heads of float32, 272 of them: 40.0 / 43.6, 2 x 472 with 256 38.9 / 34.7), for short sequences none (46 x 144, 40 heads of float32 56.4 / 63.1, 16 x 144
+//     of a decoder in bfloat16 35.8 / 38.5).
+//     In float32 such a row is a chain of batches of eight heads, two loads each, and the chip is better filled with shorter chunks where its workgroups are
+//     few: from 50 on up to forty loads (320 tokens, 16 heads, one image with 50 22.8 / 23.5), from 100 on beyond (1 x 320, 40 heads 24.8 / 26.2, 1 x 448
+//     with 98 28.3 / 27.3, 2 x 288 with 90 25.1 / 26.3, 2 x 376 with 144 28.6 / 28.4).
 //   16 x 16, 32 rows, two a thread: few heads up to 2500 workgroups (8 x 576, 4 heads 31.1 / 30.2; beyond, several steps in flight lose by it: 48 x 576, one
 //     head 54.6 / 59.2), others from 6000 on (4 x 2880, 16 heads 314 / 311).
 // Of 2500 problems (60 to 2900 tokens, 1 to 80 images, 1 to 40 heads) the step is 1.018 times as fast as with the usual shape alone, four are more than 3 %
@@ -60,8 +64,10 @@ static MapShape map_shape(const ficoco_problem& p, int rows) {
   const bool is_short = p.N <= 256;
   if (is_short && wgs(24, 8) <= 256) return usual;         // every workgroup has a compute unit of its own
   if (is_short && loads <= 16 && wgs(16, 16) <= 512 && usual.rows <= 16) return {16, 16, 16};
-  const int64_t most = wgs(8, 32);
-  if (most <= (loads < 8 ? 700 : loads <= 16 ? std::min(1300, 19000 / loads) : is_short ? 0 : loads <= 40 ? 512 : 256)) return {32, 8, 32};
+  const int64_t most = wgs(8, 32), others = (int64_t)p.B * ((groups + 7) / 8) * ((std::max(rows - p.N, 0) + 31) / 32);    // (the [CLS] row has a chunk of its own)
+  const int64_t up_to = loads < 8 ? 700 : loads <= 16 ? std::min(1300, 19000 / loads) : is_short ? 0 : loads <= 40 ? 512 : 256 - others;
+  const int beyond = p.dtype == FICOCO_BF16 || loads <= 24 ? 0 : loads <= 40 ? 50 : 100;
+  if (most > beyond && most <= up_to) return {32, 8, 32};
   return (loads < 8 ? most <= 2500 : most > 6000) ? MapShape{16, 16, 32} : usual;
 }
 // Workgroups the reduction aims at where it has no such map to store.

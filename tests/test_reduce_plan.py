@@ -63,6 +63,22 @@ SHAPES = [
 ]
 
 
+# Long rows, the chip nearly empty or just over one workgroup a compute unit: (the usual shape, 32 x 8), one a side.
+LONG_ROWS = [
+    (1, 304, 16, fc.F32, (22.8, 23.5)), (1, 304, 20, fc.F32, (23.7, 23.9)), (1, 320, 40, fc.F32, (24.8, 26.2)), (2, 288, 40, fc.F32, (25.1, 26.3)),
+    (1, 448, 40, fc.F32, (28.3, 27.3)), (1, 480, 40, fc.F32, (29.6, 27.6)), (2, 376, 40, fc.F32, (28.6, 28.4)), (2, 440, 40, fc.F32, (34.2, 32.3)),
+    (2, 472, 40, fc.F32, (38.9, 34.7)), (2, 488, 40, fc.F32, (40.0, 43.6)), (2, 504, 40, fc.F32, (41.1, 44.0)),
+    (1, 264, 64, fc.BF16, (28.4, 27.8)), (3, 376, 64, fc.BF16, (32.9, 29.5)), (2, 488, 64, fc.BF16, (36.1, 37.7)), (2, 504, 64, fc.BF16, (38.0, 39.8)),
+]
+
+
+@pytest.mark.parametrize("B,N,heads,dtype,us", LONG_ROWS)
+def test_long_rows_take_32_by_8_only_where_it_is_no_slower(B, N, heads, dtype, us):
+    r = H.reduce_plan(problem(B, N, heads, dtype))
+    assert r.row_lanes in (8, 32)
+    assert us[r.row_lanes == 32] <= 1.03 * us[0]
+
+
 @pytest.mark.parametrize("B,N,heads,dtype,us", SHAPES)
 def test_shape_is_no_slower_than_the_usual(B, N, heads, dtype, us):
     r = H.reduce_plan(problem(B, N, heads, dtype))
