@@ -458,6 +458,63 @@ __device__ __forceinline__ void qk_write_out(const QkArgs& a, int64_t b, int v0,
   }
 }
 
+// One block of queries in all, from w0 on, by W wavefronts: they take consecutive shares of the heads, operands straight from memory, and
+// their sums are added pairwise (a fixed tree) in `sums` (W x kWave places).  live: some query sees some key of the tile (from wk0 on).
+template <int KS, bool DEC, int W>
+__device__ __forceinline__ void qk_mean_narrow(const QkArgs& a, int64_t bi, int64_t b, int w0, int wk0, int wv, bool live, f32x16_t* sums) {
+  constexpr int KT = (KS > 2 ? 2 : KS) * 2;            // instructions of a block and of the features taken together
+  const int lane = threadIdx.x % kWave, l32 = lane % kQkB, hi = lane / kQkB;
+  f32x16_t P1[2];
+#pragma unroll
+  for (int kb = 0; kb < 2; ++kb) P1[kb] = qk_zero();
+  const int hs = (a.H + W - 1) / W, lo = min(wv * hs, a.H), h_end = min(lo + hs, a.H);
+  if (live) {
+    const int v = min(w0 + l32, a.nq - 1);
+    const bf16_t* q_at = a.Q + b * a.sb + (int64_t)a.row(v) * a.sn + hi * 8;
+    const bf16_t* k_at[2];
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb) k_at[kb] = a.K + b * a.sb + (int64_t)(a.vis0 + min(wk0 + kb * kQkB + l32, a.N - 1)) * a.sn + hi * 8;
+#pragma unroll 1
+    for (int h = lo; h < h_end; ++h) {
+      const float2 n = a.norm[(bi * a.H + h) * a.nq + v];
+      f32x16_t S[2];
+#pragma unroll
+      for (int c = 0; c < KS * 2; c += KT) {         // a stage's features at a time
+        bf16x8_t qf[KT], kf[2][KT];
+#pragma unroll
+        for (int kt = 0; kt < KT; ++kt) {
+          __builtin_memcpy(&qf[kt], q_at + (int64_t)h * a.sh + (c + kt) * 16, 16);
+#pragma unroll
+          for (int kb = 0; kb < 2; ++kb) __builtin_memcpy(&kf[kb][kt], k_at[kb] + (int64_t)h * a.sh + (c + kt) * 16, 16);
+        }
+        issue_fence();
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+          for (int kt = 0; kt < KT; ++kt) S[kb] = qk_mfma(kf[kb][kt], qf[kt], c + kt == 0 ? qk_zero() : S[kb]);
+      }
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+        for (int e = 0; e < kQkE; ++e) P1[kb][e] = fmaf(__builtin_amdgcn_exp2f(fmaf(S[kb][e], a.scale_log2e, -n.x)), n.y, P1[kb][e]);
+    }
+  }
+#pragma unroll
+  for (int step = W / 2; step >= 2; step /= 2) {
+    f32x16_t* slot = sums + wv % step * 2 * kWave + lane;
+    if (wv >= step && wv < 2 * step) { slot[0] = P1[0]; slot[kWave] = P1[1]; }
+    __syncthreads();
+    if (wv < step) { P1[0] += slot[0]; P1[1] += slot[kWave]; }
+    __syncthreads();
+  }
+  // the last two wavefronts write a block of keys each
+  if (wv < 2) sums[wv * kWave + lane] = wv == 0 ? P1[1] : P1[0];
+  __syncthreads();
+  if (wv >= 2) return;
+  const f32x16_t mine = wv == 0 ? P1[0] + sums[kWave + lane] : sums[lane] + P1[1];
+  qk_write_out<DEC, 1>(a, b, w0, wk0 + wv * kQkB, mine, mine);
+}
+
 // A wavefront forms 64 queries x 32 visual keys of an image, the heads added in order in registers.
 // SPLIT = false: the four wavefronts of a workgroup sit two by two on 128 queries x 64 keys and
 // share the staged rows.  SPLIT = true (few tiles): 64 x 64 by four wavefronts of one block each, and four such groups
@@ -686,59 +743,7 @@ __global__ __launch_bounds__(QkMeanShape<SPLIT>::kThreads) __attribute__((amdgpu
     }
   };
   if (narrow) {
-    // The wavefronts take consecutive shares of the heads,
-    // operands straight from memory, and their sums are added pairwise (a fixed tree).
-    constexpr int W = kWaves;
-    f32x16_t P1[2];
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb) P1[kb] = qk_zero();
-    const int hs = (a.H + W - 1) / W, lo = min(wv * hs, a.H), h_end = min(lo + hs, a.H);
-    if (!wg_dead) {
-      const int v = min(w0 + l32, a.nq - 1);
-      const bf16_t* q_at = a.Q + b * a.sb + (int64_t)a.row(v) * a.sn + hi * 8;
-      const bf16_t* k_at[2];
-#pragma unroll
-      for (int kb = 0; kb < 2; ++kb) k_at[kb] = a.K + b * a.sb + (int64_t)(a.vis0 + min(wk0 + kb * kQkB + l32, a.N - 1)) * a.sn + hi * 8;
-#pragma unroll 1
-      for (int h = lo; h < h_end; ++h) {
-        const float2 n = a.norm[(bi * a.H + h) * a.nq + v];
-        f32x16_t S[2];
-#pragma unroll
-        for (int c = 0; c < KS * 2; c += KT) {         // a stage's features at a time
-          bf16x8_t qf[KT], kf[2][KT];
-#pragma unroll
-          for (int kt = 0; kt < KT; ++kt) {
-            __builtin_memcpy(&qf[kt], q_at + (int64_t)h * a.sh + (c + kt) * 16, 16);
-#pragma unroll
-            for (int kb = 0; kb < 2; ++kb) __builtin_memcpy(&kf[kb][kt], k_at[kb] + (int64_t)h * a.sh + (c + kt) * 16, 16);
-          }
-          issue_fence();
-#pragma unroll
-          for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-            for (int kt = 0; kt < KT; ++kt) S[kb] = qk_mfma(kf[kb][kt], qf[kt], c + kt == 0 ? qk_zero() : S[kb]);
-        }
-#pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-          for (int e = 0; e < kQkE; ++e) P1[kb][e] = fmaf(__builtin_amdgcn_exp2f(fmaf(S[kb][e], a.scale_log2e, -n.x)), n.y, P1[kb][e]);
-      }
-    }
-    f32x16_t* sums = (f32x16_t*)stage_m;
-#pragma unroll
-    for (int step = W / 2; step >= 2; step /= 2) {
-      f32x16_t* slot = sums + wv % step * 2 * kWave + lane;
-      if (wv >= step && wv < 2 * step) { slot[0] = P1[0]; slot[kWave] = P1[1]; }
-      __syncthreads();
-      if (wv < step) { P1[0] += slot[0]; P1[1] += slot[kWave]; }
-      __syncthreads();
-    }
-    // the last two wavefronts write a block of keys each
-    if (wv < 2) sums[wv * kWave + lane] = wv == 0 ? P1[1] : P1[0];
-    __syncthreads();
-    if (wv >= 2) return;
-    const f32x16_t mine = wv == 0 ? P1[0] + sums[kWave + lane] : sums[lane] + P1[1];
-    qk_write_out<DEC, 1>(a, b, w0, wk0 + wv * kQkB, mine, mine);
+    qk_mean_narrow<KS, DEC, kWaves>(a, bi, b, w0, wk0, wv, !wg_dead, (f32x16_t*)stage_m);
     return;
   }
   if constexpr (QkMeanShape<SPLIT>::narrow_only(KS, DEC)) return;
@@ -773,7 +778,8 @@ __global__ __launch_bounds__(QkMeanShape<SPLIT>::kThreads) __attribute__((amdgpu
 }
 
 // ---- the same for causal maps with heads of 128 -----------------------------------------------------
-// Tiles, products and sums of the kernel above in its wide form, in the same order (the same bits).  Few wavefronts share a SIMD: 232 of
+// Tiles, products and sums of the kernel above in its wide form, in the same order (the same bits; a last tile of at most 32 queries is
+// qk_mean_narrow's here too: with its 32 heads all in line the row of one text query behind 512 others has an error of 9.5e-8 against 64 bits, so 5.8e-8).  Few wavefronts share a SIMD: 232 of
 // the 360 tiles of 8 x 675 tokens hold a key that some query sees, fewer than there are compute units, and then nothing
 // hides a wavefront's trips.  So the fragments of a stage are read into a second set of registers while the products of the one
 // before are formed, rows are loaded three stages ahead (three buffers, one barrier a stage, no wait for loads just issued),
@@ -797,8 +803,14 @@ __global__ __launch_bounds__(kQkWaves * kWave) __attribute__((amdgpu_waves_per_e
   int kt0, w0;
   qk_tile(a, unit - (int)bi * a.k_tiles * a.q_groups, causal_live_first(units, a.k_tiles), QR, kt0, w0);
   const int q0 = wq * 2 * kQkB, v0 = w0 + q0, wk0 = kt0 * kQkKeys, ik0 = wk0 + wk * kQkB;
+  const bool live = a.vis0 + wk0 <= a.row(min(w0 + QR, a.nq) - 1);      // uniform in the workgroup: some query sees some key
+  if (a.nq - w0 <= kQkB) {                             // uniform in the workgroup
+    static_assert(sizeof(buf0) >= kQkWaves * kWave * sizeof(f32x16_t), "the wavefronts' sums");
+    qk_mean_narrow<4, true, kQkWaves>(a, bi, b, w0, wk0, wv, live, (f32x16_t*)buf0);
+    return;
+  }
   f32x16_t P[2] = {qk_zero(), qk_zero()};
-  if (a.vis0 + wk0 <= a.row(min(w0 + QR, a.nq) - 1)) {  // uniform in the workgroup: some query sees some key
+  if (live) {
     const bf16_t* src[NL];                             // this thread's chunk of the stage's rows: queries, then keys
 #pragma unroll
     for (int i = 0; i < NL; ++i) {

@@ -37,3 +37,33 @@ def test_cls_row_behind_whole_tiles(B, N, d):
     got = np.sqrt(np.mean([_cls_error(B, N, H, d, s) ** 2 for s in (4, 5, 6)]))
     bound = 1.1 * np.sqrt(one ** 2 / H + 2.28 * (2.0 ** -24 / np.sqrt(3.0)) ** 2)
     assert got <= bound, (one, got, bound)
+
+
+def _text_error(B, N, H, d, seed):
+    """The same of one text query behind N visual ones of a causal map, `system` keys in front of them."""
+    g, system = torch.Generator().manual_seed(seed), 3
+    n = system + N + 1
+    Q, K = [torch.randn(B, H, n, d, generator=g).to(torch.bfloat16).cuda() for _ in range(2)]
+    X = torch.zeros(B, n, 8, dtype=torch.bfloat16, device="cuda")
+    ctx = fc.Context(0)
+    p = fc.make_problem(X, variant=fc.VARIANT_L, vis_begin=system, N=N, n_keep=N // 2, window=0, w_score=0.0, sem_src=fc.G_TEXT_ATTN, Q=Q, K=K, M=1)
+    buf = fc.Buffers(p, "cuda", X.dtype)
+    fc.ficoco_score(ctx, p, buf)
+    torch.cuda.synchronize()
+    logits = torch.matmul(K.double(), Q[:, :, -1:].double().transpose(2, 3).contiguous())[..., 0] * d ** -0.5      # [B][H][n]
+    want = -torch.softmax(logits, -1).mean(1)[:, system:system + N]
+    ctx.close()
+    return float(((buf.scores - want).pow(2).sum() / want.pow(2).sum()).sqrt())
+
+
+@pytest.mark.parametrize("B,N,H", [(4, 512, 32), (8, 384, 32), (5, 512, 16)])
+def test_text_row_behind_whole_tiles(B, N, H):
+    """Heads of 128, not split, one block of queries in the last tile of 128: four wavefronts share its heads.  Four sums of H / 4 heads, added
+    pairwise: squared, relative to the whole sum, 4 (1 + 4 + ... + (H / 4)^2) / H^2 + 2 / 4 + 1 of a rounding's share, 2.3 at 32 heads (11.2 one
+    after the other) and 1.97 at sixteen (5.84)."""
+    q = H // 4
+    shares = 4.0 * q * (q + 1) * (2 * q + 1) / 6 / H ** 2 + 1.5
+    one = np.sqrt(np.mean([_text_error(B, N, 1, 128, s) ** 2 for s in (1, 2, 3)]))
+    got = np.sqrt(np.mean([_text_error(B, N, H, 128, s) ** 2 for s in (4, 5, 6)]))
+    bound = 1.1 * np.sqrt(one ** 2 / H + shares * (2.0 ** -24 / np.sqrt(3.0)) ** 2)
+    assert got <= bound, (one, got, bound)
