@@ -36,21 +36,28 @@ namespace ficoco {
 // The usual shape is 8 lanes x 24 groups (32 beyond 1024 columns) with rows for about 512 workgroups: its loads lie close together in
 // memory, and few, long workgroups leave room for those of other streams.  Others take its place where they are faster, by the 16-byte loads that a
 // row and a column group take (`loads`: heads, twice as many in float32).  Step in us, usual / taken:
-//   16 x 16 lanes, 16 rows: up to sixteen loads, short sequences, at most 512 workgroups.  8 x 256 tokens, 16 heads 26.9 / 25.4.
+//   16 x 16 lanes, 16 rows: short sequences, up to 512 workgroups (8 x 256 tokens, 16 heads 26.9 / 25.4); with more than sixteen loads where the usual
+//     shape has 16 rows too (49 x 86, 40 heads of bfloat16 35.2 / 29.1, 12 x 219, 32 of float32, the worst of 84, 36.7 / 37.6), with 8 below 256 of them
+//     (8 x 232, 40 heads of bfloat16 28.6 / 27.3; from there on 20 x 180, 24 heads 28.4 / 30.8).
 //   32 x 8, 32 rows, a row a thread: up to sixteen loads in flight, and few partials for the one workgroup of the filter.  1 x 576 tokens, 8 heads
 //     25.9 / 24.1, 3 x 576 28.7 / 27.1.  As far as 1300 workgroups (five a compute unit: 8 x 576, 12 heads 39.7 / 39.6; with sixteen loads 1187; few heads
-//     700, from where two rows a thread are better).  Beyond sixteen loads a thread makes several trips with one row in hand: up to 512 workgroups (1 x 576,
-//     float32, 16 heads 28.3 / 26.3), with more than forty loads one a compute unit, the [CLS] rows' among them (the second is half a launch there: 2 x 488,
-//     40 heads of float32, 272 of them: 40.0 / 43.6, 2 x 472 with 256 38.9 / 34.7), for short sequences none (46 x 144, 40 heads of float32 56.4 / 63.1, 16 x 144
-//     of a decoder in bfloat16 35.8 / 38.5).
+//     700, from where two rows a thread are better).  Beyond sixteen loads a thread makes several trips with one row in hand: up to three workgroups a compute
+//     unit, the [CLS] rows' among them (3 x 658, 20 heads of bfloat16, 726 of them 39.9 / 34.5, 9 x 378, 12 of float32, 702 35.6 / 34.4, 6 x 443, 40 of
+//     bfloat16, 630 57.7 / 48.3, 3 x 660, 16 of float32, 726 44.2 / 39.0; worst 1 x 1004, 40 of bfloat16, 528 43.2 / 46.2), or 1100 of them where the usual shape
+//     has 24 rows, three a thread (2 x 1017, 40 of bfloat16, 1056 80.4 / 67.1, 2 x 918, 16 of float32, 900 55.1 / 53.7; worst 15 x 315, 16 of float32, 825
+//     48.3 / 50.4); with more than forty loads one, where the second is half a launch (2 x 488, 40 heads of float32, 272 of them: 40.0 / 43.6, 2 x 472 with 256 38.9 / 34.7), or two where
+//     the usual shape has 16 rows or more, which is short of loads in flight (3 x 510, 40 of float32, 408 of them 59.1 / 51.3, 6 x 359, 64 of bfloat16, 468
+//     60.1 / 49.5); for short sequences none (46 x 144, 40 heads of float32 56.4 / 63.1, 16 x 144 of a decoder in bfloat16 35.8 / 38.5).
 //     In float32 such a row is a chain of batches of eight heads, two loads each, and the chip is better filled with shorter chunks where its workgroups are
-//     few: from 50 on up to forty loads (320 tokens, 16 heads, one image with 50 22.8 / 23.5), from 100 on beyond (1 x 320, 40 heads 24.8 / 26.2, 1 x 448
+//     few: from 50 on up to forty loads (304 tokens, 16 heads, one image with 50 22.8 / 23.5), from 100 on beyond (1 x 320, 40 heads 24.8 / 26.2, 1 x 448
 //     with 98 28.3 / 27.3, 2 x 288 with 90 25.1 / 26.3, 2 x 376 with 144 28.6 / 28.4).
 //   16 x 16, 32 rows, two a thread: few heads up to 2500 workgroups (8 x 576, 4 heads 31.1 / 30.2; beyond, several steps in flight lose by it: 48 x 576, one
-//     head 54.6 / 59.2), others from 6000 on (4 x 2880, 16 heads 314 / 311).
-// Of 2500 problems (60 to 2900 tokens, 1 to 80 images, 1 to 40 heads) the step is 1.018 times as fast as with the usual shape alone, four are more than 3 %
-// slower (none 6 %), three steps in flight 1.005 times.  (With 8 x 24 lanes and 32 rows for all calls beyond 700 workgroups 119 were, by up to 16 %: 11 x 348,
-// 32 heads, launch 22.1 usual, 30.9.)
+//     head 54.6 / 59.2) and again from 9000 on (47 x 1145, one head 231 / 210, in flight 217 / 202), others from 6000 on (4 x 2880, 16 heads 314 / 311), and
+//     beyond 1024 columns, where the usual shape has 32 rows, up to forty loads (3 x 1129, 40 heads of bfloat16 124 / 106, 4 x 1714, 20 150 / 147, worst
+//     7 x 1092, 32 155 / 163; over 1600 such problems 1.016).
+// Of 24500 problems (40 to 2900 tokens, 1 to 64 images, 1 to 64 heads) the step is 1.015 times as fast as with the usual shape alone, 117 are more than 3 %
+// slower (26 more than 5 %), three steps in flight 1.006 times.  (With 8 x 24 lanes and 32 rows for all calls beyond 700 workgroups some were by up to
+// 16 %: 11 x 348, 32 heads, launch 22.1 usual, 30.9.)
 //
 // What the static scratch may hold is a fixed size, so no shape has fewer rows (more partials) than the usual one, whose
 // partials it has always had room for: the 16 rows end where that takes 24.
@@ -63,12 +70,17 @@ static MapShape map_shape(const ficoco_problem& p, int rows) {
   const int loads = p.dtype == FICOCO_BF16 ? p.H : 2 * p.H;
   const bool is_short = p.N <= 256;
   if (is_short && wgs(24, 8) <= 256) return usual;         // every workgroup has a compute unit of its own
-  if (is_short && loads <= 16 && wgs(16, 16) <= 512 && usual.rows <= 16) return {16, 16, 16};
-  const int64_t most = wgs(8, 32), others = (int64_t)p.B * ((groups + 7) / 8) * ((std::max(rows - p.N, 0) + 31) / 32);    // (the [CLS] row has a chunk of its own)
-  const int64_t up_to = loads < 8 ? 700 : loads <= 16 ? std::min(1300, 19000 / loads) : is_short ? 0 : loads <= 40 ? 512 : 256 - others;
+  if (is_short && usual.rows <= 16 && wgs(16, 16) <= (loads <= 16 || usual.rows == 16 ? 512 : 255)) return {16, 16, 16};
+  const int64_t most = wgs(8, 32), all = most + (int64_t)p.B * ((groups + 7) / 8) * ((std::max(rows - p.N, 0) + 31) / 32);    // (the [CLS] row has a chunk of its own)
   const int beyond = p.dtype == FICOCO_BF16 || loads <= 24 ? 0 : loads <= 40 ? 50 : 100;
-  if (most > beyond && most <= up_to) return {32, 8, 32};
-  return (loads < 8 ? most <= 2500 : most > 6000) ? MapShape{16, 16, 32} : usual;
+  const bool fills = loads < 8    ? most <= 700
+                     : loads <= 16 ? most <= std::min(1300, 19000 / loads)
+                     : is_short    ? false
+                     : loads <= 40 ? all <= (usual.rows == 24 ? 1100 : 768)
+                                   : all <= (usual.rows >= 16 ? 512 : 256);
+  if (most > beyond && fills) return {32, 8, 32};
+  const bool two_rows = loads < 8 ? most <= 2500 || most > 9000 : most > 6000 || (groups > 128 && usual.rows == 32 && loads <= 40);
+  return two_rows ? MapShape{16, 16, 32} : usual;
 }
 // Workgroups the reduction aims at where it has no such map to store.
 constexpr int64_t kWgTarget = 1024;
