@@ -123,10 +123,14 @@ inline bool text_with_features(const ficoco_problem& p, const Plan& pl) {
 // Not where its workgroups fill the chip badly and the separate passes are faster.  Step in us, one pass / separate: nine or ten wavefronts, of which one
 // workgroup has a compute unit of sixteen to itself, above 8192 rows (5120 features, 64 text tokens: 8 x 690 145.8 / 151.8, 12 x 690 184.5 / 183.9, 8 x 1152
 // 221.2 / 214.6, with 200 252.3 / 241.1; 4096 features 170.8 / 179.7); thirteen and more with over four workgroups of text profiles a compute unit in
-// the launch (8192 features, 200 text tokens: 32 x 200 253.3 / 263.6, 24 x 576 455.7 / 486.7, 64 x 64 263.6 / 251.2, 128 x 33 414.4 / 393.4).
+// the launch (8192 features, 200 text tokens: 32 x 200 253.3 / 263.6, 24 x 576 455.7 / 486.7, 64 x 64 263.6 / 251.2, 128 x 33 414.4 / 393.4); and where no
+// unit rows are wanted (correlation by attention), above 4096 features and one workgroup a compute unit (7 x 585 tokens, 8192 features, 259 workgroups 142.8 /
+// 130.3, 12 x 364, 6144, 276 124.7 / 119.0; 16 x 195, 6144, 208 86.6 / 93.7): relative to the separate passes 0.95 to 0.99
+// at 200 to 256 workgroups, 1.03 to 1.08 at 257 to 300, beyond 1.00 (5120, 6144 features) and 1.04 (7168, 8192); 4096 features 0.97, 1.00 and 0.98.
 inline bool unit_rows_summed(const ficoco_problem& p, int Df) {
   if (p.variant != FICOCO_VARIANT_L || p.dtype != FICOCO_BF16 || p.red_src != FICOCO_R_SIM_MEAN || Df % kVec != 0 || Df < 2048 || Df > 8192) return false;
   if (Df > 4096 && Df <= 5120 && (int64_t)p.B * p.N > 8192) return false;
+  if (p.corr_src != FICOCO_C_COSINE && Df > 4096 && (int64_t)p.B * ((p.N + 15) / 16) > 256) return false;
   return !(Df > 6144 && p.A_text != nullptr && (int64_t)p.B * ((p.M + 7) / 8) > 1024);
 }
 // Rows of a workgroup there: 16, or 8 where those would be fewer than half as many workgroups as there are compute units.  us per step with
